@@ -70,8 +70,6 @@ gp_status plan_batch(const std::vector<BatchJobRef>& jobs, const std::vector<gp_
     int64_t n_prog = 0;
     for (const BatchJobRef& j : jobs) n_prog += j.pd->n_prog;
     if (n_prog > 0x7FFFFFFFll) return fail(GP_E_INVAL, "batch too large");
-    plan.progs.reserve((size_t)n_prog);
-    plan.order.reserve((size_t)n_prog);
     uint64_t part_base = 0;
     std::vector<std::pair<double, UnitDesc>> units;
     for (size_t ji = 0; ji < jobs.size(); ji++) {
@@ -83,41 +81,26 @@ gp_status plan_batch(const std::vector<BatchJobRef>& jobs, const std::vector<gp_
         const int64_t tiles = (N + 64LL * vt - 1) / (64LL * vt);
         std::vector<uint32_t> jcode;
         std::vector<DevProg> jprogs;
-        gp_status st = core_translate(pd, vi, jcode, jprogs);
+        // programs of this job by falling cost, in G groups of about equal cost
+        std::vector<uint32_t> order, goff;
+        std::vector<int64_t> rec((size_t)pd.n_prog + 1);
+        cost_order(pd, order);
+        gp_status st = core_translate(pd, vi, order.data(), jcode, jprogs);
         if (st != GP_OK) return st;
         if ((plan.code.size() + jcode.size()) * 4 > 0xFFFFFFF0ull) return fail(GP_E_INVAL, "batch code exceeds 4 GiB");
-        const uint32_t code_base = (uint32_t)plan.code.size();
-        const uint32_t prog_base = (uint32_t)plan.progs.size();
+        const int64_t base = (int64_t)plan.code.size() / 4;
         plan.code.insert(plan.code.end(), jcode.begin(), jcode.end());
-        for (int32_t p = 0; p < pd.n_prog; p++) {
-            DevProg dp = jprogs[p];
-            dp.code_off += code_base;
-            dp.row = (uint64_t)p;
-            plan.progs.push_back(dp);
-        }
-        // programs of this job, longest first, dealt to groups in snake order
-        std::vector<uint32_t> idx(pd.n_prog);
-        std::iota(idx.begin(), idx.end(), 0u);
-        std::stable_sort(idx.begin(), idx.end(), [&](uint32_t a, uint32_t b) { return pd.cost[a] > pd.cost[b]; });
+        for (int32_t i = 0; i < pd.n_prog; i++) rec[i] = base + jprogs[order[i]].code_off / 4;
+        rec[pd.n_prog] = rec[pd.n_prog - 1] + jprogs[order[pd.n_prog - 1]].len;
         const int32_t G = std::max<int32_t>(1, (pd.n_prog + unit_prog - 1) / unit_prog);
-        std::vector<std::vector<uint32_t>> groups(G);
+        cut_groups(pd, order, rec, G, goff);
         std::vector<double> gcost(G, 0.0);
-        for (int32_t i = 0; i < pd.n_prog; i++) {
-            const int32_t r = i / G, k = i % G;
-            const int32_t g = (r & 1) ? G - 1 - k : k;
-            groups[g].push_back(prog_base + idx[i]);
-            gcost[g] += pd.cost[idx[i]];
-        }
-        std::vector<std::pair<uint32_t, uint32_t>> qr(G);
-        for (int32_t g = 0; g < G; g++) {
-            qr[g].first = (uint32_t)plan.order.size();
-            plan.order.insert(plan.order.end(), groups[g].begin(), groups[g].end());
-            qr[g].second = (uint32_t)plan.order.size();
-        }
+        for (int32_t g = 0, i = 0; g < G; g++)
+            for (; i < pd.n_prog && rec[i] < goff[g + 1]; i++) gcost[g] += pd.cost[order[i]];
         for (int64_t t = 0; t < tiles; t++) {
             for (int32_t g = 0; g < G; g++) {
-                if (qr[g].first == qr[g].second) continue;
-                UnitDesc u{(uint32_t)ji, (uint32_t)t, qr[g].first, qr[g].second};
+                if (goff[g] == goff[g + 1]) continue;
+                UnitDesc u{(uint32_t)ji, (uint32_t)t, goff[g], goff[g + 1]};
                 // every slot of a tile is interpreted, ragged or not; add the tile load
                 units.push_back({gcost[g] + 8.0 * pd.n_load, u});
             }
@@ -163,8 +146,7 @@ gp_status plan_batch(const std::vector<BatchJobRef>& jobs, const std::vector<gp_
 }
 
 size_t plan_device_bytes(const BatchPlan& p) {
-    return p.code.size() * 4 + p.progs.size() * sizeof(DevProg) + p.order.size() * 4 +
-           p.units.size() * sizeof(UnitDesc) + p.jobs.size() * sizeof(JobDesc) +
+    return p.code.size() * 4 + p.units.size() * sizeof(UnitDesc) + p.jobs.size() * sizeof(JobDesc) +
            p.datasets.size() * sizeof(DatasetDesc) + p.reduce.size() * sizeof(ReduceArgs) +
            (size_t)p.partial_doubles * sizeof(double) + 4096;
 }
@@ -172,8 +154,6 @@ size_t plan_device_bytes(const BatchPlan& p) {
 gp_status upload_plan(BatchPlan& p, BatchScratch& sc, hipStream_t s) {
     gp_status st;
     if ((st = sc.code.reserve(std::max<size_t>(4, p.code.size() * 4))) != GP_OK) return st;
-    if ((st = sc.progs.reserve(std::max<size_t>(1, p.progs.size()) * sizeof(DevProg))) != GP_OK) return st;
-    if ((st = sc.order.reserve(std::max<size_t>(1, p.order.size()) * 4)) != GP_OK) return st;
     if ((st = sc.units.reserve(std::max<size_t>(1, p.units.size()) * sizeof(UnitDesc))) != GP_OK) return st;
     if ((st = sc.jobs.reserve(std::max<size_t>(1, p.jobs.size()) * sizeof(JobDesc))) != GP_OK) return st;
     if ((st = sc.datasets.reserve(std::max<size_t>(1, p.datasets.size()) * sizeof(DatasetDesc))) != GP_OK) return st;
@@ -184,8 +164,6 @@ gp_status upload_plan(BatchPlan& p, BatchScratch& sc, hipStream_t s) {
     const size_t total = plan_device_bytes(p) - (size_t)p.partial_doubles * sizeof(double) + 8 * 256;
     if ((st = sc.staging.begin(total)) != GP_OK) return st;
     if ((st = sc.staging.put(p.code.data(), p.code.size() * 4, sc.code.p, s)) != GP_OK) return st;
-    if ((st = sc.staging.put(p.progs.data(), p.progs.size() * sizeof(DevProg), sc.progs.p, s)) != GP_OK) return st;
-    if ((st = sc.staging.put(p.order.data(), p.order.size() * 4, sc.order.p, s)) != GP_OK) return st;
     if ((st = sc.staging.put(p.units.data(), p.units.size() * sizeof(UnitDesc), sc.units.p, s)) != GP_OK) return st;
     if ((st = sc.staging.put(p.jobs.data(), p.jobs.size() * sizeof(JobDesc), sc.jobs.p, s)) != GP_OK) return st;
     if ((st = sc.staging.put(p.datasets.data(), p.datasets.size() * sizeof(DatasetDesc), sc.datasets.p, s)) != GP_OK)
@@ -200,8 +178,6 @@ gp_status launch_plan(const BatchPlan& p, BatchScratch& sc, hipStream_t s) {
     CoreArgs a;
     memset(&a, 0, sizeof a);
     a.code = (const uint32_t*)sc.code.p;
-    a.progs = (const DevProg*)sc.progs.p;
-    a.order = (const uint32_t*)sc.order.p;
     a.units = (const UnitDesc*)sc.units.p;
     a.jobs = (const JobDesc*)sc.jobs.p;
     a.datasets = (const DatasetDesc*)sc.datasets.p;

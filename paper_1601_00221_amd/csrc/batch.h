@@ -26,8 +26,6 @@ struct BatchPlan {
     int vi = -1;
     bool persistent = true;
     std::vector<uint32_t> code;
-    std::vector<DevProg> progs;
-    std::vector<uint32_t> order;
     std::vector<UnitDesc> units;
     std::vector<JobDesc> jobs;
     std::vector<DatasetDesc> datasets;
@@ -40,7 +38,7 @@ struct BatchPlan {
 // Device buffers of one stream's batched launches.
 struct BatchScratch {
     std::mutex mu;
-    DevBuf code, progs, order, units, jobs, datasets, reduce, partials, counter;
+    DevBuf code, units, jobs, datasets, reduce, partials, counter;
     Staging staging;
 };
 

@@ -152,11 +152,13 @@ gp_status core_ready(int vi, hipStream_t s) {
     a.probe = 1;
     a.probe_out = d;
     e = core_launch(vi, a, 1, s);
-    uint64_t base = 0;
-    if (e == hipSuccess) e = hipMemcpyAsync(&base, d, 8, hipMemcpyDeviceToHost, s);
+    uint64_t probed[2] = {0, 1};   // the handler table, and where the transcendentals' tables lie in LDS
+    if (e == hipSuccess) e = hipMemcpyAsync(probed, d, 16, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     (void)hipFree(d);
     if (e != hipSuccess) return fail(GP_E_DEVICE, "handler table probe: %s", hipGetErrorString(e));
+    const uint64_t base = probed[0];
+    if (probed[1] != 0) return fail(GP_E_DEVICE, "reduction tables at LDS offset %llu", (unsigned long long)probed[1]);
     if (base == 0 || (base & (GPX_SLOT - 1)) != 0) return fail(GP_E_DEVICE, "handler table probe returned %llx",
                                                                (unsigned long long)base);
     m.slot = variant_slots(vi);
@@ -220,6 +222,10 @@ struct Emitter {
             cst);
         phase = 0;   // the core is entered again after an exit
     }
+    // the end of a program: its row, and the records of the program that follows it
+    void end(uint32_t row, uint32_t next) {
+        if (ok) put(CK_EXIT, 0, 0, 0, (CORE_OP_END << 24) | (next & 0xFFFFFFu), row);
+    }
     // protected division, in the core (every arithmetic kernel has its
     // handlers): the exit's payload layout, without leaving
     void fail_two_constants() {
@@ -264,8 +270,8 @@ bool is_core_op(uint32_t op, bool boolean) {
 
 }  // namespace
 
-static int translate_tree(const uint32_t* w, int64_t n_instr, int vi, const VariantMap& m, uint32_t* out,
-                          int64_t cap, int64_t* n_out, char* err) {
+static int translate_tree(const uint32_t* w, int64_t n_instr, int vi, const VariantMap& m, uint32_t row, uint32_t next,
+                          uint32_t* out, int64_t cap, int64_t* n_out, char* err) {
     const CoreVariantDesc& v = kCoreVariants[vi];
     const int T = v.t, FO = core_reg_levels(vi) * T;
     Emitter e{m, out, cap, err};
@@ -368,7 +374,7 @@ static int translate_tree(const uint32_t* w, int64_t n_instr, int vi, const Vari
             default: e.exit(op, 0, 0, h * T, true, false, c); break;  // M_C
         }
     }
-    if (e.ok) e.exit(CORE_OP_END, 0, 0, 0, false, false, 0);
+    e.end(row, next);
     *n_out = e.n;
     return e.ok ? GP_OK : GP_E_INVAL;
 }
@@ -386,7 +392,8 @@ static int64_t linear_records(const uint32_t* w, int64_t n, int32_t n_reg) {
 }
 
 static int translate_linear(const uint32_t* w, int64_t n, const uint32_t* cst, int32_t n_reg, int32_t n_feat, int vi,
-                            const VariantMap& m, uint32_t* out, int64_t cap, int64_t* n_out, char* err) {
+                            const VariantMap& m, uint32_t row, uint32_t next, uint32_t* out, int64_t cap,
+                            int64_t* n_out, char* err) {
     const CoreVariantDesc& v = kCoreVariants[vi];
     const int T = v.t, FO = core_reg_levels(vi) * T;
     Emitter e{m, out, cap, err};
@@ -431,7 +438,7 @@ static int translate_linear(const uint32_t* w, int64_t n, const uint32_t* cst, i
             e.put(CK_FF, op, d, 0, (uint32_t)off(s1) | ((uint32_t)off(s2) << 8), 0);
         }
     }
-    if (e.ok) e.exit(CORE_OP_END, 0, 0, 0, false, false, 0);
+    e.end(row, next);
     *n_out = e.n;
     return e.ok ? GP_OK : GP_E_INVAL;
 }
@@ -446,76 +453,78 @@ static VariantMap map_at(int vi, uint64_t base) {
 
 // Programs are translated in parallel, each into its own counted range of
 // the code: a tree gives one core instruction per lowered instruction plus
-// the end; a register program as linear_records counts.
-static gp_status translate_with(const ProgData& pd, int vi, const VariantMap& m, std::vector<uint32_t>& code,
-                                std::vector<DevProg>& progs) {
+// the end; a register program as linear_records counts.  The code holds the
+// programs one after another in the order given (null: their own order), each
+// ending with the length of the one after it; progs[p] says where program p
+// lies.
+static gp_status translate_with(const ProgData& pd, int vi, const VariantMap& m, const uint32_t* order,
+                                std::vector<uint32_t>& code, std::vector<DevProg>& progs) {
     const int32_t P = pd.n_prog;
     progs = pd.progs;
     std::vector<int64_t> start((size_t)P + 1, 0);
-    for (int32_t p = 0; p < P; p++) {
+    auto at = [&](int32_t i) { return order ? (int32_t)order[i] : i; };
+    auto records = [&](int32_t p) {
         const DevProg& src = pd.progs[p];
-        const int64_t k = (src.meta & 1u) == FORM_TREE ? (int64_t)src.len + 1
-                                                        : linear_records(pd.code.data() + src.code_off, src.len,
-                                                                         pd.n_reg);
-        start[p + 1] = start[p] + k;
-    }
+        return (src.meta & 1u) == FORM_TREE ? (int64_t)src.len + 1
+                                            : linear_records(pd.code.data() + src.code_off, src.len, pd.n_reg);
+    };
+    for (int32_t i = 0; i < P; i++) start[i + 1] = start[i] + records(at(i));
     if (start[P] * 16 > 0xFFFFFFF0ll) return fail(GP_E_INVAL, "programs exceed 4 GiB of core code");
     // the core reads records two at a time, up to one record past a program's
     // last one: the code ends with padding
     code.assign((size_t)start[P] * 4 + 16, 0u);
     std::vector<int32_t> rc((size_t)P, GP_OK);
-    parallel_for(P, [&](int64_t p0, int64_t p1) {
+    auto translate = [&](int32_t i, uint32_t* out, int64_t cap, int64_t* n, char* err) {
+        const int32_t p = at(i);
+        const DevProg& src = pd.progs[p];
+        const uint32_t next = i + 1 < P ? (uint32_t)(start[i + 2] - start[i + 1]) : 0u;
+        const uint32_t* w = pd.code.data() + src.code_off;
+        if ((src.meta & 1u) == FORM_TREE)
+            return translate_tree(w, src.len, vi, m, (uint32_t)src.row, next, out, cap, n, err);
+        return translate_linear(w, src.len, w + src.len, pd.n_reg, pd.n_feat, vi, m, (uint32_t)src.row, next, out, cap,
+                                n, err);
+    };
+    parallel_for(P, [&](int64_t i0, int64_t i1) {
         char err[256];
-        for (int64_t p = p0; p < p1; p++) {
-            const DevProg& src = pd.progs[p];
-            uint32_t* out = code.data() + 4 * start[p];
-            const int64_t cap = start[p + 1] - start[p];
+        for (int64_t i = i0; i < i1; i++) {
+            const int64_t cap = start[i + 1] - start[i];
             int64_t n = 0;
-            if ((src.meta & 1u) == FORM_TREE)
-                rc[p] = translate_tree(pd.code.data() + src.code_off, src.len, vi, m, out, cap, &n, err);
-            else
-                rc[p] = translate_linear(pd.code.data() + src.code_off, src.len,
-                                         pd.code.data() + src.code_off + src.len, pd.n_reg, pd.n_feat, vi, m, out,
-                                         cap, &n, err);
-            if (rc[p] == GP_OK && n != cap) rc[p] = GP_E_INVAL;
+            rc[i] = translate((int32_t)i, code.data() + 4 * start[i], cap, &n, err);
+            if (rc[i] == GP_OK && n != cap) rc[i] = GP_E_INVAL;
         }
     });
-    for (int32_t p = 0; p < P; p++) {
-        if (rc[p] != GP_OK) {
+    for (int32_t i = 0; i < P; i++) {
+        const int32_t p = at(i);
+        if (rc[i] != GP_OK) {
             // translate the first failing program again on this thread for its message
-            const DevProg& src = pd.progs[p];
-            std::vector<uint32_t> tmp(4 * (size_t)(start[p + 1] - start[p] + 8));
+            std::vector<uint32_t> tmp(4 * (size_t)(start[i + 1] - start[i] + 8));
             char err[256] = "internal: core code length differs from its count";
             int64_t n = 0;
-            if ((src.meta & 1u) == FORM_TREE)
-                translate_tree(pd.code.data() + src.code_off, src.len, vi, m, tmp.data(), (int64_t)tmp.size() / 4, &n,
-                               err);
-            else
-                translate_linear(pd.code.data() + src.code_off, src.len, pd.code.data() + src.code_off + src.len,
-                                 pd.n_reg, pd.n_feat, vi, m, tmp.data(), (int64_t)tmp.size() / 4, &n, err);
-            return fail((gp_status)rc[p], "program %d: %s", p, err);
+            translate(i, tmp.data(), (int64_t)tmp.size() / 4, &n, err);
+            return fail((gp_status)rc[i], "program %d: %s", p, err);
         }
-        progs[p].code_off = (uint32_t)(4 * start[p]);   // words
-        progs[p].len = (uint32_t)(start[p + 1] - start[p]);
+        progs[p].code_off = (uint32_t)(4 * start[i]);   // words
+        progs[p].len = (uint32_t)(start[i + 1] - start[i]);
     }
     return GP_OK;
 }
 
-gp_status core_translate(const ProgData& pd, int vi, std::vector<uint32_t>& code, std::vector<DevProg>& progs) {
+gp_status core_translate(const ProgData& pd, int vi, const uint32_t* order, std::vector<uint32_t>& code,
+                         std::vector<DevProg>& progs) {
     VariantMap m;
     {
         std::lock_guard<std::mutex> g(g_mu);
         if ((int)g_maps.size() <= vi || !g_maps[vi].ready) return fail(GP_E_DEVICE, "core variant %d not probed", vi);
         m = g_maps[vi];
     }
-    return translate_with(pd, vi, m, code, progs);
+    return translate_with(pd, vi, m, order, code, progs);
 }
 
 gp_status core_translate_at(const ProgData& pd, int vi, uint64_t base, std::vector<uint32_t>& code,
                             std::vector<DevProg>& progs) {
     if (vi < 0 || vi >= core_variants()) return fail(GP_E_INVAL, "variant %d does not exist", vi);
     if (base & (GPX_SLOT - 1)) return fail(GP_E_INVAL, "table base must be %d-byte aligned", GPX_SLOT);
-    return translate_with(pd, vi, map_at(vi, base), code, progs);
+    return translate_with(pd, vi, map_at(vi, base), nullptr, code, progs);
 }
 
 int core_variant_t(int vi) { return kCoreVariants[vi].t; }

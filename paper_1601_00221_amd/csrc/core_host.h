@@ -33,8 +33,10 @@ int pick_core_variant(int n_load, int depth, double transc_frac, bool has_transc
 gp_status core_ready(int vi, hipStream_t s);
 // True if core_ready has found variant vi's handler table on the current device.
 bool core_is_ready(int vi);
-// Core instructions and per-program records of lowered programs.
-gp_status core_translate(const ProgData& pd, int vi, std::vector<uint32_t>& code, std::vector<DevProg>& progs);
+// Core instructions of lowered programs, one program after another in the
+// given order (null: their own), and where each one lies.
+gp_status core_translate(const ProgData& pd, int vi, const uint32_t* order, std::vector<uint32_t>& code,
+                         std::vector<DevProg>& progs);
 // The same with the handler table taken to start at `base` (no device needed).
 gp_status core_translate_at(const ProgData& pd, int vi, uint64_t base, std::vector<uint32_t>& code,
                             std::vector<DevProg>& progs);

@@ -8,7 +8,10 @@
 
 namespace gpx {
 
-enum : uint32_t { CORE_OP_END = 15 };   // exit operation that ends a program
+// Exit operation that ends a program.  Its record's payload holds, in the low
+// 24 bits, the number of records of the program that follows (0: none), and
+// its constant the program's row.
+enum : uint32_t { CORE_OP_END = 15 };
 
 struct DatasetDesc {
     const float* X;
@@ -27,7 +30,7 @@ struct JobDesc {
 struct UnitDesc {
     uint32_t job;
     uint32_t tile;
-    uint32_t q0, q1;            // programs order[q0 .. q1)
+    uint32_t c0, c1;            // core records of its programs, one after another
 };
 
 // Partial sums are program-major: block b of program p (its row in the
@@ -45,8 +48,6 @@ struct ReduceArgs {
 
 struct CoreArgs {
     const uint32_t* code;       // core instructions, 16 bytes each
-    const DevProg* progs;
-    const uint32_t* order;      // program indices grouped by unit
     // table of units (batched launches); null: implicit units over one dataset
     const UnitDesc* units;
     const JobDesc* jobs;
@@ -54,7 +55,7 @@ struct CoreArgs {
     uint32_t* counter;          // next unit, persistent form
     // implicit units: block unit b = (group quad b div chunks, chunk b mod
     // chunks); a chunk is tiles_per_wave consecutive tiles
-    const uint32_t* group_off;
+    const uint32_t* group_off;  // group g holds the core records group_off[g] .. group_off[g + 1)
     const float* X;
     const float* y;
     int64_t N;
@@ -65,8 +66,8 @@ struct CoreArgs {
     int32_t persistent;
     int32_t tiles_per_wave;
     int32_t chunks;
-    int32_t prefetch;           // scalar loads in flight when a program's code is burst-loaded into the
-                                // scalar cache before it runs (1-15), or 0: no burst load
+    int32_t prefetch;           // 64-byte lines of the next program's code loaded into the scalar cache at a
+                                // time (1-14), or 0: none
     int32_t n_groups;           // program groups (implicit units)
     int32_t same_group;         // implicit units: the four waves of a block run one group on four chunks
     int64_t n_bits;             // Boolean kernels: cases (bits) in the N words of each row

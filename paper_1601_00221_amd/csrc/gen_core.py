@@ -685,7 +685,574 @@ def phase_b(h, tag):
     return c
 
 
-def asm_text(T, D, NF, tag, hs):
+# ---------------------------------------------------------------------------
+# Around the handlers: the unit's tile, the end of a program, sin/cos/exp/log
+# ---------------------------------------------------------------------------
+# Scalar registers the block is entered with (besides s[60:62], s63, s78):
+#   s[82:83] case matrix at the tile's first case   s[84:85] bytes from one feature row to the next
+#   s86 features to load    s87 cases from the tile's start to the end of the data (at most the tile)
+#   s[88:89] targets at the tile                    s[90:91] partial sums of the tile's first block
+#   s92 bytes from one program's partial sums to the next
+#   s93 fitness kind        s[94:95] per-case outputs at the tile    s96 byte offset where the unit's code ends
+#   s97 LDS address of the wave's targets           s98 bits from the tile's start to the end (Boolean)
+#   s[100:101] the series coefficients (COEF)
+# s[24:55] hold the coefficients (kernels with sin/cos/exp/log); s58, s59, s79-s81, s99, s72-s77 are temporaries.
+PF_LINES = 14                    # 64-byte lines of the next program fetched beside its first records
+FIT_SUM_ABS, FIT_MSE, FIT_HITS, OUT_CASES, FIT_CLASS = 0, 1, 2, 3, 4
+
+# binary64 series constants in SGPR pairs, in the order of gmath::kCoreCoef
+COEF = {n: 24 + 2 * i for i, n in enumerate(
+    ("KPI", "P1", "P2", "P3", "S0", "S2", "C2", "KLN", "L1", "L2", "E1", "E3", "LN2", "G1", "G2", "G4"))}
+# constants a VOP3 needs in VGPRs beside one of those (it reads one scalar pair): high and low words
+VCONST = {"R": (0x43380000, 0x00000000), "S1": (0x3F811111, 0x11111111), "C1": (0x3FA55555, 0x55555555),
+          "E2": (0x3FA55555, 0x55555555), "G3": (0x3FC99999, 0x9999999A)}
+# LDS byte offsets of the reduction tables (gp_math.h: kTabSC, kTabExp, kTabLog, kTabPi, in doubles)
+LDS_SC, LDS_EXP, LDS_LOG = 0, 256 * 8, 320 * 8
+LDS_PI = LDS_LOG + 2 * 257 * 8
+LOG_K0 = 0x7E6A
+
+
+def transc_slots(NCV):
+    """Slots whose sin/cos/exp/log are computed side by side: two where the compiler's range has room."""
+    return 2 if NCV >= 48 else 1
+
+
+def work_regs(NCV, mode):
+    """VGPRs below the core's range that the block uses (and clobbers)."""
+    if mode in (0, 4):
+        n = 14 * transc_slots(NCV) + 2
+        return n + (2 * len(VCONST) if NCV >= 64 else 0)
+    return 0 if mode == 2 else DIV_TMP
+
+
+def pair(n):
+    return "v[%d:%d]" % (n, n + 1)
+
+
+def quad(n):
+    return "v[%d:%d]" % (n, n + 3)
+
+
+def sp(n):
+    return "s[%d:%d]" % (n, n + 1)
+
+
+def exec_slot(j, left="s87"):
+    """exec = the lanes of slot j that hold a case: 64 j + lane < left."""
+    return ["s_sub_i32 s72, %s, %d" % (left, 64 * j),
+            "s_bfm_b64 s[74:75], s72, 0",
+            "s_cmp_gt_i32 s72, 63",
+            "s_cselect_b64 s[74:75], -1, s[74:75]",
+            "s_cmp_lt_i32 s72, 1",
+            "s_cselect_b64 exec, 0, s[74:75]"]
+
+
+def unit_start(T, D, NF, V0, FO, tag, mode):
+    """Start of a unit: the first records and code lines (into the scalar
+    cache), the tile's targets (to LDS, read again at the end of every
+    program) and features (straight into their registers), all in flight
+    together.  Rows of lanes past the data are not read."""
+    vl4, vy = "v%d" % (V0 + T), "v%d" % (V0 + T + 1)     # stack level 1 is free here
+    L = ["v_mbcnt_lo_u32_b32 %s, -1, 0" % vy, "v_mbcnt_hi_u32_b32 %s, -1, %s" % (vy, vy),
+         "v_lshlrev_b32_e32 %s, 2, %s" % (vl4, vy), "v_lshl_add_u32 %s, %s, 4, s97" % (vy, vy),
+         "s_load_dwordx8 s[64:71], s[60:61], s62"]
+    if mode in (0, 4):
+        L += ["s_load_dwordx16 s[24:39], s[100:101], 0x0", "s_load_dwordx16 s[40:55], s[100:101], 0x40"]
+    L += prefetch_start(tag, "0", "s96") + ["s_mov_b32 s99, 0"]
+    for j in range(T):
+        L += exec_slot(j)
+        L += ["s_cbranch_execz .Lgpx_tile_%s" % tag]
+        L += ["s_cmp_eq_u32 s93, %d" % OUT_CASES, "s_cbranch_scc1 .Lgpx_noy%d_%s" % (j, tag),
+              "global_load_dword v%d, %s, s[88:89] offset:%d" % (V0 + j, vl4, 256 * j),
+              ".Lgpx_noy%d_%s:" % (j, tag), "s_mov_b64 s[72:73], s[82:83]"]
+        for f in range(NF):
+            L += ["s_cmp_le_u32 s86, %d" % f, "s_cbranch_scc1 .Lgpx_row%d_%s" % (j, tag),
+                  "global_load_dword v%d, %s, s[72:73] offset:%d" % (V0 + FO + f * T + j, vl4, 256 * j),
+                  "s_add_u32 s72, s72, s84", "s_addc_u32 s73, s73, s85"]
+        L += [".Lgpx_row%d_%s:" % (j, tag)]
+    L += [".Lgpx_tile_%s:" % tag, "s_mov_b64 exec, -1", "s_waitcnt vmcnt(0) lgkmcnt(0)"]
+    for k in range(T // 4):
+        L += ["ds_write_b128 %s, %s offset:%d" % (vy, quad(V0 + 4 * k), 1024 * k)]
+    if mode in (0, 4) and work_regs(V0, mode) > 14 * transc_slots(V0) + 2:
+        for i, (hi, lo) in enumerate(VCONST.values()):
+            r = vconst_reg(V0, mode, i)
+            L += ["v_mov_b32_e32 v%d, 0x%x" % (r, lo), "v_mov_b32_e32 v%d, 0x%x" % (r + 1, hi)]
+    L += ["s_waitcnt lgkmcnt(0)", "s_branch .Lgpx_rest_%s" % tag]
+    return L
+
+
+def vconst_reg(V0, mode, i):
+    return V0 - work_regs(V0, mode) + 2 * i
+
+
+def prefetch_start(tag, n, limit):
+    """Fetch the 64-byte lines after the one at s62, up to byte offset
+    `limit`, into the scalar cache: at most s78 (<= PF_LINES) now, without
+    waiting; s[58:59] and s99 (lines still to fetch) let `rest` go on."""
+    L = ["s_and_b32 s72, s62, 0xffffffc0", "s_add_u32 s58, s60, s72", "s_addc_u32 s59, s61, 0",
+         "s_sub_u32 s73, %s, 1" % limit, "s_lshr_b32 s73, s73, 6", "s_lshr_b32 s72, s72, 6",
+         "s_sub_i32 s99, s73, s72", "s_max_i32 s99, s99, 0", "s_cmp_eq_u32 s78, 0", "s_cselect_b32 s99, 0, s99"]
+    return L + prefetch_lines(tag, n)
+
+
+def prefetch_lines(tag, n):
+    """One round: the next min(s99, s78) lines after s[58:59], by a jump into straight-line loads."""
+    L = ["s_min_u32 s72, s99, s78", "s_sub_u32 s99, s99, s72",
+         "s_lshl_b32 s73, s72, 3", "s_getpc_b64 s[74:75]", ".Lgpx_pf%s_%s:" % (n, tag),
+         "s_add_u32 s74, s74, .Lgpx_pfe%s_%s-.Lgpx_pf%s_%s" % (n, tag, n, tag), "s_addc_u32 s75, s75, 0",
+         "s_sub_u32 s74, s74, s73", "s_subb_u32 s75, s75, 0", "s_setpc_b64 s[74:75]"]
+    for k in range(PF_LINES, 0, -1):
+        L += ["s_load_dword s79, s[58:59], 0x%x" % (64 * k)]
+    return L + [".Lgpx_pfe%s_%s:" % (n, tag)]
+
+
+def program_end(T, D, NF, V0, FO, tag, mode):
+    """End of a program: s66 holds its payload (low 24 bits: records of the
+    program after it), s67 its row.  The next program's first records and
+    lines are requested, the fitness terms of the tile are formed and summed
+    over the wave in the fixed order, and the interpreter goes on."""
+    m = V0 + T                       # stack levels above the result are free
+    vl, vy, vo = m, m + 1, m + 1
+    acc = [m + 2, m + 4]
+    tmp = m + 6
+    yr = m + 8
+    assert yr + T <= V0 + FO
+    y = lambda j: "v%d" % (yr + j)   # noqa: E731
+    o = lambda j: "v%d" % (V0 + j)   # noqa: E731
+    nb = T // 4
+    full = 64 * T
+    L = ["s_mov_b32 s80, s67", "s_and_b32 s81, s66, 0xffffff", "s_add_u32 s62, s62, 16",
+         "v_mbcnt_lo_u32_b32 v%d, -1, 0" % vl, "v_mbcnt_hi_u32_b32 v%d, -1, v%d" % (vl, vl),
+         "v_lshl_add_u32 v%d, v%d, 4, s97" % (vy, vl)]
+    for k in range(nb):
+        L += ["ds_read_b128 %s, v%d offset:%d" % (quad(yr + 4 * k), vy, 1024 * k)]
+    L += ["s_waitcnt lgkmcnt(0)", "s_load_dwordx8 s[64:71], s[60:61], s62",
+          "s_lshl_b32 s81, s81, 4", "s_add_u32 s81, s81, s62"]
+    L += prefetch_start(tag, "1", "s81")
+    kinds = [FIT_HITS, OUT_CASES] if mode == 2 else [FIT_MSE, FIT_SUM_ABS, FIT_HITS, FIT_CLASS, OUT_CASES]
+    lab = {FIT_MSE: "mse", FIT_SUM_ABS: "abs", FIT_HITS: "hits", FIT_CLASS: "cls", OUT_CASES: "cases"}
+    for k in kinds[1:]:
+        L += ["s_cmp_eq_u32 s93, %d" % k, "s_cbranch_scc1 .Lgpx_%s_%s" % (lab[k], tag)]
+
+    to_partials = ["s_mul_i32 s72, s80, s92", "s_mul_hi_u32 s73, s80, s92",
+                   "s_add_u32 s80, s72, s90", "s_addc_u32 s81, s73, s91"]
+
+    def store_sum():
+        # one block: any lane holds the sum; two: lane 0 the first block's, lane 32 the second's
+        if nb == 1:
+            return ["v_mov_b32_e32 v%d, 0" % vo, "s_mov_b64 exec, 1",
+                    "global_store_dwordx2 v%d, %s, s[80:81]" % (vo, pair(acc[0])), "s_mov_b64 exec, -1"]
+        return ["v_lshrrev_b32_e32 v%d, 5, v%d" % (vo, vl), "v_lshlrev_b32_e32 v%d, 3, v%d" % (vo, vo),
+                "s_cmp_gt_i32 s87, 256", "s_cselect_b32 s75, 1, 0", "s_mov_b32 s74, 1", "s_mov_b64 exec, s[74:75]",
+                "global_store_dwordx2 v%d, %s, s[80:81]" % (vo, pair(acc[0])), "s_mov_b64 exec, -1"]
+
+    def wave_sum():
+        """The butterfly sum over lanes 32, 16, 8, 4, 2, 1 apart, without LDS:
+        half and row exchanges (v_permlane*_swap), then rotations within a row
+        and a quad, which reach the same partner once the wider steps have
+        made the values equal."""
+        S = []
+        a, t = acc[0], tmp
+        if nb == 1:
+            S += ["v_mov_b32_e32 v%d, v%d" % (t, a), "v_mov_b32_e32 v%d, v%d" % (t + 1, a + 1)]
+        else:
+            t = acc[1]
+        S += ["s_nop 1", "v_permlane32_swap_b32 v%d, v%d" % (a, t), "v_permlane32_swap_b32 v%d, v%d" % (a + 1, t + 1),
+              "s_nop 1", "v_add_f64 %s, %s, %s" % (pair(a), pair(a), pair(t))]
+        t = tmp
+        S += ["v_mov_b32_e32 v%d, v%d" % (t, a), "v_mov_b32_e32 v%d, v%d" % (t + 1, a + 1), "s_nop 1",
+              "v_permlane16_swap_b32 v%d, v%d" % (a, t), "v_permlane16_swap_b32 v%d, v%d" % (a + 1, t + 1),
+              "s_nop 1", "v_add_f64 %s, %s, %s" % (pair(a), pair(a), pair(t))]
+        for ctl in ("row_ror:8", "row_ror:4", "quad_perm:[2,3,0,1]", "quad_perm:[1,0,3,2]"):
+            S += ["s_nop 1", "v_mov_b32_dpp v%d, v%d %s row_mask:0xf bank_mask:0xf" % (t, a, ctl),
+                  "v_mov_b32_dpp v%d, v%d %s row_mask:0xf bank_mask:0xf" % (t + 1, a + 1, ctl),
+                  "v_add_f64 %s, %s, %s" % (pair(a), pair(a), pair(t))]
+        return S
+
+    done = ["s_branch .Lgpx_next_%s" % tag]
+    for k in kinds:
+        name = lab[k]
+        if k != kinds[0]:
+            L += [".Lgpx_%s_%s:" % (name, tag)]
+        if k == OUT_CASES:
+            L += ["v_lshlrev_b32_e32 v%d, 2, v%d" % (vl, vl),
+                  "s_mul_i32 s72, s80, s84", "s_mul_hi_u32 s73, s80, s84", "s_mul_i32 s74, s80, s85",
+                  "s_add_u32 s73, s73, s74", "s_add_u32 s80, s72, s94", "s_addc_u32 s81, s73, s95"]
+            for j in range(T):
+                L += exec_slot(j)
+                L += ["global_store_dword v%d, %s, s[80:81] offset:%d" % (vl, o(j), 256 * j)]
+            L += ["s_mov_b64 exec, -1"] + done
+            continue
+        L += to_partials
+        if k in (FIT_MSE, FIT_SUM_ABS):
+            cvt = (lambda d, s: "v_cvt_f64_f32_e32 %s, %s" % (pair(d), s)) if k == FIT_MSE else \
+                (lambda d, s: "v_cvt_f64_f32_e64 %s, |%s|" % (pair(d), s))
+            for j in range(T):
+                L += ["v_sub_f32_e32 %s, %s, %s" % (o(j), o(j), y(j))]
+                if k == FIT_MSE:
+                    L += ["v_mul_f32_e32 %s, %s, %s" % (o(j), o(j), o(j))]
+            L += ["s_cmp_lt_i32 s87, %d" % full, "s_cbranch_scc1 .Lgpx_r%s_%s" % (name, tag)]
+            for b in range(nb):
+                L += [cvt(acc[b], o(4 * b))]
+                for j in range(4 * b + 1, 4 * b + 4):
+                    L += [cvt(tmp, o(j)), "v_add_f64 %s, %s, %s" % (pair(acc[b]), pair(acc[b]), pair(tmp))]
+            L += [".Lgpx_w%s_%s:" % (name, tag)] + wave_sum()
+        elif mode == 2:
+            # words: matching bits, counted per lane, then over the row and the wave (whole numbers: any order)
+            L += ["s_cmp_lt_u32 s98, %d" % (32 * full), "s_cbranch_scc1 .Lgpx_r%s_%s" % (name, tag)]
+            for j in range(T):
+                L += ["v_xnor_b32_e32 %s, %s, %s" % (o(j), o(j), y(j))]
+            L += [".Lgpx_w%s_%s:" % (name, tag)]
+            for b in range(nb):
+                L += ["v_bcnt_u32_b32 v%d, %s, 0" % (acc[b], o(4 * b))]
+                for j in range(4 * b + 1, 4 * b + 4):
+                    L += ["v_bcnt_u32_b32 v%d, %s, v%d" % (acc[b], o(j), acc[b])]
+            for b in range(nb):
+                for ctl in ("row_ror:8", "row_ror:4", "row_ror:2", "row_ror:1"):
+                    L += ["s_nop 1", "v_add_u32_dpp v%d, v%d, v%d %s row_mask:0xf bank_mask:0xf"
+                          % (acc[b], acc[b], acc[b], ctl)]
+            L += ["s_nop 1"]
+            for b in range(nb):
+                L += ["v_readlane_b32 s72, v%d, 0" % acc[b], "v_readlane_b32 s73, v%d, 16" % acc[b],
+                      "v_readlane_b32 s74, v%d, 32" % acc[b], "v_readlane_b32 s75, v%d, 48" % acc[b],
+                      "s_add_u32 s72, s72, s73", "s_add_u32 s74, s74, s75", "s_add_u32 s%d, s72, s74" % (77 if b else 76)]
+            L += count_out(nb, acc, tmp)
+        else:
+            L += ["s_cmp_lt_i32 s87, %d" % full, "s_cbranch_scc1 .Lgpx_r%s_%s" % (name, tag)]
+            L += hit_terms(k, T, o, y, False)
+            L += [".Lgpx_w%s_%s:" % (name, tag)] + count_out(nb, acc, tmp)
+        L += store_sum() + done
+    # ragged tiles (and, for Boolean programs, the data's last words)
+    for k in kinds:
+        name = lab[k]
+        if k == OUT_CASES:
+            continue
+        L += [".Lgpx_r%s_%s:" % (name, tag)]
+        if k in (FIT_MSE, FIT_SUM_ABS):
+            for b in range(nb):
+                L += ["v_mov_b32_e32 v%d, 0" % acc[b], "v_mov_b32_e32 v%d, 0" % (acc[b] + 1)]
+            for j in range(T):
+                a = acc[j // 4]
+                cv = "v_cvt_f64_f32_e32 %s, %s" % (pair(tmp), o(j)) if k == FIT_MSE else \
+                    "v_cvt_f64_f32_e64 %s, |%s|" % (pair(tmp), o(j))
+                L += exec_slot(j) + [cv, "v_add_f64 %s, %s, %s" % (pair(a), pair(a), pair(tmp))]
+            L += ["s_mov_b64 exec, -1"]
+        elif mode == 2:
+            # bits left in the word of slot j: s98 - 32 (64 j + lane), as a mask of 0 .. 32 low bits
+            L += ["v_lshlrev_b32_e32 v%d, 5, v%d" % (tmp, vl), "v_sub_u32_e32 v%d, s98, v%d" % (tmp, tmp)]
+            for j in range(T):
+                L += ["v_add_u32_e32 v%d, 0x%x, v%d" % (tmp + 1, (-2048 * j) & 0xFFFFFFFF, tmp),
+                      "v_med3_i32 v%d, v%d, 0, 32" % (tmp + 1, tmp + 1),
+                      "v_sub_u32_e32 v%d, 32, v%d" % (tmp + 1, tmp + 1),
+                      # ~0 >> (32 - bits); the shift takes 5 bits, so no bits at all is patched to 0
+                      "v_lshrrev_b32_e64 v%d, v%d, -1" % (vo, tmp + 1),
+                      "v_cmp_gt_u32_e32 vcc, 32, v%d" % (tmp + 1),
+                      "v_xnor_b32_e32 %s, %s, %s" % (o(j), o(j), y(j)), "s_nop 1",
+                      "v_cndmask_b32_e32 v%d, 0, v%d, vcc" % (vo, vo),
+                      "v_and_b32_e32 %s, %s, v%d" % (o(j), o(j), vo)]
+        else:
+            L += hit_terms(k, T, o, y, True)
+            L += ["s_mov_b64 exec, -1"]
+        L += ["s_branch .Lgpx_w%s_%s" % (name, tag)]
+    L += [".Lgpx_next_%s:" % tag, "s_cmp_ge_u32 s62, s96", "s_cbranch_scc0 .Lgpx_rest_%s" % tag,
+          ".Lgpx_probe_%s:" % tag, "s_branch .Lgpx_leave_%s" % tag]
+    L += [".Lgpx_rest_%s:" % tag, "s_waitcnt lgkmcnt(0)", "s_cmp_eq_u32 s99, 0", "s_cbranch_scc1 .Lgpx_go_%s" % tag,
+          "s_lshl_b32 s72, s78, 6", "s_add_u32 s58, s58, s72", "s_addc_u32 s59, s59, 0"]
+    L += prefetch_lines(tag, "2")
+    L += ["s_branch .Lgpx_rest_%s" % tag, ".Lgpx_go_%s:" % tag, "s_setpc_b64 s[64:65]"]
+    return L
+
+
+def hit_terms(kind, T, o, y, ragged):
+    """Counts of a block's hits (sign rule) or class errors (rint(o) is not the class), into s[76 + block]."""
+    L = []
+    for j in range(T):
+        cnt = "s%d" % (76 + j // 4)
+        if ragged:
+            # a compare writes 0 for the lanes outside exec
+            L += exec_slot(j)
+        if kind == FIT_HITS:
+            L += ["v_cmp_lt_f32_e32 vcc, 0, %s" % o(j), "v_cmp_lt_f32_e64 s[72:73], 0, %s" % y(j),
+                  "s_xnor_b64 s[72:73], vcc, s[72:73]"]
+            if ragged:
+                L += ["s_and_b64 s[72:73], s[72:73], exec"]
+        else:
+            L += ["v_rndne_f32_e32 %s, %s" % (o(j), o(j)), "v_cmp_neq_f32_e64 s[72:73], %s, %s" % (o(j), y(j))]
+        if j % 4 == 0:
+            L += ["s_bcnt1_i32_b64 %s, s[72:73]" % cnt]
+        else:
+            L += ["s_bcnt1_i32_b64 s74, s[72:73]", "s_add_u32 %s, %s, s74" % (cnt, cnt)]
+    return L
+
+
+def count_out(nb, acc, tmp):
+    """Block counts in s76 (and s77) as binary64, where store_sum takes them."""
+    L = ["v_mov_b32_e32 v%d, s76" % tmp]
+    if nb == 2:
+        L += ["s_mov_b32 s74, 0", "s_mov_b32 s75, -1", "s_mov_b64 exec, s[74:75]", "v_mov_b32_e32 v%d, s77" % tmp,
+              "s_mov_b64 exec, -1"]
+    return L + ["v_cvt_f64_u32_e32 %s, v%d" % (pair(acc[0]), tmp)]
+
+
+def transc(T, V0, NCV, tag, mode):
+    """sin, cos, exp and log of T slots (s72 the operation, s66 the payload,
+    s67 a constant operand): the arithmetic of gp_math.h, instruction by
+    instruction, in the block's work registers, with operand and result
+    through the index mode and no copies for cos and log.  The record pair
+    after the exit is loaded meanwhile."""
+    n = transc_slots(NCV)
+    w0 = V0 - 14 * n - 2
+    G = V0 - 2                                  # a pair shared by the slots (large arguments)
+    keep = NCV >= 64
+
+    def reg(i):
+        b = w0 + 14 * i                          # X r V C D(4) E a
+        return dict(X=b, R=b + 2, V=b + 4, C=b + 6, D=b + 8, E=b + 12, a=b + 13)
+
+    names = list(VCONST)
+
+    def vc(nm):                                  # register of a VGPR constant
+        return vconst_reg(V0, mode, names.index(nm)) if keep else None
+
+    def coef(nm):
+        return sp(COEF[nm])
+    L = [".Lgpx_fn_%s:" % tag, "s_and_b32 s73, s66, 0xff", "s_bfe_u32 s79, s66, 0x80010", "s_bitcmp1_b32 s66, 28",
+         "s_cbranch_scc0 .Lgpx_fa_%s" % tag, "s_set_gpr_idx_on s79, gpr_idx(DST)"]
+    L += ["v_mov_b32_e32 v%d, s67" % (V0 + j) for j in range(T)]
+    L += ["s_set_gpr_idx_off", "s_mov_b32 s73, s79", ".Lgpx_fa_%s:" % tag, "s_add_u32 s62, s62, 16",
+          "s_load_dwordx8 s[64:71], s[60:61], s62",
+          "s_cmp_eq_u32 s72, 6", "s_cbranch_scc1 .Lgpx_exp_%s" % tag,
+          "s_cmp_eq_u32 s72, 7", "s_cbranch_scc1 .Lgpx_log_%s" % tag,
+          "s_cmp_eq_u32 s72, 5", "s_cbranch_scc1 .Lgpx_cos_%s" % tag]
+    fin = ["s_waitcnt lgkmcnt(0)", "s_setpc_b64 s[64:65]"]
+    out_of_line = []
+
+    def const(nm, into):
+        """A VGPR constant's register: kept, or moved into `into` now."""
+        if keep:
+            return pair(vc(nm)), []
+        hi, lo = VCONST[nm]
+        return pair(into), ["v_mov_b32_e32 v%d, 0x%x" % (into, lo), "v_mov_b32_e32 v%d, 0x%x" % (into + 1, hi)]
+
+    def weave(seqs):
+        out = []
+        for k in range(max(len(x) for x in seqs)):
+            out += [x[k] for x in seqs if k < len(x)]
+        return out
+
+    def idx(sreg, field, body):
+        return ["s_set_gpr_idx_on %s, gpr_idx(%s)" % (sreg, field)] + body + ["s_set_gpr_idx_off"]
+
+    for fn in ("sin", "cos"):
+        if fn == "cos":
+            L += [".Lgpx_cos_%s:" % tag]
+        for g in range(0, T, n):
+            rs = [reg(i) for i in range(n)]
+            src = ["v%d" % (V0 + g + i) for i in range(n)]
+            if fn == "sin":
+                L += idx("s73", "SRC0", ["v_mov_b32_e32 v%d, %s" % (r["a"], s) for r, s in zip(rs, src)])
+                L += ["v_cvt_f64_f32_e32 %s, v%d" % (pair(r["X"]), r["a"]) for r in rs]
+            else:
+                L += idx("s73", "SRC0", ["v_cvt_f64_f32_e32 %s, %s" % (pair(r["X"]), s) for r, s in zip(rs, src)])
+            seqs = []
+            for r in rs:
+                q = []
+                R, mv = const("R", r["C"])
+                q += mv
+                q += ["v_fma_f64 %s, %s, %s, %s" % (pair(r["V"]), pair(r["X"]), coef("KPI"), R),
+                      "v_add_f64 %s, %s, -%s" % (pair(r["C"]), pair(r["V"]), R),
+                      "v_fma_f64 %s, -%s, %s, %s" % (pair(r["R"]), pair(r["C"]), coef("P1"), pair(r["X"])),
+                      "v_fma_f64 %s, -%s, %s, %s" % (pair(r["R"]), pair(r["C"]), coef("P2"), pair(r["R"])),
+                      "v_fma_f64 %s, -%s, %s, %s" % (pair(r["R"]), pair(r["C"]), coef("P3"), pair(r["R"]))]
+                seqs.append(q)
+            L += weave(seqs)
+            # any argument of 2^44 or more (its high word; the sign shifted out): another reduction
+            big, back = ".Lgpx_big_%s%d_%s" % (fn, g, tag), ".Lgpx_red_%s%d_%s" % (fn, g, tag)
+            if n == 2:
+                L += ["v_max_f64 %s, |%s|, |%s|" % (pair(rs[0]["D"]), pair(rs[0]["X"]), pair(rs[1]["X"]))]
+                L += ["v_cmp_lt_u32_e32 vcc, 0x42afffff, v%d" % (rs[0]["D"] + 1)]
+            else:
+                L += ["v_and_b32_e32 v%d, 0x7fffffff, v%d" % (rs[0]["D"], rs[0]["X"] + 1),
+                      "v_cmp_lt_u32_e32 vcc, 0x42afffff, v%d" % rs[0]["D"]]
+            L += ["s_cbranch_vccnz %s" % big, "%s:" % back]
+            out_of_line += ["%s:" % big]
+            for r in rs:
+                out_of_line += big_reduction(r, G)
+            out_of_line += ["s_branch %s" % back]
+            seqs = []
+            for r in rs:
+                q = ["v_lshlrev_b32_e32 v%d, 4, v%d" % (r["V"], r["V"])]
+                if fn == "cos":      # a quarter turn on: entry j + 32
+                    q = ["v_lshlrev_b32_e32 v%d, 4, v%d" % (r["V"], r["V"]), "v_add_u32_e32 v%d, 0x200, v%d" % (r["V"], r["V"])]
+                q += ["v_and_b32_e32 v%d, 0x7f0, v%d" % (r["V"], r["V"]),
+                      "ds_read_b128 %s, v%d offset:%d" % (quad(r["D"]), r["V"], LDS_SC),
+                      "v_mul_f64 %s, %s, %s" % (pair(r["C"]), pair(r["R"]), pair(r["R"]))]
+                S1, mv = const("S1", r["V"])
+                q += mv + ["v_fma_f64 %s, %s, %s, %s" % (pair(r["X"]), pair(r["C"]), coef("S2"), S1),
+                           "v_fma_f64 %s, %s, %s, %s" % (pair(r["X"]), pair(r["X"]), pair(r["C"]), coef("S0"))]
+                C1, mv = const("C1", r["V"])
+                tv = pair(r["V"])
+                q += mv + ["v_fma_f64 %s, %s, %s, %s" % (tv, pair(r["C"]), coef("C2"), C1),
+                           "v_fma_f64 %s, %s, %s, -0.5" % (tv, tv, pair(r["C"])),
+                           "v_fma_f64 %s, %s, %s, 1.0" % (tv, tv, pair(r["C"])),            # cos r
+                           "v_mul_f64 %s, %s, %s" % (pair(r["C"]), pair(r["R"]), pair(r["C"])),
+                           "v_fma_f64 %s, %s, %s, %s" % (pair(r["R"]), pair(r["C"]), pair(r["X"]), pair(r["R"]))]  # sin r
+                seqs.append(q)
+            L += weave(seqs) + ["s_waitcnt lgkmcnt(0)"]
+            seqs = []
+            for r in rs:
+                seqs.append(["v_mul_f64 %s, %s, %s" % (pair(r["R"]), pair(r["D"] + 2), pair(r["R"])),
+                             "v_fma_f64 %s, %s, %s, %s" % (pair(r["R"]), pair(r["D"]), pair(r["V"]), pair(r["R"]))])
+            L += weave(seqs)
+            if fn == "sin":
+                for r in rs:
+                    L += ["v_cvt_f32_f64_e32 v%d, %s" % (r["V"], pair(r["R"]))]
+                L += ["s_mov_b32 s80, 0x39800000"]            # |a| below 2^-12: a itself
+                for i, r in enumerate(rs):
+                    L += ["v_cmp_lt_f32_e64 s[%d:%d], |v%d|, s80" % (74 + 2 * i, 75 + 2 * i, r["a"])]
+                L += ["s_nop 1"]
+                L += idx("s79", "DST", ["v_cndmask_b32_e64 %s, v%d, v%d, s[%d:%d]" % (s, r["V"], r["a"], 74 + 2 * i, 75 + 2 * i)
+                                        for i, (r, s) in enumerate(zip(rs, src))])
+            else:
+                L += idx("s79", "DST", ["v_cvt_f32_f64_e32 %s, %s" % (s, pair(r["R"])) for r, s in zip(rs, src)])
+        L += fin
+    L += [".Lgpx_exp_%s:" % tag, "s_mov_b32 s80, 0xc2d00000", "s_mov_b32 s81, 0x42b00000"]
+    for g in range(0, T, n):
+        rs = [reg(i) for i in range(n)]
+        src = ["v%d" % (V0 + g + i) for i in range(n)]
+        L += idx("s73", "SRC0", ["v_mov_b32_e32 v%d, %s" % (r["a"], s) for r, s in zip(rs, src)])
+        seqs = []
+        for r in rs:
+            # clamped to [-104, 88]; a NaN is put back at the end
+            q = ["v_max_f32_e32 v%d, s80, v%d" % (r["E"], r["a"]), "v_min_f32_e32 v%d, s81, v%d" % (r["E"], r["E"]),
+                 "v_cvt_f64_f32_e32 %s, v%d" % (pair(r["X"]), r["E"])]
+            R, mv = const("R", r["C"])
+            q += mv + ["v_fma_f64 %s, %s, %s, %s" % (pair(r["V"]), pair(r["X"]), coef("KLN"), R),
+                       "v_add_f64 %s, %s, -%s" % (pair(r["C"]), pair(r["V"]), R),
+                       "v_lshlrev_b32_e32 v%d, 3, v%d" % (r["E"], r["V"]), "v_and_b32_e32 v%d, 0x1f8, v%d" % (r["E"], r["E"]),
+                       "ds_read_b64 %s, v%d offset:%d" % (pair(r["D"]), r["E"], LDS_EXP),
+                       "v_fma_f64 %s, -%s, %s, %s" % (pair(r["X"]), pair(r["C"]), coef("L1"), pair(r["X"])),
+                       "v_fma_f64 %s, -%s, %s, %s" % (pair(r["X"]), pair(r["C"]), coef("L2"), pair(r["X"])),
+                       "v_ashrrev_i32_e32 v%d, 6, v%d" % (r["E"], r["V"])]
+            E2, mv = const("E2", r["C"])
+            t = pair(r["R"])
+            q += mv + ["v_fma_f64 %s, %s, %s, %s" % (t, pair(r["X"]), coef("E3"), E2),
+                       "v_fma_f64 %s, %s, %s, %s" % (t, t, pair(r["X"]), coef("E1")),
+                       "v_fma_f64 %s, %s, %s, 0.5" % (t, t, pair(r["X"])),
+                       "v_fma_f64 %s, %s, %s, 1.0" % (t, t, pair(r["X"])),
+                       "v_fma_f64 %s, %s, %s, 1.0" % (t, t, pair(r["X"]))]
+            seqs.append(q)
+        L += weave(seqs) + ["s_waitcnt lgkmcnt(0)"]
+        seqs = [["v_mul_f64 %s, %s, %s" % (pair(r["R"]), pair(r["D"]), pair(r["R"])),
+                 "v_ldexp_f64 %s, %s, v%d" % (pair(r["R"]), pair(r["R"]), r["E"]),
+                 "v_cvt_f32_f64_e32 v%d, %s" % (r["V"], pair(r["R"])),
+                 "v_cmp_u_f32_e64 s[%d:%d], v%d, v%d" % (74 + 2 * i, 75 + 2 * i, r["a"], r["a"])] for i, r in enumerate(rs)]
+        L += weave(seqs) + ["s_nop 1"]
+        L += idx("s79", "DST", ["v_cndmask_b32_e64 %s, v%d, v%d, s[%d:%d]" % (s, r["V"], r["a"], 74 + 2 * i, 75 + 2 * i)
+                                for i, (r, s) in enumerate(zip(rs, src))])
+    L += fin
+    L += [".Lgpx_log_%s:" % tag, "s_mov_b32 s80, 0x%x" % DIV_THRESHOLD, "s_mov_b32 s81, 0x7f800000"]
+    c0 = (0x3F3504F3 + 0x4000 - (LOG_K0 << 15)) & 0xFFFFFFFF
+    for g in range(0, T, n):
+        rs = [reg(i) for i in range(n)]
+        src = ["v%d" % (V0 + g + i) for i in range(n)]
+        L += idx("s73", "SRC1", ["v_and_b32_e32 v%d, 0x7fffffff, %s" % (r["a"], s) for r, s in zip(rs, src)])
+        seqs = []
+        for r in rs:
+            # the encoding relative to sqrt(1/2): exponent e, f in [sqrt(1/2), sqrt(2)), its bucket's table entry;
+            # any encoding gives a valid bucket, so zeros, infinities and NaN are put right at the end
+            q = ["v_add_u32_e32 v%d, 0x%x, v%d" % (r["V"], (-0x3F3504F3) & 0xFFFFFFFF, r["a"]),
+                 "v_ashrrev_i32_e32 v%d, 23, v%d" % (r["E"], r["V"]),
+                 "v_and_b32_e32 v%d, 0x7fffff, v%d" % (r["V"], r["V"]),
+                 "v_add_u32_e32 v%d, 0x%x, v%d" % (r["V"] + 1, c0, r["V"]),
+                 "v_lshrrev_b32_e32 v%d, 11, v%d" % (r["V"] + 1, r["V"] + 1),
+                 "v_and_b32_e32 v%d, 0xfffffff0, v%d" % (r["V"] + 1, r["V"] + 1),
+                 "ds_read_b128 %s, v%d offset:%d" % (quad(r["D"]), r["V"] + 1, LDS_LOG),
+                 "v_add_u32_e32 v%d, 0x3f3504f3, v%d" % (r["V"], r["V"]),
+                 "v_cvt_f64_f32_e32 %s, v%d" % (pair(r["X"]), r["V"]),
+                 "v_cvt_f64_i32_e32 %s, v%d" % (pair(r["R"]), r["E"])]
+            seqs.append(q)
+        L += weave(seqs) + ["s_waitcnt lgkmcnt(0)"]
+        seqs = []
+        for i, r in enumerate(rs):
+            G3, mv = const("G3", r["C"])
+            t = pair(r["V"])
+            q = ["v_fma_f64 %s, %s, %s, -1.0" % (pair(r["X"]), pair(r["X"]), pair(r["D"]))]
+            q += mv + ["v_fma_f64 %s, %s, %s, %s" % (t, pair(r["X"]), coef("G4"), G3),
+                       "v_fma_f64 %s, %s, %s, %s" % (t, t, pair(r["X"]), coef("G2")),
+                       "v_fma_f64 %s, %s, %s, %s" % (t, t, pair(r["X"]), coef("G1")),
+                       "v_fma_f64 %s, %s, %s, -0.5" % (t, t, pair(r["X"])),
+                       "v_mul_f64 %s, %s, %s" % (pair(r["C"]), pair(r["X"]), pair(r["X"])),
+                       "v_fma_f64 %s, %s, %s, %s" % (t, pair(r["C"]), t, pair(r["X"])),
+                       "v_add_f64 %s, %s, %s" % (t, pair(r["D"] + 2), t),
+                       "v_fma_f64 %s, %s, %s, %s" % (t, pair(r["R"]), coef("LN2"), t),
+                       "v_cvt_f32_f64_e32 v%d, %s" % (r["V"], t),
+                       "v_cmp_gt_u32_e64 s[%d:%d], s81, v%d" % (74 + 2 * i, 75 + 2 * i, r["a"]), "s_nop 1",
+                       "v_cndmask_b32_e64 v%d, v%d, v%d, s[%d:%d]" % (r["V"], r["a"], r["V"], 74 + 2 * i, 75 + 2 * i),
+                       "v_cmp_gt_f32_e64 s[%d:%d], s80, v%d" % (74 + 2 * i, 75 + 2 * i, r["a"])]
+            seqs.append(q)
+        L += weave(seqs) + ["s_nop 1"]
+        L += idx("s79", "DST", ["v_cndmask_b32_e64 %s, v%d, 0, s[%d:%d]" % (s, r["V"], 74 + 2 * i, 75 + 2 * i)
+                                for i, (r, s) in enumerate(zip(rs, src))])
+    L += fin
+    return L + out_of_line
+
+
+def big_reduction(r, G):
+    """x mod 2 pi for the lanes with |x| >= 2^44 (gp_math.h, reduce_big):
+    r and the low word of V (k) are replaced there.  E: 37 n >> 10 is n div 28
+    for n up to 103."""
+    X, A, P2, K = pair(r["X"]), pair(r["C"]), pair(r["D"] + 2), pair(G)
+    D = pair(r["D"])
+    E = "v%d" % r["E"]
+    v1 = pair(r["D"])
+    L = ["v_cvt_f32_f64_e64 %s, |%s|" % (E, X),
+         "v_lshrrev_b32_e32 %s, 23, %s" % (E, E), "v_max_u32_e32 %s, 0xab, %s" % (E, E),
+         "v_subrev_u32_e32 %s, 0x98, %s" % (E, E), "v_mul_u32_u24_e32 %s, 37, %s" % (E, E),
+         "v_lshrrev_b32_e32 %s, 10, %s" % (E, E), "v_lshlrev_b32_e32 %s, 3, %s" % (E, E),
+         # v0 in C
+         "ds_read_b64 %s, %s offset:%d" % (A, E, LDS_PI), "s_waitcnt lgkmcnt(0)",
+         "v_mul_f64 %s, |%s|, %s" % (A, X, A), "v_ldexp_f64 %s, %s, -7" % (K, A), "v_floor_f64_e32 %s, %s" % (K, K),
+         "v_ldexp_f64 %s, -%s, 7" % (K, K), "v_add_f64 %s, %s, %s" % (A, K, A),
+         # v1 in D
+         "ds_read_b64 %s, %s offset:%d" % (v1, E, LDS_PI + 8), "s_waitcnt lgkmcnt(0)",
+         "v_mul_f64 %s, |%s|, %s" % (v1, X, v1), "v_ldexp_f64 %s, %s, -7" % (K, v1), "v_floor_f64_e32 %s, %s" % (K, K),
+         "v_ldexp_f64 %s, -%s, 7" % (K, K), "v_add_f64 %s, %s, %s" % (v1, K, v1),
+         # p2, and kd = rint(v0 + v1 + p2)
+         "ds_read_b64 %s, %s offset:%d" % (P2, E, LDS_PI + 16), "s_waitcnt lgkmcnt(0)",
+         "v_mul_f64 %s, |%s|, %s" % (P2, X, P2),
+         "v_add_f64 %s, %s, %s" % (K, A, v1), "v_add_f64 %s, %s, %s" % (K, K, P2), "v_rndne_f64_e32 %s, %s" % (K, K),
+         # s = (((v0 - kd) + v1) + p2 + p3) + p4
+         "v_add_f64 %s, %s, -%s" % (A, A, K), "v_add_f64 %s, %s, %s" % (A, A, v1), "v_add_f64 %s, %s, %s" % (A, A, P2),
+         "ds_read_b64 %s, %s offset:%d" % (v1, E, LDS_PI + 24), "ds_read_b64 %s, %s offset:%d" % (P2, E, LDS_PI + 32),
+         "s_waitcnt lgkmcnt(0)",
+         "v_mul_f64 %s, |%s|, %s" % (v1, X, v1), "v_mul_f64 %s, |%s|, %s" % (P2, X, P2),
+         "v_add_f64 %s, %s, %s" % (A, A, v1), "v_add_f64 %s, %s, %s" % (A, A, P2),
+         "v_mul_f64 %s, %s, %s" % (A, A, sp(COEF["P1"])),
+         # the sign of x, on r and k
+         "v_and_b32_e32 %s, 0x80000000, v%d" % (E, r["X"] + 1),
+         "v_xor_b32_e32 v%d, %s, v%d" % (r["C"] + 1, E, r["C"] + 1), "v_xor_b32_e32 v%d, %s, v%d" % (G + 1, E, G + 1),
+         "v_cvt_i32_f64_e32 v%d, %s" % (G, K),
+         "v_and_b32_e32 %s, 0x7fffffff, v%d" % (E, r["X"] + 1), "v_cmp_lt_u32_e32 vcc, 0x42afffff, %s" % E, "s_nop 1",
+         "v_cndmask_b32_e32 v%d, v%d, v%d, vcc" % (r["R"], r["R"], r["C"]),
+         "v_cndmask_b32_e32 v%d, v%d, v%d, vcc" % (r["R"] + 1, r["R"] + 1, r["C"] + 1),
+         "v_cndmask_b32_e32 v%d, v%d, v%d, vcc" % (r["V"], r["V"], G)]
+    return L
+
+
+def tail_lines(T, D, NF, V0, FO, tag, mode):
+    """What follows the handlers in the block: an exit's record is in s[66:67]."""
+    L = [".Lgpx_end_%s:" % tag]
+    if mode in (0, 4):
+        L += ["s_bfe_u32 s72, s66, 0x40018", "s_cmp_lg_u32 s72, 15", "s_cbranch_scc1 .Lgpx_fn_%s" % tag]
+    L += program_end(T, D, NF, V0, FO, tag, mode)
+    if mode in (0, 4):
+        L += transc(T, V0, V0, tag, mode)
+    L += [".Lgpx_leave_%s:" % tag, "s_waitcnt vmcnt(0) lgkmcnt(0)"]
+    return L
+
+
+def asm_text(T, D, NF, V0, FO, tag, hs, mode):
     L = []
     L.append("s_getpc_b64 s[76:77]")
     L.append(".Lgpx_pc_%s:" % tag)
@@ -693,30 +1260,9 @@ def asm_text(T, D, NF, tag, hs):
     L.append("s_cbranch_scc1 .Lgpx_run_%s" % tag)
     L.append("s_add_u32 s76, s76, .Lgpx_table_%s-.Lgpx_pc_%s" % (tag, tag))
     L.append("s_addc_u32 s77, s77, 0")
-    L.append("s_branch .Lgpx_end_%s" % tag)
+    L.append("s_branch .Lgpx_probe_%s" % tag)
     L.append(".Lgpx_run_%s:" % tag)
-    # Burst-load the program's remaining 64-byte lines (from the current
-    # record's line up to byte offset s75) into the scalar cache, up to s78
-    # loads in flight, so the handlers' record loads then hit.  s75 = 0 skips
-    # it (re-entry after an exit).  s76 only receives data; every load is
-    # waited for before the first handler runs.
-    L.append("s_and_b32 s73, s62, 0xffffffc0")
-    L.append("s_mov_b32 s74, 0")
-    L.append(".Lgpx_pf_%s:" % tag)
-    L.append("s_cmp_lt_u32 s73, s75")
-    L.append("s_cbranch_scc0 .Lgpx_pfdone_%s" % tag)
-    L.append("s_load_dword s76, s[60:61], s73")
-    L.append("s_add_u32 s73, s73, 64")
-    L.append("s_add_u32 s74, s74, 1")
-    L.append("s_cmp_lt_u32 s74, s78")
-    L.append("s_cbranch_scc1 .Lgpx_pf_%s" % tag)
-    L.append("s_waitcnt lgkmcnt(0)")
-    L.append("s_mov_b32 s74, 0")
-    L.append("s_branch .Lgpx_pf_%s" % tag)
-    L.append(".Lgpx_pfdone_%s:" % tag)
-    L.append("s_load_dwordx8 s[64:71], s[60:61], s62")   # this record and the next: phase A
-    L.append("s_waitcnt lgkmcnt(0)")
-    L.append("s_setpc_b64 s[64:65]")
+    L += unit_start(T, D, NF, V0, FO, tag, mode)
     L.append(".p2align %d" % (SLOT.bit_length() - 1))
     L.append(".Lgpx_table_%s:" % tag)
     for i, h in enumerate(hs):
@@ -730,44 +1276,20 @@ def asm_text(T, D, NF, tag, hs):
         # pad to the slot boundary (never executed: every handler ends in a jump)
         pad = (-h.size) % SLOT
         L.extend(["s_nop 0"] * (pad // 4))
-    L.append(".Lgpx_end_%s:" % tag)
-    return "\\n\\t".join(L)
+    L += tail_lines(T, D, NF, V0, FO, tag, mode)
+    # one string literal a line: the compiler locates each line of one long literal anew from its start
+    return "\\n\\t\"\n            \"".join(L)
 
 
-def gather_scatter(T, V0):
-    """C++ helpers moving T slots between compiler VGPRs and the core's range."""
+def relabelled(hs, tag):
+    """The handlers with their jumps to this block's own labels (two kernels may share a handler table's layout)."""
+    import re
     out = []
-    tv = "%d, %d" % (T, V0)
-    outs = ", ".join('"=v"(v[%d])' % j for j in range(T))
-    movs = "".join("v_mov_b32_e32 %%%d, %s\\n\\t" % (j, vr(V0 + j)) for j in range(T))
-    out.append("template <> __device__ __forceinline__ void core_gather<%s>(uint32_t off, float (&v)[%d]) {" % (tv, T))
-    out.append("#ifdef __HIP_DEVICE_COMPILE__")
-    out.append('    asm volatile("s_set_gpr_idx_on %%%d, gpr_idx(SRC0)\\n\\t%ss_set_gpr_idx_off" : %s : "s"(off) : "m0");'
-               % (T, movs, outs))
-    out.append("#endif")
-    out.append("}")
-    # gather, or broadcast the constant when use_const is nonzero: one scalar
-    # branch inside the asm, so the compiler cannot run both paths
-    cmovs = "".join("v_mov_b32_e32 %%%d, %%%d\\n\\t" % (j, T + 2) for j in range(T))
-    gmovs = "".join("v_mov_b32_e32 %%%d, %s\\n\\t" % (j, vr(V0 + j)) for j in range(T))
-    out.append("template <> __device__ __forceinline__ void core_gather_or_const<%s>(uint32_t off, uint32_t use_const, "
-               "uint32_t cbits, float (&v)[%d]) {" % (tv, T))
-    out.append("#ifdef __HIP_DEVICE_COMPILE__")
-    out.append('    asm volatile("s_cmp_eq_u32 %%%d, 0\\n\\ts_cbranch_scc1 1f\\n\\t%ss_branch 2f\\n1:\\n\\t'
-               's_set_gpr_idx_on %%%d, gpr_idx(SRC0)\\n\\t%ss_set_gpr_idx_off\\n2:" : %s : "s"(off), "s"(use_const), '
-               '"s"(cbits) : "m0", "scc");' % (T + 1, cmovs, T, gmovs, outs))
-    out.append("#endif")
-    out.append("}")
-    ins = ", ".join('"v"(v[%d])' % j for j in range(T))
-    movs = "".join("v_mov_b32_e32 %s, %%%d\\n\\t" % (vr(V0 + j), j + 1) for j in range(T))
-    out.append("template <> __device__ __forceinline__ void core_scatter<%s>(uint32_t off, const float (&v)[%d]) {"
-               % (tv, T))
-    out.append("#ifdef __HIP_DEVICE_COMPILE__")
-    out.append('    asm volatile("s_set_gpr_idx_on %%0, gpr_idx(DST)\\n\\t%ss_set_gpr_idx_off" : : "s"(off), %s : "m0");'
-               % (movs, ins))
-    out.append("#endif")
-    out.append("}")
-    return "\n".join(out)
+    for h in hs:
+        c = Handler(h.kind, h.op, h.p1, h.p2)
+        c.lines, c.size, c.slot = [re.sub(r"(\.Lgpx_end_)\w+", r"\g<1>" + tag, x) for x in h.lines], h.size, h.slot
+        out.append(c)
+    return out
 
 
 def main(out_dir):
@@ -780,47 +1302,51 @@ def main(out_dir):
     lines.append("#define GPX_CORE_VARIANTS(X) \\")
     lines.append(" \\\n".join("    X(%d, %d, %d, %d, %d)" % v for v in VARIANTS))
     lines.append("")
-    clob_s = ", ".join('"s%d"' % n for n in (63, 64, 65, 66, 67, 70, 71, 72, 76, 77))
-    lines.append("template <int T, int D, int NF, int V0, int K> struct Core;   // K: 0 arithmetic, 2 Boolean, 3 trees only")
-    lines.append("template <int T, int V0> __device__ void core_gather(uint32_t off, float (&v)[T]);")
-    lines.append("template <int T, int V0> __device__ void core_scatter(uint32_t off, const float (&v)[T]);")
-    lines.append("template <int T, int V0> __device__ void core_gather_or_const(uint32_t off, uint32_t use_const, "
-                 "uint32_t cbits, float (&v)[T]);")
-    for T, V0 in sorted(set((v[0], v[3]) for v in VARIANTS)):
-        lines.append(gather_scatter(T, V0))
+    cores = []
+    lines.append("template <int T, int D, int NF, int V0, int K> struct Core;   // K: kernel mode")
+    lines.append("struct CoreUnit {")
+    lines.append("    uint64_t code, X, stride, y, partials, cases, coef;")
+    lines.append("    uint32_t off, end, n_load, left, part_stride, kind, lds_y, bits, burst;")
+    lines.append("};")
     host = []
     seen = {}
     for (T, D, NF, NCV, AR) in VARIANTS:
-        B = AR == 2
-        core = (T, D, NF, NCV, {1: 0, 4: 3}.get(AR, AR))   # modes 0 and 1 share a core, so do 3 and 4
-        if core in seen:
-            host.append((T, D, NF, NCV, AR) + seen[core])
-            continue
+        core = (T, D, NF, NCV, AR)
         tag, V0, FO, hs, nslots = gen_variant(T, D, NF, NCV, AR)
-        seen[core] = (tag, hs, nslots)
-        text = asm_text(T, D, NF, tag, hs)
-        clob_v = ", ".join('"%s"' % vr(n) for n in range(NCV, NCV + FO + NF * T))
-        if AR != 2:    # the division and classification handlers' temporaries, flags, indexes and threshold
-            clob_v += ", " + ", ".join('"%s"' % vr(n) for n in range(NCV - DIV_TMP, NCV)) + \
-                ', "vcc", "s79", "s80", "s81"'
-            assert NCV - DIV_TMP >= 24
+        tag += "A" if AR == 1 else "S" if AR == 4 else ""
+        key = (T, D, NF, NCV, {1: 0, 4: 3}.get(AR, AR))    # modes 0 and 1 share a handler table, so do 3 and 4
+        hs_tag, hs, nslots = seen.setdefault(key, (tag, hs, nslots))
+        text = asm_text(T, D, NF, V0, FO, tag, relabelled(hs, tag), AR)
         assert NCV + FO + NF * T <= 256
-        lines.append("template <> struct Core<%d, %d, %d, %d, %d> {" % (T, D, NF, NCV, core[4]))
-        lines.append("    // run from byte offset `off` until an exit; returns the exit's payload and constant")
-        lines.append("    // pf_end: byte offset where the program ends (its code is first burst-loaded into the")
-        lines.append("    // scalar cache, `burst` loads in flight at a time), or 0")
-        lines.append("    static __device__ __forceinline__ void run(uint64_t base, uint32_t& off, uint32_t& pay,"
-                     " uint32_t& cst, uint32_t probe, uint32_t pf_end, uint32_t burst, uint64_t& table) {")
-        lines.append("#ifdef __HIP_DEVICE_COMPILE__")
-        lines.append('        asm volatile("%s"' % text)
-        lines.append('            : "+{s62}"(off), "={s66}"(pay), "={s67}"(cst), "={s[76:77]}"(table)')
-        lines.append('            : "{s[60:61]}"(base), "{s63}"(probe), "{s75}"(pf_end), "{s78}"(burst)')
-        lines.append('            : %s, "s64", "s65", "s68", "s69", "s70", "s71", "s72", "s73", "s74", "scc", "m0",'
-                     ' "memory");' % clob_v)
-        lines.append("#endif")
-        lines.append("    }")
-        lines.append("};")
-        host.append((T, D, NF, NCV, AR, tag, hs, nslots))
+        work = work_regs(NCV, AR)
+        assert NCV - work >= 14, (T, D, NF, NCV, AR)
+        clob = ["v%d" % n for n in range(NCV - work, NCV + FO + NF * T)] + ["vcc", "scc", "m0", "memory"]
+        clob += ["s%d" % n for n in [58, 59] + list(range(64, 76)) + [79, 80, 81, 99]]
+        if AR in (0, 4):
+            clob += ["s%d" % n for n in range(24, 56)]
+        core_lines = []
+        core_lines.append("template <> struct Core<%d, %d, %d, %d, %d> {" % core)
+        core_lines.append("    // runs one unit: its tile is loaded, then its programs run to their partial sums (or outputs);")
+        core_lines.append("    // with `probe` only the address of the handler table is returned")
+        core_lines.append("    static __device__ __forceinline__ void run(const CoreUnit& u, uint32_t probe, uint64_t& table) {")
+        core_lines.append("#ifdef __HIP_DEVICE_COMPILE__")
+        core_lines.append("        uint32_t off = u.off;")
+        core_lines.append('        asm volatile("%s"' % text)
+        core_lines.append('            : "+{s62}"(off), "={s[76:77]}"(table)')
+        ins = [("s[60:61]", "u.code"), ("s63", "probe"), ("s78", "u.burst"), ("s[82:83]", "u.X"), ("s[84:85]", "u.stride"),
+               ("s86", "u.n_load"), ("s87", "u.left"), ("s[88:89]", "u.y"), ("s[90:91]", "u.partials"),
+               ("s92", "u.part_stride"), ("s93", "u.kind"), ("s[94:95]", "u.cases"), ("s96", "u.end"), ("s97", "u.lds_y")]
+        if AR == 2:
+            ins.append(("s98", "u.bits"))
+        if AR in (0, 4):
+            ins.append(("s[100:101]", "u.coef"))
+        core_lines.append("            : " + ", ".join('"{%s}"(%s)' % i for i in ins))
+        core_lines.append("            : " + ", ".join('"%s"' % x for x in clob) + ");")
+        core_lines.append("#endif")
+        core_lines.append("    }")
+        core_lines.append("};")
+        cores.append(core_lines)
+        host.append((T, D, NF, NCV, AR, hs_tag, hs, nslots))
     lines.append("")
     lines.append("struct CoreHandlerKey { uint8_t kind, op; int8_t p1, p2; };")
     done = set()
@@ -847,12 +1373,12 @@ def main(out_dir):
     disp = ["// Generated by gen_core.py -- do not edit.", "#pragma once", "",
             "typedef hipError_t (*CoreLaunchFn)(const CoreArgs&, uint32_t, hipStream_t);",
             "typedef int (*CoreOccupancyFn)();"]
-    for (T, D, NF, NCV, AR, tag, hs, nslots) in host:
+    for core_lines, (T, D, NF, NCV, AR, tag, hs, nslots) in zip(cores, host):
         name = vname((T, D, NF, NCV, AR))
         disp.append("hipError_t core_launch_%s(const CoreArgs& a, uint32_t blocks, hipStream_t s);" % name)
         disp.append("int core_occupancy_%s();" % name)
         tu = ["// Generated by gen_core.py -- do not edit.  Kernel variant %s." % tag,
-              '#include "core_body.h"', "", "namespace gpx {",
+              '#include "core_body.h"', "", "namespace gpx {"] + core_lines + ["",
               "GPX_KERNEL(%d, %d, %d, %d, %d, %s)" % (T, D, NF, NCV, AR, name), "",
               "hipError_t core_launch_%s(const CoreArgs& a, uint32_t blocks, hipStream_t s) {" % name,
               "    hipLaunchKernelGGL(k_core_%s, dim3(blocks), dim3(256), 0, s, a);" % name,

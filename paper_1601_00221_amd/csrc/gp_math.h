@@ -92,6 +92,17 @@ GPX_TABLE double kCoef[kCoSize] = {
     -0x1.5555555555555p-3,
 };
 
+// Constants of the evaluation kernel's own sin/cos/exp/log (gen_core.py, COEF
+// names their order), which performs the arithmetic of this file in the
+// interpreter block: 64/pi, pi/64 in three parts, the series coefficients it
+// reads from scalar registers, 64/ln 2, ln2/64 in two parts, ln 2.
+GPX_TABLE double kCoreCoef[16] = {
+    0x1.45f306dc9c883p+4, 0x1.921fb54442d18p-5, 0x1.1a62633145c07p-59, -0x1.f1976b7ed8fbcp-115,
+    kCoef[kCoSin], kCoef[kCoSin + 2], kCoef[kCoCos + 2], 0x1.71547652b82fep+6,
+    0x1.62e42fefa39efp-7, 0x1.abc9e3b39803fp-62, kCoef[kCoExp + 1], kCoef[kCoExp + 3],
+    0x1.62e42fefa39efp-1, kCoef[kCoLog + 1], kCoef[kCoLog + 2], kCoef[kCoLog + 4],
+};
+
 // 1.5 * 2^52: adding it to a binary64 value v with |v| < 2^51 rounds v to the
 // nearest integer, which the low 32 bits of the sum then hold (two's
 // complement).

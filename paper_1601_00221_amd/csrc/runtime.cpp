@@ -403,24 +403,32 @@ gp_status build_linear(const uint32_t* code, const int64_t* off, const float* cs
     return GP_OK;
 }
 
-// Programs sorted by cost (longest first) and dealt to G groups in snake
-// order, so every group carries about the same work.
-static void make_groups(const ProgData& pd, int32_t G, std::vector<uint32_t>& order,
-                        std::vector<uint32_t>& goff) {
+// Programs by falling cost: the order their code lies in on the device.
+void cost_order(const ProgData& pd, std::vector<uint32_t>& order) {
+    order.resize(pd.n_prog);
+    std::iota(order.begin(), order.end(), 0u);
+    std::stable_sort(order.begin(), order.end(), [&](uint32_t a, uint32_t b) { return pd.cost[a] > pd.cost[b]; });
+}
+
+// Cut the programs, in that order, into G runs of about equal cost: a group
+// is a range of records, so a wave walks one stream of code.  Each group takes
+// programs up to the mean of what is left (at least one), so with as many
+// groups as programs each holds one.
+void cut_groups(const ProgData& pd, const std::vector<uint32_t>& order, const std::vector<int64_t>& rec, int32_t G,
+                std::vector<uint32_t>& goff) {
     const int32_t P = pd.n_prog;
-    std::vector<uint32_t> idx(P);
-    std::iota(idx.begin(), idx.end(), 0u);
-    std::stable_sort(idx.begin(), idx.end(), [&](uint32_t a, uint32_t b) { return pd.cost[a] > pd.cost[b]; });
-    std::vector<std::vector<uint32_t>> g(G);
-    for (int32_t i = 0; i < P; i++) {
-        const int32_t r = i / G, k = i % G;
-        g[(r & 1) ? G - 1 - k : k].push_back(idx[i]);
-    }
-    order.clear();
-    goff.assign(1, 0);
-    for (int32_t k = 0; k < G; k++) {
-        order.insert(order.end(), g[k].begin(), g[k].end());
-        goff.push_back((uint32_t)order.size());
+    double left = 0.0;
+    for (int32_t i = 0; i < P; i++) left += pd.cost[order[i]];
+    goff.assign(1, (uint32_t)rec[0]);
+    int32_t i = 0;
+    for (int32_t g = 0; g < G; g++) {
+        const double want = left / (G - g);
+        const int32_t most = P - (G - g - 1);     // leave one program for each later group
+        double got = 0.0;
+        while (i < most && (got == 0.0 || got + 0.5 * pd.cost[order[i]] <= want)) got += pd.cost[order[i++]];
+        if (g == G - 1) i = P;
+        left -= got;
+        goff.push_back((uint32_t)rec[i]);
     }
 }
 
@@ -430,9 +438,8 @@ static void make_groups(const ProgData& pd, int32_t G, std::vector<uint32_t>& or
 // (`fresh`) keep a single group layout, replaced on every call.  G <= 0:
 // programs only.
 static gp_status prepare_programs(const ProgData& pd, int vi, DevProgs& dp, bool fresh, int32_t G, hipStream_t s,
-                                  Workspace& w, const uint32_t** order, const uint32_t** goff) {
-    std::vector<uint32_t> code, o, g;
-    std::vector<DevProg> progs;
+                                  Workspace& w, const uint32_t** goff) {
+    std::vector<uint32_t> code, g;
     gp_status st;
     const bool upload = fresh || !dp.uploaded;
     if (!upload && dp.ready) {
@@ -440,40 +447,34 @@ static gp_status prepare_programs(const ProgData& pd, int vi, DevProgs& dp, bool
         hipError_t e = hipStreamWaitEvent(s, dp.ready, 0);
         if (e != hipSuccess) return fail(GP_E_DEVICE, "hipStreamWaitEvent: %s", hipGetErrorString(e));
     }
-    if (upload && (st = core_translate(pd, vi, code, progs)) != GP_OK) return st;
+    if (upload) {
+        std::vector<DevProg> progs;
+        cost_order(pd, dp.order);
+        if ((st = core_translate(pd, vi, dp.order.data(), code, progs)) != GP_OK) return st;
+        dp.rec.resize((size_t)pd.n_prog + 1);
+        for (int32_t i = 0; i < pd.n_prog; i++) dp.rec[i] = progs[dp.order[i]].code_off / 4;
+        const DevProg& last = progs[dp.order[pd.n_prog - 1]];
+        dp.rec[pd.n_prog] = last.code_off / 4 + last.len;
+    }
     DevBuf* gb = nullptr;
-    int64_t n_order = 0;
     if (fresh) {
         gb = &dp.groups_once;
     } else {
         auto it = dp.groups_by_G.find(G);
-        if (it != dp.groups_by_G.end()) {
-            gb = &it->second.second;
-            n_order = it->second.first;
-        }
+        if (it != dp.groups_by_G.end()) gb = &it->second;
     }
     const bool new_groups = G > 0 && (fresh || gb == nullptr);
     if (new_groups) {
-        make_groups(pd, G, o, g);
-        n_order = (int64_t)o.size();
-        if (!fresh) gb = &dp.groups_by_G.emplace(G, std::make_pair(n_order, DevBuf())).first->second.second;
-        if ((st = gb->reserve((o.size() + g.size()) * 4)) != GP_OK) return st;
+        cut_groups(pd, dp.order, dp.rec, G, g);
+        if (!fresh) gb = &dp.groups_by_G[G];
+        if ((st = gb->reserve(g.size() * 4)) != GP_OK) return st;
     }
     if (upload || new_groups) {
-        if (upload) {
-            if ((st = dp.code.reserve(std::max<size_t>(16, code.size() * 4))) != GP_OK) return st;
-            if ((st = dp.progs.reserve(std::max<size_t>(1, progs.size()) * sizeof(DevProg))) != GP_OK) return st;
-        }
-        const size_t bytes = code.size() * 4 + progs.size() * sizeof(DevProg) + (o.size() + g.size()) * 4 + 1024;
+        if (upload && (st = dp.code.reserve(std::max<size_t>(16, code.size() * 4))) != GP_OK) return st;
+        const size_t bytes = code.size() * 4 + g.size() * 4 + 1024;
         if ((st = w.staging.begin(bytes)) != GP_OK) return st;
-        if (upload) {
-            if ((st = w.staging.put(code.data(), code.size() * 4, dp.code.p, s)) != GP_OK) return st;
-            if ((st = w.staging.put(progs.data(), progs.size() * sizeof(DevProg), dp.progs.p, s)) != GP_OK) return st;
-        }
-        if (new_groups) {
-            if ((st = w.staging.put(o.data(), o.size() * 4, gb->p, s)) != GP_OK) return st;
-            if ((st = w.staging.put(g.data(), g.size() * 4, (uint32_t*)gb->p + o.size(), s)) != GP_OK) return st;
-        }
+        if (upload && (st = w.staging.put(code.data(), code.size() * 4, dp.code.p, s)) != GP_OK) return st;
+        if (new_groups && (st = w.staging.put(g.data(), g.size() * 4, gb->p, s)) != GP_OK) return st;
         if ((st = w.staging.end(s)) != GP_OK) return st;
         if (!dp.ready) {
             hipError_t e = hipEventCreateWithFlags(&dp.ready, hipEventDisableTiming);
@@ -483,12 +484,11 @@ static gp_status prepare_programs(const ProgData& pd, int vi, DevProgs& dp, bool
         if (e != hipSuccess) return fail(GP_E_DEVICE, "hipEventRecord: %s", hipGetErrorString(e));
         dp.uploaded = true;
     }
-    if (order) *order = gb ? (const uint32_t*)gb->p : nullptr;
-    if (goff) *goff = gb ? (const uint32_t*)gb->p + n_order : nullptr;
+    if (goff) *goff = gb ? (const uint32_t*)gb->p : nullptr;
     return GP_OK;
 }
 
-// Launch shape of one evaluation.  Programs are dealt into G groups of
+// Launch shape of one evaluation.  Programs are cut into G groups of
 // about `group_instr` core instructions; each block runs four groups (one
 // per wave) on a chunk of tiles_per_wave tiles.  Chunks lengthen only while
 // four times `target_blocks` blocks remain; with few tiles, groups are made
@@ -507,13 +507,12 @@ static int32_t env_int(const char* name, int32_t dflt) {
 }
 
 int32_t code_prefetch() {
-    // GP2D_CODE_PREFETCH: 0 = no burst load, n = n loads in flight (at most 15, the scalar
-    // memory counter's limit), unset = 15 (measured best: 2-3 % faster than 8 on the
-    // interpreter-bound workloads)
+    // GP2D_CODE_PREFETCH: 0 = no burst load, n = n lines in flight beside the next records (at most 14:
+    // the scalar memory counter holds 15 loads), unset = 14
     const char* v = getenv("GP2D_CODE_PREFETCH");
-    if (!v || !*v) return 15;
+    if (!v || !*v) return 14;
     const long n = strtol(v, nullptr, 10);
-    return n <= 0 ? 0 : (n > 15 ? 15 : (int32_t)n);
+    return n <= 0 ? 0 : (n > 14 ? 14 : (int32_t)n);
 }
 
 static LaunchShape launch_shape(const ProgData& pd, int32_t tiles, const EvalOptions* opt, int32_t force_G = 0) {
@@ -644,7 +643,7 @@ gp_status eval_core(const ProgData& pd, std::map<int, DevProgs>& dps, bool fresh
     if (units > (1LL << 31) - 64) return fail(GP_E_INVAL, "too many work units");
     const int64_t n_blocks = (N + 255) / 256;
     const size_t part_bytes = kind == GP_OUT_CASES ? 0 : (size_t)n_blocks * pd.n_prog * sizeof(double);
-    const uint32_t *order, *goff;
+    const uint32_t* goff;
     double* partials = nullptr;
     if (no_alloc) {
         auto git = dp.groups_by_G.find(G);
@@ -656,20 +655,17 @@ gp_status eval_core(const ProgData& pd, std::map<int, DevProgs>& dps, bool fresh
                         opt->partials_bytes);
         hipError_t e = hipStreamWaitEvent(s, dp.ready, 0);
         if (e != hipSuccess) return fail(GP_E_DEVICE, "hipStreamWaitEvent: %s", hipGetErrorString(e));
-        order = (const uint32_t*)git->second.second.p;
-        goff = order + git->second.first;
+        goff = (const uint32_t*)git->second.p;
         partials = opt->partials;
     } else {
         if (!w) return fail(GP_E_INVAL, "internal: no workspace");
-        if ((st = prepare_programs(pd, vi, dp, fresh, G, s, *w, &order, &goff)) != GP_OK) return st;
+        if ((st = prepare_programs(pd, vi, dp, fresh, G, s, *w, &goff)) != GP_OK) return st;
         if (part_bytes && (st = w->partials.reserve(part_bytes)) != GP_OK) return st;
         partials = (double*)w->partials.p;
     }
     CoreArgs a;
     memset(&a, 0, sizeof a);
     a.code = (const uint32_t*)dp.code.p;
-    a.progs = (const DevProg*)dp.progs.p;
-    a.order = order;
     a.group_off = goff;
     a.X = X;
     a.y = kind == GP_OUT_CASES ? nullptr : y;
@@ -807,7 +803,7 @@ static gp_status progset_finish(ProgData&& pd, void* stream, gp_progset** ps) {
         Workspace& w = workspace(s);
         std::lock_guard<std::mutex> g(w.mu);
         p->groups = base_groups(p->pd);
-        if ((st = prepare_programs(p->pd, vi, p->dps[vi], false, p->groups, s, w, nullptr, nullptr)) != GP_OK)
+        if ((st = prepare_programs(p->pd, vi, p->dps[vi], false, p->groups, s, w, nullptr)) != GP_OK)
             return st;
     }
     *ps = p.release();

@@ -83,14 +83,15 @@ struct ProgData {
 };
 
 // Device copies of programs translated for one core variant, plus their
-// group layouts (program order and group offsets) by group count.  `ready`
+// group layouts (the first record of each group) by group count.  `ready`
 // is recorded on the stream of the last upload into these buffers; a launch
 // on any stream waits for it.
 struct DevProgs {
     bool uploaded = false;
     DevBuf code;
-    DevBuf progs;
-    std::map<int32_t, std::pair<int64_t, DevBuf>> groups_by_G;
+    std::vector<uint32_t> order;   // programs in the order of the code (host)
+    std::vector<int64_t> rec;      // first record of each, in that order, and the end (host)
+    std::map<int32_t, DevBuf> groups_by_G;
     DevBuf groups_once;        // one-shot calls: the group layout of the current programs
     hipEvent_t ready = nullptr;
     DevProgs() = default;
@@ -100,7 +101,6 @@ struct DevProgs {
     void release() {
         uploaded = false;
         code.release();
-        progs.release();
         groups_by_G.clear();
         groups_once.release();
         if (ready) (void)hipEventDestroy(ready);
@@ -136,6 +136,12 @@ Workspace& workspace(hipStream_t s);
 // takes part); small ranges run on the calling thread.  Calls take turns.
 void parallel_for(int64_t n, const std::function<void(int64_t, int64_t)>& fn);
 int32_t code_prefetch();
+// Programs by falling cost, and such a sequence cut into G groups of about
+// equal cost (goff: G + 1 record offsets, from rec, each program's first
+// record in that order and the end).
+void cost_order(const ProgData& pd, std::vector<uint32_t>& order);
+void cut_groups(const ProgData& pd, const std::vector<uint32_t>& order, const std::vector<int64_t>& rec, int32_t G,
+                std::vector<uint32_t>& goff);
 
 // Kernel timing brackets (active only while gp_timing_enable(1)).
 hipError_t timed_launch_begin(hipStream_t s, int* slot);

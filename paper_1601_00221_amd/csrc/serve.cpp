@@ -151,11 +151,11 @@ static gp_status launch_batch(Server& S, const std::vector<gp_dataset>& ds, int 
     // The stream's buffers only grow; when they hold more than this batch needs and more than the
     // stream's share of the budget, free them first, so memory held between batches stays bounded
     // (the free waits for the device, which is rare: only after an unusually large batch).
-    const size_t held = sc.code.cap + sc.progs.cap + sc.order.cap + sc.units.cap + sc.jobs.cap + sc.datasets.cap +
+    const size_t held = sc.code.cap + sc.units.cap + sc.jobs.cap + sc.datasets.cap +
                         sc.reduce.cap + sc.partials.cap + sc.counter.cap;
     const size_t need = plan_device_bytes(plan);
     if (held > need && held > S.cfg.memory_budget / (size_t)S.cfg.n_streams) {
-        sc.code.release(); sc.progs.release(); sc.order.release(); sc.units.release(); sc.jobs.release();
+        sc.code.release(); sc.units.release(); sc.jobs.release();
         sc.datasets.release(); sc.reduce.release(); sc.partials.release(); sc.counter.release();
     }
     if ((st = upload_plan(plan, sc, s)) != GP_OK) return st;
@@ -495,7 +495,7 @@ gp_status gp_serve_destroy(gp_server* sv) {
     for (hipStream_t s : S.streams)
         if (s) (void)hipStreamDestroy(s);
     for (auto& sc : S.scratch) {
-        sc->code.release(); sc->progs.release(); sc->order.release(); sc->units.release();
+        sc->code.release(); sc->units.release();
         sc->jobs.release(); sc->datasets.release(); sc->reduce.release(); sc->partials.release();
         sc->counter.release();
         sc->staging.release();
