@@ -96,7 +96,7 @@ def build(verbose: bool = False, incremental: bool = False) -> str:
     gen_core = _gen_core()
     gen_core.main(GEN)   # the hand-written interpreter core of every kernel variant
     jobs = [(os.path.join(CSRC, s), None) for s in SOURCES]
-    jobs += [(os.path.join(GEN, f), v) for f, v in zip(gen_core.variant_sources(), gen_core.VARIANTS)]
+    jobs += [(os.path.join(GEN, f), v) for f, v in zip(gen_core.variant_sources(), gen_core.VARIANTS + gen_core.RING_VARIANTS)]
     workers = max(1, min(16, os.cpu_count() or 1, len(jobs)))
     with cf.ThreadPoolExecutor(max_workers=workers) as ex:
         objs = list(ex.map(lambda j: _compile(j[0], incremental, j[1]), jobs))

@@ -179,11 +179,13 @@ namespace {
 
 // Handlers come in two phases (records are fetched two at a time, see
 // gen_core.py): instructions alternate A, B, A, ... and every entry into the
-// core -- a program's start, the return from an exit -- begins with A.
+// core -- a program's start, the return from an exit -- begins with A.  Ring
+// cores have four, taken in turn.
 constexpr int kPhaseB = 0x80;
 
 // Writes core instructions (4 words each) to `out`, at most `cap` of them.
 struct Emitter {
+    const CoreVariantDesc& v;
     const VariantMap& m;
     uint32_t* out;
     int64_t cap;
@@ -195,7 +197,7 @@ struct Emitter {
     void put(int kind, int op, int p1, int p2, uint32_t pay, uint32_t cst) {
         uint16_t slot = 0;
         const bool have = m.slot.find(key_of(kind | phase, op, p1, p2), &slot);
-        phase ^= kPhaseB;
+        phase = v.ring ? (phase + (1 << GPX_RING_PHASE)) & (3 << GPX_RING_PHASE) : phase ^ kPhaseB;
         if (!have) {
             snprintf(err, 256, "no core handler for kind %d op %d (%d, %d)", kind, op, p1, p2);
             ok = false;
@@ -206,7 +208,7 @@ struct Emitter {
             ok = false;
             return;
         }
-        const uint64_t addr = m.base + (uint64_t)slot * GPX_SLOT;
+        const uint64_t addr = m.base + (uint64_t)slot * v.slot_bytes;
         uint32_t* o = out + 4 * n++;
         o[0] = (uint32_t)addr;
         o[1] = (uint32_t)(addr >> 32);
@@ -274,7 +276,7 @@ static int translate_tree(const uint32_t* w, int64_t n_instr, int vi, const Vari
                           uint32_t* out, int64_t cap, int64_t* n_out, char* err) {
     const CoreVariantDesc& v = kCoreVariants[vi];
     const int T = v.t, FO = core_reg_levels(vi) * T;
-    Emitter e{m, out, cap, err};
+    Emitter e{v, m, out, cap, err};
     for (int64_t i = 0; i < n_instr && e.ok; i++) {
         const uint32_t w0 = w[2 * i], c = w[2 * i + 1];
         const uint32_t op = w0 & 15u, mode = (w0 >> 4) & 15u;
@@ -396,7 +398,7 @@ static int translate_linear(const uint32_t* w, int64_t n, const uint32_t* cst, i
                             int64_t* n_out, char* err) {
     const CoreVariantDesc& v = kCoreVariants[vi];
     const int T = v.t, FO = core_reg_levels(vi) * T;
-    Emitter e{m, out, cap, err};
+    Emitter e{v, m, out, cap, err};
     auto off = [&](int id) { return id < n_reg ? id * T : FO + (id - n_reg) * T; };
     // registers start as r[k] = x[k mod n_feat]
     for (int k = 0; k < n_reg && e.ok; k++) e.put(CK_MOVX, 0, k, 0, (uint32_t)(FO + (k % n_feat) * T), 0);
@@ -451,6 +453,8 @@ static VariantMap map_at(int vi, uint64_t base) {
     return m;
 }
 
+constexpr int kCodePadding = 32;   // words
+
 // Programs are translated in parallel, each into its own counted range of
 // the code: a tree gives one core instruction per lowered instruction plus
 // the end; a register program as linear_records counts.  The code holds the
@@ -470,9 +474,9 @@ static gp_status translate_with(const ProgData& pd, int vi, const VariantMap& m,
     };
     for (int32_t i = 0; i < P; i++) start[i + 1] = start[i] + records(at(i));
     if (start[P] * 16 > 0xFFFFFFF0ll) return fail(GP_E_INVAL, "programs exceed 4 GiB of core code");
-    // the core reads records two at a time, up to one record past a program's
-    // last one: the code ends with padding
-    code.assign((size_t)start[P] * 4 + 16, 0u);
+    // the core reads records two or four at a time, ahead of the one it runs: up
+    // to seven past a program's last one, so the code ends with padding
+    code.assign((size_t)start[P] * 4 + kCodePadding, 0u);
     std::vector<int32_t> rc((size_t)P, GP_OK);
     auto translate = [&](int32_t i, uint32_t* out, int64_t cap, int64_t* n, char* err) {
         const int32_t p = at(i);

@@ -77,12 +77,7 @@ VARIANTS = [
     (8, 8, 8, 40, 1),
     (4, 8, 16, 40, 1),
     (4, 12, 32, 40, 1),
-    (8, 6, 8, 56, 3),
-    (8, 8, 8, 40, 3),
-    (4, 8, 16, 48, 3),
     (4, 8, 44, 48, 4),
-    (8, 6, 20, 48, 2),
-    (8, 8, 20, 32, 2),
     (4, 12, 32, 40, 2),
     # deep programs: every tree of at most GP_MAX_LEN nodes needs at most 20
     # levels (15 without IF), 16 for the binary Boolean set; with more than 32
@@ -90,14 +85,26 @@ VARIANTS = [
     (4, 20, 32, 40, 0),
     (4, 12, 44, 32, 4),
     (4, 16, 32, 40, 2),
-    # Boolean, 4 waves per SIMD: 5 % faster than (8, 6, 20, 48) on the 20-multiplexer (2 waves, the same 16
-    # slots per SIMD); 3-wave forms of it were slower
-    (4, 6, 20, 24, 2),
-    # 4 waves per SIMD at T = 4 for the functions that stay in the core: the Shuttle shape's 9 inputs (16 %
-    # faster than (4, 8, 16, 48) with 3 waves) and register programs over 16 features (13 % faster than
-    # (4, 8, 16, 40))
-    (4, 8, 12, 48, 3),
+    # 4 waves per SIMD at T = 4: register programs over 16 features (13 % faster than (4, 8, 16, 40))
     (4, 8, 16, 32, 1),
+]
+
+# Variants on ring cores (below): trees of functions that stay in the core, whose instructions are short enough for
+# the scalar cache's latency to show.  5 levels hold the benchmark populations of up to 256 nodes without IF; the
+# compiled code needs few registers, so 128 of them (4 waves per SIMD) hold T = 8 over 8 features: 0.631 ms on the
+# {+,-,*} workload against 0.711 with 3 waves, both before the ring.
+RING_VARIANTS = [
+    (8, 5, 8, 24, 3),
+    (8, 8, 8, 24, 3),
+    (8, 5, 4, 24, 3),
+    (8, 6, 2, 24, 3),
+    (4, 6, 12, 24, 3),
+    (4, 8, 16, 24, 3),
+    (4, 6, 24, 24, 3),
+    (4, 8, 44, 24, 3),
+    (8, 6, 12, 16, 2),
+    (4, 6, 20, 16, 2),
+    (4, 8, 20, 16, 2),
 ]
 
 
@@ -167,13 +174,15 @@ class Handler:
         self.lines = []
         self.size = 0
         self.phases = None      # (phase A lines, phase B lines) of a handler written per phase
+        self.body = None        # its operation, a function of the registers that hold its offsets and constant
+        self.n_idx = 0          # and the number of those offsets
 
     def emit(self, text, nbytes):
         self.lines.append(text)
         self.size += nbytes
 
 
-def gen_variant(T, D, NF, NCV, mode=0):
+def gen_variant(T, D, NF, NCV, mode=0, ring=False):
     V0 = NCV
     FO = reg_levels(D, mode) * T       # register/stack block, then the features
     assert FO + NF * T <= 256, "index range exceeds 8 bits"
@@ -218,7 +227,7 @@ def gen_variant(T, D, NF, NCV, mode=0):
 
     if mode == 2:
         bool_handlers(hs, T, D, V0, FO, prologue, idx_on, epilogue, valu)
-        return finish(hs, tag, V0, FO)
+        return finish(hs, tag, V0, FO, ring)
 
     # ---------------------------------------------------------------- trees
     for op in ("add", "sub", "mul"):
@@ -328,7 +337,7 @@ def gen_variant(T, D, NF, NCV, mode=0):
     hs.append(if_handler(T, V0))
 
     if mode >= 3:                      # trees only: no linear handlers
-        return finish(hs, tag, V0, FO)
+        return finish(hs, tag, V0, FO, ring)
 
     # ---------------------------------------------------------------- linear
     R = LIN_REGS
@@ -392,7 +401,7 @@ def gen_variant(T, D, NF, NCV, mode=0):
         epilogue(h)
         hs.append(h)
 
-    return finish(hs, tag, V0, FO)
+    return finish(hs, tag, V0, FO, ring)
 
 
 def div_handler(kind, T, V0):
@@ -455,7 +464,7 @@ def div_handler(kind, T, V0):
     lb = ["s_mov_b32 s73, s70", "s_lshr_b32 s74, s70, 8", "s_lshr_b32 s79, s70, 16", "s_mov_b32 s72, s71",
           "s_add_u32 s62, s62, 16", "s_load_dwordx8 s[64:71], s[60:61], s62"] + body("s73", "s74", "s79", "s72")
     lb += ["s_waitcnt lgkmcnt(0)", "s_setpc_b64 s[64:65]"]
-    h.phases = (la, lb)
+    h.phases, h.body, h.n_idx = (la, lb), lambda A, B, Dx, C, _: body(A, B, Dx, C), 3
     return h
 
 
@@ -485,7 +494,7 @@ def phases_of(h, body, n_idx):
     la += ["s_add_u32 s62, s62, 16", "s_setpc_b64 s[68:69]"]
     lb += ["s_add_u32 s62, s62, 16", "s_load_dwordx8 s[64:71], s[60:61], s62"] + body(*regs_b)
     lb += ["s_waitcnt lgkmcnt(0)", "s_setpc_b64 s[64:65]"]
-    h.phases = (la, lb)
+    h.phases, h.body, h.n_idx = (la, lb), body, n_idx
     return h
 
 
@@ -599,14 +608,86 @@ def bool_handlers(hs, T, D, V0, FO, prologue, idx_on, epilogue, valu):
     hs.append(h)
 
 
-def finish(hs, tag, V0, FO):
-    """Both phases of every handler, laid out in 64-byte slots."""
-    hs = [phase_a(h, tag) for h in hs] + [phase_b(h, tag) for h in hs]
+def finish(hs, tag, V0, FO, ring=False):
+    """Every phase of every handler (two, or four in a ring core), laid out in slots."""
+    if ring:
+        hs, unit = [phase_ring(h, k, tag) for k in range(4) for h in hs], RING_SLOT
+    else:
+        hs, unit = [phase_a(h, tag) for h in hs] + [phase_b(h, tag) for h in hs], SLOT
     slot = 0
     for h in hs:
         h.slot = slot
-        slot += (h.size + SLOT - 1) // SLOT
+        slot += (h.size + unit - 1) // unit
     return tag, V0, FO, hs, slot
+
+
+# Ring cores.  The pair scheme below still waits once in two instructions for
+# most of the scalar cache's latency (measured on the 20-multiplexer: 43 of
+# the 100 cycles an instruction takes a wave).  A ring core keeps four records,
+# two pairs, in s[36:51] and has four phases of every handler: phase k works
+# from record k and jumps to record k + 1.  The odd phases first wait for the
+# other pair, requested two instructions ago, then, their own pair being used
+# up, request the pair after it.  s62 is the byte offset of the pair requested
+# last: the record after an exit is at s62 - 16 in an even phase, at s62 in an
+# odd one.  Twice the handlers, so the slots are 32 bytes.
+RING = 36
+RING_SLOT = 32
+RING_PHASE = 6                   # the phase's place in a handler key's kind
+
+
+def phase_ring(h, k, tag):
+    c = _copy(h, h.kind | (k << RING_PHASE))
+    r = RING + 4 * k
+    pay, cst = "s%d" % (r + 2), "s%d" % (r + 3)
+    own = RING + 8 * (k >> 1)
+    nxt = "s_setpc_b64 %s" % sp(RING + 4 * ((k + 1) & 3))
+    odd = k & 1
+    fetch = ["s_add_u32 s62, s62, 32", "s_load_dwordx8 s[%d:%d], s[60:61], s62" % (own, own + 7)]
+    if h.kind == K["EXIT"]:
+        L = ["s_set_gpr_idx_off"] + ([] if odd else ["s_sub_u32 s62, s62, 16"]) + \
+            ["s_mov_b32 s66, %s" % pay, "s_mov_b32 s67, %s" % cst, "s_branch .Lgpx_end_%s" % tag]
+    elif h.body and not odd:
+        if h.n_idx == 3:
+            L = ["s_lshr_b32 s74, %s, 8" % pay, "s_lshr_b32 s79, %s, 16" % pay] + h.body(pay, "s74", "s79", cst, None)
+        else:
+            L = ["s_lshr_b32 s74, %s, 8" % pay, "s_lshr_b32 s73, %s, 16" % pay, "s_lshr_b32 s79, %s, 24" % pay] + \
+                h.body(pay, "s74", "s79", None, "s73")
+        L += [nxt]
+    elif h.body:
+        L = ["s_waitcnt lgkmcnt(0)", "s_mov_b32 s73, %s" % pay, "s_lshr_b32 s74, %s, 8" % pay]
+        if h.n_idx == 3:
+            L += ["s_lshr_b32 s79, %s, 16" % pay, "s_mov_b32 s72, %s" % cst] + fetch + h.body("s73", "s74", "s79", "s72", None)
+        else:
+            L += ["s_lshr_b32 s72, %s, 16" % pay, "s_lshr_b32 s79, %s, 24" % pay] + fetch + \
+                h.body("s73", "s74", "s79", None, "s72")
+        L += [nxt]
+    else:
+        L = ["s_waitcnt lgkmcnt(0)"] if odd else []
+        for x in h.lines:
+            if x.startswith(("s_waitcnt", "s_setpc")):
+                continue
+            if x == "s_mov_b32 s72, s67":
+                if odd:
+                    L.append("s_mov_b32 s72, %s" % cst)
+            elif x == "s_mov_b32 s70, s66":
+                if odd:
+                    L.append("s_mov_b32 s73, %s" % pay)
+            elif x == "s_lshr_b32 s71, s66, 8":
+                L.append("s_lshr_b32 s74, %s, 8" % pay)
+            elif x.startswith("s_add_u32 s62"):
+                if odd:
+                    L += fetch
+            elif x.startswith("s_load_dwordx4"):
+                pass
+            else:
+                x = x.replace("s_set_gpr_idx_on s66,", "s_set_gpr_idx_on %s," % pay)
+                x = x.replace("s_set_gpr_idx_on s70,", "s_set_gpr_idx_on %s," % ("s73" if odd else pay))
+                x = x.replace("s_set_gpr_idx_on s71,", "s_set_gpr_idx_on s74,")
+                L.append(x if odd else x.replace("s72", cst))
+        L += [nxt]
+    for x in L:
+        c.emit(x, insn_bytes(x))
+    return c
 
 
 # Two copies of every handler.  Records are fetched two at a time: a phase-B
@@ -747,7 +828,15 @@ def exec_slot(j, left="s87"):
             "s_cselect_b64 exec, 0, s[74:75]"]
 
 
-def unit_start(T, D, NF, V0, FO, tag, mode):
+def first_records(ring):
+    """Requests the records at s62, and enters the program there once they have come."""
+    if ring:
+        return "s_load_dwordx16 s[%d:%d], s[60:61], s62" % (RING, RING + 15), \
+            ["s_add_u32 s62, s62, 32", "s_setpc_b64 %s" % sp(RING)]
+    return "s_load_dwordx8 s[64:71], s[60:61], s62", ["s_setpc_b64 s[64:65]"]
+
+
+def unit_start(T, D, NF, V0, FO, tag, mode, ring):
     """Start of a unit: the first records and code lines (into the scalar
     cache), the tile's targets (to LDS, read again at the end of every
     program) and features (straight into their registers), all in flight
@@ -755,7 +844,7 @@ def unit_start(T, D, NF, V0, FO, tag, mode):
     vl4, vy = "v%d" % (V0 + T), "v%d" % (V0 + T + 1)     # stack level 1 is free here
     L = ["v_mbcnt_lo_u32_b32 %s, -1, 0" % vy, "v_mbcnt_hi_u32_b32 %s, -1, %s" % (vy, vy),
          "v_lshlrev_b32_e32 %s, 2, %s" % (vl4, vy), "v_lshl_add_u32 %s, %s, 4, s97" % (vy, vy),
-         "s_load_dwordx8 s[64:71], s[60:61], s62"]
+         first_records(ring)[0]]
     if mode in (0, 4):
         L += ["s_load_dwordx16 s[24:39], s[100:101], 0x0", "s_load_dwordx16 s[40:55], s[100:101], 0x40"]
     L += prefetch_start(tag, "0", "s96") + ["s_mov_b32 s99, 0"]
@@ -806,7 +895,7 @@ def prefetch_lines(tag, n):
     return L + [".Lgpx_pfe%s_%s:" % (n, tag)]
 
 
-def program_end(T, D, NF, V0, FO, tag, mode):
+def program_end(T, D, NF, V0, FO, tag, mode, ring):
     """End of a program: s66 holds its payload (low 24 bits: records of the
     program after it), s67 its row.  The next program's first records and
     lines are requested, the fitness terms of the tile are formed and summed
@@ -821,12 +910,12 @@ def program_end(T, D, NF, V0, FO, tag, mode):
     o = lambda j: "v%d" % (V0 + j)   # noqa: E731
     nb = T // 4
     full = 64 * T
-    L = ["s_mov_b32 s80, s67", "s_and_b32 s81, s66, 0xffffff", "s_add_u32 s62, s62, 16",
-         "v_mbcnt_lo_u32_b32 v%d, -1, 0" % vl, "v_mbcnt_hi_u32_b32 v%d, -1, v%d" % (vl, vl),
+    L = ["s_mov_b32 s80, s67", "s_and_b32 s81, s66, 0xffffff"] + ([] if ring else ["s_add_u32 s62, s62, 16"])
+    L += ["v_mbcnt_lo_u32_b32 v%d, -1, 0" % vl, "v_mbcnt_hi_u32_b32 v%d, -1, v%d" % (vl, vl),
          "v_lshl_add_u32 v%d, v%d, 4, s97" % (vy, vl)]
     for k in range(nb):
         L += ["ds_read_b128 %s, v%d offset:%d" % (quad(yr + 4 * k), vy, 1024 * k)]
-    L += ["s_waitcnt lgkmcnt(0)", "s_load_dwordx8 s[64:71], s[60:61], s62",
+    L += ["s_waitcnt lgkmcnt(0)", first_records(ring)[0],
           "s_lshl_b32 s81, s81, 4", "s_add_u32 s81, s81, s62"]
     L += prefetch_start(tag, "1", "s81")
     kinds = [FIT_HITS, OUT_CASES] if mode == 2 else [FIT_MSE, FIT_SUM_ABS, FIT_HITS, FIT_CLASS, OUT_CASES]
@@ -959,7 +1048,7 @@ def program_end(T, D, NF, V0, FO, tag, mode):
     L += [".Lgpx_rest_%s:" % tag, "s_waitcnt lgkmcnt(0)", "s_cmp_eq_u32 s99, 0", "s_cbranch_scc1 .Lgpx_go_%s" % tag,
           "s_lshl_b32 s72, s78, 6", "s_add_u32 s58, s58, s72", "s_addc_u32 s59, s59, 0"]
     L += prefetch_lines(tag, "2")
-    L += ["s_branch .Lgpx_rest_%s" % tag, ".Lgpx_go_%s:" % tag, "s_setpc_b64 s[64:65]"]
+    L += ["s_branch .Lgpx_rest_%s" % tag, ".Lgpx_go_%s:" % tag] + first_records(ring)[1]
     return L
 
 
@@ -1240,19 +1329,21 @@ def big_reduction(r, G):
     return L
 
 
-def tail_lines(T, D, NF, V0, FO, tag, mode):
+def tail_lines(T, D, NF, V0, FO, tag, mode, ring):
     """What follows the handlers in the block: an exit's record is in s[66:67]."""
     L = [".Lgpx_end_%s:" % tag]
     if mode in (0, 4):
         L += ["s_bfe_u32 s72, s66, 0x40018", "s_cmp_lg_u32 s72, 15", "s_cbranch_scc1 .Lgpx_fn_%s" % tag]
-    L += program_end(T, D, NF, V0, FO, tag, mode)
+    L += program_end(T, D, NF, V0, FO, tag, mode, ring)
     if mode in (0, 4):
         L += transc(T, V0, V0, tag, mode)
     L += [".Lgpx_leave_%s:" % tag, "s_waitcnt vmcnt(0) lgkmcnt(0)"]
     return L
 
 
-def asm_text(T, D, NF, V0, FO, tag, hs, mode):
+def asm_text(T, D, NF, V0, FO, tag, hs, mode, ring=False):
+    assert not (ring and mode in (0, 4))     # their coefficients use the ring's registers
+    slot = RING_SLOT if ring else SLOT
     L = []
     L.append("s_getpc_b64 s[76:77]")
     L.append(".Lgpx_pc_%s:" % tag)
@@ -1262,21 +1353,21 @@ def asm_text(T, D, NF, V0, FO, tag, hs, mode):
     L.append("s_addc_u32 s77, s77, 0")
     L.append("s_branch .Lgpx_probe_%s" % tag)
     L.append(".Lgpx_run_%s:" % tag)
-    L += unit_start(T, D, NF, V0, FO, tag, mode)
+    L += unit_start(T, D, NF, V0, FO, tag, mode, ring)
     L.append(".p2align %d" % (SLOT.bit_length() - 1))
     L.append(".Lgpx_table_%s:" % tag)
     for i, h in enumerate(hs):
         lab = ".Lgpx_h%d_%s" % (i, tag)
         L.append("%s:" % lab)
         # the host addresses handlers by slot: check the slot arithmetic
-        L.append(".if (%s - .Lgpx_table_%s) != %d" % (lab, tag, h.slot * SLOT))
+        L.append(".if (%s - .Lgpx_table_%s) != %d" % (lab, tag, h.slot * slot))
         L.append('.error \\"gpx handler %d misplaced\\"' % i)
         L.append(".endif")
         L.extend(h.lines)
         # pad to the slot boundary (never executed: every handler ends in a jump)
-        pad = (-h.size) % SLOT
+        pad = (-h.size) % slot
         L.extend(["s_nop 0"] * (pad // 4))
-    L += tail_lines(T, D, NF, V0, FO, tag, mode)
+    L += tail_lines(T, D, NF, V0, FO, tag, mode, ring)
     # one string literal a line: the compiler locates each line of one long literal anew from its start
     return "\\n\\t\"\n            \"".join(L)
 
@@ -1297,6 +1388,7 @@ def main(out_dir):
     lines = ["// Generated by gen_core.py -- do not edit.", "#pragma once", ""]
     lines.append("#define GPX_LIN_REGS %d" % LIN_REGS)
     lines.append("#define GPX_SLOT %d" % SLOT)
+    lines.append("#define GPX_RING_PHASE %d" % RING_PHASE)
     lines.append("enum CoreKind {" + ", ".join("CK_%s = %d" % (k, i) for i, k in enumerate(KINDS)) + "};")
     lines.append("")
     lines.append("#define GPX_CORE_VARIANTS(X) \\")
@@ -1310,13 +1402,15 @@ def main(out_dir):
     lines.append("};")
     host = []
     seen = {}
-    for (T, D, NF, NCV, AR) in VARIANTS:
+    for vi, (T, D, NF, NCV, AR) in enumerate(VARIANTS + RING_VARIANTS):
         core = (T, D, NF, NCV, AR)
-        tag, V0, FO, hs, nslots = gen_variant(T, D, NF, NCV, AR)
-        tag += "A" if AR == 1 else "S" if AR == 4 else ""
-        key = (T, D, NF, NCV, {1: 0, 4: 3}.get(AR, AR))    # modes 0 and 1 share a handler table, so do 3 and 4
+        ring = vi >= len(VARIANTS)
+        assert core not in (VARIANTS + RING_VARIANTS)[:vi], core
+        tag, V0, FO, hs, nslots = gen_variant(T, D, NF, NCV, AR, ring)
+        tag += ("A" if AR == 1 else "S" if AR == 4 else "") + ("Q" if ring else "")
+        key = (T, D, NF, NCV, {1: 0, 4: 3}.get(AR, AR), ring)    # modes 0 and 1 share a handler table, so do 3 and 4
         hs_tag, hs, nslots = seen.setdefault(key, (tag, hs, nslots))
-        text = asm_text(T, D, NF, V0, FO, tag, relabelled(hs, tag), AR)
+        text = asm_text(T, D, NF, V0, FO, tag, relabelled(hs, tag), AR, ring)
         assert NCV + FO + NF * T <= 256
         work = work_regs(NCV, AR)
         assert NCV - work >= 14, (T, D, NF, NCV, AR)
@@ -1324,6 +1418,8 @@ def main(out_dir):
         clob += ["s%d" % n for n in [58, 59] + list(range(64, 76)) + [79, 80, 81, 99]]
         if AR in (0, 4):
             clob += ["s%d" % n for n in range(24, 56)]
+        if ring:
+            clob += ["s%d" % n for n in range(RING, RING + 16)]
         core_lines = []
         core_lines.append("template <> struct Core<%d, %d, %d, %d, %d> {" % core)
         core_lines.append("    // runs one unit: its tile is loaded, then its programs run to their partial sums (or outputs);")
@@ -1346,11 +1442,11 @@ def main(out_dir):
         core_lines.append("    }")
         core_lines.append("};")
         cores.append(core_lines)
-        host.append((T, D, NF, NCV, AR, hs_tag, hs, nslots))
+        host.append((T, D, NF, NCV, AR, hs_tag, hs, nslots, ring))
     lines.append("")
     lines.append("struct CoreHandlerKey { uint8_t kind, op; int8_t p1, p2; };")
     done = set()
-    for (T, D, NF, NCV, AR, tag, hs, nslots) in host:
+    for (T, D, NF, NCV, AR, tag, hs, nslots, ring) in host:
         if tag in done:
             continue
         done.add(tag)
@@ -1361,11 +1457,11 @@ def main(out_dir):
         lines.append("    " + ", ".join(str(h.slot) for h in hs))
         lines.append("};")
     lines.append("struct CoreVariantDesc { int t, d, nf, ncv, arith; const CoreHandlerKey* keys; const uint16_t* slots; "
-                 "int n; int table_bytes; };")
+                 "int n; int slot_bytes; bool ring; };")
     lines.append("static const CoreVariantDesc kCoreVariants[] = {")
-    for (T, D, NF, NCV, AR, tag, hs, nslots) in host:
-        lines.append("    {%d, %d, %d, %d, %d, kCoreKeys_%s, kCoreSlots_%s, %d, %d}," % (T, D, NF, NCV, AR, tag, tag, len(hs),
-                                                                                    nslots * SLOT))
+    for (T, D, NF, NCV, AR, tag, hs, nslots, ring) in host:
+        lines.append("    {%d, %d, %d, %d, %d, kCoreKeys_%s, kCoreSlots_%s, %d, %d, %s},"
+                     % (T, D, NF, NCV, AR, tag, tag, len(hs), RING_SLOT if ring else SLOT, "true" if ring else "false"))
     lines.append("};")
     path = os.path.join(out_dir, "core_gen.inc")
     write_if_changed(path, "\n".join(lines) + "\n")
@@ -1373,7 +1469,7 @@ def main(out_dir):
     disp = ["// Generated by gen_core.py -- do not edit.", "#pragma once", "",
             "typedef hipError_t (*CoreLaunchFn)(const CoreArgs&, uint32_t, hipStream_t);",
             "typedef int (*CoreOccupancyFn)();"]
-    for core_lines, (T, D, NF, NCV, AR, tag, hs, nslots) in zip(cores, host):
+    for core_lines, (T, D, NF, NCV, AR, tag, hs, nslots, ring) in zip(cores, host):
         name = vname((T, D, NF, NCV, AR))
         disp.append("hipError_t core_launch_%s(const CoreArgs& a, uint32_t blocks, hipStream_t s);" % name)
         disp.append("int core_occupancy_%s();" % name)
@@ -1393,14 +1489,14 @@ def main(out_dir):
     disp.append("static const CoreOccupancyFn kCoreOccupancy[] = {%s};"
                 % ", ".join("core_occupancy_" + n for n in names))
     write_if_changed(os.path.join(out_dir, "core_dispatch.inc"), "\n".join(disp) + "\n")
-    for (T, D, NF, NCV, AR, tag, hs, nslots) in host:
-        print("%s%s: %d handlers, %d slots (%d KiB)" % (tag, "a" if AR == 1 else "", len(hs), nslots, nslots * SLOT // 1024))
+    for (T, D, NF, NCV, AR, tag, hs, nslots, ring) in host:
+        print("%s%s: %d handlers, %d slots (%d KiB)" % (tag, "a" if AR == 1 else "", len(hs), nslots, nslots * (RING_SLOT if ring else SLOT) // 1024))
     return path
 
 
 def variant_sources():
     """File names of the generated per-variant translation units."""
-    return ["core_v_%s.hip" % vname(v) for v in VARIANTS]
+    return ["core_v_%s.hip" % vname(v) for v in VARIANTS + RING_VARIANTS]
 
 
 def write_if_changed(path, text):

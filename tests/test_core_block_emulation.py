@@ -25,6 +25,7 @@ import gen_core  # noqa: E402
 
 sys.path.pop(0)
 
+ALL = gen_core.VARIANTS + gen_core.RING_VARIANTS
 CODE, XBASE, YBASE, PART, CASES, COEF = (0x100000000 * k for k in (16, 32, 48, 64, 80, 96))
 TEXT = 0x7F0000000000
 M32, M64 = 0xFFFFFFFF, 0xFFFFFFFFFFFFFFFF
@@ -64,10 +65,11 @@ def fma(a, b, c):
 
 class BlockEmu:
     def __init__(self, vi):
-        T, D, NF, NCV, mode = gen_core.VARIANTS[vi]
-        tag, V0, FO, hs, _ = gen_core.gen_variant(T, D, NF, NCV, mode)
+        T, D, NF, NCV, mode = ALL[vi]
+        ring = vi >= len(gen_core.VARIANTS)
+        tag, V0, FO, hs, _ = gen_core.gen_variant(T, D, NF, NCV, mode, ring)
         self.T, self.mode = T, mode
-        text = gen_core.asm_text(T, D, NF, V0, FO, tag, hs, mode)
+        text = gen_core.asm_text(T, D, NF, V0, FO, tag, hs, mode, ring)
         lines = [x.strip() for x in re.split(r'\\n\\t"?\s*"?', text)]
         self.ins, self.label, at, skip = [], {}, TEXT, False
         for x in lines:
@@ -478,7 +480,7 @@ def emulate(vi, pop, X, y, kind, n_bits=0):
     words = words.copy()
     P = pop.n_prog
     # rows and following lengths, as the library writes them for a group of consecutive programs
-    ends = [int(prog_off[p + 1]) // 4 for p in range(P - 1)] + [(len(words) - 16) // 4]
+    ends = [int(prog_off[p + 1]) // 4 for p in range(P - 1)] + [(len(words) - 32) // 4]
     for p in range(P):
         nxt = ends[p + 1] - ends[p] if p + 1 < P else 0
         assert words[4 * (ends[p] - 1) + 2] & 0xFF000000 == 15 << 24
@@ -537,15 +539,15 @@ def same(a, b):
     return ((a == b) | (np.isnan(a) & np.isnan(b))).all()
 
 
-REAL = [i for i, v in enumerate(gen_core.VARIANTS) if v[4] != 2]
-BOOL = [i for i, v in enumerate(gen_core.VARIANTS) if v[4] == 2]
+REAL = [i for i, v in enumerate(ALL) if v[4] != 2]
+BOOL = [i for i, v in enumerate(ALL) if v[4] == 2]
 SETS = {0: synth.FULL, 1: synth.BASIC, 3: synth.SHUTTLE_SET, 4: synth.KDD_SET}
 
 
 @pytest.mark.parametrize("vi", REAL)
 def test_block_programs_and_fitness(vi):
     """A unit of several programs, full and ragged tiles, with each fitness kind on a different size."""
-    T, D, NF, NCV, mode = gen_core.VARIANTS[vi]
+    T, D, NF, NCV, mode = ALL[vi]
     F = min(NF, 9 if vi % 2 else 3)
     rng = synth.rng_for(700 + vi)
     pop = synth.ptc2_population(rng, 6, SETS[mode], F, 1, 60, 0.2)
@@ -560,7 +562,7 @@ def test_block_programs_and_fitness(vi):
 
 @pytest.mark.parametrize("vi", BOOL)
 def test_block_boolean_hits(vi):
-    T, D, NF, NCV, _ = gen_core.VARIANTS[vi]
+    T, D, NF, NCV, _ = ALL[vi]
     F = min(NF, 7)
     rng = synth.rng_for(800 + vi)
     pop = synth.ptc2_population(rng, 5, synth.BOOL_SET, F, 1, 60, 0.0)
@@ -572,11 +574,11 @@ def test_block_boolean_hits(vi):
         assert same(got, expected(o, y.view(np.float32), "hits", n_bits))
 
 
-@pytest.mark.parametrize("vi", [i for i in REAL if gen_core.VARIANTS[i][4] in (0, 4)])
+@pytest.mark.parametrize("vi", [i for i in REAL if ALL[i][4] in (0, 4)])
 def test_block_transcendentals(vi):
     """sin, cos, exp and log of ordinary, large, tiny and special arguments, of a variable and in place on the stack.
     The emulated fused operation may round a tie twice, so one ulp is allowed now and then."""
-    T = gen_core.VARIANTS[vi][0]
+    T = ALL[vi][0]
     from tests import progs
     exprs = ["(%s x0)" % f for f in ("sin", "cos", "exp", "log")] + \
             ["(%s (* x0 x1))" % f for f in ("sin", "cos", "exp", "log")] + ["(sin 0.75)", "(log (exp (cos x0)))"]
