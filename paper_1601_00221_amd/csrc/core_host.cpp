@@ -101,6 +101,7 @@ int pick_core_variant(int n_load, int depth, double transc_frac, bool has_transc
     // the widest tile, on a kernel without that code if they use none of it.  Ties go to the fewest feature slots, then the fewest
     // handlers (least code).  (Measured on the 4096 x 65,536 tree workloads.)
     const bool heavy = transc_frac > 0.2;
+    // (ring cores before pair cores of the same shape)
     int best = -1;
     auto waves = [](const CoreVariantDesc& v) {
         const int lv = v.arith >= 2 || v.d > GPX_LIN_REGS ? v.d : GPX_LIN_REGS;
@@ -108,7 +109,7 @@ int pick_core_variant(int n_load, int depth, double transc_frac, bool has_transc
         return 512 / vg;
     };
     auto score = [&](const CoreVariantDesc& v) {
-        if (heavy) return (v.ncv >= 64) * 100000000 + waves(v) * 1000000 + v.t * 10000 - v.nf * 100 - v.n / 100;
+        if (heavy) return (v.ncv >= 48) * 100000000 + waves(v) * 1000000 + v.ring * 100000 + v.t * 10000 - v.nf * 100 - v.n / 100;
         // trees-only kernels first (the smallest handler tables), then those without sin/cos/exp/log code, the
         // widest tile, then the most waves per SIMD (4 against 3 at T = 4: 13-16 % on the linear and Shuttle-shaped
         // workloads)
@@ -251,6 +252,31 @@ struct Emitter {
     }
     // the binary functions the arithmetic kernels apply in their own handlers: protected division and the
     // classification functions (sin/cos/exp/log are unary and leave the core)
+    // ring cores: functions of a stack entry and the one above it or a variable, at level l = offset / T
+    static uint32_t swapped(uint32_t op) { return op == GP_GT ? (uint32_t)GP_LT : op == GP_LT ? (uint32_t)GP_GT : op; }
+    bool ring_apply(uint32_t op, uint32_t mode, int h, int xa, int xb) {
+        if (!v.ring || v.arith == 2) return false;
+        const int T = v.t;
+        if (op == GP_PDIV) {
+            // the level above the operand holds a variable's copy, so the top level takes the general form
+            switch (mode) {
+                case M_SS: put(CK_DSS, (int)op, h - 2, 0, 0, 0); return true;
+                case M_SSR: put(CK_DSSR, (int)op, h - 2, 0, 0, 0); return true;
+                case M_SX: case M_XS:
+                    if (h - 1 > v.d - 2) return false;
+                    put(mode == M_SX ? CK_DSX : CK_DXS, (int)op, h - 1, 0, (uint32_t)(mode == M_SX ? xb : xa), 0);
+                    return true;
+                default: return false;
+            }
+        }
+        switch (mode) {
+            case M_SS: put(CK_CSS, (int)op, 0, 0, (uint32_t)((h - 2) * T), 0); return true;
+            case M_SSR: put(CK_CSS, (int)swapped(op), 0, 0, (uint32_t)((h - 2) * T), 0); return true;
+            case M_SX: put(CK_CSX, (int)op, h - 1, 0, (uint32_t)xb, 0); return true;
+            case M_XS: put(CK_CSX, (int)swapped(op), h - 1, 0, (uint32_t)xa, 0); return true;
+            default: return false;
+        }
+    }
     void apply(uint32_t op, bool boolean, int oa, int ob, int od, bool a_const, bool b_const, uint32_t cst) {
         if (!boolean && op == GP_PDIV) {
             div(oa, ob, od, a_const, b_const, cst);
@@ -311,6 +337,10 @@ static int translate_tree(const uint32_t* w, int64_t n_instr, int vi, const Vari
                 return GP_E_INVAL;
             }
             // IF runs in the core: operands at three offsets, the result to the lowest, s[h-3]
+            if (v.ring) {
+                e.put(CK_IF3, GP_IF, 3 * fa + fb, 0, (uint32_t)((h - 3) * T), 0);
+                continue;
+            }
             e.put(CK_IF3, GP_IF, 0, 0,
                   (uint32_t)((h - 3 + fa) * T) | ((uint32_t)((h - 3 + fb) * T) << 8) |
                       ((uint32_t)((h - 3 + pc) * T) << 16) | ((uint32_t)((h - 3) * T) << 24),
@@ -336,7 +366,7 @@ static int translate_tree(const uint32_t* w, int64_t n_instr, int vi, const Vari
                     else e.put(CK_CS, op, 0, 0, (uint32_t)((h - 1) * T), c);
                     break;
                 case M_XX:
-                    if (v.nf <= 8 && v.arith != 2) {   // (Boolean kernels have no one-pass XX handlers)
+                    if (h < v.xx) {
                         if (comm) {
                             const int a = fa < fb ? fa : fb, b = fa < fb ? fb : fa;
                             e.put(CK_XX, op, h, b - a, (uint32_t)(a * T), 0);
@@ -361,6 +391,9 @@ static int translate_tree(const uint32_t* w, int64_t n_instr, int vi, const Vari
         // protected division has handlers of its own; the transcendentals and the classification
         // functions leave the core
         const bool bl = v.arith == 2;
+        if (!bl && (op == GP_PDIV || op == GP_GT || op == GP_LT || op == GP_EQ || op == GP_AND || op == GP_OR) &&
+            e.ring_apply(op, mode, h, xa, xb))
+            continue;
         switch (mode) {
             case M_SS: e.apply(op, bl, (h - 2) * T, (h - 1) * T, (h - 2) * T, false, false, 0); break;
             case M_SSR: e.apply(op, bl, (h - 1) * T, (h - 2) * T, (h - 2) * T, false, false, 0); break;

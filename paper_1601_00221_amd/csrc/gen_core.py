@@ -77,7 +77,6 @@ VARIANTS = [
     (8, 8, 8, 40, 1),
     (4, 8, 16, 40, 1),
     (4, 12, 32, 40, 1),
-    (4, 8, 44, 48, 4),
     (4, 12, 32, 40, 2),
     # deep programs: every tree of at most GP_MAX_LEN nodes needs at most 20
     # levels (15 without IF), 16 for the binary Boolean set; with more than 32
@@ -105,6 +104,11 @@ RING_VARIANTS = [
     (8, 6, 12, 16, 2),
     (4, 6, 20, 16, 2),
     (4, 8, 20, 16, 2),
+    (4, 8, 8, 64, 4),
+    (4, 6, 12, 56, 4),
+    (4, 8, 16, 56, 4),
+    (4, 6, 24, 48, 4),
+    (4, 8, 44, 48, 4),
 ]
 
 
@@ -132,6 +136,16 @@ def bool_op(op, d, a, b):
     return "v_bitop3_b32 %s, %s, %s, %s bitop3:0x%x" % (d, a, b, b, ins)
 
 
+def xx_levels(D, NF, mode, ring):
+    """Levels at which two variables are pushed in one pass, by a handler for
+    every distance between them: all of them over up to 8 features (a deep
+    ring core keeps to the lowest three, so that its table stays within a
+    branch's reach), the lowest two in Boolean ring cores, where most are."""
+    if mode == 2:
+        return 2 if ring else 0
+    return 0 if NF > 8 else 3 if ring and D > 6 else D
+
+
 def reg_levels(D, mode):
     """Register/stack levels before the features: linear programs need
     LIN_REGS registers; Boolean and trees-only kernels have none."""
@@ -139,7 +153,9 @@ def reg_levels(D, mode):
 
 # handler kinds (keep in sync with the generated enum below)
 KINDS = ["EXIT", "SS", "SSR", "SX", "XS", "SC", "CS", "XX", "XX2", "XC", "CX", "PUSHX", "PUSHC",
-         "RR", "XR", "FF", "CR", "RC", "MOVC", "MOVX", "DVV", "DVC", "DCV", "CVV", "CVC", "CCV", "IF3"]
+         "RR", "XR", "FF", "CR", "RC", "MOVC", "MOVX", "DVV", "DVC", "DCV", "CVV", "CVC", "CCV", "IF3",
+         # ring cores: compares and logic of two stack entries or of one and a variable, divisions with a stack entry
+         "CSS", "CSX", "DSS", "DSSR", "DSX", "DXS"]
 # Protected division runs in the core: a / b with a and b at any two offsets
 # (DVV), b the constant (DVC) or a the constant (DCV), the result to a third
 # offset.  Its temporaries are the last DIV_TMP registers of the compiler's
@@ -176,6 +192,7 @@ class Handler:
         self.phases = None      # (phase A lines, phase B lines) of a handler written per phase
         self.body = None        # its operation, a function of the registers that hold its offsets and constant
         self.n_idx = 0          # and the number of those offsets
+        self.then = None        # ring cores: a shared body that the handler goes on to
 
     def emit(self, text, nbytes):
         self.lines.append(text)
@@ -227,7 +244,18 @@ def gen_variant(T, D, NF, NCV, mode=0, ring=False):
 
     if mode == 2:
         bool_handlers(hs, T, D, V0, FO, prologue, idx_on, epilogue, valu)
-        return finish(hs, tag, V0, FO, ring)
+        if ring:
+            # two variables in one pass (as XX above), at the levels where most of them are pushed
+            for op in BOOL_OPS:
+                for l in range(xx_levels(D, NF, mode, ring)):
+                    for dl in range(NF):
+                        h = Handler(K["XX"], BOOL_ID[op], l, dl)
+                        prologue(h, index=["SRC0", "SRC1"])
+                        for j in range(T):
+                            valu(h, bool_op(op, vr(V0 + l * T + j), vr(V0 + FO + j), vr(V0 + FO + dl * T + j)))
+                        epilogue(h)
+                        hs.append(h)
+        return finish(hs, tag, V0, FO, ring, mode)
 
     # ---------------------------------------------------------------- trees
     for op in ("add", "sub", "mul"):
@@ -278,7 +306,7 @@ def gen_variant(T, D, NF, NCV, mode=0, ring=False):
         # the second one displaced by delta = b - a feature rows
         for op in ("add", "mul", "sub"):
             deltas = range(0, NF) if op != "sub" else range(-(NF - 1), NF)
-            for l in range(D):
+            for l in range(xx_levels(D, NF, mode, ring)):
                 for dl in deltas:
                     h = Handler(K["XX"], OP_ID[op], l, dl)
                     prologue(h, index=["SRC0", "SRC1"])
@@ -333,11 +361,14 @@ def gen_variant(T, D, NF, NCV, mode=0, ring=False):
         hs.append(div_handler(kind, T, V0))
     for op in list(CMP_OPS) + list(LOGIC_OPS):
         for kind in ("CVV", "CVC", "CCV"):
-            hs.append(cmp_handler(kind, op, T, V0))
-    hs.append(if_handler(T, V0))
+            hs.append(cmp_handler(kind, op, T, V0, ring))
+    if not ring:
+        hs.append(if_handler(T, V0))
+    else:
+        ring_handlers(hs, T, D, V0, prologue, epilogue, valu)
 
     if mode >= 3:                      # trees only: no linear handlers
-        return finish(hs, tag, V0, FO, ring)
+        return finish(hs, tag, V0, FO, ring, mode)
 
     # ---------------------------------------------------------------- linear
     R = LIN_REGS
@@ -401,7 +432,110 @@ def gen_variant(T, D, NF, NCV, mode=0, ring=False):
         epilogue(h)
         hs.append(h)
 
-    return finish(hs, tag, V0, FO, ring)
+    return finish(hs, tag, V0, FO, ring, mode)
+
+
+def ring_handlers(hs, T, D, V0, prologue, epilogue, valu):
+    """Classification functions and divisions of a ring core.  Operands on the
+    stack lie next to each other (or at a level the handler knows), so one
+    index serves a whole instruction: a compare and a select a slot, where the
+    general form also copies an operand and sets three indexes a slot.  Masks
+    go to s[64:71], four slots at a time, which also spaces a compare from
+    the select that reads it."""
+    def masked(h, test, d, sel):
+        for j0 in range(0, T, 4):
+            for j in range(j0, j0 + 4):
+                test(h, j, "s[%d:%d]" % (64 + 2 * (j - j0), 65 + 2 * (j - j0)))
+            for j in range(j0, j0 + 4):
+                valu(h, "v_cndmask_b32_e64 %s, %s, s[%d:%d]" % (d(j), sel(j), 64 + 2 * (j - j0), 65 + 2 * (j - j0)))
+
+    def tester(op, a, b):
+        """mask = a(j) op b(j)"""
+        def test(h, j, m):
+            if op in CMP_OPS:
+                valu(h, "v_cmp_%s_f32_e64 %s, %s, %s" % (CMP_OPS[op], m, a(j), b(j)))
+            else:
+                valu(h, "v_cmp_neq_f32_e64 %s, 0, %s" % (m, a(j)))
+                valu(h, "v_cmp_neq_f32_e32 vcc, 0, %s" % b(j))
+                h.emit("%s %s, vcc, %s" % (LOGIC_OPS[op], m, m), 4)
+        return test
+
+    for op in list(CMP_OPS) + list(LOGIC_OPS):
+        h = Handler(K["CSS"], op)                   # s[h-2] = s[h-2] op s[h-1]; index (h-2)*T
+        prologue(h, index=["SRC0", "SRC1", "DST"])
+        masked(h, tester(op, lambda j: vr(V0 + j), lambda j: vr(V0 + T + j)), lambda j: vr(V0 + j), lambda j: "0, 1.0")
+        epilogue(h)
+        hs.append(h)
+        for l in range(D):
+            h = Handler(K["CSX"], op, l)            # s[l] = s[l] op x; index = feature offset
+            lev = lambda j, l=l: vr(V0 + l * T + j)   # noqa: E731
+            # compares read the variable as their second source, under its index; a test against 0 has the
+            # stack entry there, so it goes first, with the index off
+            if op in CMP_OPS:
+                prologue(h, index=["SRC1"])
+                masked(h, tester(op, lev, lambda j: vr(V0 + j)), lev, lambda j: "0, 1.0")
+            else:
+                prologue(h, index=["SRC0"])
+                swap = lambda h, j, m, op=op, lev=lev: (   # noqa: E731
+                    valu(h, "v_cmp_neq_f32_e64 %s, 0, %s" % (m, lev(j))),
+                    valu(h, "v_cmp_neq_f32_e64 vcc, %s, 0" % vr(V0 + j)),
+                    h.emit("%s %s, vcc, %s" % (LOGIC_OPS[op], m, m), 4))
+                masked(h, swap, lev, lambda j: "0, 1.0")
+            epilogue(h)
+            hs.append(h)
+    for pa in range(3):                             # IF of three stack entries, by where each operand landed
+        for pb in range(3):
+            if pa == pb:
+                continue
+            pc = 3 - pa - pb
+            h = Handler(K["IF3"], 15, 3 * pa + pb)
+            prologue(h, index=["SRC0", "SRC1", "DST"])
+            masked(h, lambda h, j, m: valu(h, "v_cmp_neq_f32_e64 %s, 0, %s" % (m, vr(V0 + pa * T + j))),
+                   lambda j: vr(V0 + j), lambda j: "%s, %s" % (vr(V0 + pc * T + j), vr(V0 + pb * T + j)))
+            epilogue(h)
+            hs.append(h)
+    # divisions: the arithmetic itself is shared by the phases (division_bodies)
+    for l in range(D - 1):
+        for kind in ("DSS", "DSSR", "DSX", "DXS"):
+            h = Handler(K[kind], 3, l)
+            if kind in ("DSX", "DXS"):              # the variable is copied to the level above
+                prologue(h, index=["SRC0"])
+                for j in range(T):
+                    valu(h, "v_mov_b32_e32 %s, %s" % (vr(V0 + (l + 1) * T + j), vr(V0 + j)))
+                h.emit("s_set_gpr_idx_off", 4)
+            else:
+                prologue(h, index="off")
+            h.then = "%s%d" % ("dss" if kind in ("DSS", "DSX") else "dssr", l)
+            epilogue(h)
+            hs.append(h)
+
+
+def division_bodies(T, D, V0, tag):
+    """s[l] = s[l] / s[l+1] (dss) or s[l+1] / s[l] (dssr), protected; on to the address in s[76:77].  The sequence of
+    div_handler without copies: the test of the divisor goes first, to s[64:65]."""
+    tD, tR, tN, tE, tF = (vr(V0 - DIV_TMP + k) for k in range(2, 7))
+    L = []
+    for l in range(D - 1):
+        for name in ("dss", "dssr"):
+            L += [".Lgpx_%s%d_%s:" % (name, l, tag), "s_mov_b32 s80, 0x%x" % DIV_THRESHOLD]
+            for j in range(T):
+                d = vr(V0 + l * T + j)
+                A, B = (d, vr(V0 + (l + 1) * T + j)) if name == "dss" else (vr(V0 + (l + 1) * T + j), d)
+                L += ["v_div_scale_f32 %s, vcc, %s, %s, %s" % (tD, B, B, A),
+                      "v_cmp_nlt_f32_e64 s[64:65], |%s|, s80" % B,
+                      "v_rcp_f32_e32 %s, %s" % (tR, tD),
+                      "v_div_scale_f32 %s, vcc, %s, %s, %s" % (tN, A, B, A),
+                      "v_fma_f32 %s, -%s, %s, 1.0" % (tE, tD, tR),
+                      "v_fmac_f32_e32 %s, %s, %s" % (tR, tE, tR),
+                      "v_mul_f32_e32 %s, %s, %s" % (tE, tN, tR),
+                      "v_fma_f32 %s, -%s, %s, %s" % (tF, tD, tE, tN),
+                      "v_fmac_f32_e32 %s, %s, %s" % (tE, tF, tR),
+                      "v_fma_f32 %s, -%s, %s, %s" % (tD, tD, tE, tN),
+                      "v_div_fmas_f32 %s, %s, %s, %s" % (tD, tD, tR, tE),
+                      "v_div_fixup_f32 %s, %s, %s, %s" % (tD, tD, B, A),
+                      "v_cndmask_b32_e64 %s, 1.0, %s, s[64:65]" % (d, tD)]
+            L += ["s_setpc_b64 s[76:77]"]
+    return L
 
 
 def div_handler(kind, T, V0):
@@ -498,7 +632,7 @@ def phases_of(h, body, n_idx):
     return h
 
 
-def cmp_handler(kind, op, T, V0):
+def cmp_handler(kind, op, T, V0, ring=False):
     """d = a op b for op in >, <, ==, AND, OR (1 or 0 per slot), a and b at
     two offsets (CVV) or one of them the record's constant (CVC: b, CCV: a),
     d at a third; the payload is the exit's layout.  A compare writes vcc
@@ -540,6 +674,41 @@ def cmp_handler(kind, op, T, V0):
                   "v_cndmask_b32_e64 %s, 0, 1.0, vcc" % vr(V0 + j)]
         return L
 
+    def body_by_four(A, B, Dx, C, _):
+        """Ring cores: the same four slots at a time, masks in s[64:71], one index for each pass."""
+        L = []
+        if name is None and (a_const or b_const):
+            L += ["v_cmp_neq_f32_e64 s[80:81], 0, %s" % C]
+        for j0 in range(0, T, 4):
+            js = range(j0, j0 + 4)
+            m = {j: "s[%d:%d]" % (64 + 2 * (j - j0), 65 + 2 * (j - j0)) for j in js}
+            t = {j: vr(V0 - DIV_TMP + j - j0) for j in js}
+            first = B if a_const or (name is not None and not b_const) else A
+            if name is not None and not (a_const or b_const):
+                L += ["s_set_gpr_idx_on %s, gpr_idx(SRC0)" % B] + ["v_mov_b32_e32 %s, %s" % (t[j], vr(V0 + j)) for j in js]
+                L += ["s_set_gpr_idx_on %s, gpr_idx(SRC0)" % A]
+                L += ["v_cmp_%s_f32_e64 %s, %s, %s" % (name, m[j], vr(V0 + j), t[j]) for j in js]
+            elif name is not None:
+                rel = name if a_const else CMP_SWAP[name]
+                L += ["s_set_gpr_idx_on %s, gpr_idx(SRC1)" % first]
+                L += ["v_cmp_%s_f32_e64 %s, %s, %s" % (rel, m[j], C, vr(V0 + j)) for j in js]
+            else:
+                L += ["s_set_gpr_idx_on %s, gpr_idx(SRC1)" % first]
+                L += ["v_cmp_neq_f32_e64 %s, 0, %s" % (m[j], vr(V0 + j)) for j in js]
+                if not (a_const or b_const):
+                    L += ["s_set_gpr_idx_on %s, gpr_idx(SRC1)" % B]
+                for j in js:
+                    if not (a_const or b_const):
+                        L += ["v_cmp_neq_f32_e32 vcc, 0, %s" % vr(V0 + j)]
+                    L += ["%s %s, %s, %s" % (LOGIC_OPS[op], m[j], "s[80:81]" if a_const or b_const else "vcc", m[j])]
+            L += ["s_set_gpr_idx_on %s, gpr_idx(DST)" % Dx]
+            L += ["v_cndmask_b32_e64 %s, 0, 1.0, %s" % (vr(V0 + j), m[j]) for j in js]
+        return L
+
+    if ring:
+        h = Handler(K[kind], op)
+        h.body, h.n_idx = body_by_four, 3
+        return h
     return phases_of(Handler(K[kind], op), body, 3)
 
 
@@ -608,10 +777,13 @@ def bool_handlers(hs, T, D, V0, FO, prologue, idx_on, epilogue, valu):
     hs.append(h)
 
 
-def finish(hs, tag, V0, FO, ring=False):
+def finish(hs, tag, V0, FO, ring=False, mode=0):
     """Every phase of every handler (two, or four in a ring core), laid out in slots."""
     if ring:
-        hs, unit = [phase_ring(h, k, tag) for k in range(4) for h in hs], RING_SLOT
+        # all phases of the plain arithmetic first, so that they lie close together in the instruction cache
+        plain = [h for h in hs if h.kind < K["DVV"]]
+        rest = [h for h in hs if h.kind >= K["DVV"]]
+        hs, unit = [phase_ring(h, k, tag, ring_base(mode)) for g in (plain, rest) for k in range(4) for h in g], RING_SLOT
     else:
         hs, unit = [phase_a(h, tag) for h in hs] + [phase_b(h, tag) for h in hs], SLOT
     slot = 0
@@ -624,23 +796,27 @@ def finish(hs, tag, V0, FO, ring=False):
 # Ring cores.  The pair scheme below still waits once in two instructions for
 # most of the scalar cache's latency (measured on the 20-multiplexer: 43 of
 # the 100 cycles an instruction takes a wave).  A ring core keeps four records,
-# two pairs, in s[36:51] and has four phases of every handler: phase k works
+# two pairs, in 16 scalar registers and has four phases of every handler: phase k works
 # from record k and jumps to record k + 1.  The odd phases first wait for the
 # other pair, requested two instructions ago, then, their own pair being used
 # up, request the pair after it.  s62 is the byte offset of the pair requested
 # last: the record after an exit is at s62 - 16 in an even phase, at s62 in an
 # odd one.  Twice the handlers, so the slots are 32 bytes.
-RING = 36
 RING_SLOT = 32
 RING_PHASE = 6                   # the phase's place in a handler key's kind
 
 
-def phase_ring(h, k, tag):
+def ring_base(mode):
+    """First register of the ring: beside the series coefficients where there are any."""
+    return 8 if mode == 4 else 36
+
+
+def phase_ring(h, k, tag, base):
     c = _copy(h, h.kind | (k << RING_PHASE))
-    r = RING + 4 * k
+    r = base + 4 * k
     pay, cst = "s%d" % (r + 2), "s%d" % (r + 3)
-    own = RING + 8 * (k >> 1)
-    nxt = "s_setpc_b64 %s" % sp(RING + 4 * ((k + 1) & 3))
+    own = base + 8 * (k >> 1)
+    nxt = "s_setpc_b64 %s" % sp(base + 4 * ((k + 1) & 3))
     odd = k & 1
     fetch = ["s_add_u32 s62, s62, 32", "s_load_dwordx8 s[%d:%d], s[60:61], s62" % (own, own + 7)]
     if h.kind == K["EXIT"]:
@@ -684,7 +860,10 @@ def phase_ring(h, k, tag):
                 x = x.replace("s_set_gpr_idx_on s70,", "s_set_gpr_idx_on %s," % ("s73" if odd else pay))
                 x = x.replace("s_set_gpr_idx_on s71,", "s_set_gpr_idx_on s74,")
                 L.append(x if odd else x.replace("s72", cst))
-        L += [nxt]
+        if h.then:
+            L += ["s_mov_b64 s[76:77], %s" % sp(base + 4 * ((k + 1) & 3)), "s_branch .Lgpx_%s_%s" % (h.then, tag)]
+        else:
+            L += [nxt]
     for x in L:
         c.emit(x, insn_bytes(x))
     return c
@@ -828,11 +1007,12 @@ def exec_slot(j, left="s87"):
             "s_cselect_b64 exec, 0, s[74:75]"]
 
 
-def first_records(ring):
+def first_records(ring, mode=0):
     """Requests the records at s62, and enters the program there once they have come."""
     if ring:
-        return "s_load_dwordx16 s[%d:%d], s[60:61], s62" % (RING, RING + 15), \
-            ["s_add_u32 s62, s62, 32", "s_setpc_b64 %s" % sp(RING)]
+        b = ring_base(mode)
+        return "s_load_dwordx16 s[%d:%d], s[60:61], s62" % (b, b + 15), \
+            ["s_add_u32 s62, s62, 32", "s_setpc_b64 %s" % sp(b)]
     return "s_load_dwordx8 s[64:71], s[60:61], s62", ["s_setpc_b64 s[64:65]"]
 
 
@@ -844,7 +1024,7 @@ def unit_start(T, D, NF, V0, FO, tag, mode, ring):
     vl4, vy = "v%d" % (V0 + T), "v%d" % (V0 + T + 1)     # stack level 1 is free here
     L = ["v_mbcnt_lo_u32_b32 %s, -1, 0" % vy, "v_mbcnt_hi_u32_b32 %s, -1, %s" % (vy, vy),
          "v_lshlrev_b32_e32 %s, 2, %s" % (vl4, vy), "v_lshl_add_u32 %s, %s, 4, s97" % (vy, vy),
-         first_records(ring)[0]]
+         first_records(ring, mode)[0]]
     if mode in (0, 4):
         L += ["s_load_dwordx16 s[24:39], s[100:101], 0x0", "s_load_dwordx16 s[40:55], s[100:101], 0x40"]
     L += prefetch_start(tag, "0", "s96") + ["s_mov_b32 s99, 0"]
@@ -915,7 +1095,7 @@ def program_end(T, D, NF, V0, FO, tag, mode, ring):
          "v_lshl_add_u32 v%d, v%d, 4, s97" % (vy, vl)]
     for k in range(nb):
         L += ["ds_read_b128 %s, v%d offset:%d" % (quad(yr + 4 * k), vy, 1024 * k)]
-    L += ["s_waitcnt lgkmcnt(0)", first_records(ring)[0],
+    L += ["s_waitcnt lgkmcnt(0)", first_records(ring, mode)[0],
           "s_lshl_b32 s81, s81, 4", "s_add_u32 s81, s81, s62"]
     L += prefetch_start(tag, "1", "s81")
     kinds = [FIT_HITS, OUT_CASES] if mode == 2 else [FIT_MSE, FIT_SUM_ABS, FIT_HITS, FIT_CLASS, OUT_CASES]
@@ -1048,7 +1228,7 @@ def program_end(T, D, NF, V0, FO, tag, mode, ring):
     L += [".Lgpx_rest_%s:" % tag, "s_waitcnt lgkmcnt(0)", "s_cmp_eq_u32 s99, 0", "s_cbranch_scc1 .Lgpx_go_%s" % tag,
           "s_lshl_b32 s72, s78, 6", "s_add_u32 s58, s58, s72", "s_addc_u32 s59, s59, 0"]
     L += prefetch_lines(tag, "2")
-    L += ["s_branch .Lgpx_rest_%s" % tag, ".Lgpx_go_%s:" % tag] + first_records(ring)[1]
+    L += ["s_branch .Lgpx_rest_%s" % tag, ".Lgpx_go_%s:" % tag] + first_records(ring, mode)[1]
     return L
 
 
@@ -1083,7 +1263,7 @@ def count_out(nb, acc, tmp):
     return L + ["v_cvt_f64_u32_e32 %s, v%d" % (pair(acc[0]), tmp)]
 
 
-def transc(T, V0, NCV, tag, mode):
+def transc(T, V0, NCV, tag, mode, ring):
     """sin, cos, exp and log of T slots (s72 the operation, s66 the payload,
     s67 a constant operand): the arithmetic of gp_math.h, instruction by
     instruction, in the block's work registers, with operand and result
@@ -1108,12 +1288,13 @@ def transc(T, V0, NCV, tag, mode):
     L = [".Lgpx_fn_%s:" % tag, "s_and_b32 s73, s66, 0xff", "s_bfe_u32 s79, s66, 0x80010", "s_bitcmp1_b32 s66, 28",
          "s_cbranch_scc0 .Lgpx_fa_%s" % tag, "s_set_gpr_idx_on s79, gpr_idx(DST)"]
     L += ["v_mov_b32_e32 v%d, s67" % (V0 + j) for j in range(T)]
-    L += ["s_set_gpr_idx_off", "s_mov_b32 s73, s79", ".Lgpx_fa_%s:" % tag, "s_add_u32 s62, s62, 16",
-          "s_load_dwordx8 s[64:71], s[60:61], s62",
+    L += ["s_set_gpr_idx_off", "s_mov_b32 s73, s79", ".Lgpx_fa_%s:" % tag]
+    L += ["s_waitcnt lgkmcnt(0)"] if ring else ["s_add_u32 s62, s62, 16"]
+    L += [first_records(ring, mode)[0],
           "s_cmp_eq_u32 s72, 6", "s_cbranch_scc1 .Lgpx_exp_%s" % tag,
           "s_cmp_eq_u32 s72, 7", "s_cbranch_scc1 .Lgpx_log_%s" % tag,
           "s_cmp_eq_u32 s72, 5", "s_cbranch_scc1 .Lgpx_cos_%s" % tag]
-    fin = ["s_waitcnt lgkmcnt(0)", "s_setpc_b64 s[64:65]"]
+    fin = ["s_waitcnt lgkmcnt(0)"] + first_records(ring, mode)[1]
     out_of_line = []
 
     def const(nm, into):
@@ -1336,13 +1517,14 @@ def tail_lines(T, D, NF, V0, FO, tag, mode, ring):
         L += ["s_bfe_u32 s72, s66, 0x40018", "s_cmp_lg_u32 s72, 15", "s_cbranch_scc1 .Lgpx_fn_%s" % tag]
     L += program_end(T, D, NF, V0, FO, tag, mode, ring)
     if mode in (0, 4):
-        L += transc(T, V0, V0, tag, mode)
+        L += transc(T, V0, V0, tag, mode, ring)
+    if ring and mode != 2:
+        L += division_bodies(T, D, V0, tag)
     L += [".Lgpx_leave_%s:" % tag, "s_waitcnt vmcnt(0) lgkmcnt(0)"]
     return L
 
 
 def asm_text(T, D, NF, V0, FO, tag, hs, mode, ring=False):
-    assert not (ring and mode in (0, 4))     # their coefficients use the ring's registers
     slot = RING_SLOT if ring else SLOT
     L = []
     L.append("s_getpc_b64 s[76:77]")
@@ -1378,7 +1560,7 @@ def relabelled(hs, tag):
     out = []
     for h in hs:
         c = Handler(h.kind, h.op, h.p1, h.p2)
-        c.lines, c.size, c.slot = [re.sub(r"(\.Lgpx_end_)\w+", r"\g<1>" + tag, x) for x in h.lines], h.size, h.slot
+        c.lines, c.size, c.slot = [re.sub(r"(\.Lgpx_[a-z]+\d*_)\w+", r"\g<1>" + tag, x) for x in h.lines], h.size, h.slot
         out.append(c)
     return out
 
@@ -1419,7 +1601,7 @@ def main(out_dir):
         if AR in (0, 4):
             clob += ["s%d" % n for n in range(24, 56)]
         if ring:
-            clob += ["s%d" % n for n in range(RING, RING + 16)]
+            clob += ["s%d" % n for n in range(ring_base(AR), ring_base(AR) + 16)]
         core_lines = []
         core_lines.append("template <> struct Core<%d, %d, %d, %d, %d> {" % core)
         core_lines.append("    // runs one unit: its tile is loaded, then its programs run to their partial sums (or outputs);")
@@ -1457,11 +1639,12 @@ def main(out_dir):
         lines.append("    " + ", ".join(str(h.slot) for h in hs))
         lines.append("};")
     lines.append("struct CoreVariantDesc { int t, d, nf, ncv, arith; const CoreHandlerKey* keys; const uint16_t* slots; "
-                 "int n; int slot_bytes; bool ring; };")
+                 "int n; int slot_bytes; int xx; bool ring; };   // xx: levels with one-pass handlers of two variables")
     lines.append("static const CoreVariantDesc kCoreVariants[] = {")
     for (T, D, NF, NCV, AR, tag, hs, nslots, ring) in host:
-        lines.append("    {%d, %d, %d, %d, %d, kCoreKeys_%s, kCoreSlots_%s, %d, %d, %s},"
-                     % (T, D, NF, NCV, AR, tag, tag, len(hs), RING_SLOT if ring else SLOT, "true" if ring else "false"))
+        lines.append("    {%d, %d, %d, %d, %d, kCoreKeys_%s, kCoreSlots_%s, %d, %d, %d, %s},"
+                     % (T, D, NF, NCV, AR, tag, tag, len(hs), RING_SLOT if ring else SLOT, xx_levels(D, NF, AR, ring),
+                        "true" if ring else "false"))
     lines.append("};")
     path = os.path.join(out_dir, "core_gen.inc")
     write_if_changed(path, "\n".join(lines) + "\n")

@@ -597,3 +597,43 @@ def test_block_transcendentals(vi):
     exact = (gi == oi) | (np.isnan(got) & np.isnan(o))
     assert (exact | (np.abs(gi - oi) <= 1)).all(), np.argwhere(~exact)[:5]
     assert exact.mean() > 0.999
+
+
+@pytest.mark.parametrize("vi", [i for i in REAL if i >= len(gen_core.VARIANTS)])
+def test_ring_core_operand_forms(vi):
+    """Every operand form of division, the compares, AND, OR and IF on a ring core, at the lowest and at the highest
+    levels the core has (where a variable has no level above it to be copied to), with protected divisors, signed
+    zeros, NaN and equal operands among the cases: the oracle's bits."""
+    T, D, NF, NCV, mode = ALL[vi]
+    F = min(NF, 3)
+    x = lambda k: "x%d" % (k % F)   # noqa: E731
+    ops = ("/", ">", "<", "==", "and", "or")
+
+    def deep(e, levels):
+        """e evaluated with `levels` values below it on the stack: each partner is a tree that needs as many levels."""
+        full = lambda n: x(n) if n == 0 else "(+ %s %s)" % (full(n - 1), full(n - 1))   # noqa: E731
+        for n in range(levels):
+            e = "(- %s %s)" % (full(D - 1 - (levels - 1 - n)), e)
+        return e
+    exprs = []
+    for f in ops:
+        p, q = "(+ %s %s)" % (x(0), x(2)), "(* %s %s)" % (x(1), x(2))
+        exprs += ["(%s %s %s)" % (f, a, b) for a, b in (
+            (p, q), (p, "(+ %s (* %s %s))" % (x(0), q, p)), ("(- %s (* %s %s))" % (x(1), q, p), p), (p, x(1)), (x(1), q),
+            (x(0), x(1)), (x(1), x(1)), (p, "0.5"), ("-0.0", q), (x(0), "2"), ("0.25", x(1)))]
+        exprs += [deep("(%s (+ %s 0.5) %s)" % (f, x(0), x(1)), n) for n in (1, 2)]
+    exprs += ["(if %s %s %s)" % (x(0), x(1), x(2)), "(if (> %s %s) (* %s 3) -1.5)" % (x(0), x(1), x(2)),
+              "(if (+ %s 1) (* (- %s %s) (+ %s %s)) %s)" % (x(0), x(1), x(2), x(1), x(0), x(1)),
+              "(if %s (* (- %s %s) (+ %s %s)) (- 1 %s))" % (x(0), x(1), x(2), x(1), x(0), x(1)),
+              "(if (- 1 %s) %s (* (- %s %s) (+ %s %s)))" % (x(0), x(1), x(1), x(2), x(1), x(0))]
+    from tests import progs
+    pop = progs.pop(*exprs)
+    N = 64 * T + 19
+    X = np.round(synth.uniform_cases(synth.rng_for(950 + vi), F, N, -2, 2))
+    X[0, ::7] = -0.0
+    X[F - 1, 1::9] = np.nan
+    X[0, 2::11] = 5e-7
+    o = oracle.tree_outputs(pop.tok, pop.cst, pop.off, X)
+    got = emulate(vi, pop, X, np.zeros(N, np.float32), "cases")
+    bad = np.argwhere(~((got.view(np.int32) == o.view(np.int32)) | (np.isnan(got) & np.isnan(o))))
+    assert not len(bad), (exprs[bad[0][0]], got[tuple(bad[0])], o[tuple(bad[0])])
