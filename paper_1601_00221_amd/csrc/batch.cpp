@@ -84,8 +84,8 @@ gp_status plan_batch(const std::vector<BatchJobRef>& jobs, const std::vector<gp_
         // programs of this job by falling cost, in G groups of about equal cost
         std::vector<uint32_t> order, goff;
         std::vector<int64_t> rec((size_t)pd.n_prog + 1);
-        cost_order(pd, order);
-        gp_status st = core_translate(pd, vi, order.data(), jcode, jprogs);
+        cost_order(pd.cost, order);
+        gp_status st = core_translate(pd, vi, order.data(), nullptr, jcode, jprogs);
         if (st != GP_OK) return st;
         if ((plan.code.size() + jcode.size()) * 4 > 0xFFFFFFF0ull) return fail(GP_E_INVAL, "batch code exceeds 4 GiB");
         const int64_t base = (int64_t)plan.code.size() / 4;
@@ -93,7 +93,7 @@ gp_status plan_batch(const std::vector<BatchJobRef>& jobs, const std::vector<gp_
         for (int32_t i = 0; i < pd.n_prog; i++) rec[i] = base + jprogs[order[i]].code_off / 4;
         rec[pd.n_prog] = rec[pd.n_prog - 1] + jprogs[order[pd.n_prog - 1]].len;
         const int32_t G = std::max<int32_t>(1, (pd.n_prog + unit_prog - 1) / unit_prog);
-        cut_groups(pd, order, rec, G, goff);
+        cut_groups(pd.cost, order, rec, G, goff);
         std::vector<double> gcost(G, 0.0);
         for (int32_t g = 0, i = 0; g < G; g++)
             for (; i < pd.n_prog && rec[i] < goff[g + 1]; i++) gcost[g] += pd.cost[order[i]];
@@ -186,8 +186,9 @@ gp_status launch_plan(const BatchPlan& p, BatchScratch& sc, hipStream_t s) {
     a.n_units = (int32_t)p.units.size();
     a.persistent = p.persistent ? 1 : 0;
     a.prefetch = code_prefetch();
+    const size_t waves = (size_t)core_variant_waves(p.vi);
     const uint32_t grid = p.persistent ? (uint32_t)(device_cus() * core_blocks_per_cu(p.vi))
-                                       : (uint32_t)((p.units.size() + 3) / 4);
+                                       : (uint32_t)((p.units.size() + waves - 1) / waves);
     int slot;
     hipError_t e = hipSuccess;
     if (p.persistent) e = core_zero_counter(a.counter, s);

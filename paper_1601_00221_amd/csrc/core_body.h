@@ -54,11 +54,13 @@ __device__ __forceinline__ uint32_t lds_address(const void* p) {
     return (uint32_t)(uintptr_t)(LdsPtr)(void*)p;
 }
 
-template <int T, bool TABLES>
+template <int T, int W, bool TABLES>
 struct Shared {
     double tab[TABLES ? gmath::kTabSize + (gmath::kTabSize & 1) : 2];
-    float y[4][64 * T];          // each wave's targets of its tile
+    float y[W][64 * T];          // each wave's targets of its tile
 };
+// The rows of a block's tile (sin, cos, exp or log of a feature), behind Shared.
+extern __shared__ __attribute__((aligned(16))) float s_rows[];
 
 // A wave-uniform value in scalar registers.
 __device__ __forceinline__ uint32_t uniform(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
@@ -68,16 +70,16 @@ __device__ __forceinline__ uint64_t uniform(uint64_t v) {
 
 // Units come either from a table (batched launches: persistent waves pull
 // them longest first from a counter, or one wave per unit) or implicitly
-// over one dataset: block unit b = (group quad b div chunks, chunk b mod
-// chunks); wave w of the block runs program group 4 * quad + w on tiles
-// chunk * tiles_per_wave + i, i = 0 .. tiles_per_wave - 1.  The four waves of
+// over one dataset: block unit b = (W groups from W * (b div chunks) on, chunk
+// b mod chunks); wave w of the block runs the w-th of those groups on tiles
+// chunk * tiles_per_wave + i, i = 0 .. tiles_per_wave - 1.  The W waves of
 // a block work on the same tiles with different instruction streams, so
 // their scalar-cache misses do not fall on the same cycles.
-template <int T, int D, int NF, int V0, int MODE>
+template <int T, int D, int NF, int V0, int MODE, int W, bool ROWS>
 __device__ __forceinline__ void k_core_body(const CoreArgs& a) {
     static_assert(T % 4 == 0, "a tile holds whole 256-case blocks");
     constexpr bool kTables = MODE == 0 || MODE == 4;
-    __shared__ __attribute__((aligned(16))) Shared<T, kTables> sh;
+    __shared__ __attribute__((aligned(16))) Shared<T, W, kTables> sh;
     // the transcendentals' reduction tables, copied into LDS by the whole block
     if constexpr (kTables) {
         gmath::tab_fill(sh.tab, (int)threadIdx.x, (int)blockDim.x);
@@ -88,7 +90,7 @@ __device__ __forceinline__ void k_core_body(const CoreArgs& a) {
     const bool table = a.units != nullptr;
     uint32_t u, grp = 0, chunk = 0;
     if (table) {
-        u = blockIdx.x * 4u + wib;
+        u = blockIdx.x * (uint32_t)W + wib;
     } else {
         // Blocks go to the 8 XCDs round robin; give each XCD a contiguous
         // range of block units so a program group's code stays in one L2.
@@ -97,16 +99,17 @@ __device__ __forceinline__ void k_core_body(const CoreArgs& a) {
         if (!a.probe) {
             if (u >= (uint32_t)a.n_units) return;
             if (a.same_group) {
-                // wave w of the block runs group u div q on chunk 4 (u mod q) + w, q = chunks / 4 rounded up
-                const uint32_t q = ((uint32_t)a.chunks + 3u) / 4u;
+                // wave w of the block runs group u div q on chunk W (u mod q) + w, q = chunks / W rounded up
+                const uint32_t q = ((uint32_t)a.chunks + (uint32_t)W - 1u) / (uint32_t)W;
                 grp = u / q;
-                chunk = (u % q) * 4u + wib;
+                chunk = (u % q) * (uint32_t)W + wib;
                 if (chunk >= (uint32_t)a.chunks) return;
             } else {
-                grp = (u / (uint32_t)a.chunks) * 4u + wib;
+                grp = (u / (uint32_t)a.chunks) * (uint32_t)W + wib;
                 chunk = u % (uint32_t)a.chunks;
             }
-            if (grp >= (uint32_t)a.n_groups) return;
+            // (a wave without a group still computes its share of the block's rows)
+            if (grp >= (uint32_t)a.n_groups && !(ROWS && a.n_rows)) return;
         }
     }
     CoreUnit w;
@@ -126,8 +129,10 @@ __device__ __forceinline__ void k_core_body(const CoreArgs& a) {
             if (it >= (uint32_t)a.tiles_per_wave) return;
             tile = chunk * (uint32_t)a.tiles_per_wave + it;
             if (tile >= (uint32_t)a.tiles) return;
-            c0 = a.group_off[grp];
-            c1 = a.group_off[grp + 1];
+            if (grp < (uint32_t)a.n_groups) {
+                c0 = a.group_off[grp];
+                c1 = a.group_off[grp + 1];
+            }
             X = a.X;
             y = a.y;
             N = a.N;
@@ -155,14 +160,27 @@ __device__ __forceinline__ void k_core_body(const CoreArgs& a) {
             kind = jd.kind;
             pbase = jd.part_base;
         }
-        if (c0 >= c1 && !a.probe) continue;
+        const bool rows = ROWS && a.n_rows > 0;
+        if (c0 >= c1 && !a.probe && !rows) continue;
         const int64_t tile0 = (int64_t)tile * (64 * T);        // first case of the tile
         const int64_t left = N - tile0, n_blocks = (N + 255) / 256;
+        if constexpr (ROWS) {
+            // first the wave's share of the rows: records row_off[w] .. row_off[w + 1)
+            w.own_off = uniform(c0 * 16u);
+            w.own_end = uniform(c1 * 16u);
+            w.own_kind = rows ? uniform((uint32_t)kind) : 0xFFFFFFFFu;
+            if (rows) {
+                c0 = a.row_off[wib];
+                c1 = a.row_off[wib + 1];
+                kind = CORE_TO_ROW;
+            }
+        }
         w.off = uniform(c0 * 16u);
         w.end = uniform(c1 * 16u);
         w.X = uniform((uint64_t)(X + tile0));
         w.stride = uniform((uint64_t)N * 4u);
-        w.y = uniform((uint64_t)(y + tile0));
+        // (per-case outputs need no targets, but a block that starts with rows loads some: a feature then)
+        w.y = uniform((uint64_t)((y ? y : X) + tile0));
         w.n_load = uniform((uint32_t)n_load);
         w.left = uniform((uint32_t)(left < 64 * T ? left : 64 * T));
         w.kind = uniform((uint32_t)kind);
@@ -182,6 +200,7 @@ __device__ __forceinline__ void k_core_body(const CoreArgs& a) {
             if (threadIdx.x == 0) {
                 a.probe_out[0] = handlers;
                 a.probe_out[1] = lds_address(sh.tab);
+                a.probe_out[2] = ROWS ? lds_address(s_rows) : 0u;
             }
             return;
         }
@@ -193,10 +212,11 @@ __device__ __forceinline__ void k_core_body(const CoreArgs& a) {
 // reserved-register report); the core owns v[V0 ...].  MODE: 0 full, 1 no
 // sin/cos/exp/log code (for programs without them), 2 Boolean, 3 trees only
 // without sin/cos/exp/log code, 4 trees only with it.
-#define GPX_KERNEL(T, D, NF, V0, MODE, NAME)                                                            \
-    __global__ __launch_bounds__(256) __attribute__((amdgpu_num_vgpr((V0) / 2))) void                   \
+// W: waves of a block; ROWS: the block computes rows for its tile first.
+#define GPX_KERNEL(T, D, NF, V0, MODE, W, ROWS, NAME)                                                   \
+    __global__ __launch_bounds__(64 * (W)) __attribute__((amdgpu_num_vgpr((V0) / 2))) void              \
         k_core_##NAME(CoreArgs a) {                                                                     \
-        k_core_body<T, D, NF, V0, (MODE)>(a);                                                           \
+        k_core_body<T, D, NF, V0, (MODE), (W), (ROWS)>(a);                                              \
     }
 
 }  // namespace gpx

@@ -5,6 +5,7 @@
 #include <stdio.h>
 #include <string.h>
 
+#include <algorithm>
 #include <mutex>
 #include <unordered_map>
 #include <vector>
@@ -13,6 +14,7 @@
 #include "core_host.h"
 #include "core_kernels.h"
 #include "gp_internal.h"
+#include "gp_math.h"
 #include "runtime.h"
 
 namespace gpx {
@@ -153,13 +155,15 @@ gp_status core_ready(int vi, hipStream_t s) {
     a.probe = 1;
     a.probe_out = d;
     e = core_launch(vi, a, 1, s);
-    uint64_t probed[2] = {0, 1};   // the handler table, and where the transcendentals' tables lie in LDS
-    if (e == hipSuccess) e = hipMemcpyAsync(probed, d, 16, hipMemcpyDeviceToHost, s);
+    uint64_t probed[3] = {0, 1, 1};   // the handler table, and where the reduction tables and the rows lie in LDS
+    if (e == hipSuccess) e = hipMemcpyAsync(probed, d, 24, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     (void)hipFree(d);
     if (e != hipSuccess) return fail(GP_E_DEVICE, "handler table probe: %s", hipGetErrorString(e));
     const uint64_t base = probed[0];
-    if (probed[1] != 0) return fail(GP_E_DEVICE, "reduction tables at LDS offset %llu", (unsigned long long)probed[1]);
+    if (probed[1] != 0 || probed[2] != (uint64_t)kCoreVariants[vi].rows_base)
+        return fail(GP_E_DEVICE, "reduction tables at LDS offset %llu, rows at %llu", (unsigned long long)probed[1],
+                    (unsigned long long)probed[2]);
     if (base == 0 || (base & (GPX_SLOT - 1)) != 0) return fail(GP_E_DEVICE, "handler table probe returned %llx",
                                                                (unsigned long long)base);
     m.slot = variant_slots(vi);
@@ -298,8 +302,27 @@ bool is_core_op(uint32_t op, bool boolean) {
 
 }  // namespace
 
-static int translate_tree(const uint32_t* w, int64_t n_instr, int vi, const VariantMap& m, uint32_t row, uint32_t next,
-                          uint32_t* out, int64_t cap, int64_t* n_out, char* err) {
+// sin, cos, exp or log of a constant, as the kernel computes it
+static uint32_t unary_of_constant(uint32_t op, uint32_t bits) {
+    static const std::vector<double> tab = [] {
+        std::vector<double> t(gmath::kTabSize);
+        gmath::tab_fill(t.data(), 0, 1);
+        return t;
+    }();
+    float a[1] = {gmath::float_of(bits)};
+    switch (op) {
+        case GP_SIN: gmath::sincos_n<1>(a, false, tab.data(), 0); break;
+        case GP_COS: gmath::sincos_n<1>(a, true, tab.data(), 0); break;
+        case GP_EXPC: gmath::expc_n<1>(a, tab.data(), 0); break;
+        default: gmath::plog_n<1>(a, tab.data(), 0); break;
+    }
+    return gmath::bits_of(a[0]);
+}
+
+static int row_key(uint32_t op, int f) { return (int)(op - GP_SIN) * GP_MAX_FEAT + f; }
+
+static int translate_tree(const uint32_t* w, int64_t n_instr, int vi, const VariantMap& m, const RowPlan* rows,
+                          uint32_t row, uint32_t next, uint32_t* out, int64_t cap, int64_t* n_out, char* err) {
     const CoreVariantDesc& v = kCoreVariants[vi];
     const int T = v.t, FO = core_reg_levels(vi) * T;
     Emitter e{v, m, out, cap, err};
@@ -405,8 +428,16 @@ static int translate_tree(const uint32_t* w, int64_t n_instr, int vi, const Vari
             case M_XC: e.apply(op, bl, xa, 0, h * T, false, true, c); break;
             case M_CX: e.apply(op, bl, 0, xb, h * T, true, false, c); break;
             case M_S: e.exit(op, (h - 1) * T, 0, (h - 1) * T, false, false, 0); break;
-            case M_X: e.exit(op, xa, 0, h * T, false, false, 0); break;
-            default: e.exit(op, 0, 0, h * T, true, false, c); break;  // M_C
+            case M_X: {
+                const int r = rows && rows->n() > 0 ? rows->row[row_key(op, fa)] : -1;
+                if (r >= 0) e.put(CK_PUSHR, 0, h, 0, (uint32_t)(r * 256 * T), 0);
+                else e.exit(op, xa, 0, h * T, false, false, 0);
+                break;
+            }
+            default:  // M_C
+                if (v.ring) e.put(CK_PUSHC, 0, 0, 0, (uint32_t)(h * T), unary_of_constant(op, c));
+                else e.exit(op, 0, 0, h * T, true, false, c);
+                break;
         }
     }
     e.end(row, next);
@@ -493,8 +524,10 @@ constexpr int kCodePadding = 32;   // words
 // the end; a register program as linear_records counts.  The code holds the
 // programs one after another in the order given (null: their own order), each
 // ending with the length of the one after it; progs[p] says where program p
-// lies.
-static gp_status translate_with(const ProgData& pd, int vi, const VariantMap& m, const uint32_t* order,
+// lies.  With `rows`, functions of a feature that have a row push it, and the
+// programs that compute the rows follow the others: two records each, a
+// share for every wave of a block.
+static gp_status translate_with(const ProgData& pd, int vi, const VariantMap& m, const uint32_t* order, RowPlan* rows,
                                 std::vector<uint32_t>& code, std::vector<DevProg>& progs) {
     const int32_t P = pd.n_prog;
     progs = pd.progs;
@@ -509,7 +542,20 @@ static gp_status translate_with(const ProgData& pd, int vi, const VariantMap& m,
     if (start[P] * 16 > 0xFFFFFFF0ll) return fail(GP_E_INVAL, "programs exceed 4 GiB of core code");
     // the core reads records two or four at a time, ahead of the one it runs: up
     // to seven past a program's last one, so the code ends with padding
-    code.assign((size_t)start[P] * 4 + kCodePadding, 0u);
+    const int32_t R = rows ? rows->n() : 0;
+    code.assign((size_t)(start[P] + 2 * R) * 4 + kCodePadding, 0u);
+    if (rows) {
+        const CoreVariantDesc& v = kCoreVariants[vi];
+        rows->rec.clear();
+        for (int32_t w = 0; w <= v.waves; w++) rows->rec.push_back((uint32_t)(start[P] + 2 * ((int64_t)R * w / v.waves)));
+        char err[256];
+        for (int32_t r = 0; r < R; r++) {
+            Emitter e{v, m, code.data() + 4 * (start[P] + 2 * r), 2, err};
+            e.exit(rows->op[r], (core_reg_levels(vi) + rows->feat[r]) * v.t, 0, 0, false, false, 0);
+            e.end((uint32_t)r, 2);
+            if (!e.ok) return fail(GP_E_INVAL, "row %d: %s", r, err);
+        }
+    }
     std::vector<int32_t> rc((size_t)P, GP_OK);
     auto translate = [&](int32_t i, uint32_t* out, int64_t cap, int64_t* n, char* err) {
         const int32_t p = at(i);
@@ -517,7 +563,7 @@ static gp_status translate_with(const ProgData& pd, int vi, const VariantMap& m,
         const uint32_t next = i + 1 < P ? (uint32_t)(start[i + 2] - start[i + 1]) : 0u;
         const uint32_t* w = pd.code.data() + src.code_off;
         if ((src.meta & 1u) == FORM_TREE)
-            return translate_tree(w, src.len, vi, m, (uint32_t)src.row, next, out, cap, n, err);
+            return translate_tree(w, src.len, vi, m, rows, (uint32_t)src.row, next, out, cap, n, err);
         return translate_linear(w, src.len, w + src.len, pd.n_reg, pd.n_feat, vi, m, (uint32_t)src.row, next, out, cap,
                                 n, err);
     };
@@ -546,7 +592,47 @@ static gp_status translate_with(const ProgData& pd, int vi, const VariantMap& m,
     return GP_OK;
 }
 
-gp_status core_translate(const ProgData& pd, int vi, const uint32_t* order, std::vector<uint32_t>& code,
+// The rows worth computing: those used by at least one and a half programs
+// for each block that computes them (over the fewest groups the programs are
+// cut into), the most used first, as many as the LDS beside the resident
+// blocks holds.  A row costs a block one evaluation a tile, by one of its
+// waves; a use then reads 16 bytes a lane instead of evaluating the function
+// again (about 90 vector instructions at T = 4).
+static constexpr uint32_t kRowSaving = 33;   // of the cost of one use (runtime.cpp, op_cost)
+
+void plan_rows(const ProgData& pd, int vi, int64_t blocks, RowPlan& plan) {
+    plan = RowPlan();
+    const CoreVariantDesc& v = kCoreVariants[vi];
+    plan.cost = pd.cost;
+    if (v.rows_base == 0 || pd.form != FORM_TREE || pd.n_transc == 0 || pd.n_load > GP_MAX_FEAT) return;
+    std::vector<int64_t> uses(4 * GP_MAX_FEAT, 0);
+    auto each = [&](const DevProg& p, auto&& fn) {
+        const uint32_t* w = pd.code.data() + p.code_off;
+        for (uint32_t i = 0; i < p.len; i++) {
+            const uint32_t op = w[2 * i] & 15u, mode = (w[2 * i] >> 4) & 15u;
+            if (mode == M_X && op >= GP_SIN && op <= GP_PLOG) fn(row_key(op, (int)((w[2 * i] >> 8) & 255u)));
+        }
+    };
+    for (const DevProg& p : pd.progs) each(p, [&](int k) { uses[k]++; });
+    const int per_cu = std::max(1, 4 * (512 / ((v.ncv + (core_reg_levels(vi) + v.nf) * v.t + 7) / 8 * 8)) / v.waves);
+    const int most = ((160 << 10) / per_cu - v.rows_base) / (256 * v.t);
+    std::vector<int> keys;
+    for (int k = 0; k < (int)uses.size(); k++)
+        if (2 * uses[k] >= 3 * std::max<int64_t>(2, blocks)) keys.push_back(k);
+    std::stable_sort(keys.begin(), keys.end(), [&](int a, int b) { return uses[a] > uses[b]; });
+    if ((int)keys.size() > most) keys.resize(std::max(0, most));
+    if (keys.empty()) return;
+    plan.row.assign(uses.size(), -1);
+    for (size_t r = 0; r < keys.size(); r++) {
+        plan.row[keys[r]] = (int32_t)r;
+        plan.op.push_back(GP_SIN + (uint32_t)(keys[r] / GP_MAX_FEAT));
+        plan.feat.push_back(keys[r] % GP_MAX_FEAT);
+    }
+    for (size_t i = 0; i < pd.progs.size(); i++)
+        each(pd.progs[i], [&](int k) { if (plan.row[k] >= 0) plan.cost[i] -= std::min(plan.cost[i] - 1, kRowSaving); });
+}
+
+gp_status core_translate(const ProgData& pd, int vi, const uint32_t* order, RowPlan* rows, std::vector<uint32_t>& code,
                          std::vector<DevProg>& progs) {
     VariantMap m;
     {
@@ -554,16 +640,17 @@ gp_status core_translate(const ProgData& pd, int vi, const uint32_t* order, std:
         if ((int)g_maps.size() <= vi || !g_maps[vi].ready) return fail(GP_E_DEVICE, "core variant %d not probed", vi);
         m = g_maps[vi];
     }
-    return translate_with(pd, vi, m, order, code, progs);
+    return translate_with(pd, vi, m, order, rows, code, progs);
 }
 
 gp_status core_translate_at(const ProgData& pd, int vi, uint64_t base, std::vector<uint32_t>& code,
                             std::vector<DevProg>& progs) {
     if (vi < 0 || vi >= core_variants()) return fail(GP_E_INVAL, "variant %d does not exist", vi);
     if (base & (GPX_SLOT - 1)) return fail(GP_E_INVAL, "table base must be %d-byte aligned", GPX_SLOT);
-    return translate_with(pd, vi, map_at(vi, base), nullptr, code, progs);
+    return translate_with(pd, vi, map_at(vi, base), nullptr, nullptr, code, progs);
 }
 
+int core_variant_waves(int vi) { return kCoreVariants[vi].waves; }
 int core_variant_t(int vi) { return kCoreVariants[vi].t; }
 int core_variant_ncv(int vi) { return kCoreVariants[vi].ncv; }
 int core_variant_d(int vi) { return kCoreVariants[vi].d; }

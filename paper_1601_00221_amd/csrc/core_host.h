@@ -33,9 +33,14 @@ int pick_core_variant(int n_load, int depth, double transc_frac, bool has_transc
 gp_status core_ready(int vi, hipStream_t s);
 // True if core_ready has found variant vi's handler table on the current device.
 bool core_is_ready(int vi);
+int core_variant_waves(int vi);    // waves of a block
+// Which functions of a feature a launch computes once a tile into LDS, for variant vi, where `blocks` blocks share a
+// tile's programs; and the programs' costs without them.
+void plan_rows(const ProgData& pd, int vi, int64_t blocks, RowPlan& plan);
 // Core instructions of lowered programs, one program after another in the
-// given order (null: their own), and where each one lies.
-gp_status core_translate(const ProgData& pd, int vi, const uint32_t* order, std::vector<uint32_t>& code,
+// given order (null: their own), and where each one lies.  rows (may be null)
+// is read, and told where the rows' programs lie.
+gp_status core_translate(const ProgData& pd, int vi, const uint32_t* order, RowPlan* rows, std::vector<uint32_t>& code,
                          std::vector<DevProg>& progs);
 // The same with the handler table taken to start at `base` (no device needed).
 gp_status core_translate_at(const ProgData& pd, int vi, uint64_t base, std::vector<uint32_t>& code,

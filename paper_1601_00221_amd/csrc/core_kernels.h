@@ -13,6 +13,8 @@ namespace gpx {
 // its constant the program's row.
 enum : uint32_t { CORE_OP_END = 15 };
 
+enum : int32_t { CORE_TO_ROW = 5 };     // "fitness kind" of the programs that compute a block's rows
+
 struct DatasetDesc {
     const float* X;
     const float* y;
@@ -69,7 +71,10 @@ struct CoreArgs {
     int32_t prefetch;           // 64-byte lines of the next program's code loaded into the scalar cache at a
                                 // time (1-14), or 0: none
     int32_t n_groups;           // program groups (implicit units)
-    int32_t same_group;         // implicit units: the four waves of a block run one group on four chunks
+    int32_t n_rows;             // rows (sin, cos, exp or log of a feature) each block computes for its tile into LDS,
+                                // by the programs row_off[w] .. row_off[w + 1] of its wave w; 0: none
+    const uint32_t* row_off;
+    int32_t same_group;         // implicit units: the waves of a block run one group on as many chunks
     int64_t n_bits;             // Boolean kernels: cases (bits) in the N words of each row
     uint32_t probe;             // nonzero: write the handler table address and return
     double* partials;

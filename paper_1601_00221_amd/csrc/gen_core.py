@@ -146,6 +146,24 @@ def xx_levels(D, NF, mode, ring):
     return 0 if NF > 8 else 3 if ring and D > 6 else D
 
 
+def waves_per_block(T, D, NF, NCV, mode, ring):
+    """Four; eight in ring cores with sin/cos/exp/log whose occupancy eight
+    divides: the waves of a block share the rows of its tile in LDS, and a
+    wider block has room for more of them."""
+    simd = 512 // ((NCV + (reg_levels(D, mode) + NF) * T + 7) // 8 * 8)
+    return 8 if ring and mode == 4 and simd % 2 == 0 else 4
+
+
+def rows_base(T, D, NF, NCV, mode):
+    """LDS address of a block's rows: behind the reduction tables and each wave's targets."""
+    return LDS_PI + 8 * 8 + 256 * T * waves_per_block(T, D, NF, NCV, mode, True)
+
+
+def row_address(V0):
+    """The register that holds a lane's offset in a row."""
+    return V0 - work_regs(V0, 4, True)
+
+
 def reg_levels(D, mode):
     """Register/stack levels before the features: linear programs need
     LIN_REGS registers; Boolean and trees-only kernels have none."""
@@ -155,7 +173,9 @@ def reg_levels(D, mode):
 KINDS = ["EXIT", "SS", "SSR", "SX", "XS", "SC", "CS", "XX", "XX2", "XC", "CX", "PUSHX", "PUSHC",
          "RR", "XR", "FF", "CR", "RC", "MOVC", "MOVX", "DVV", "DVC", "DCV", "CVV", "CVC", "CCV", "IF3",
          # ring cores: compares and logic of two stack entries or of one and a variable, divisions with a stack entry
-         "CSS", "CSX", "DSS", "DSSR", "DSX", "DXS"]
+         "CSS", "CSX", "DSS", "DSSR", "DSX", "DXS",
+         # ring cores with sin/cos/exp/log: push a row that the block has computed for its tile
+         "PUSHR"]
 # Protected division runs in the core: a / b with a and b at any two offsets
 # (DVV), b the constant (DVC) or a the constant (DCV), the result to a third
 # offset.  Its temporaries are the last DIV_TMP registers of the compiler's
@@ -177,7 +197,7 @@ VOP3_ONLY = ("v_bitop3", "v_div_scale_f32", "v_fma_f32", "v_div_fmas_f32", "v_di
 def insn_bytes(text):
     """Encoded size of an instruction the handlers use: scalar loads, VOP3
     encodings and a scalar move of a literal take 8 bytes, everything else 4."""
-    if text.startswith(("s_load",) + VOP3_ONLY) or text.split(" ")[0].endswith("_e64"):
+    if text.startswith(("s_load", "ds_") + VOP3_ONLY) or text.split(" ")[0].endswith("_e64"):
         return 8
     if text.startswith("s_mov_b32") and "0x" in text:
         return 8
@@ -193,6 +213,7 @@ class Handler:
         self.body = None        # its operation, a function of the registers that hold its offsets and constant
         self.n_idx = 0          # and the number of those offsets
         self.then = None        # ring cores: a shared body that the handler goes on to
+        self.row = None         # a push of a row: its first register, the lane's offset, a temporary, the rows' LDS address
 
     def emit(self, text, nbytes):
         self.lines.append(text)
@@ -366,6 +387,9 @@ def gen_variant(T, D, NF, NCV, mode=0, ring=False):
         hs.append(if_handler(T, V0))
     else:
         ring_handlers(hs, T, D, V0, prologue, epilogue, valu)
+        for l in range(D if mode == 4 else 0):
+            hs.append(Handler(K["PUSHR"], 0, l))
+            hs[-1].row = (V0 + l * T, row_address(V0), V0 - 1, rows_base(T, D, NF, NCV, mode))
 
     if mode >= 3:                      # trees only: no linear handlers
         return finish(hs, tag, V0, FO, ring, mode)
@@ -822,6 +846,13 @@ def phase_ring(h, k, tag, base):
     if h.kind == K["EXIT"]:
         L = ["s_set_gpr_idx_off"] + ([] if odd else ["s_sub_u32 s62, s62, 16"]) + \
             ["s_mov_b32 s66, %s" % pay, "s_mov_b32 s67, %s" % cst, "s_branch .Lgpx_end_%s" % tag]
+    elif h.row:
+        # the pair is requested after the row has come, so that only the row is waited for
+        reg, at, tmp, base_lds = h.row
+        L = ["s_waitcnt lgkmcnt(0)"] if odd else []
+        L += ["s_set_gpr_idx_off", "v_add_u32_e32 v%d, %s, v%d" % (tmp, pay, at),
+              "ds_read_b128 %s, v%d offset:%d" % (quad(reg), tmp, base_lds), "s_waitcnt lgkmcnt(0)"]
+        L += (fetch if odd else []) + [nxt]
     elif h.body and not odd:
         if h.n_idx == 3:
             L = ["s_lshr_b32 s74, %s, 8" % pay, "s_lshr_b32 s79, %s, 16" % pay] + h.body(pay, "s74", "s79", cst, None)
@@ -956,9 +987,12 @@ def phase_b(h, tag):
 #   s93 fitness kind        s[94:95] per-case outputs at the tile    s96 byte offset where the unit's code ends
 #   s97 LDS address of the wave's targets           s98 bits from the tile's start to the end (Boolean)
 #   s[100:101] the series coefficients (COEF)
+# Ring cores with sin/cos/exp/log first run the programs that compute their share of the tile's rows (kind TO_ROW),
+# meet the block's other waves, and go on to their own:
+#   s56, s57 byte offsets of those, s98 their kind; s98 = -1: no rows, s62, s96 and s93 are the wave's own
 # s[24:55] hold the coefficients (kernels with sin/cos/exp/log); s58, s59, s79-s81, s99, s72-s77 are temporaries.
 PF_LINES = 14                    # 64-byte lines of the next program fetched beside its first records
-FIT_SUM_ABS, FIT_MSE, FIT_HITS, OUT_CASES, FIT_CLASS = 0, 1, 2, 3, 4
+FIT_SUM_ABS, FIT_MSE, FIT_HITS, OUT_CASES, FIT_CLASS, TO_ROW = 0, 1, 2, 3, 4, 5
 
 # binary64 series constants in SGPR pairs, in the order of gmath::kCoreCoef
 COEF = {n: 24 + 2 * i for i, n in enumerate(
@@ -977,10 +1011,10 @@ def transc_slots(NCV):
     return 2 if NCV >= 48 else 1
 
 
-def work_regs(NCV, mode):
+def work_regs(NCV, mode, ring=False):
     """VGPRs below the core's range that the block uses (and clobbers)."""
     if mode in (0, 4):
-        n = 14 * transc_slots(NCV) + 2
+        n = 14 * transc_slots(NCV) + 2 + (2 if ring and mode == 4 else 0)    # a lane's offset in a row, alone at the bottom
         return n + (2 * len(VCONST) if NCV >= 64 else 0)
     return 0 if mode == 2 else DIV_TMP
 
@@ -1025,6 +1059,11 @@ def unit_start(T, D, NF, V0, FO, tag, mode, ring):
     L = ["v_mbcnt_lo_u32_b32 %s, -1, 0" % vy, "v_mbcnt_hi_u32_b32 %s, -1, %s" % (vy, vy),
          "v_lshlrev_b32_e32 %s, 2, %s" % (vl4, vy), "v_lshl_add_u32 %s, %s, 4, s97" % (vy, vy),
          first_records(ring, mode)[0]]
+    rows = ring and mode == 4
+    if rows:
+        # the block's rows are no longer read when every wave is here
+        L += ["v_lshlrev_b32_e32 v%d, 2, %s" % (row_address(V0), vl4),
+              "s_cmp_eq_u32 s98, -1", "s_cbranch_scc1 .Lgpx_alone_%s" % tag, "s_barrier", ".Lgpx_alone_%s:" % tag]
     if mode in (0, 4):
         L += ["s_load_dwordx16 s[24:39], s[100:101], 0x0", "s_load_dwordx16 s[40:55], s[100:101], 0x40"]
     L += prefetch_start(tag, "0", "s96") + ["s_mov_b32 s99, 0"]
@@ -1042,16 +1081,16 @@ def unit_start(T, D, NF, V0, FO, tag, mode, ring):
     L += [".Lgpx_tile_%s:" % tag, "s_mov_b64 exec, -1", "s_waitcnt vmcnt(0) lgkmcnt(0)"]
     for k in range(T // 4):
         L += ["ds_write_b128 %s, %s offset:%d" % (vy, quad(V0 + 4 * k), 1024 * k)]
-    if mode in (0, 4) and work_regs(V0, mode) > 14 * transc_slots(V0) + 2:
+    if mode in (0, 4) and V0 >= 64:
         for i, (hi, lo) in enumerate(VCONST.values()):
             r = vconst_reg(V0, mode, i)
             L += ["v_mov_b32_e32 v%d, 0x%x" % (r, lo), "v_mov_b32_e32 v%d, 0x%x" % (r + 1, hi)]
-    L += ["s_waitcnt lgkmcnt(0)", "s_branch .Lgpx_rest_%s" % tag]
+    L += ["s_waitcnt lgkmcnt(0)", "s_branch .Lgpx_%s_%s" % ("next" if rows else "rest", tag)]
     return L
 
 
 def vconst_reg(V0, mode, i):
-    return V0 - work_regs(V0, mode) + 2 * i
+    return V0 - 14 * transc_slots(V0) - 2 - 2 * len(VCONST) + 2 * i
 
 
 def prefetch_start(tag, n, limit):
@@ -1098,6 +1137,9 @@ def program_end(T, D, NF, V0, FO, tag, mode, ring):
     L += ["s_waitcnt lgkmcnt(0)", first_records(ring, mode)[0],
           "s_lshl_b32 s81, s81, 4", "s_add_u32 s81, s81, s62"]
     L += prefetch_start(tag, "1", "s81")
+    rows = ring and mode == 4
+    if rows:
+        L += ["s_cmp_eq_u32 s93, %d" % TO_ROW, "s_cbranch_scc1 .Lgpx_row_%s" % tag]
     kinds = [FIT_HITS, OUT_CASES] if mode == 2 else [FIT_MSE, FIT_SUM_ABS, FIT_HITS, FIT_CLASS, OUT_CASES]
     lab = {FIT_MSE: "mse", FIT_SUM_ABS: "abs", FIT_HITS: "hits", FIT_CLASS: "cls", OUT_CASES: "cases"}
     for k in kinds[1:]:
@@ -1223,8 +1265,18 @@ def program_end(T, D, NF, V0, FO, tag, mode, ring):
             L += hit_terms(k, T, o, y, True)
             L += ["s_mov_b64 exec, -1"]
         L += ["s_branch .Lgpx_w%s_%s" % (name, tag)]
-    L += [".Lgpx_next_%s:" % tag, "s_cmp_ge_u32 s62, s96", "s_cbranch_scc0 .Lgpx_rest_%s" % tag,
-          ".Lgpx_probe_%s:" % tag, "s_branch .Lgpx_leave_%s" % tag]
+    if rows:
+        L += [".Lgpx_row_%s:" % tag, "s_lshl_b32 s72, s80, %d" % (8 + T.bit_length() - 1),
+              "v_lshl_add_u32 v%d, v%d, 4, s72" % (vy, vl),
+              "ds_write_b128 v%d, %s offset:%d" % (vy, quad(V0), rows_base(T, D, NF, V0, mode))]
+        assert T == 4
+    L += [".Lgpx_next_%s:" % tag, "s_cmp_ge_u32 s62, s96", "s_cbranch_scc0 .Lgpx_rest_%s" % tag]
+    if rows:
+        L += ["s_cmp_eq_u32 s98, -1", "s_cbranch_scc1 .Lgpx_probe_%s" % tag, "s_waitcnt lgkmcnt(0)", "s_barrier",
+              "s_mov_b32 s62, s56", "s_mov_b32 s96, s57", "s_mov_b32 s93, s98", "s_mov_b32 s98, -1",
+              "s_cmp_ge_u32 s62, s96", "s_cbranch_scc1 .Lgpx_probe_%s" % tag, first_records(ring, mode)[0]]
+        L += prefetch_start(tag, "3", "s96") + ["s_mov_b32 s99, 0", "s_branch .Lgpx_rest_%s" % tag]
+    L += [".Lgpx_probe_%s:" % tag, "s_branch .Lgpx_leave_%s" % tag]
     L += [".Lgpx_rest_%s:" % tag, "s_waitcnt lgkmcnt(0)", "s_cmp_eq_u32 s99, 0", "s_cbranch_scc1 .Lgpx_go_%s" % tag,
           "s_lshl_b32 s72, s78, 6", "s_add_u32 s58, s58, s72", "s_addc_u32 s59, s59, 0"]
     L += prefetch_lines(tag, "2")
@@ -1581,6 +1633,7 @@ def main(out_dir):
     lines.append("struct CoreUnit {")
     lines.append("    uint64_t code, X, stride, y, partials, cases, coef;")
     lines.append("    uint32_t off, end, n_load, left, part_stride, kind, lds_y, bits, burst;")
+    lines.append("    uint32_t own_off, own_end, own_kind;   // after the rows (ring cores with sin/cos/exp/log)")
     lines.append("};")
     host = []
     seen = {}
@@ -1594,7 +1647,8 @@ def main(out_dir):
         hs_tag, hs, nslots = seen.setdefault(key, (tag, hs, nslots))
         text = asm_text(T, D, NF, V0, FO, tag, relabelled(hs, tag), AR, ring)
         assert NCV + FO + NF * T <= 256
-        work = work_regs(NCV, AR)
+        work = work_regs(NCV, AR, ring)
+        rows = ring and AR == 4
         assert NCV - work >= 14, (T, D, NF, NCV, AR)
         clob = ["v%d" % n for n in range(NCV - work, NCV + FO + NF * T)] + ["vcc", "scc", "m0", "memory"]
         clob += ["s%d" % n for n in [58, 59] + list(range(64, 76)) + [79, 80, 81, 99]]
@@ -1608,12 +1662,17 @@ def main(out_dir):
         core_lines.append("    // with `probe` only the address of the handler table is returned")
         core_lines.append("    static __device__ __forceinline__ void run(const CoreUnit& u, uint32_t probe, uint64_t& table) {")
         core_lines.append("#ifdef __HIP_DEVICE_COMPILE__")
-        core_lines.append("        uint32_t off = u.off;")
+        core_lines.append("        uint32_t off = u.off, end = u.end, kind = u.kind;")
+        if rows:
+            core_lines.append("        uint32_t own_kind = u.own_kind;")
         core_lines.append('        asm volatile("%s"' % text)
-        core_lines.append('            : "+{s62}"(off), "={s[76:77]}"(table)')
+        core_lines.append('            : "+{s62}"(off), "+{s96}"(end), "+{s93}"(kind), "={s[76:77]}"(table)'
+                          + (', "+{s98}"(own_kind)' if rows else ''))
         ins = [("s[60:61]", "u.code"), ("s63", "probe"), ("s78", "u.burst"), ("s[82:83]", "u.X"), ("s[84:85]", "u.stride"),
                ("s86", "u.n_load"), ("s87", "u.left"), ("s[88:89]", "u.y"), ("s[90:91]", "u.partials"),
-               ("s92", "u.part_stride"), ("s93", "u.kind"), ("s[94:95]", "u.cases"), ("s96", "u.end"), ("s97", "u.lds_y")]
+               ("s92", "u.part_stride"), ("s[94:95]", "u.cases"), ("s97", "u.lds_y")]
+        if rows:
+            ins += [("s56", "u.own_off"), ("s57", "u.own_end")]
         if AR == 2:
             ins.append(("s98", "u.bits"))
         if AR in (0, 4):
@@ -1639,12 +1698,15 @@ def main(out_dir):
         lines.append("    " + ", ".join(str(h.slot) for h in hs))
         lines.append("};")
     lines.append("struct CoreVariantDesc { int t, d, nf, ncv, arith; const CoreHandlerKey* keys; const uint16_t* slots; "
-                 "int n; int slot_bytes; int xx; bool ring; };   // xx: levels with one-pass handlers of two variables")
+                 "int n; int slot_bytes; int xx; bool ring; "
+                 "int waves, rows_base; };")
+    lines.append("// xx: levels with one-pass handlers of two variables; waves: waves of a block; rows_base: LDS address of its rows, or 0")
     lines.append("static const CoreVariantDesc kCoreVariants[] = {")
     for (T, D, NF, NCV, AR, tag, hs, nslots, ring) in host:
-        lines.append("    {%d, %d, %d, %d, %d, kCoreKeys_%s, kCoreSlots_%s, %d, %d, %d, %s},"
+        lines.append("    {%d, %d, %d, %d, %d, kCoreKeys_%s, kCoreSlots_%s, %d, %d, %d, %s, %d, %d},"
                      % (T, D, NF, NCV, AR, tag, tag, len(hs), RING_SLOT if ring else SLOT, xx_levels(D, NF, AR, ring),
-                        "true" if ring else "false"))
+                        "true" if ring else "false", waves_per_block(T, D, NF, NCV, AR, ring),
+                        rows_base(T, D, NF, NCV, AR) if ring and AR == 4 else 0))
     lines.append("};")
     path = os.path.join(out_dir, "core_gen.inc")
     write_if_changed(path, "\n".join(lines) + "\n")
@@ -1654,17 +1716,18 @@ def main(out_dir):
             "typedef int (*CoreOccupancyFn)();"]
     for core_lines, (T, D, NF, NCV, AR, tag, hs, nslots, ring) in zip(cores, host):
         name = vname((T, D, NF, NCV, AR))
+        W = waves_per_block(T, D, NF, NCV, AR, ring)
         disp.append("hipError_t core_launch_%s(const CoreArgs& a, uint32_t blocks, hipStream_t s);" % name)
         disp.append("int core_occupancy_%s();" % name)
         tu = ["// Generated by gen_core.py -- do not edit.  Kernel variant %s." % tag,
               '#include "core_body.h"', "", "namespace gpx {"] + core_lines + ["",
-              "GPX_KERNEL(%d, %d, %d, %d, %d, %s)" % (T, D, NF, NCV, AR, name), "",
+              "GPX_KERNEL(%d, %d, %d, %d, %d, %d, %s, %s)" % (T, D, NF, NCV, AR, W, "true" if ring and AR == 4 else "false", name), "",
               "hipError_t core_launch_%s(const CoreArgs& a, uint32_t blocks, hipStream_t s) {" % name,
-              "    hipLaunchKernelGGL(k_core_%s, dim3(blocks), dim3(256), 0, s, a);" % name,
+              "    hipLaunchKernelGGL(k_core_%s, dim3(blocks), dim3(%d), (uint32_t)a.n_rows * %du, s, a);" % (name, 64 * W, 256 * T),
               "    return hipGetLastError();", "}", "",
               "int core_occupancy_%s() {" % name,
               "    int n = 0;",
-              "    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_core_%s, 256, 0) != hipSuccess) n = 1;" % name,
+              "    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_core_%s, %d, 0) != hipSuccess) n = 1;" % (name, 64 * W),
               "    return n;", "}", "}  // namespace gpx", ""]
         write_if_changed(os.path.join(out_dir, "core_v_%s.hip" % name), "\n".join(tu))
     names = [vname(h[:5]) for h in host]

@@ -404,28 +404,28 @@ gp_status build_linear(const uint32_t* code, const int64_t* off, const float* cs
 }
 
 // Programs by falling cost: the order their code lies in on the device.
-void cost_order(const ProgData& pd, std::vector<uint32_t>& order) {
-    order.resize(pd.n_prog);
+void cost_order(const std::vector<uint32_t>& cost, std::vector<uint32_t>& order) {
+    order.resize(cost.size());
     std::iota(order.begin(), order.end(), 0u);
-    std::stable_sort(order.begin(), order.end(), [&](uint32_t a, uint32_t b) { return pd.cost[a] > pd.cost[b]; });
+    std::stable_sort(order.begin(), order.end(), [&](uint32_t a, uint32_t b) { return cost[a] > cost[b]; });
 }
 
 // Cut the programs, in that order, into G runs of about equal cost: a group
 // is a range of records, so a wave walks one stream of code.  Each group takes
 // programs up to the mean of what is left (at least one), so with as many
 // groups as programs each holds one.
-void cut_groups(const ProgData& pd, const std::vector<uint32_t>& order, const std::vector<int64_t>& rec, int32_t G,
-                std::vector<uint32_t>& goff) {
-    const int32_t P = pd.n_prog;
+void cut_groups(const std::vector<uint32_t>& cost, const std::vector<uint32_t>& order, const std::vector<int64_t>& rec,
+                int32_t G, std::vector<uint32_t>& goff) {
+    const int32_t P = (int32_t)cost.size();
     double left = 0.0;
-    for (int32_t i = 0; i < P; i++) left += pd.cost[order[i]];
+    for (int32_t i = 0; i < P; i++) left += cost[order[i]];
     goff.assign(1, (uint32_t)rec[0]);
     int32_t i = 0;
     for (int32_t g = 0; g < G; g++) {
         const double want = left / (G - g);
         const int32_t most = P - (G - g - 1);     // leave one program for each later group
         double got = 0.0;
-        while (i < most && (got == 0.0 || got + 0.5 * pd.cost[order[i]] <= want)) got += pd.cost[order[i++]];
+        while (i < most && (got == 0.0 || got + 0.5 * cost[order[i]] <= want)) got += cost[order[i++]];
         if (g == G - 1) i = P;
         left -= got;
         goff.push_back((uint32_t)rec[i]);
@@ -433,7 +433,7 @@ void cut_groups(const ProgData& pd, const std::vector<uint32_t>& order, const st
 }
 
 // Translate and upload the programs for variant vi (when `fresh` or not yet
-// uploaded) and the group layout for G groups (when not cached), all in one
+// uploaded; dp.rows is planned) and the group layout for G groups (when not cached), all in one
 // staging pass on stream s, then record dp.ready on s.  One-shot calls
 // (`fresh`) keep a single group layout, replaced on every call.  G <= 0:
 // programs only.
@@ -449,8 +449,8 @@ static gp_status prepare_programs(const ProgData& pd, int vi, DevProgs& dp, bool
     }
     if (upload) {
         std::vector<DevProg> progs;
-        cost_order(pd, dp.order);
-        if ((st = core_translate(pd, vi, dp.order.data(), code, progs)) != GP_OK) return st;
+        cost_order(dp.rows.cost, dp.order);
+        if ((st = core_translate(pd, vi, dp.order.data(), &dp.rows, code, progs)) != GP_OK) return st;
         dp.rec.resize((size_t)pd.n_prog + 1);
         for (int32_t i = 0; i < pd.n_prog; i++) dp.rec[i] = progs[dp.order[i]].code_off / 4;
         const DevProg& last = progs[dp.order[pd.n_prog - 1]];
@@ -465,7 +465,8 @@ static gp_status prepare_programs(const ProgData& pd, int vi, DevProgs& dp, bool
     }
     const bool new_groups = G > 0 && (fresh || gb == nullptr);
     if (new_groups) {
-        cut_groups(pd, dp.order, dp.rec, G, g);
+        cut_groups(dp.rows.cost, dp.order, dp.rec, G, g);
+        g.insert(g.end(), dp.rows.rec.begin(), dp.rows.rec.end());   // where each wave's share of the rows lies
         if (!fresh) gb = &dp.groups_by_G[G];
         if ((st = gb->reserve(g.size() * 4)) != GP_OK) return st;
     }
@@ -515,7 +516,8 @@ int32_t code_prefetch() {
     return n <= 0 ? 0 : (n > 14 ? 14 : (int32_t)n);
 }
 
-static LaunchShape launch_shape(const ProgData& pd, int32_t tiles, const EvalOptions* opt, int32_t force_G = 0) {
+static LaunchShape launch_shape(const ProgData& pd, int vi, int32_t tiles, const EvalOptions* opt, const RowPlan* rows,
+                                int32_t force_G = 0) {
     // Program groups of about 1024 core instructions when the programs read at most 12 features, else
     // 4096: every wave loads the features of its tile before it runs its group, and a longer group
     // spreads those loads over more instructions.  Measured on the 4096-program workloads (kernel
@@ -525,12 +527,22 @@ static LaunchShape launch_shape(const ProgData& pd, int32_t tiles, const EvalOpt
     const bool few_feat = pd.n_load <= 12;
     const int32_t group_instr =
         opt && opt->group_instr > 0 ? opt->group_instr : env_int("GP2D_GROUP_INSTR", few_feat ? 1024 : 4096);
-    const int32_t target_blocks = opt && opt->target_blocks > 0 ? opt->target_blocks : env_int("GP2D_TARGET_BLOCKS", 4096);
+    // (a block counts as four waves)
+    const int64_t W = core_variant_waves(vi);
+    const int32_t target_blocks =
+        (int32_t)((4 * (int64_t)(opt && opt->target_blocks > 0 ? opt->target_blocks : env_int("GP2D_TARGET_BLOCKS", 4096)) +
+                   W - 1) / W);
     int64_t G = (pd.n_instr + group_instr - 1) / group_instr;
-    if (((G + 3) / 4) * tiles < target_blocks) G = 4 * ((target_blocks + tiles - 1) / tiles);
+    if (((G + W - 1) / W) * tiles < target_blocks) G = W * ((target_blocks + tiles - 1) / tiles);
+    if (rows && rows->n() > 0) {
+        // every block computes the rows of its tile: at least four times their cost for its programs
+        double cost = 0.0;
+        for (uint32_t c : rows->cost) cost += c;
+        G = std::min<int64_t>(G, W * std::max<int64_t>(1, (int64_t)(cost / (4.0 * 35.0 * rows->n()))));
+    }
     G = std::max<int64_t>(1, std::min<int64_t>(G, pd.n_prog));
     if (force_G > 0) G = force_G;
-    const int64_t quads = (G + 3) / 4;
+    const int64_t quads = (G + W - 1) / W;
     int32_t tpw = opt && opt->tiles_per_wave > 0 ? opt->tiles_per_wave : env_int("GP2D_TILES_PER_WAVE", 0);
     if (tpw <= 0) {
         tpw = 1;
@@ -578,7 +590,12 @@ hipError_t timed_launch_end(hipStream_t s, int slot) {
     return hipEventRecord(g_tm_events[slot].second, s);
 }
 
-int32_t base_groups(const ProgData& pd) { return launch_shape(pd, 1 << 30, nullptr).G; }
+int32_t base_groups(const ProgData& pd, int vi) { return launch_shape(pd, vi, 1 << 30, nullptr, nullptr).G; }
+
+static void plan_rows_for(const ProgData& pd, int vi, RowPlan& rows) {
+    const int32_t W = core_variant_waves(vi);
+    plan_rows(pd, vi, (base_groups(pd, vi) + W - 1) / W, rows);
+}
 
 int default_variant(const ProgData& pd) {
     return pick_core_variant(pd.n_load, pd.max_depth, pd.n_instr ? (double)pd.n_transc / pd.n_instr : 0.0,
@@ -636,10 +653,13 @@ gp_status eval_core(const ProgData& pd, std::map<int, DevProgs>& dps, bool fresh
     const int64_t tiles64 = (N + 64LL * T - 1) / (64LL * T);
     if (tiles64 > (1LL << 30)) return fail(GP_E_INVAL, "n_cases too large");
     const int32_t tiles = (int32_t)tiles64;
-    const LaunchShape L = launch_shape(pd, tiles, opt, no_alloc ? opt->groups : 0);
+    if (fresh || !dp.uploaded) plan_rows_for(pd, vi, dp.rows);
+    const LaunchShape L = launch_shape(pd, vi, tiles, opt, &dp.rows, no_alloc ? opt->groups : 0);
     const int32_t G = L.G;
-    const int32_t same_group = env_int("GP2D_SAME_GROUP", 0) > 0 ? 1 : 0;
-    const int64_t units = same_group ? (int64_t)G * ((L.chunks + 3) / 4) : (int64_t)L.chunks * ((G + 3) / 4);
+    // (rows are those of the one tile that a block's waves share)
+    const int32_t same_group = dp.rows.n() == 0 && env_int("GP2D_SAME_GROUP", 0) > 0 ? 1 : 0;
+    const int32_t W = core_variant_waves(vi);
+    const int64_t units = same_group ? (int64_t)G * ((L.chunks + W - 1) / W) : (int64_t)L.chunks * ((G + W - 1) / W);
     if (units > (1LL << 31) - 64) return fail(GP_E_INVAL, "too many work units");
     const int64_t n_blocks = (N + 255) / 256;
     const size_t part_bytes = kind == GP_OUT_CASES ? 0 : (size_t)n_blocks * pd.n_prog * sizeof(double);
@@ -679,6 +699,8 @@ gp_status eval_core(const ProgData& pd, std::map<int, DevProgs>& dps, bool fresh
     a.prefetch = code_prefetch();
     a.n_groups = G;
     a.same_group = same_group;
+    a.n_rows = dp.rows.n();
+    a.row_off = goff + G + 1;
     a.n_bits = n_bits;
     a.partials = partials;
     a.cases_out = kind == GP_OUT_CASES ? (float*)out : nullptr;
@@ -802,7 +824,8 @@ static gp_status progset_finish(ProgData&& pd, void* stream, gp_progset** ps) {
         if ((st = core_ready(vi, s)) != GP_OK) return st;
         Workspace& w = workspace(s);
         std::lock_guard<std::mutex> g(w.mu);
-        p->groups = base_groups(p->pd);
+        p->groups = base_groups(p->pd, vi);
+        plan_rows_for(p->pd, vi, p->dps[vi].rows);
         if ((st = prepare_programs(p->pd, vi, p->dps[vi], false, p->groups, s, w, nullptr)) != GP_OK)
             return st;
     }

@@ -82,6 +82,17 @@ struct ProgData {
     std::vector<uint32_t> cost;
 };
 
+// Rows: sin, cos, exp or log of a feature, computed once a tile by a block for
+// all its programs (ring cores with those functions).
+struct RowPlan {
+    std::vector<int32_t> row;      // by function and feature: the row, or -1
+    std::vector<uint32_t> op;      // of each row
+    std::vector<int32_t> feat;
+    std::vector<uint32_t> rec;     // first record of each wave's share of the rows' programs, and the end
+    std::vector<uint32_t> cost;    // of each program, its rows read instead of computed
+    int32_t n() const { return (int32_t)op.size(); }
+};
+
 // Device copies of programs translated for one core variant, plus their
 // group layouts (the first record of each group) by group count.  `ready`
 // is recorded on the stream of the last upload into these buffers; a launch
@@ -91,6 +102,7 @@ struct DevProgs {
     DevBuf code;
     std::vector<uint32_t> order;   // programs in the order of the code (host)
     std::vector<int64_t> rec;      // first record of each, in that order, and the end (host)
+    RowPlan rows;
     std::map<int32_t, DevBuf> groups_by_G;
     DevBuf groups_once;        // one-shot calls: the group layout of the current programs
     hipEvent_t ready = nullptr;
@@ -139,9 +151,9 @@ int32_t code_prefetch();
 // Programs by falling cost, and such a sequence cut into G groups of about
 // equal cost (goff: G + 1 record offsets, from rec, each program's first
 // record in that order and the end).
-void cost_order(const ProgData& pd, std::vector<uint32_t>& order);
-void cut_groups(const ProgData& pd, const std::vector<uint32_t>& order, const std::vector<int64_t>& rec, int32_t G,
-                std::vector<uint32_t>& goff);
+void cost_order(const std::vector<uint32_t>& cost, std::vector<uint32_t>& order);
+void cut_groups(const std::vector<uint32_t>& cost, const std::vector<uint32_t>& order, const std::vector<int64_t>& rec,
+                int32_t G, std::vector<uint32_t>& goff);
 
 // Kernel timing brackets (active only while gp_timing_enable(1)).
 hipError_t timed_launch_begin(hipStream_t s, int* slot);
@@ -171,8 +183,8 @@ namespace gpx {
 // it was created.
 gp_status progset_eval_no_alloc(gp_progset* ps, const float* X, int32_t n_feat, int64_t n_cases, const float* y,
                                 int32_t kind, void* out, hipStream_t s, double* partials, size_t partials_bytes);
-// Program groups of a launch over plentiful case tiles (the layout a program
-// set uploads when it is created).
-int32_t base_groups(const ProgData& pd);
+// Program groups of a launch of variant vi over plentiful case tiles (the
+// layout a program set uploads when it is created).
+int32_t base_groups(const ProgData& pd, int vi);
 
 }  // namespace gpx

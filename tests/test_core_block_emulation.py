@@ -209,7 +209,7 @@ class BlockEmu:
     def step(self, addr, x):
         op, _, rest = x.partition(" ")
         a = [t.strip() for t in rest.split(",")]
-        if op in ("s_nop", "s_waitcnt"):
+        if op in ("s_nop", "s_waitcnt", "s_barrier"):
             return None
         if op.startswith("s_"):
             return self.salu(addr, op, a, rest)
@@ -499,7 +499,7 @@ def emulate(vi, pop, X, y, kind, n_bits=0):
     for tile in range((N + W - 1) // W):
         left = min(W, N - tile * W)
         s = {63: 0, 62: 0, 78: 14, 86: F, 87: left, 92: blocks * 8, 93: KIND[kind], 96: ends[-1] * 16, 97: lds_y,
-             98: min(32 * W, max(0, n_bits - 32 * tile * W))}
+             98: min(32 * W, max(0, n_bits - 32 * tile * W)) if emu.mode == 2 else M32}
         for r, val in ((60, CODE), (82, XBASE + 4 * tile * W), (84, 4 * N), (88, YBASE + 4 * tile * W),
                        (90, PART + 8 * tile * (emu.T // 4)), (94, CASES + 4 * tile * W), (100, COEF)):
             s[r], s[r + 1] = val & M32, val >> 32
@@ -637,3 +637,56 @@ def test_ring_core_operand_forms(vi):
     got = emulate(vi, pop, X, np.zeros(N, np.float32), "cases")
     bad = np.argwhere(~((got.view(np.int32) == o.view(np.int32)) | (np.isnan(got) & np.isnan(o))))
     assert not len(bad), (exprs[bad[0][0]], got[tuple(bad[0])], o[tuple(bad[0])])
+
+
+@pytest.mark.parametrize("vi", [i for i in REAL if ALL[i][4] == 4 and i >= len(gen_core.VARIANTS)])
+def test_rows_are_computed_and_pushed(vi):
+    """A unit with rows: the programs that compute them (sin, exp and cos of features, to LDS) run first, then the
+    wave's own, which push them at two levels in every phase and go on; a wave without programs ends after its rows.
+    LDS beyond the rows stays as it was."""
+    T, D, NF, NCV, mode = ALL[vi]
+    emu = BlockEmu(vi)
+    tag, V0, FO, hs, _ = gen_core.gen_variant(T, D, NF, NCV, mode, True)
+    K, ph = gen_core.K, gen_core.RING_PHASE
+    slot = {(h.kind, h.op, h.p1, h.p2): emu.table + h.slot * gen_core.RING_SLOT for h in hs}
+    base = gen_core.rows_base(T, D, NF, NCV, mode)
+
+    def records(*items):
+        """(kind, op, p1, payload, constant), phases in turn from 0, again from 0 after a function's exit"""
+        out, k = [], 0
+        for kind, op, p1, pay, cst in items:
+            a = slot[(K[kind] | (k << ph), op, p1, 0)]
+            out.append((a & M32, a >> 32, pay, cst))
+            k = 0 if kind == "EXIT" else (k + 1) & 3
+        return out
+    F, N = 3, 64 * T - 5
+    fx = lambda f: FO + f * T   # noqa: E731
+    rows = [(4, 0), (6, 2), (5, 1)]
+    own = [records(("PUSHR", 0, 0, 256 * T * 1, 0), ("PUSHR", 0, 1, 256 * T * 2, 0), ("SS", 0, 0, 0, 0), ("PUSHR", 0, 1, 0, 0),
+                   ("SS", 2, 0, 0, 0), ("PUSHR", 0, 1, 256 * T * 1, 0), ("SS", 1, 0, 0, 0), ("EXIT", 0, 0, 15 << 24 | 2, 0)),
+           records(("PUSHR", 0, 0, 0, 0), ("EXIT", 0, 0, 15 << 24, 1))]
+    derived = [records(("EXIT", 0, 0, fx(f) | op << 24, 0), ("EXIT", 0, 0, 15 << 24 | 2, r)) for r, (op, f) in enumerate(rows)]
+    code = sum(own, []) + sum(derived, [])
+    words = np.array(code + [(0, 0, 0, 0)] * 8, np.uint64).astype(np.uint32).reshape(-1)
+    n_own = sum(len(p) for p in own)
+    X = synth.uniform_cases(synth.rng_for(40 + vi), F, N, -2, 2)
+    y = np.zeros(N, np.float32)
+    out = np.full((2, N), np.nan, np.float32)
+    tab, coef = tables()
+    emu.lds[:] = 0xA5
+    emu.lds[:8 * len(tab)] = tab.view(np.uint8)
+    emu.lds_used = base + 256 * T * len(rows)
+    for b, arr in ((CODE, words), (XBASE, X), (YBASE, y), (CASES, out), (COEF, coef), (PART, np.zeros((2, 1)))):
+        emu.region(b, arr)
+    s = {63: 0, 62: 16 * n_own, 78: 14, 86: F, 87: N, 92: 8, 93: gen_core.TO_ROW, 96: 16 * len(code), 97: 8 * len(tab),
+         56: 0, 57: 16 * n_own, 98: KIND["cases"]}
+    for r, val in ((60, CODE), (82, XBASE), (84, 4 * N), (88, YBASE), (90, PART), (94, CASES), (100, COEF)):
+        s[r], s[r + 1] = val & M32, val >> 32
+    emu.run(dict(s))
+    f = [np.array([oracle.apply(op, v) for v in X[k]], np.float32) for op, k in rows]
+    want = np.stack([(f[1] + f[2]) * f[0] - f[1], f[0]]).astype(np.float32)
+    assert np.abs(out.view(np.int32).astype(np.int64) - want.view(np.int32)).max() <= 1
+    assert (emu.lds[emu.lds_used:] == 0xA5).all()
+    out[:] = np.nan
+    emu.run(dict(s, **{}) | {56: 16 * n_own, 57: 16 * n_own})     # no programs of its own
+    assert np.isnan(out).all()
