@@ -98,7 +98,11 @@ __device__ __forceinline__ void k_core_body(const CoreArgs& a) {
         u = (b & 7u) * (nb >> 3) + (b >> 3);
         if (!a.probe) {
             if (u >= (uint32_t)a.n_units) return;
-            if (a.same_group) {
+            if (a.direct) {
+                // the block's waves run one group on all the tiles there are, and finish its fitness values
+                grp = u;
+                chunk = wib;
+            } else if (a.same_group) {
                 // wave w of the block runs group u div q on chunk W (u mod q) + w, q = chunks / W rounded up
                 const uint32_t q = ((uint32_t)a.chunks + (uint32_t)W - 1u) / (uint32_t)W;
                 grp = u / q;
@@ -126,9 +130,9 @@ __device__ __forceinline__ void k_core_body(const CoreArgs& a) {
         if (a.probe) {
             if (u != 0 || wib != 0) return;
         } else if (!table) {
-            if (it >= (uint32_t)a.tiles_per_wave) return;
+            if (it >= (uint32_t)a.tiles_per_wave) break;
             tile = chunk * (uint32_t)a.tiles_per_wave + it;
-            if (tile >= (uint32_t)a.tiles) return;
+            if (tile >= (uint32_t)a.tiles) break;
             if (grp < (uint32_t)a.n_groups) {
                 c0 = a.group_off[grp];
                 c1 = a.group_off[grp + 1];
@@ -203,6 +207,20 @@ __device__ __forceinline__ void k_core_body(const CoreArgs& a) {
                 a.probe_out[2] = ROWS ? lds_address(s_rows) : 0u;
             }
             return;
+        }
+    }
+    if (!table && a.direct) {
+        // The group's partial sums were written by this block (the stores have been waited for): a thread a program
+        // adds them up in block order.  Read past the vector cache, which may not hold another wave's stores.
+        __syncthreads();
+        const uint32_t q1 = a.group_prog[grp + 1];
+        const int32_t n_blocks = (int32_t)((a.N + 255) / 256);
+        for (uint32_t q = a.group_prog[grp] + threadIdx.x; q < q1; q += blockDim.x) {
+            const uint64_t p = a.order[q];
+            double sum = 0.0;
+            for (int32_t b = 0; b < n_blocks; b++)
+                sum += __hip_atomic_load(a.partials + p * (uint64_t)n_blocks + b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            finish_sum(a.kind, a.N, a.out, (int64_t)p, sum);
         }
     }
 }

@@ -630,6 +630,7 @@ void plan_rows(const ProgData& pd, int vi, int64_t blocks, RowPlan& plan) {
     }
     for (size_t i = 0; i < pd.progs.size(); i++)
         each(pd.progs[i], [&](int k) { if (plan.row[k] >= 0) plan.cost[i] -= std::min(plan.cost[i] - 1, kRowSaving); });
+    for (uint32_t c : plan.cost) plan.total += c;
 }
 
 gp_status core_translate(const ProgData& pd, int vi, const uint32_t* order, RowPlan* rows, std::vector<uint32_t>& code,

@@ -4,7 +4,11 @@
 #include <hip/hip_runtime_api.h>
 #include <stdint.h>
 
+#include "../../include/gp.h"
 #include "gp_internal.h"
+#ifdef __HIPCC__
+#include <hip/hip_runtime.h>
+#endif
 
 namespace gpx {
 
@@ -74,6 +78,11 @@ struct CoreArgs {
     int32_t n_rows;             // rows (sin, cos, exp or log of a feature) each block computes for its tile into LDS,
                                 // by the programs row_off[w] .. row_off[w + 1] of its wave w; 0: none
     const uint32_t* row_off;
+    int32_t direct;             // implicit units, at most as many tiles as a block has waves: a block runs one group on
+                                // every tile and writes its programs' fitness to `out` itself (no reduction launch):
+    const uint32_t* group_prog; // group g holds the programs order[group_prog[g] .. group_prog[g + 1])
+    const uint32_t* order;
+    void* out;
     int32_t same_group;         // implicit units: the waves of a block run one group on as many chunks
     int64_t n_bits;             // Boolean kernels: cases (bits) in the N words of each row
     uint32_t probe;             // nonzero: write the handler table address and return
@@ -81,6 +90,15 @@ struct CoreArgs {
     float* cases_out;
     uint64_t* probe_out;
 };
+
+// Program p's fitness from the sum of its partials.
+#ifdef __HIPCC__
+__device__ __forceinline__ void finish_sum(int32_t kind, int64_t N, void* out, int64_t p, double s) {
+    if (kind == GP_FIT_HITS || kind == GP_FIT_CLASS_ERR) ((int32_t*)out)[p] = (int32_t)s;
+    else if (kind == GP_FIT_MSE) ((float*)out)[p] = (float)(s / (double)N);
+    else ((float*)out)[p] = (float)s;
+}
+#endif
 
 hipError_t core_launch(int variant, const CoreArgs& a, uint32_t blocks, hipStream_t s);
 int core_blocks_per_cu(int variant);

@@ -25,18 +25,13 @@ __global__ void k_zero_u32(uint32_t* p) { *p = 0u; }
 // need no order: a wave a program, lanes side by side.
 constexpr int kProgs = 16, kChunk = 128, kPer = kProgs * kChunk / 256;
 
-__device__ __forceinline__ void finish_sum(const ReduceArgs& r, int64_t p, double s) {
-    if (r.kind == GP_FIT_HITS || r.kind == GP_FIT_CLASS_ERR) ((int32_t*)r.out)[p] = (int32_t)s;
-    else if (r.kind == GP_FIT_MSE) ((float*)r.out)[p] = (float)(s / (double)r.N);
-    else ((float*)r.out)[p] = (float)s;
-}
-
 __device__ __forceinline__ void reduce_block(const ReduceArgs& r) {
     const int64_t p0 = (int64_t)blockIdx.x * kProgs;
     if (p0 >= r.n_prog) return;
     const double* part = r.partials + r.part_base;
     const int t = (int)threadIdx.x, B = r.blocks;
-    if (r.kind == GP_FIT_HITS || r.kind == GP_FIT_CLASS_ERR) {
+    // (short rows go the other way: four programs a wave, one after another, wait for memory four times)
+    if ((r.kind == GP_FIT_HITS || r.kind == GP_FIT_CLASS_ERR) && B > 4 * kChunk) {
         for (int k = t >> 6; k < kProgs; k += 4) {
             const int64_t p = p0 + k;
             if (p >= r.n_prog) break;
@@ -44,7 +39,7 @@ __device__ __forceinline__ void reduce_block(const ReduceArgs& r) {
             for (int b = t & 63; b < B; b += 64) s += part[p * B + b];
 #pragma unroll
             for (int d = 32; d >= 1; d >>= 1) s += __shfl_xor(s, d, 64);
-            if ((t & 63) == 0) finish_sum(r, p, s);
+            if ((t & 63) == 0) finish_sum(r.kind, r.N, r.out, p, s);
         }
         return;
     }
@@ -82,7 +77,7 @@ __device__ __forceinline__ void reduce_block(const ReduceArgs& r) {
             for (; k < n; k++) s += x[k];
         }
     }
-    if (t < kProgs && p0 + t < r.n_prog) finish_sum(r, p0 + t, s);
+    if (t < kProgs && p0 + t < r.n_prog) finish_sum(r.kind, r.N, r.out, p0 + t, s);
 }
 
 // Program block blockIdx.x of job blockIdx.y

@@ -80,6 +80,7 @@ struct ProgData {
     std::vector<uint32_t> code;
     std::vector<DevProg> progs;
     std::vector<uint32_t> cost;
+    int variant = -1;       // default_variant of the programs, once asked for
 };
 
 // Rows: sin, cos, exp or log of a feature, computed once a tile by a block for
@@ -90,6 +91,7 @@ struct RowPlan {
     std::vector<int32_t> feat;
     std::vector<uint32_t> rec;     // first record of each wave's share of the rows' programs, and the end
     std::vector<uint32_t> cost;    // of each program, its rows read instead of computed
+    double total = 0.0;            // of all of them
     int32_t n() const { return (int32_t)op.size(); }
 };
 
@@ -106,6 +108,7 @@ struct DevProgs {
     std::map<int32_t, DevBuf> groups_by_G;
     DevBuf groups_once;        // one-shot calls: the group layout of the current programs
     hipEvent_t ready = nullptr;
+    bool settled = false;          // `ready` has been seen to have passed: no launch waits for it any more
     DevProgs() = default;
     DevProgs(const DevProgs&) = delete;
     DevProgs& operator=(const DevProgs&) = delete;
@@ -150,10 +153,10 @@ void parallel_for(int64_t n, const std::function<void(int64_t, int64_t)>& fn);
 int32_t code_prefetch();
 // Programs by falling cost, and such a sequence cut into G groups of about
 // equal cost (goff: G + 1 record offsets, from rec, each program's first
-// record in that order and the end).
+// record in that order and the end; gprog: the same as places in the order).
 void cost_order(const std::vector<uint32_t>& cost, std::vector<uint32_t>& order);
 void cut_groups(const std::vector<uint32_t>& cost, const std::vector<uint32_t>& order, const std::vector<int64_t>& rec,
-                int32_t G, std::vector<uint32_t>& goff);
+                int32_t G, std::vector<uint32_t>& goff, std::vector<uint32_t>* gprog = nullptr);
 
 // Kernel timing brackets (active only while gp_timing_enable(1)).
 hipError_t timed_launch_begin(hipStream_t s, int* slot);
