@@ -337,12 +337,16 @@ typedef struct {
 } gp_batch_config;
 
 /* cfg NULL: the configuration the autotuner stored for this batch shape,
- * else a default.  Stream ordered and asynchronous like gp_eval_tree. */
+ * else a default: jobs that share form, dataset and fitness kind and are
+ * large together are evaluated as one population by the kernel that suits
+ * them, the others in one launch as above.  Stream ordered and asynchronous
+ * like gp_eval_tree. */
 gp_status gp_eval_batch(const gp_dataset* ds, int32_t n_ds, const gp_job* jobs, int32_t n_jobs,
                         const gp_batch_config* cfg, void* stream);
 /* Time every candidate configuration `reps` times on this batch (runs on
  * `stream` and synchronizes on it), store the fastest for the batch's shape
- * and return it with its median time.  The store is kept in memory and, when
+ * (unless the default of gp_eval_batch is faster still) and return it with
+ * its median time.  The store is kept in memory and, when
  * the environment names a file in GP2D_TUNE_CACHE, in that JSON file. */
 gp_status gp_tune_batch(const gp_dataset* ds, int32_t n_ds, const gp_job* jobs, int32_t n_jobs, int32_t reps,
                         gp_batch_config* best, double* best_ms, void* stream);

@@ -71,7 +71,7 @@ void DevBuf::release() {
 }
 
 gp_status Staging::begin(size_t n) {
-    cur ^= 1;
+    cur = (cur + 1) & 3;
     Half& h = half[cur];
     if (h.pending) {
         hipError_t e = hipEventSynchronize(h.ev);
@@ -675,7 +675,8 @@ gp_status eval_core(const ProgData& pd, std::map<int, DevProgs>& dps, bool fresh
     const int32_t W = core_variant_waves(vi);
     // Few tiles: a block takes a group on all of them and finishes its fitness values, without the reduction launch
     // (100 trees x 1024 cases: 10.6 -> 7.4 us of host time a call, and 1 us less from call to result).
-    const bool direct = kind != GP_OUT_CASES && dp.rows.n() == 0 && !same_group && tiles <= W && L.tiles_per_wave == 1;
+    const std::vector<EvalSegment>* seg = opt ? opt->segments : nullptr;
+    const bool direct = kind != GP_OUT_CASES && !seg && dp.rows.n() == 0 && !same_group && tiles <= W && L.tiles_per_wave == 1;
     const int64_t units = direct ? (int64_t)G : same_group ? (int64_t)G * ((L.chunks + W - 1) / W) : (int64_t)L.chunks * ((G + W - 1) / W);
     if (units > (1LL << 31) - 64) return fail(GP_E_INVAL, "too many work units");
     const int64_t n_blocks = (N + 255) / 256;
@@ -742,8 +743,15 @@ gp_status eval_core(const ProgData& pd, std::map<int, DevProgs>& dps, bool fresh
     r.out = out;
     r.blocks = (int32_t)n_blocks;
     r.kind = kind;
-    e = core_reduce_one(r, s);
-    if (e != hipSuccess) return fail(GP_E_DEVICE, "reduction launch: %s", hipGetErrorString(e));
+    const EvalSegment all{0, pd.n_prog, out};
+    for (size_t k = 0; k < (seg ? seg->size() : 1); k++) {
+        const EvalSegment& g = seg ? (*seg)[k] : all;
+        r.part_base = (uint64_t)g.first * (uint64_t)n_blocks;
+        r.n_prog = g.n_prog;
+        r.out = g.out;
+        e = core_reduce_one(r, s);
+        if (e != hipSuccess) return fail(GP_E_DEVICE, "reduction launch: %s", hipGetErrorString(e));
+    }
     return GP_OK;
 }
 

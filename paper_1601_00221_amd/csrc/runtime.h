@@ -45,9 +45,9 @@ struct DevBuf {
     void release();
 };
 
-// Pinned host staging for host-to-device copies, in two halves used in
-// turn: begin() takes the other half and waits only until the copies of
-// that half's previous use (two uses ago) have left it, so a call does not
+// Pinned host staging for host-to-device copies, in four parts used in
+// turn: begin() takes the next part and waits only until the copies of
+// its previous use (four uses ago) have left it, so a call does not
 // wait for its own copies or for the kernels queued before them.
 struct Staging {
     struct Half {
@@ -56,7 +56,7 @@ struct Staging {
         hipEvent_t ev = nullptr;
         bool pending = false;
     };
-    Half half[2];
+    Half half[4];
     int cur = 0;
     size_t used = 0;
     gp_status begin(size_t n);
@@ -132,6 +132,12 @@ struct Workspace {
     DevBuf bg_code, bg_meta;           // programs of the one-dimensional-stack comparator
 };
 
+// Consecutive programs of an evaluation whose results go to an array of their own.
+struct EvalSegment {
+    int32_t first, n_prog;
+    void* out;
+};
+
 struct EvalOptions {
     int variant = -1;            // core variant index, -1 = chosen from the programs
     int32_t group_instr = 0;     // core instructions per program group, 0 = automatic
@@ -144,6 +150,8 @@ struct EvalOptions {
     int32_t groups = 0;
     double* partials = nullptr;
     size_t partials_bytes = 0;
+    // Several populations evaluated as one (not for GP_OUT_CASES): their parts of the programs, in order.
+    const std::vector<EvalSegment>* segments = nullptr;
 };
 
 Workspace& workspace(hipStream_t s);
