@@ -39,7 +39,7 @@ static double transc_fraction(const std::vector<BatchJobRef>& jobs) {
     int64_t e = 0, n = 0;
     for (const BatchJobRef& j : jobs) {
         e += j.pd->n_transc;
-        n += j.pd->n_instr;
+        n += j.pd->n_named;
     }
     return n ? (double)e / (double)n : 0.0;
 }
@@ -80,7 +80,7 @@ gp_status plan_batch(const std::vector<BatchJobRef>& jobs, const std::vector<gp_
         const int64_t N = d.n_cases;
         const int64_t blocks = (N + 255) / 256;
         const int64_t tiles = (N + 64LL * vt - 1) / (64LL * vt);
-        std::vector<uint32_t> jcode;
+        RawWords jcode;
         std::vector<DevProg> jprogs;
         // programs of this job by falling cost, in G groups of about equal cost
         std::vector<uint32_t> order, goff;
@@ -262,7 +262,7 @@ static std::string batch_key(const std::vector<BatchJobRef>& jobs, const std::ve
     for (const BatchJobRef& j : jobs) {
         // program counts and mean lengths rounded to powers of two
         const int64_t P = j.pd->n_prog;
-        const int64_t mean = P ? j.pd->n_instr / P : 0;
+        const int64_t mean = P ? j.pd->n_named / P : 0;
         int lp = 0, lm = 0;
         while ((1LL << lp) < P) lp++;
         while ((1LL << lm) < mean) lm++;

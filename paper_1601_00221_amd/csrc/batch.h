@@ -25,7 +25,7 @@ struct BatchJobRef {
 struct BatchPlan {
     int vi = -1;
     bool persistent = true;
-    std::vector<uint32_t> code;
+    RawWords code;
     std::vector<UnitDesc> units;
     std::vector<JobDesc> jobs;
     std::vector<DatasetDesc> datasets;

@@ -102,7 +102,7 @@ extern "C" gp_status gp_eval_tree_1d(const int32_t* tok, const float* cst, const
     std::vector<uint32_t> code, meta(2 * (size_t)n_prog);
     uint32_t max_len = 0;
     if (form == GP_1D_LGP) {
-        code = pd.code;
+        code.assign(pd.code.begin(), pd.code.end());
         for (int32_t p = 0; p < n_prog; p++) {
             const DevProg& d = pd.progs[p];
             if (d.len > GP_1D_MAX_LEN)

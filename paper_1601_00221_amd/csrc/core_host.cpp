@@ -6,6 +6,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <memory>
 #include <mutex>
 #include <unordered_map>
 #include <vector>
@@ -62,7 +63,7 @@ struct VariantMap {
 };
 
 std::mutex g_mu;
-std::vector<VariantMap> g_maps;
+std::vector<std::shared_ptr<const VariantMap>> g_maps;   // by variant, once its table is found
 
 uint32_t key_of(int kind, int op, int p1, int p2) {
     return (uint32_t)kind | ((uint32_t)op << 8) | ((uint32_t)(uint8_t)(int8_t)p1 << 16) |
@@ -145,8 +146,7 @@ gp_status core_ready(int vi, hipStream_t s) {
     if (e != hipSuccess) return fail(GP_E_DEVICE, "hipGetDevice: %s", hipGetErrorString(e));
     std::lock_guard<std::mutex> g(g_mu);
     if ((int)g_maps.size() < core_variants()) g_maps.resize(core_variants());
-    VariantMap& m = g_maps[vi];
-    if (m.ready && m.device == dev) return GP_OK;
+    if (g_maps[vi] && g_maps[vi]->device == dev) return GP_OK;
     uint64_t* d = nullptr;
     e = hipMalloc(&d, 256);
     if (e != hipSuccess) return fail(GP_E_DEVICE, "hipMalloc: %s", hipGetErrorString(e));
@@ -166,10 +166,12 @@ gp_status core_ready(int vi, hipStream_t s) {
                     (unsigned long long)probed[2]);
     if (base == 0 || (base & (GPX_SLOT - 1)) != 0) return fail(GP_E_DEVICE, "handler table probe returned %llx",
                                                                (unsigned long long)base);
-    m.slot = variant_slots(vi);
-    m.base = base;
-    m.device = dev;
-    m.ready = true;
+    auto m = std::make_shared<VariantMap>();
+    m->slot = variant_slots(vi);
+    m->base = base;
+    m->device = dev;
+    m->ready = true;
+    g_maps[vi] = m;
     return GP_OK;
 }
 
@@ -177,7 +179,7 @@ bool core_is_ready(int vi) {
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) return false;
     std::lock_guard<std::mutex> g(g_mu);
-    return vi >= 0 && vi < (int)g_maps.size() && g_maps[vi].ready && g_maps[vi].device == dev;
+    return vi >= 0 && vi < (int)g_maps.size() && g_maps[vi] && g_maps[vi]->device == dev;
 }
 
 namespace {
@@ -445,10 +447,10 @@ static int translate_tree(const uint32_t* w, int64_t n_instr, int vi, const Vari
     return e.ok ? GP_OK : GP_E_INVAL;
 }
 
-// Core instructions of a register program: the register set-up, one or two
-// per instruction, and the end.
-static int64_t linear_records(const uint32_t* w, int64_t n, int32_t n_reg) {
-    int64_t k = n_reg + n + 1;
+// Core instructions of a register program: the set-up of the registers whose
+// starting value it reads, one or two per instruction, and the end.
+static int64_t linear_records(const uint32_t* w, int64_t n, uint32_t live) {
+    int64_t k = __builtin_popcount(live) + n + 1;
     for (int64_t i = 0; i < n; i++) {
         const uint32_t op = w[i] & 255u;
         const bool c1 = ((w[i] >> 16) & 255u) >= GP_SRC_CONST, c2 = (w[i] >> 24) >= GP_SRC_CONST;
@@ -457,7 +459,7 @@ static int64_t linear_records(const uint32_t* w, int64_t n, int32_t n_reg) {
     return k;
 }
 
-static int translate_linear(const uint32_t* w, int64_t n, const uint32_t* cst, int32_t n_reg, int32_t n_feat, int vi,
+static int translate_linear(const uint32_t* w, int64_t n, uint32_t live, const uint32_t* cst, int32_t n_reg, int32_t n_feat, int vi,
                             const VariantMap& m, uint32_t row, uint32_t next, uint32_t* out, int64_t cap,
                             int64_t* n_out, char* err) {
     const CoreVariantDesc& v = kCoreVariants[vi];
@@ -465,7 +467,8 @@ static int translate_linear(const uint32_t* w, int64_t n, const uint32_t* cst, i
     Emitter e{v, m, out, cap, err};
     auto off = [&](int id) { return id < n_reg ? id * T : FO + (id - n_reg) * T; };
     // registers start as r[k] = x[k mod n_feat]
-    for (int k = 0; k < n_reg && e.ok; k++) e.put(CK_MOVX, 0, k, 0, (uint32_t)(FO + (k % n_feat) * T), 0);
+    for (int k = 0; k < n_reg && e.ok; k++)
+        if ((live >> k) & 1u) e.put(CK_MOVX, 0, k, 0, (uint32_t)(FO + (k % n_feat) * T), 0);
     for (int64_t i = 0; i < n && e.ok; i++) {
         const uint32_t wd = w[i];
         const uint32_t op = wd & 255u;
@@ -528,7 +531,7 @@ constexpr int kCodePadding = 32;   // words
 // programs that compute the rows follow the others: two records each, a
 // share for every wave of a block.
 static gp_status translate_with(const ProgData& pd, int vi, const VariantMap& m, const uint32_t* order, RowPlan* rows,
-                                std::vector<uint32_t>& code, std::vector<DevProg>& progs) {
+                                RawWords& code, std::vector<DevProg>& progs) {
     const int32_t P = pd.n_prog;
     progs = pd.progs;
     std::vector<int64_t> start((size_t)P + 1, 0);
@@ -536,14 +539,15 @@ static gp_status translate_with(const ProgData& pd, int vi, const VariantMap& m,
     auto records = [&](int32_t p) {
         const DevProg& src = pd.progs[p];
         return (src.meta & 1u) == FORM_TREE ? (int64_t)src.len + 1
-                                            : linear_records(pd.code.data() + src.code_off, src.len, pd.n_reg);
+                                            : linear_records(pd.code.data() + src.code_off, src.len, src.live);
     };
     for (int32_t i = 0; i < P; i++) start[i + 1] = start[i] + records(at(i));
     if (start[P] * 16 > 0xFFFFFFF0ll) return fail(GP_E_INVAL, "programs exceed 4 GiB of core code");
     // the core reads records two or four at a time, ahead of the one it runs: up
     // to seven past a program's last one, so the code ends with padding
     const int32_t R = rows ? rows->n() : 0;
-    code.assign((size_t)(start[P] + 2 * R) * 4 + kCodePadding, 0u);
+    code.resize((size_t)(start[P] + 2 * R) * 4 + kCodePadding);
+    std::fill(code.end() - kCodePadding, code.end(), 0u);
     if (rows) {
         const CoreVariantDesc& v = kCoreVariants[vi];
         rows->rec.clear();
@@ -564,7 +568,7 @@ static gp_status translate_with(const ProgData& pd, int vi, const VariantMap& m,
         const uint32_t* w = pd.code.data() + src.code_off;
         if ((src.meta & 1u) == FORM_TREE)
             return translate_tree(w, src.len, vi, m, rows, (uint32_t)src.row, next, out, cap, n, err);
-        return translate_linear(w, src.len, w + src.len, pd.n_reg, pd.n_feat, vi, m, (uint32_t)src.row, next, out, cap,
+        return translate_linear(w, src.len, src.live, w + src.len, pd.n_reg, pd.n_feat, vi, m, (uint32_t)src.row, next, out, cap,
                                 n, err);
     };
     parallel_for(P, [&](int64_t i0, int64_t i1) {
@@ -633,18 +637,18 @@ void plan_rows(const ProgData& pd, int vi, int64_t blocks, RowPlan& plan) {
     for (uint32_t c : plan.cost) plan.total += c;
 }
 
-gp_status core_translate(const ProgData& pd, int vi, const uint32_t* order, RowPlan* rows, std::vector<uint32_t>& code,
+gp_status core_translate(const ProgData& pd, int vi, const uint32_t* order, RowPlan* rows, RawWords& code,
                          std::vector<DevProg>& progs) {
-    VariantMap m;
+    std::shared_ptr<const VariantMap> m;
     {
         std::lock_guard<std::mutex> g(g_mu);
-        if ((int)g_maps.size() <= vi || !g_maps[vi].ready) return fail(GP_E_DEVICE, "core variant %d not probed", vi);
-        m = g_maps[vi];
+        if ((int)g_maps.size() > vi) m = g_maps[vi];
     }
-    return translate_with(pd, vi, m, order, rows, code, progs);
+    if (!m) return fail(GP_E_DEVICE, "core variant %d not probed", vi);
+    return translate_with(pd, vi, *m, order, rows, code, progs);
 }
 
-gp_status core_translate_at(const ProgData& pd, int vi, uint64_t base, std::vector<uint32_t>& code,
+gp_status core_translate_at(const ProgData& pd, int vi, uint64_t base, RawWords& code,
                             std::vector<DevProg>& progs) {
     if (vi < 0 || vi >= core_variants()) return fail(GP_E_INVAL, "variant %d does not exist", vi);
     if (base & (GPX_SLOT - 1)) return fail(GP_E_INVAL, "table base must be %d-byte aligned", GPX_SLOT);

@@ -40,10 +40,10 @@ void plan_rows(const ProgData& pd, int vi, int64_t blocks, RowPlan& plan);
 // Core instructions of lowered programs, one program after another in the
 // given order (null: their own), and where each one lies.  rows (may be null)
 // is read, and told where the rows' programs lie.
-gp_status core_translate(const ProgData& pd, int vi, const uint32_t* order, RowPlan* rows, std::vector<uint32_t>& code,
+gp_status core_translate(const ProgData& pd, int vi, const uint32_t* order, RowPlan* rows, RawWords& code,
                          std::vector<DevProg>& progs);
 // The same with the handler table taken to start at `base` (no device needed).
-gp_status core_translate_at(const ProgData& pd, int vi, uint64_t base, std::vector<uint32_t>& code,
+gp_status core_translate_at(const ProgData& pd, int vi, uint64_t base, RawWords& code,
                             std::vector<DevProg>& progs);
 
 }  // namespace gpx

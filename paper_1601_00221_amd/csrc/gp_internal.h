@@ -55,7 +55,7 @@ struct DevProg {
     uint32_t len;          // instructions (trees: 2 words each; linear: 1 word each,
                            //   followed by the program's constants)
     uint32_t meta;         // bit 0 form; bits 8-15 stack depth (tree) or n_reg (linear)
-    uint32_t reserved0;
+    uint32_t live;         // linear: registers whose starting value the program reads (bit per register)
     uint64_t reserved1;
     uint64_t row;          // program index within its population (per-case output row)
 };
@@ -88,5 +88,11 @@ int lower_tree(const int32_t* tok, const float* cst, int64_t n, int32_t n_feat,
 // Validates one register linear program.
 int check_linear(const uint32_t* code, int64_t n, int64_t n_cst, int32_t n_reg, int32_t n_feat,
                  char* err);
+
+// Copies to `out` the instructions of a valid register program that its
+// result, register 0 at the end, depends on, in order, and returns their
+// number; *live gets the registers whose starting value they read (bit 0 as
+// well if none of them writes register 0).
+int64_t needed_linear(const uint32_t* code, int64_t n, int32_t n_reg, uint32_t* out, uint32_t* live);
 
 }  // namespace gpx

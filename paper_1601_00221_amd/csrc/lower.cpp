@@ -327,4 +327,25 @@ int check_linear(const uint32_t* code, int64_t n, int64_t n_cst, int32_t n_reg, 
     return GP_OK;
 }
 
+// Walked backwards with the set of registers whose value is still wanted: an
+// instruction that writes another register changes nothing that is returned
+// (the structural introns of linear GP).  No function has a side effect.
+int64_t needed_linear(const uint32_t* code, int64_t n, int32_t n_reg, uint32_t* out, uint32_t* live) {
+    uint32_t want = 1u;
+    int64_t k = n;
+    for (int64_t i = n - 1; i >= 0 && want; i--) {
+        const uint32_t wd = code[i], bit = 1u << ((wd >> 8) & 0xFF);
+        if (!(want & bit)) continue;
+        want &= ~bit;
+        const uint32_t s1 = (wd >> 16) & 0xFF, s2 = wd >> 24;
+        if ((int32_t)s1 < n_reg) want |= 1u << s1;
+        if (arity_of((int)(wd & 0xFF)) == 2 && (int32_t)s2 < n_reg) want |= 1u << s2;
+        out[--k] = wd;
+    }
+    *live = want;
+    const int64_t m = n - k;
+    memmove(out, out + k, sizeof(uint32_t) * (size_t)m);
+    return m;
+}
+
 }  // namespace gpx

@@ -10,6 +10,7 @@
 #include <algorithm>
 #include <atomic>
 #include <condition_variable>
+#include <exception>
 #include <functional>
 #include <map>
 #include <memory>
@@ -155,15 +156,42 @@ Workspace& workspace(hipStream_t s) {
 // Host threads: a fixed pool that splits a range of programs
 // ---------------------------------------------------------------------------
 namespace {
+// One range being worked on.  Threads hold it by shared pointer: one that
+// wakes up late finds nothing left to take and never touches `fn`, which is
+// the caller's and is used only while items are outstanding.
+struct Work {
+    const std::function<void(int64_t, int64_t)>* fn;
+    int64_t n, chunk;
+    std::atomic<int64_t> next{0}, done{0};
+    std::atomic<bool> failed{false};
+    std::exception_ptr error;   // the first one, thrown again by the caller when every item has ended
+    Work(const std::function<void(int64_t, int64_t)>* f, int64_t count, int64_t c) : fn(f), n(count), chunk(c) {}
+    void take() {
+        for (;;) {
+            const int64_t lo = next.fetch_add(chunk);
+            if (lo >= n) return;
+            const int64_t hi = std::min(n, lo + chunk);
+            try {
+                (*fn)(lo, hi);
+            } catch (...) {
+                if (!failed.exchange(true)) error = std::current_exception();
+            }
+            done.fetch_add(hi - lo, std::memory_order_acq_rel);
+        }
+    }
+};
+
+// The caller works from the start and returns when every item is done, however
+// many threads have woken up by then (waiting for all fifteen to report took
+// 100-200 us a range).  A thread that has run out of work looks for the next
+// range for some 50 us before it sleeps: lowering and translation follow each
+// other within one call.
 struct Pool {
     std::mutex mu;
-    std::condition_variable cv, done_cv;
+    std::condition_variable cv;
     std::vector<std::thread> th;
-    const std::function<void(int64_t, int64_t)>* fn = nullptr;
-    int64_t n = 0, chunk = 1;
-    std::atomic<int64_t> next{0};
-    int active = 0;
-    uint64_t gen = 0;
+    std::shared_ptr<Work> work;
+    std::atomic<uint64_t> gen{0};
     bool stop = false;
 
     explicit Pool(int k) {
@@ -173,44 +201,41 @@ struct Pool {
         {
             std::lock_guard<std::mutex> g(mu);
             stop = true;
+            gen++;
         }
         cv.notify_all();
         for (auto& t : th) t.join();
     }
-    void take() {
-        for (;;) {
-            const int64_t lo = next.fetch_add(chunk);
-            if (lo >= n) return;
-            (*fn)(lo, std::min(n, lo + chunk));
-        }
-    }
     void worker() {
         uint64_t seen = 0;
-        std::unique_lock<std::mutex> lk(mu);
         for (;;) {
-            cv.wait(lk, [&] { return stop || gen != seen; });
-            if (stop) return;
-            seen = gen;
-            lk.unlock();
-            take();
-            lk.lock();
-            if (--active == 0) done_cv.notify_all();
+            for (int spin = 0; spin < 2000 && gen.load(std::memory_order_acquire) == seen; spin++) __builtin_ia32_pause();
+            std::shared_ptr<Work> w;
+            {
+                std::unique_lock<std::mutex> lk(mu);
+                cv.wait(lk, [&] { return stop || gen.load() != seen; });
+                if (stop) return;
+                seen = gen.load();
+                w = work;
+            }
+            if (w) w->take();
         }
     }
     void run(int64_t count, const std::function<void(int64_t, int64_t)>& f) {
-        std::unique_lock<std::mutex> lk(mu);
-        fn = &f;
-        n = count;
-        chunk = std::max<int64_t>(1, count / (8 * (int64_t)(th.size() + 1)));
-        next = 0;
-        active = (int)th.size();
-        gen++;
+        auto w = std::make_shared<Work>(&f, count, std::max<int64_t>(1, count / (8 * (int64_t)(th.size() + 1))));
+        {
+            std::lock_guard<std::mutex> g(mu);
+            work = w;
+            gen++;
+        }
         cv.notify_all();
-        lk.unlock();
-        take();
-        lk.lock();
-        done_cv.wait(lk, [&] { return active == 0; });
-        fn = nullptr;
+        w->take();
+        while (w->done.load(std::memory_order_acquire) < count) __builtin_ia32_pause();   // the last chunks of others
+        {
+            std::lock_guard<std::mutex> g(mu);
+            if (work == w) work.reset();
+        }
+        if (w->failed) std::rethrow_exception(w->error);
     }
 };
 
@@ -321,7 +346,7 @@ gp_status build_tree(const int32_t* tok, const float* cst, const int64_t* off, i
         d.code_off = (uint32_t)(2 * off[p]);
         d.len = (uint32_t)st.n_instr;
         d.meta = FORM_TREE | ((uint32_t)st.max_depth << 8);
-        d.reserved0 = 0;
+        d.live = 0;
         d.reserved1 = 0;
         d.row = (uint64_t)p;
         max_feat = std::max(max_feat, pfeat[p]);
@@ -330,6 +355,7 @@ gp_status build_tree(const int32_t* tok, const float* cst, const int64_t* off, i
         pd.n_instr += st.n_instr;
         pd.n_gpop += st.n_nodes;
     }
+    pd.n_named = pd.n_instr;
     pd.n_load = max_feat + 1 > 0 ? max_feat + 1 : 1;
     return GP_OK;
 }
@@ -360,44 +386,55 @@ gp_status build_linear(const uint32_t* code, const int64_t* off, const float* cs
         total += n + nc;
     }
     if (total > 0xFFFFFFFFll) return fail(GP_E_INVAL, "programs exceed 2^32 device words");
+    // Program p lies at word off[p] plus the constants before it, so the programs are independent: they are checked,
+    // freed of the instructions that the result does not depend on, and copied in parallel.
     pd.code.resize((size_t)total);
     pd.progs.resize(P);
     pd.cost.resize(P);
-    int64_t w = 0;
+    std::vector<int32_t> prc(P, GP_OK), pfeat(P, -1), ptransc(P, 0);
+    parallel_for(P, [&](int64_t p0, int64_t p1) {
+        char err[256];
+        for (int64_t p = p0; p < p1; p++) {
+            const int64_t n = off[p + 1] - off[p];
+            const int64_t c0 = cst_off ? cst_off[p] : 0, nc = cst_off ? cst_off[p + 1] - c0 : 0;
+            const uint32_t* src = code + off[p];
+            if ((prc[p] = check_linear(src, n, nc, n_reg, n_feat, err)) != GP_OK) return;
+            for (int64_t i = 0; i < n; i++) {
+                const uint32_t wd = src[i];
+                const bool unary = (wd & 0xFF) >= GP_SIN && (wd & 0xFF) <= GP_PLOG;
+                ptransc[p] += unary;
+                for (int q = 0; q < (unary ? 1 : 2); q++) {
+                    const int32_t id = (int32_t)((wd >> (16 + 8 * q)) & 0xFF);
+                    if (id >= n_reg && id < GP_SRC_CONST) pfeat[p] = std::max(pfeat[p], id - n_reg);
+                }
+            }
+            uint32_t* dst = pd.code.data() + off[p] + c0;
+            DevProg& d = pd.progs[p];
+            d.code_off = (uint32_t)(off[p] + c0);
+            d.len = (uint32_t)needed_linear(src, n, n_reg, dst, &d.live);
+            if (nc) memcpy(dst + d.len, cst + c0, sizeof(float) * (size_t)nc);
+            d.meta = FORM_LINEAR | ((uint32_t)n_reg << 8);
+            d.reserved1 = 0;
+            d.row = (uint64_t)p;
+            uint32_t cost = 2u * (uint32_t)__builtin_popcount(d.live);
+            for (uint32_t i = 0; i < d.len; i++) cost += op_cost(dst[i] & 0xFF, OPSET_REAL);
+            pd.cost[p] = cost + 16;
+        }
+    });
     int32_t max_feat = std::min(n_feat, n_reg) - 1;  // registers start from these features
-    char err[256];
     for (int32_t p = 0; p < P; p++) {
         const int64_t n = off[p + 1] - off[p];
-        const int64_t nc = cst_off ? cst_off[p + 1] - cst_off[p] : 0;
-        const uint32_t* src = code + off[p];
-        int rc = check_linear(src, n, nc, n_reg, n_feat, err);
-        if (rc != GP_OK) return fail((gp_status)rc, "program %d: %s", p, err);
-        uint32_t cost = 0;
-        for (int64_t i = 0; i < n; i++) {
-            const uint32_t wd = src[i];
-            const int op = wd & 0xFF;
-            cost += op_cost(op, OPSET_REAL);
-            const bool unary = op >= GP_SIN && op <= GP_PLOG;
-            pd.n_transc += unary;
-            const int na = unary ? 1 : 2;
-            for (int q = 0; q < na; q++) {
-                const int id = (int)((wd >> (16 + 8 * q)) & 0xFF);
-                if (id >= n_reg && id < GP_SRC_CONST) max_feat = std::max(max_feat, id - n_reg);
-            }
+        if (prc[p] != GP_OK) {
+            // check the first failing program again on this thread for its message
+            char err[256];
+            check_linear(code + off[p], n, cst_off ? cst_off[p + 1] - cst_off[p] : 0, n_reg, n_feat, err);
+            return fail((gp_status)prc[p], "program %d: %s", p, err);
         }
-        memcpy(pd.code.data() + w, src, sizeof(uint32_t) * (size_t)n);
-        if (nc) memcpy(pd.code.data() + w + n, cst + cst_off[p], sizeof(float) * (size_t)nc);
-        DevProg& d = pd.progs[p];
-        d.code_off = (uint32_t)w;
-        d.len = (uint32_t)n;
-        d.meta = FORM_LINEAR | ((uint32_t)n_reg << 8);
-        d.reserved0 = 0;
-        d.reserved1 = 0;
-        d.row = (uint64_t)p;
-        pd.cost[p] = cost + 16;
-        pd.n_instr += n;
+        max_feat = std::max(max_feat, pfeat[p]);
+        pd.n_transc += ptransc[p];
+        pd.n_instr += pd.progs[p].len;
+        pd.n_named += n;
         pd.n_gpop += n;
-        w += n + nc;
     }
     pd.n_load = max_feat + 1;
     return GP_OK;
@@ -441,7 +478,8 @@ void cut_groups(const std::vector<uint32_t>& cost, const std::vector<uint32_t>& 
 // programs only.
 static gp_status prepare_programs(const ProgData& pd, int vi, DevProgs& dp, bool fresh, int32_t G, hipStream_t s,
                                   Workspace& w, const uint32_t** goff) {
-    std::vector<uint32_t> code, g, gprog;
+    RawWords code;
+    std::vector<uint32_t> g, gprog;
     gp_status st;
     const bool upload = fresh || !dp.uploaded;
     if (!upload && dp.ready && !dp.settled) {
@@ -547,7 +585,8 @@ static LaunchShape launch_shape(const ProgData& pd, int vi, int32_t tiles, const
     const int32_t target_blocks =
         (int32_t)((4 * (int64_t)(opt && opt->target_blocks > 0 ? opt->target_blocks : env_int("GP2D_TARGET_BLOCKS", 4096)) +
                    W - 1) / W);
-    int64_t G = (pd.n_instr + group_instr - 1) / group_instr;
+    // (the end of a program takes about as long as four instructions)
+    int64_t G = (pd.n_instr + 4 * (int64_t)pd.n_prog + group_instr - 1) / group_instr;
     if (((G + W - 1) / W) * tiles < target_blocks) G = W * ((target_blocks + tiles - 1) / tiles);
     if (rows && rows->n() > 0) {
         // every block computes the rows of its tile: at least four times their cost for its programs
@@ -612,7 +651,7 @@ static void plan_rows_for(const ProgData& pd, int vi, RowPlan& rows) {
 
 int default_variant(const ProgData& pd) {
     if (pd.variant >= 0) return pd.variant;
-    return pick_core_variant(pd.n_load, pd.max_depth, pd.n_instr ? (double)pd.n_transc / pd.n_instr : 0.0,
+    return pick_core_variant(pd.n_load, pd.max_depth, pd.n_named ? (double)pd.n_transc / pd.n_named : 0.0,
                              pd.n_transc > 0, pd.opset == OPSET_BOOL, pd.form == FORM_TREE);
 }
 
@@ -918,7 +957,7 @@ gp_status gp_progset_get_info(const gp_progset* ps, gp_progset_info* info) {
     info->form = ps->pd.form;
     info->n_feat = ps->pd.n_feat;
     info->max_depth = ps->pd.max_depth;
-    info->n_instr = ps->pd.n_instr;
+    info->n_instr = ps->pd.n_named;
     info->n_gpop = ps->pd.n_gpop;
     info->variant = tuned_variant(ps->pd);
     info->pad = 0;
@@ -935,7 +974,7 @@ gp_status gp_progset_destroy(gp_progset* ps) {
 
 static gp_status core_lower_common(ProgData& pd, int32_t variant, uint64_t table_base, uint32_t* words,
                                    int64_t max_words, int64_t* prog_off, int64_t* n_words) {
-    std::vector<uint32_t> code;
+    RawWords code;
     std::vector<DevProg> progs;
     gp_status st = core_translate_at(pd, variant, table_base, code, progs);
     if (st != GP_OK) return st;

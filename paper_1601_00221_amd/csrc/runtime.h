@@ -65,6 +65,25 @@ struct Staging {
     void release();
 };
 
+// Words that are all written before they are read: growing does not clear
+// them (a population's code is a megabyte or more, fresh on every call).
+template <typename T>
+struct RawAlloc : std::allocator<T> {
+    template <typename U>
+    struct rebind {
+        typedef RawAlloc<U> other;
+    };
+    template <typename U>
+    void construct(U* p) noexcept {
+        ::new ((void*)p) U;
+    }
+    template <typename U, typename... A>
+    void construct(U* p, A&&... a) {
+        ::new ((void*)p) U(std::forward<A>(a)...);
+    }
+};
+typedef std::vector<uint32_t, RawAlloc<uint32_t>> RawWords;
+
 // Lowered programs on the host.
 struct ProgData {
     int form = 0;
@@ -74,10 +93,11 @@ struct ProgData {
     int32_t n_reg = 0;
     int32_t n_load = 1;     // features the programs actually read (max index + 1)
     int32_t max_depth = 0;
-    int64_t n_instr = 0;
-    int64_t n_gpop = 0;     // GP operations per case: tree nodes or linear instructions
-    int64_t n_transc = 0;   // sin/cos/exp/log instructions (evaluated in binary64 by compiled code)
-    std::vector<uint32_t> code;
+    int64_t n_instr = 0;    // instructions that are run (register programs: those the result depends on)
+    int64_t n_named = 0;    // instructions as given
+    int64_t n_gpop = 0;     // GP operations per case: tree nodes or linear instructions, as given
+    int64_t n_transc = 0;   // sin/cos/exp/log instructions, as given (evaluated in binary64)
+    RawWords code;
     std::vector<DevProg> progs;
     std::vector<uint32_t> cost;
     int variant = -1;       // default_variant of the programs, once asked for
