@@ -6,6 +6,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <functional>
 #include <memory>
 #include <mutex>
 #include <unordered_map>
@@ -599,16 +600,23 @@ static gp_status translate_with(const ProgData& pd, int vi, const VariantMap& m,
 // The rows worth computing: those used by at least one and a half programs
 // for each block that computes them (over the fewest groups the programs are
 // cut into), the most used first, as many as the LDS beside the resident
-// blocks holds.  A row costs a block one evaluation a tile, by one of its
+// blocks holds.  Whether a launch then uses them is another question
+// (runtime.cpp, translation_for).  A row costs a block one evaluation a tile, by one of its
 // waves; a use then reads 16 bytes a lane instead of evaluating the function
 // again (about 90 vector instructions at T = 4).
 static constexpr uint32_t kRowSaving = 33;   // of the cost of one use (runtime.cpp, op_cost)
 
-void plan_rows(const ProgData& pd, int vi, int64_t blocks, RowPlan& plan) {
+void no_rows(const ProgData& pd, RowPlan& plan) {
     plan = RowPlan();
-    const CoreVariantDesc& v = kCoreVariants[vi];
     plan.cost = pd.cost;
+    plan.sum();
+}
+
+void plan_rows(const ProgData& pd, int vi, int64_t blocks, RowPlan& plan) {
+    no_rows(pd, plan);
+    const CoreVariantDesc& v = kCoreVariants[vi];
     if (v.rows_base == 0 || pd.form != FORM_TREE || pd.n_transc == 0 || pd.n_load > GP_MAX_FEAT) return;
+    if (2 * pd.n_transc < 3 * blocks) return;
     std::vector<int64_t> uses(4 * GP_MAX_FEAT, 0);
     auto each = [&](const DevProg& p, auto&& fn) {
         const uint32_t* w = pd.code.data() + p.code_off;
@@ -617,9 +625,22 @@ void plan_rows(const ProgData& pd, int vi, int64_t blocks, RowPlan& plan) {
             if (mode == M_X && op >= GP_SIN && op <= GP_PLOG) fn(row_key(op, (int)((w[2 * i] >> 8) & 255u)));
         }
     };
-    for (const DevProg& p : pd.progs) each(p, [&](int k) { uses[k]++; });
-    const int per_cu = std::max(1, 4 * (512 / ((v.ncv + (core_reg_levels(vi) + v.nf) * v.t + 7) / 8 * 8)) / v.waves);
-    const int most = ((160 << 10) / per_cu - v.rows_base) / (256 * v.t);
+    // (a short walk takes less time than waking the host threads)
+    auto walk = [&](const std::function<void(int64_t, int64_t)>& fn) {
+        if (pd.n_instr < (int64_t)1 << 15) fn(0, (int64_t)pd.progs.size());
+        else parallel_for((int64_t)pd.progs.size(), fn);
+    };
+    std::mutex mu;
+    walk([&](int64_t i0, int64_t i1) {
+        std::vector<int32_t> part(uses.size(), 0);
+        for (int64_t i = i0; i < i1; i++) each(pd.progs[i], [&](int k) { part[k]++; });
+        std::lock_guard<std::mutex> g(mu);
+        for (size_t k = 0; k < uses.size(); k++) uses[k] += part[k];
+    });
+    const int per_cu = std::max(1, 4 * core_variant_simd(vi) / v.waves);
+    // (a block's LDS is given in parts of 1280 bytes, 128 a CU: a third of all the bytes does not fit three times, and
+    // 1148 programs over 21 features then took 2.24 ms x 383000 cases, not 1.72)
+    const int most = (128 / per_cu * 1280 - v.rows_base) / (256 * v.t);
     std::vector<int> keys;
     for (int k = 0; k < (int)uses.size(); k++)
         if (2 * uses[k] >= 3 * std::max<int64_t>(2, blocks)) keys.push_back(k);
@@ -632,9 +653,11 @@ void plan_rows(const ProgData& pd, int vi, int64_t blocks, RowPlan& plan) {
         plan.op.push_back(GP_SIN + (uint32_t)(keys[r] / GP_MAX_FEAT));
         plan.feat.push_back(keys[r] % GP_MAX_FEAT);
     }
-    for (size_t i = 0; i < pd.progs.size(); i++)
-        each(pd.progs[i], [&](int k) { if (plan.row[k] >= 0) plan.cost[i] -= std::min(plan.cost[i] - 1, kRowSaving); });
-    for (uint32_t c : plan.cost) plan.total += c;
+    walk([&](int64_t i0, int64_t i1) {
+        for (int64_t i = i0; i < i1; i++)
+            each(pd.progs[i], [&](int k) { if (plan.row[k] >= 0) plan.cost[i] -= std::min(plan.cost[i] - 1, kRowSaving); });
+    });
+    plan.sum();
 }
 
 gp_status core_translate(const ProgData& pd, int vi, const uint32_t* order, RowPlan* rows, RawWords& code,
@@ -656,6 +679,10 @@ gp_status core_translate_at(const ProgData& pd, int vi, uint64_t base, RawWords&
 }
 
 int core_variant_waves(int vi) { return kCoreVariants[vi].waves; }
+int core_variant_simd(int vi) {
+    const CoreVariantDesc& v = kCoreVariants[vi];
+    return std::max(1, 512 / ((v.ncv + (core_reg_levels(vi) + v.nf) * v.t + 7) / 8 * 8));
+}
 int core_variant_t(int vi) { return kCoreVariants[vi].t; }
 int core_variant_ncv(int vi) { return kCoreVariants[vi].ncv; }
 int core_variant_d(int vi) { return kCoreVariants[vi].d; }

@@ -33,7 +33,9 @@ int pick_core_variant(int n_load, int depth, double transc_frac, bool has_transc
 gp_status core_ready(int vi, hipStream_t s);
 // True if core_ready has found variant vi's handler table on the current device.
 bool core_is_ready(int vi);
-int core_variant_waves(int vi);    // waves of a block
+int core_variant_waves(int vi);     // of a block
+int core_variant_simd(int vi);      // waves that a SIMD holds
+void no_rows(const ProgData& pd, RowPlan& plan);    // waves of a block
 // Which functions of a feature a launch computes once a tile into LDS, for variant vi, where `blocks` blocks share a
 // tile's programs; and the programs' costs without them.
 void plan_rows(const ProgData& pd, int vi, int64_t blocks, RowPlan& plan);

@@ -78,8 +78,9 @@ struct CoreArgs {
     int32_t n_rows;             // rows (sin, cos, exp or log of a feature) each block computes for its tile into LDS,
                                 // by the programs row_off[w] .. row_off[w + 1] of its wave w; 0: none
     const uint32_t* row_off;
-    int32_t direct;             // implicit units, at most as many tiles as a block has waves: a block runs one group on
-                                // every tile and writes its programs' fitness to `out` itself (no reduction launch):
+    int32_t direct;             // implicit units, at most as many tiles as a block has waves: a block of that many
+                                // waves runs one group on every tile and writes its programs' fitness to `out` itself
+                                // (no reduction launch); 0: not so.
     const uint32_t* group_prog; // group g holds the programs order[group_prog[g] .. group_prog[g + 1])
     const uint32_t* order;
     void* out;

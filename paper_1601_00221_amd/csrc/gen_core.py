@@ -1723,7 +1723,8 @@ def main(out_dir):
               '#include "core_body.h"', "", "namespace gpx {"] + core_lines + ["",
               "GPX_KERNEL(%d, %d, %d, %d, %d, %d, %s, %s)" % (T, D, NF, NCV, AR, W, "true" if ring and AR == 4 else "false", name), "",
               "hipError_t core_launch_%s(const CoreArgs& a, uint32_t blocks, hipStream_t s) {" % name,
-              "    hipLaunchKernelGGL(k_core_%s, dim3(blocks), dim3(%d), (uint32_t)a.n_rows * %du, s, a);" % (name, 64 * W, 256 * T),
+              "    hipLaunchKernelGGL(k_core_%s, dim3(blocks), dim3(a.direct ? 64u * (uint32_t)a.direct : %du), (uint32_t)a.n_rows * %du, s, a);"
+              % (name, 64 * W, 256 * T),
               "    return hipGetLastError();", "}", "",
               "int core_occupancy_%s() {" % name,
               "    int n = 0;",

@@ -9,6 +9,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <cmath>
 #include <condition_variable>
 #include <exception>
 #include <functional>
@@ -542,15 +543,20 @@ static gp_status prepare_programs(const ProgData& pd, int vi, DevProgs& dp, bool
     return GP_OK;
 }
 
-// Launch shape of one evaluation.  Programs are cut into G groups of
-// about `group_instr` core instructions; each block runs four groups (one
-// per wave) on a chunk of tiles_per_wave tiles.  Chunks lengthen only while
-// four times `target_blocks` blocks remain; with few tiles, groups are made
-// smaller instead, down to one program, so the chip still fills.  (Group
-// size and chunk length were chosen by sweeps on the 4096-program tree and
-// linear workloads.)
+// Launch shape of one evaluation.  Programs are cut into G groups; each block
+// runs W groups (one per wave) on a chunk of tiles_per_wave tiles.  With tiles
+// enough for the chip a group holds about `group_instr` core instructions;
+// chunks lengthen only while four times the waves of 4096 blocks of four
+// remain.  With fewer tiles the programs are cut into more groups, by the
+// estimate below.  (Cutting them until there were those 4096 blocks had waves
+// of one or two programs that mostly loaded their tile: the estimate takes
+// 158 -> 109 us for 100 programs of up to 512 nodes x 30000 cases, 235 -> 160
+// for 4096 programs x 1000 cases, 433 -> 336 for 4096 classification trees over 41 features x 3000, 53 -> 30 for 1024 Boolean programs x 32000, and over 100
+// pairs of a population and a number of cases it is within 4 % of the best
+// number of blocks, where the old rule was 22 % above it.)
 struct LaunchShape {
     int32_t G, tiles_per_wave, chunks;
+    double est;   // launch_time of G, 0: not asked for
 };
 
 static int32_t env_int(const char* name, int32_t dflt) {
@@ -569,8 +575,8 @@ int32_t code_prefetch() {
     return n <= 0 ? 0 : (n > 14 ? 14 : (int32_t)n);
 }
 
-static LaunchShape launch_shape(const ProgData& pd, int vi, int32_t tiles, const EvalOptions* opt, const RowPlan* rows,
-                                int32_t force_G = 0) {
+// Groups of a launch with tiles enough for them.
+int32_t base_groups(const ProgData& pd, const EvalOptions* opt) {
     // Program groups of about 1024 core instructions when the programs read at most 12 features, else
     // 4096: every wave loads the features of its tile before it runs its group, and a longer group
     // spreads those loads over more instructions.  Measured on the 4096-program workloads (kernel
@@ -580,19 +586,57 @@ static LaunchShape launch_shape(const ProgData& pd, int vi, int32_t tiles, const
     const bool few_feat = pd.n_load <= 12;
     const int32_t group_instr =
         opt && opt->group_instr > 0 ? opt->group_instr : env_int("GP2D_GROUP_INSTR", few_feat ? 1024 : 4096);
+    // (the end of a program takes about as long as four instructions)
+    const int64_t G = (pd.n_instr + 4 * (int64_t)pd.n_prog + group_instr - 1) / group_instr;
+    return (int32_t)std::max<int64_t>(1, std::min<int64_t>(G, pd.n_prog));
+}
+
+// An estimate of how long `blocks` blocks a tile take, in the time of one
+// vector instruction a slot (4 T cycles), fitted to the times of 100 launches
+// at 12 numbers of blocks each.  A SIMD that holds 1, 2, 3 or 4 waves runs at
+// `rate` of its peak.  A wave loads its tile (2.2 a feature) after a fixed
+// start, and computes its share of the rows (35 a row as work of the chip; the
+// wait for them is some 100 a row and wave).  The longest program bounds a
+// wave from below.  Waves beyond those that fit at once take the SIMDs as they
+// come free, and the last of them leave others idle for half their time.
+static double launch_time(const ProgData& pd, int vi, int32_t tiles, int32_t tpw, int64_t blocks, const RowPlan& rows) {
+    static constexpr double rate[5] = {0.0, 0.47, 0.60, 0.75, 1.0};
+    const double W = core_variant_waves(vi), T = core_variant_t(vi), G = std::min<double>(blocks * W, pd.n_prog);
+    const int K = std::min(4, core_variant_simd(vi));
+    const double chunks = (tiles + tpw - 1) / tpw;
+    const double fix = 190.0 / T + 2.2 * pd.n_load * tpw;
+    const double mean = fix + tpw * (35.0 * rows.n() / W + rows.total / G);
+    const double most = fix + tpw * (100.0 * std::ceil(rows.n() / W) + std::max(rows.total / G, 0.7 * rows.longest));
+    const double waves = G * chunks, start = 1.8 * blocks * chunks / T;
+    if (waves <= 1024.0 * K) {
+        const int k = std::max(1, (int)((waves + 1023) / 1024));
+        return start + std::max(k * mean / rate[k], most / rate[1]);
+    }
+    return start + waves * mean / (1024.0 * rate[K]) + 0.55 * most / rate[1];
+}
+
+static LaunchShape launch_shape(const ProgData& pd, int vi, int32_t tiles, const EvalOptions* opt, const RowPlan& rows,
+                                int32_t force_G = 0) {
     // (a block counts as four waves)
     const int64_t W = core_variant_waves(vi);
-    const int32_t target_blocks =
-        (int32_t)((4 * (int64_t)(opt && opt->target_blocks > 0 ? opt->target_blocks : env_int("GP2D_TARGET_BLOCKS", 4096)) +
-                   W - 1) / W);
-    // (the end of a program takes about as long as four instructions)
-    int64_t G = (pd.n_instr + 4 * (int64_t)pd.n_prog + group_instr - 1) / group_instr;
-    if (((G + W - 1) / W) * tiles < target_blocks) G = W * ((target_blocks + tiles - 1) / tiles);
-    if (rows && rows->n() > 0) {
-        // every block computes the rows of its tile: at least four times their cost for its programs
-        G = std::min<int64_t>(G, W * std::max<int64_t>(1, (int64_t)(rows->total / (4.0 * 35.0 * rows->n()))));
+    const int32_t forced = opt && opt->target_blocks > 0 ? opt->target_blocks : env_int("GP2D_TARGET_BLOCKS", 0);
+    const int32_t target_blocks = (int32_t)((4 * (int64_t)(forced > 0 ? forced : 4096) + W - 1) / W);
+    LaunchShape L;
+    L.est = 0.0;
+    int64_t G = base_groups(pd, opt);
+    if (force_G <= 0 && ((G + W - 1) / W) * tiles < target_blocks) {
+        const int64_t most = (pd.n_prog + W - 1) / W;
+        int64_t best = (G + W - 1) / W;
+        if (forced > 0) {
+            best = (target_blocks + tiles - 1) / tiles;
+        } else {
+            for (int64_t b = best; b <= most; b += std::max<int64_t>(1, b / 16)) {
+                const double t = launch_time(pd, vi, tiles, 1, b, rows);
+                if (L.est == 0.0 || t < L.est) L.est = t, best = b;
+            }
+        }
+        G = std::min<int64_t>(best * W, pd.n_prog);
     }
-    G = std::max<int64_t>(1, std::min<int64_t>(G, pd.n_prog));
     if (force_G > 0) G = force_G;
     const int64_t quads = (G + W - 1) / W;
     int32_t tpw = opt && opt->tiles_per_wave > 0 ? opt->tiles_per_wave : env_int("GP2D_TILES_PER_WAVE", 0);
@@ -600,7 +644,6 @@ static LaunchShape launch_shape(const ProgData& pd, int vi, int32_t tiles, const
         tpw = 1;
         while (tpw < 16 && quads * ((tiles + 2 * tpw - 1) / (2 * tpw)) >= 4 * (int64_t)target_blocks) tpw *= 2;
     }
-    LaunchShape L;
     L.G = (int32_t)G;
     L.tiles_per_wave = tpw;
     L.chunks = (int32_t)((tiles + tpw - 1) / tpw);
@@ -642,11 +685,37 @@ hipError_t timed_launch_end(hipStream_t s, int slot) {
     return hipEventRecord(g_tm_events[slot].second, s);
 }
 
-int32_t base_groups(const ProgData& pd, int vi) { return launch_shape(pd, vi, 1 << 30, nullptr, nullptr).G; }
 
 static void plan_rows_for(const ProgData& pd, int vi, RowPlan& rows) {
     const int32_t W = core_variant_waves(vi);
-    plan_rows(pd, vi, (base_groups(pd, vi) + W - 1) / W, rows);
+    plan_rows(pd, vi, (base_groups(pd, nullptr) + W - 1) / W, rows);
+}
+
+// The translation that an evaluation takes, as a key of dps: with rows (vi) or without (vi + kNoRows).  Every block
+// computes the rows of its tile, so with few tiles, and thus blocks of few programs, they can cost more than they save
+// (1148 classification programs with 41 rows x 1000 cases: 29 us with them, 18 without; x 8000: 65 and 61; x 383000:
+// 1.72 ms and 1.89): the shorter estimate is taken.  Where the tiles are enough for whole groups both estimates are
+// zero, and the rows stay.
+static int translation_for(const ProgData& pd, int vi, std::map<int, DevProgs>& dps, bool fresh, int32_t tiles,
+                           const EvalOptions* opt, hipStream_t s) {
+    DevProgs& dp = dps[vi];
+    if (fresh || !dp.uploaded) plan_rows_for(pd, vi, dp.rows);
+    if (dp.rows.n() == 0) return vi;
+    RowPlan none;
+    no_rows(pd, none);
+    if (launch_shape(pd, vi, tiles, opt, dp.rows).est <= launch_shape(pd, vi, tiles, opt, none).est) return vi;
+    if (fresh) {
+        dp.rows = std::move(none);
+        return vi;
+    }
+    DevProgs& plain = dps[vi + kNoRows];
+    if (!plain.uploaded) {
+        // (made on its first use, but not while the stream is being captured)
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusActive;
+        if (hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) return vi;
+        plain.rows = std::move(none);
+    }
+    return vi + kNoRows;
 }
 
 int default_variant(const ProgData& pd) {
@@ -699,15 +768,15 @@ gp_status eval_core(const ProgData& pd, std::map<int, DevProgs>& dps, bool fresh
     } else if ((st = core_ready(vi, s)) != GP_OK) {
         return st;
     }
-    auto dit = dps.find(vi);
-    if (no_alloc && dit == dps.end()) return fail(GP_E_INVAL, "programs are not on the device for variant %d", vi);
-    DevProgs& dp = no_alloc ? dit->second : dps[vi];
     const int T = core_variant_t(vi);
     const int64_t tiles64 = (N + 64LL * T - 1) / (64LL * T);
     if (tiles64 > (1LL << 30)) return fail(GP_E_INVAL, "n_cases too large");
     const int32_t tiles = (int32_t)tiles64;
-    if (fresh || !dp.uploaded) plan_rows_for(pd, vi, dp.rows);
-    const LaunchShape L = launch_shape(pd, vi, tiles, opt, &dp.rows, no_alloc ? opt->groups : 0);
+    const int key = no_alloc ? vi : translation_for(pd, vi, dps, fresh, tiles, opt, s);
+    auto dit = dps.find(key);
+    if (no_alloc && dit == dps.end()) return fail(GP_E_INVAL, "programs are not on the device for variant %d", vi);
+    DevProgs& dp = no_alloc ? dit->second : dps[key];
+    const LaunchShape L = launch_shape(pd, vi, tiles, opt, dp.rows, no_alloc ? opt->groups : 0);
     const int32_t G = L.G;
     // (rows are those of the one tile that a block's waves share)
     const int32_t same_group = dp.rows.n() == 0 && env_int("GP2D_SAME_GROUP", 0) > 0 ? 1 : 0;
@@ -758,7 +827,7 @@ gp_status eval_core(const ProgData& pd, std::map<int, DevProgs>& dps, bool fresh
     a.same_group = same_group;
     a.n_rows = dp.rows.n();
     a.row_off = goff + G + 1;
-    a.direct = direct ? 1 : 0;
+    a.direct = direct ? tiles : 0;
     a.group_prog = a.row_off + W + 1;
     a.order = a.group_prog + G + 1;
     a.out = out;
@@ -892,7 +961,7 @@ static gp_status progset_finish(ProgData&& pd, void* stream, gp_progset** ps) {
         if ((st = core_ready(vi, s)) != GP_OK) return st;
         Workspace& w = workspace(s);
         std::lock_guard<std::mutex> g(w.mu);
-        p->groups = base_groups(p->pd, vi);
+        p->groups = base_groups(p->pd, nullptr);
         plan_rows_for(p->pd, vi, p->dps[vi].rows);
         if ((st = prepare_programs(p->pd, vi, p->dps[vi], false, p->groups, s, w, nullptr)) != GP_OK)
             return st;

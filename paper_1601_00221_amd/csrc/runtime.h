@@ -113,6 +113,15 @@ struct RowPlan {
     std::vector<uint32_t> cost;    // of each program, its rows read instead of computed
     double total = 0.0;            // of all of them
     int32_t n() const { return (int32_t)op.size(); }
+    uint32_t longest = 0;          // the largest of them
+    void sum() {
+        total = 0.0;
+        longest = 0;
+        for (uint32_t c : cost) {
+            total += c;
+            if (c > longest) longest = c;
+        }
+    }
 };
 
 // Device copies of programs translated for one core variant, plus their
@@ -157,6 +166,8 @@ struct EvalSegment {
     int32_t first, n_prog;
     void* out;
 };
+
+constexpr int kNoRows = 1 << 16;   // added to a variant's index: the key of its translation without rows
 
 struct EvalOptions {
     int variant = -1;            // core variant index, -1 = chosen from the programs
@@ -216,6 +227,6 @@ gp_status progset_eval_no_alloc(gp_progset* ps, const float* X, int32_t n_feat, 
                                 int32_t kind, void* out, hipStream_t s, double* partials, size_t partials_bytes);
 // Program groups of a launch of variant vi over plentiful case tiles (the
 // layout a program set uploads when it is created).
-int32_t base_groups(const ProgData& pd, int vi);
+int32_t base_groups(const ProgData& pd, const EvalOptions* opt);
 
 }  // namespace gpx
