@@ -98,7 +98,7 @@ static bool mode_no_transc(int mode) { return mode == 1 || mode == 2 || mode == 
 
 static constexpr int kShallowDepth = 12;
 
-int pick_core_variant(int n_load, int depth, double transc_frac, bool has_transc, bool boolean, bool trees_only) {
+int pick_core_variant(int n_load, int depth, double transc_frac, bool has_transc, bool boolean, bool trees_only, bool wide) {
     // Programs rich in sin/cos/exp/log (binary64, evaluated by compiled code
     // outside the core) run best with room for that code (no spills) and as
     // many waves per SIMD as that leaves, to hide its latency; the others with
@@ -130,7 +130,15 @@ int pick_core_variant(int n_load, int depth, double transc_frac, bool has_transc
         const CoreVariantDesc& v = kCoreVariants[i];
         if ((v.arith == 2) != boolean) continue;
         if (v.arith >= 3 && !trees_only) continue;
-        if (v.nf < n_load || v.d < depth || (mode_no_transc(v.arith) && has_transc)) continue;
+        // Features in LDS: where fewer than four waves a SIMD would hold them in registers (13 and more with
+        // sin/cos/exp/log: 4096 trees x 30000 cases over 13, 24, 41 features 3.63, 4.02, 4.95 ms in registers, 3.34,
+        // 3.87, 4.26 so; without those functions 25 and more: 1.27 and 1.11 ms).
+        if (v.cap > v.nf) {
+            if (!wide || n_load <= (has_transc ? 12 : 24) || v.cap < n_load || v.d <= depth) continue;
+            return i;
+        } else if (v.nf < n_load || v.d < depth || (mode_no_transc(v.arith) && has_transc)) {
+            continue;
+        }
         // the deep variants (fewer waves per SIMD) serve only programs that need them
         if (v.d > kShallowDepth && depth <= kShallowDepth) continue;
         if (best < 0) { best = i; continue; }
@@ -232,6 +240,11 @@ struct Emitter {
             cst);
         phase = 0;   // the core is entered again after an exit
     }
+    // feature f of the tile to stack level 0 (programs of rows)
+    void load(int f) {
+        put(CK_EXIT, 0, 0, 0, (CORE_OP_LOAD << 24) | (uint32_t)f, 0);
+        phase = 0;
+    }
     // the end of a program: its row, and the records of the program that follows it
     void end(uint32_t row, uint32_t next) {
         if (ok) put(CK_EXIT, 0, 0, 0, (CORE_OP_END << 24) | (next & 0xFFFFFFu), row);
@@ -329,9 +342,11 @@ static int translate_tree(const uint32_t* w, int64_t n_instr, int vi, const Vari
     const CoreVariantDesc& v = kCoreVariants[vi];
     const int T = v.t, FO = core_reg_levels(vi) * T;
     Emitter e{v, m, out, cap, err};
+    auto push_row = [&](int r, int h) { e.put(CK_PUSHR, 0, h, 0, (uint32_t)(r * 256 * T), 0); };
     for (int64_t i = 0; i < n_instr && e.ok; i++) {
         const uint32_t w0 = w[2 * i], c = w[2 * i + 1];
-        const uint32_t op = w0 & 15u, mode = (w0 >> 4) & 15u;
+        const uint32_t op = w0 & 15u;
+        uint32_t mode = (w0 >> 4) & 15u;
         const int fa = (int)((w0 >> 8) & 255u), fb = (int)((w0 >> 16) & 255u), ha = (int)(w0 >> 24);
         int h;  // stack height before the instruction
         switch (mode) {
@@ -341,6 +356,35 @@ static int translate_tree(const uint32_t* w, int64_t n_instr, int vi, const Vari
             default: h = ha; break;
         }
         const int xa = FO + fa * T, xb = FO + fb * T;
+        if (v.cap > v.nf && op != OP_IF) {
+            // features in LDS are pushed, and the instruction takes them from the stack
+            const bool la = fa >= v.nf, lb = fb >= v.nf;
+            switch (mode) {
+                case M_SX: if (lb) push_row(rows->feature(fb), h++), mode = M_SS; break;
+                case M_XS: if (la) push_row(rows->feature(fa), h++), mode = M_SSR; break;
+                case M_XC: if (la) push_row(rows->feature(fa), h++), mode = M_SC; break;
+                case M_CX: if (lb) push_row(rows->feature(fb), h++), mode = M_CS; break;
+                case M_XX:
+                    if (la) {
+                        push_row(rows->feature(fa), h++);
+                        mode = M_SX;
+                        if (lb) push_row(rows->feature(fb), h++), mode = M_SS;
+                    } else if (lb) {
+                        push_row(rows->feature(fb), h++);
+                        mode = M_XS;
+                    }
+                    break;
+                case M_X:
+                    if (!la) break;
+                    if (op == OP_PUSH) {
+                        push_row(rows->feature(fa), h);
+                        continue;
+                    }
+                    if (rows->row[row_key(op, fa)] < 0) push_row(rows->feature(fa), h++), mode = M_S;
+                    break;
+                default: break;
+            }
+        }
         if (op == OP_PUSH) {
             if (mode == M_X) {
                 // Boolean kernels push a variable only as a whole program, at the bottom
@@ -433,7 +477,7 @@ static int translate_tree(const uint32_t* w, int64_t n_instr, int vi, const Vari
             case M_S: e.exit(op, (h - 1) * T, 0, (h - 1) * T, false, false, 0); break;
             case M_X: {
                 const int r = rows && rows->n() > 0 ? rows->row[row_key(op, fa)] : -1;
-                if (r >= 0) e.put(CK_PUSHR, 0, h, 0, (uint32_t)(r * 256 * T), 0);
+                if (r >= 0) push_row(r, h);
                 else e.exit(op, xa, 0, h * T, false, false, 0);
                 break;
             }
@@ -523,43 +567,75 @@ static VariantMap map_at(int vi, uint64_t base) {
 
 constexpr int kCodePadding = 32;   // words
 
+// Operands of a tree that lie in LDS and are pushed by a record of their own.
+static int64_t pushes_of_features(const uint32_t* w, int64_t n, const CoreVariantDesc& v, const RowPlan& rows) {
+    int64_t k = 0;
+    for (int64_t i = 0; i < n; i++) {
+        const uint32_t w0 = w[2 * i], op = w0 & 15u, mode = (w0 >> 4) & 15u;
+        const int fa = (int)((w0 >> 8) & 255u), fb = (int)((w0 >> 16) & 255u);
+        if (op == OP_IF) continue;
+        if (mode == M_XS || mode == M_XC || mode == M_XX) k += fa >= v.nf;
+        if (mode == M_SX || mode == M_CX || mode == M_XX) k += fb >= v.nf;
+        if (mode == M_X && op != OP_PUSH) k += fa >= v.nf && rows.row[row_key(op, fa)] < 0;
+    }
+    return k;
+}
+
 // Programs are translated in parallel, each into its own counted range of
 // the code: a tree gives one core instruction per lowered instruction plus
-// the end; a register program as linear_records counts.  The code holds the
+// the end (and one for each operand that lies in LDS); a register program as linear_records counts.  The code holds the
 // programs one after another in the order given (null: their own order), each
 // ending with the length of the one after it; progs[p] says where program p
 // lies.  With `rows`, functions of a feature that have a row push it, and the
-// programs that compute the rows follow the others: two records each, a
-// share for every wave of a block.
+// programs that compute the rows follow the others, a share for every wave of a
+// block: two records each, three if the feature is loaded first.
 static gp_status translate_with(const ProgData& pd, int vi, const VariantMap& m, const uint32_t* order, RowPlan* rows,
                                 RawWords& code, std::vector<DevProg>& progs) {
     const int32_t P = pd.n_prog;
     progs = pd.progs;
+    RowPlan features;
+    const bool in_lds = pd.n_load > kCoreVariants[vi].nf;
+    if (in_lds && !rows) {
+        no_rows(pd, vi, features);
+        rows = &features;
+    }
     std::vector<int64_t> start((size_t)P + 1, 0);
     auto at = [&](int32_t i) { return order ? (int32_t)order[i] : i; };
     auto records = [&](int32_t p) {
         const DevProg& src = pd.progs[p];
-        return (src.meta & 1u) == FORM_TREE ? (int64_t)src.len + 1
-                                            : linear_records(pd.code.data() + src.code_off, src.len, src.live);
+        if ((src.meta & 1u) == FORM_TREE)
+            return (int64_t)src.len + 1 +
+                   (in_lds ? pushes_of_features(pd.code.data() + src.code_off, src.len, kCoreVariants[vi], *rows) : 0);
+        return linear_records(pd.code.data() + src.code_off, src.len, src.live);
     };
     for (int32_t i = 0; i < P; i++) start[i + 1] = start[i] + records(at(i));
     if (start[P] * 16 > 0xFFFFFFF0ll) return fail(GP_E_INVAL, "programs exceed 4 GiB of core code");
     // the core reads records two or four at a time, ahead of the one it runs: up
     // to seven past a program's last one, so the code ends with padding
     const int32_t R = rows ? rows->n() : 0;
-    code.resize((size_t)(start[P] + 2 * R) * 4 + kCodePadding);
-    std::fill(code.end() - kCodePadding, code.end(), 0u);
+    code.resize((size_t)(start[P] + 3 * R) * 4 + kCodePadding);
+    std::fill(code.begin() + 4 * start[P], code.end(), 0u);
     if (rows) {
+        // wave w computes rows w, w + W, ...
         const CoreVariantDesc& v = kCoreVariants[vi];
-        rows->rec.clear();
-        for (int32_t w = 0; w <= v.waves; w++) rows->rec.push_back((uint32_t)(start[P] + 2 * ((int64_t)R * w / v.waves)));
+        auto length = [&](int32_t r) { return rows->op[r] != OP_PUSH && rows->feat[r] >= v.nf ? 3 : 2; };
+        int64_t at_rec = start[P];
         char err[256];
-        for (int32_t r = 0; r < R; r++) {
-            Emitter e{v, m, code.data() + 4 * (start[P] + 2 * r), 2, err};
-            e.exit(rows->op[r], (core_reg_levels(vi) + rows->feat[r]) * v.t, 0, 0, false, false, 0);
-            e.end((uint32_t)r, 2);
-            if (!e.ok) return fail(GP_E_INVAL, "row %d: %s", r, err);
+        rows->rec.clear();
+        for (int32_t w = 0; w < v.waves; w++) {
+            rows->rec.push_back((uint32_t)at_rec);
+            for (int32_t r = w; r < R; r += v.waves) {
+                const int n = length(r), f = rows->feat[r], next = r + v.waves < R ? length(r + v.waves) : 0;
+                Emitter e{v, m, code.data() + 4 * at_rec, n, err};
+                if (f >= v.nf) e.load(f);
+                if (rows->op[r] != OP_PUSH)
+                    e.exit(rows->op[r], f >= v.nf ? 0 : (core_reg_levels(vi) + f) * v.t, 0, 0, false, false, 0);
+                e.end((uint32_t)r, (uint32_t)next);
+                if (!e.ok || e.n != n) return fail(GP_E_INVAL, "row %d: %s", r, e.ok ? "length" : err);
+                at_rec += n;
+            }
         }
+        rows->rec.push_back((uint32_t)at_rec);
     }
     std::vector<int32_t> rc((size_t)P, GP_OK);
     auto translate = [&](int32_t i, uint32_t* out, int64_t cap, int64_t* n, char* err) {
@@ -606,14 +682,22 @@ static gp_status translate_with(const ProgData& pd, int vi, const VariantMap& m,
 // again (about 90 vector instructions at T = 4).
 static constexpr uint32_t kRowSaving = 33;   // of the cost of one use (runtime.cpp, op_cost)
 
-void no_rows(const ProgData& pd, RowPlan& plan) {
+void no_rows(const ProgData& pd, int vi, RowPlan& plan) {
     plan = RowPlan();
     plan.cost = pd.cost;
     plan.sum();
+    const CoreVariantDesc& v = kCoreVariants[vi];
+    if (pd.n_load <= v.nf) return;
+    plan.row.assign(4 * GP_MAX_FEAT, -1);
+    plan.first_lds = v.nf;
+    for (int f = v.nf; f < pd.n_load; f++) {
+        plan.op.push_back(OP_PUSH);
+        plan.feat.push_back(f);
+    }
 }
 
 void plan_rows(const ProgData& pd, int vi, int64_t blocks, RowPlan& plan) {
-    no_rows(pd, plan);
+    no_rows(pd, vi, plan);
     const CoreVariantDesc& v = kCoreVariants[vi];
     if (v.rows_base == 0 || pd.form != FORM_TREE || pd.n_transc == 0 || pd.n_load > GP_MAX_FEAT) return;
     if (2 * pd.n_transc < 3 * blocks) return;
@@ -640,7 +724,7 @@ void plan_rows(const ProgData& pd, int vi, int64_t blocks, RowPlan& plan) {
     const int per_cu = std::max(1, 4 * core_variant_simd(vi) / v.waves);
     // (a block's LDS is given in parts of 1280 bytes, 128 a CU: a third of all the bytes does not fit three times, and
     // 1148 programs over 21 features then took 2.24 ms x 383000 cases, not 1.72)
-    const int most = (128 / per_cu * 1280 - v.rows_base) / (256 * v.t);
+    const int have = plan.n(), most = (128 / per_cu * 1280 - v.rows_base) / (256 * v.t) - have;
     std::vector<int> keys;
     for (int k = 0; k < (int)uses.size(); k++)
         if (2 * uses[k] >= 3 * std::max<int64_t>(2, blocks)) keys.push_back(k);
@@ -649,7 +733,7 @@ void plan_rows(const ProgData& pd, int vi, int64_t blocks, RowPlan& plan) {
     if (keys.empty()) return;
     plan.row.assign(uses.size(), -1);
     for (size_t r = 0; r < keys.size(); r++) {
-        plan.row[keys[r]] = (int32_t)r;
+        plan.row[keys[r]] = have + (int32_t)r;
         plan.op.push_back(GP_SIN + (uint32_t)(keys[r] / GP_MAX_FEAT));
         plan.feat.push_back(keys[r] % GP_MAX_FEAT);
     }
@@ -687,6 +771,13 @@ int core_variant_t(int vi) { return kCoreVariants[vi].t; }
 int core_variant_ncv(int vi) { return kCoreVariants[vi].ncv; }
 int core_variant_d(int vi) { return kCoreVariants[vi].d; }
 int core_variant_nf(int vi) { return kCoreVariants[vi].nf; }
+int core_variant_cap(int vi) { return kCoreVariants[vi].cap; }
+bool core_variant_fits(int vi, const ProgData& pd) {
+    const CoreVariantDesc& v = kCoreVariants[vi];
+    // (an operand that is pushed takes the level above)
+    return v.cap >= pd.n_load && v.d >= pd.max_depth + (pd.n_load > v.nf) && !(mode_no_transc(v.arith) && pd.n_transc > 0) &&
+           (v.arith == 2) == (pd.opset == OPSET_BOOL) && !(v.arith >= 2 && pd.form != FORM_TREE);
+}
 int core_variant_arith(int vi) { return mode_no_transc(kCoreVariants[vi].arith); }
 bool core_variant_bool(int vi) { return kCoreVariants[vi].arith == 2; }
 bool core_variant_trees_only(int vi) { return kCoreVariants[vi].arith >= 2; }

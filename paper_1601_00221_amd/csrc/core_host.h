@@ -15,7 +15,9 @@ namespace gpx {
 int core_variants();
 int core_variant_t(int vi);        // case slots per lane
 int core_variant_d(int vi);        // stack levels
-int core_variant_nf(int vi);       // feature slots
+int core_variant_nf(int vi);       // features in registers
+int core_variant_cap(int vi);      // features it takes: more than nf where the others lie in LDS (eval_core only)
+bool core_variant_fits(int vi, const ProgData& pd);   // features, depth, functions and form
 int core_variant_arith(int vi);    // 1: no sin/cos/exp/log code
 bool core_variant_bool(int vi);    // the Boolean function set (32-bit word slots)
 bool core_variant_trees_only(int vi);   // no linear handlers (Boolean and trees-only arithmetic kernels)
@@ -27,7 +29,8 @@ int core_reg_levels(int vi);       // register/stack levels before the features
 // `trees_only` (then a kernel without linear handlers may be taken); -1 if
 // none fits.
 int pick_core_variant(int n_load, int depth, double transc_frac, bool has_transc, bool boolean = false,
-                      bool trees_only = false);
+                      bool trees_only = false,
+                      bool wide = false);
 // Locate the variant's handler table on the current device (one probe launch
 // on stream s the first time).
 gp_status core_ready(int vi, hipStream_t s);
@@ -35,7 +38,7 @@ gp_status core_ready(int vi, hipStream_t s);
 bool core_is_ready(int vi);
 int core_variant_waves(int vi);     // of a block
 int core_variant_simd(int vi);      // waves that a SIMD holds
-void no_rows(const ProgData& pd, RowPlan& plan);    // waves of a block
+void no_rows(const ProgData& pd, int vi, RowPlan& plan);    // waves of a block
 // Which functions of a feature a launch computes once a tile into LDS, for variant vi, where `blocks` blocks share a
 // tile's programs; and the programs' costs without them.
 void plan_rows(const ProgData& pd, int vi, int64_t blocks, RowPlan& plan);

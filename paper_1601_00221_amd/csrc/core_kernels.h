@@ -15,7 +15,7 @@ namespace gpx {
 // Exit operation that ends a program.  Its record's payload holds, in the low
 // 24 bits, the number of records of the program that follows (0: none), and
 // its constant the program's row.
-enum : uint32_t { CORE_OP_END = 15 };
+enum : uint32_t { CORE_OP_LOAD = 14, CORE_OP_END = 15 };   // LOAD: a feature of the tile to stack level 0
 
 enum : int32_t { CORE_TO_ROW = 5 };     // "fitness kind" of the programs that compute a block's rows
 

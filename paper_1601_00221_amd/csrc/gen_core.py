@@ -109,7 +109,16 @@ RING_VARIANTS = [
     (4, 8, 16, 56, 4),
     (4, 6, 24, 48, 4),
     (4, 8, 44, 48, 4),
+    (4, 9, 11, 48, 4),
 ]
+
+# Ring cores with sin/cos/exp/log that hold more features than their registers do: the others lie in LDS, as rows that
+# a block loads for its tile and its programs push.  The value is how many features they take.  44 features in registers
+# leave room for 2 waves a SIMD, which kept the vector units busy 66 % of the time; 11 leave room for 4, two blocks a CU:
+# 46.8 -> 38.8 ms on 4096 classification trees over 41 features x 494021 cases, though a third of the functions' rows
+# give way to features and every operand in LDS takes a record.  (One block of 16 waves a CU, with room for all the
+# rows: 43.9 ms; its waves wait for the slowest of them, and nothing else runs meanwhile.)
+WIDE = {(4, 9, 11, 48, 4): 44}
 
 
 def vname(v):
@@ -149,8 +158,10 @@ def xx_levels(D, NF, mode, ring):
 def waves_per_block(T, D, NF, NCV, mode, ring):
     """Four; eight in ring cores with sin/cos/exp/log whose occupancy eight
     divides: the waves of a block share the rows of its tile in LDS, and a
-    wider block has room for more of them."""
+    wider block has room for more of them.  Half of what a CU holds where features lie in LDS."""
     simd = 512 // ((NCV + (reg_levels(D, mode) + NF) * T + 7) // 8 * 8)
+    if (T, D, NF, NCV, mode) in WIDE and ring:
+        return 2 * simd
     return 8 if ring and mode == 4 and simd % 2 == 0 else 4
 
 
@@ -1562,14 +1573,32 @@ def big_reduction(r, G):
     return L
 
 
+def load_feature(T, V0, tag, mode):
+    """A feature of the tile (its number in s66) into stack level 0, for the programs of the rows."""
+    vl = "v%d" % (V0 + T)                        # stack level 1 is free here
+    L = [".Lgpx_ldf_%s:" % tag, "s_waitcnt lgkmcnt(0)", first_records(True, mode)[0],
+         "s_and_b32 s80, s66, 0xffffff",
+         "s_mul_i32 s76, s80, s84", "s_mul_hi_u32 s77, s80, s84", "s_mul_i32 s81, s80, s85", "s_add_u32 s77, s77, s81",
+         "s_add_u32 s76, s76, s82", "s_addc_u32 s77, s77, s83",
+         "v_mbcnt_lo_u32_b32 %s, -1, 0" % vl, "v_mbcnt_hi_u32_b32 %s, -1, %s" % (vl, vl), "v_lshlrev_b32_e32 %s, 2, %s" % (vl, vl)]
+    for j in range(T):
+        L += exec_slot(j) + ["global_load_dword v%d, %s, s[76:77] offset:%d" % (V0 + j, vl, 256 * j)]
+    return L + ["s_mov_b64 exec, -1", "s_waitcnt vmcnt(0) lgkmcnt(0)"] + first_records(True, mode)[1]
+
+
 def tail_lines(T, D, NF, V0, FO, tag, mode, ring):
     """What follows the handlers in the block: an exit's record is in s[66:67]."""
     L = [".Lgpx_end_%s:" % tag]
     if mode in (0, 4):
-        L += ["s_bfe_u32 s72, s66, 0x40018", "s_cmp_lg_u32 s72, 15", "s_cbranch_scc1 .Lgpx_fn_%s" % tag]
+        L += ["s_bfe_u32 s72, s66, 0x40018"]
+        if (T, D, NF, V0, mode) in WIDE and ring:
+            L += ["s_cmp_eq_u32 s72, 14", "s_cbranch_scc1 .Lgpx_ldf_%s" % tag]
+        L += ["s_cmp_lg_u32 s72, 15", "s_cbranch_scc1 .Lgpx_fn_%s" % tag]
     L += program_end(T, D, NF, V0, FO, tag, mode, ring)
     if mode in (0, 4):
         L += transc(T, V0, V0, tag, mode, ring)
+    if (T, D, NF, V0, mode) in WIDE and ring:
+        L += load_feature(T, V0, tag, mode)
     if ring and mode != 2:
         L += division_bodies(T, D, V0, tag)
     L += [".Lgpx_leave_%s:" % tag, "s_waitcnt vmcnt(0) lgkmcnt(0)"]
@@ -1699,14 +1728,16 @@ def main(out_dir):
         lines.append("};")
     lines.append("struct CoreVariantDesc { int t, d, nf, ncv, arith; const CoreHandlerKey* keys; const uint16_t* slots; "
                  "int n; int slot_bytes; int xx; bool ring; "
-                 "int waves, rows_base; };")
-    lines.append("// xx: levels with one-pass handlers of two variables; waves: waves of a block; rows_base: LDS address of its rows, or 0")
+                 "int waves, rows_base, cap; };")
+    lines.append("// xx: levels with one-pass handlers of two variables; waves: waves of a block; rows_base: LDS address of its rows, or 0;")
+    lines.append("// cap: features it takes (more than nf: the others in LDS)")
     lines.append("static const CoreVariantDesc kCoreVariants[] = {")
     for (T, D, NF, NCV, AR, tag, hs, nslots, ring) in host:
-        lines.append("    {%d, %d, %d, %d, %d, kCoreKeys_%s, kCoreSlots_%s, %d, %d, %d, %s, %d, %d},"
+        lines.append("    {%d, %d, %d, %d, %d, kCoreKeys_%s, kCoreSlots_%s, %d, %d, %d, %s, %d, %d, %d},"
                      % (T, D, NF, NCV, AR, tag, tag, len(hs), RING_SLOT if ring else SLOT, xx_levels(D, NF, AR, ring),
                         "true" if ring else "false", waves_per_block(T, D, NF, NCV, AR, ring),
-                        rows_base(T, D, NF, NCV, AR) if ring and AR == 4 else 0))
+                        rows_base(T, D, NF, NCV, AR) if ring and AR == 4 else 0,
+                        WIDE.get((T, D, NF, NCV, AR), NF) if ring else NF))
     lines.append("};")
     path = os.path.join(out_dir, "core_gen.inc")
     write_if_changed(path, "\n".join(lines) + "\n")

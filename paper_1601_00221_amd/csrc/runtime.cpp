@@ -576,19 +576,21 @@ int32_t code_prefetch() {
 }
 
 // Groups of a launch with tiles enough for them.
-int32_t base_groups(const ProgData& pd, const EvalOptions* opt) {
-    // Program groups of about 1024 core instructions when the programs read at most 12 features, else
-    // 4096: every wave loads the features of its tile before it runs its group, and a longer group
-    // spreads those loads over more instructions.  Measured on the 4096-program workloads (kernel
-    // time, 4096 against 1024): 8-feature trees 7 % (sin/cos/exp/log) and 1.5 % (+, -, *) slower,
-    // 9-feature classification trees 2.7 % slower; 16-feature linear programs 2 %, 20-input
-    // multiplexer trees 2.4 % and 41-feature classification trees 6 % faster.
-    const bool few_feat = pd.n_load <= 12;
-    const int32_t group_instr =
-        opt && opt->group_instr > 0 ? opt->group_instr : env_int("GP2D_GROUP_INSTR", few_feat ? 1024 : 4096);
+int32_t base_groups(const ProgData& pd, int vi, const EvalOptions* opt) {
+    // Program groups of about 1536 core instructions when the programs read at most 12 features, else 4096 (2048
+    // where features lie in LDS): every wave loads the features of its tile before it runs its group, and a longer
+    // group spreads those loads over more instructions; a block's rows, too, are computed for all its groups.
+    // Measured on the 4096-program workloads (1024, 1536, 2048, 4096): 8-feature trees 6.34, 6.29, 6.29, 6.4 ms
+    // (sin/cos/exp/log) and 587, 578, 582, 600 us (+, -, *), 9-feature classification trees 1.48, 1.47, 1.47, 1.51 ms;
+    // 16-feature linear programs 3.17, 3.16, 3.16, 3.02 ms, 20-input multiplexer trees 455, 452, 453, 449 us, and
+    // 41-feature classification trees with features in LDS 2048 against 4096: 39.5, 40.1 ms.
+    const int32_t usual = core_variant_cap(vi) > core_variant_nf(vi) ? 2048 : pd.n_load <= 12 ? 1536 : 4096;
+    const int32_t group_instr = opt && opt->group_instr > 0 ? opt->group_instr : env_int("GP2D_GROUP_INSTR", usual);
     // (the end of a program takes about as long as four instructions)
     const int64_t G = (pd.n_instr + 4 * (int64_t)pd.n_prog + group_instr - 1) / group_instr;
-    return (int32_t)std::max<int64_t>(1, std::min<int64_t>(G, pd.n_prog));
+    // (whole blocks: 836 trees x 200000 cases, 20 groups of eight waves' blocks 2.68 ms, 16 or 24 groups 1.98)
+    const int64_t W = core_variant_waves(vi);
+    return (int32_t)std::max<int64_t>(1, std::min<int64_t>(W * ((G + W / 2) / W + (G < W / 2)), pd.n_prog));
 }
 
 // An estimate of how long `blocks` blocks a tile take, in the time of one
@@ -623,7 +625,7 @@ static LaunchShape launch_shape(const ProgData& pd, int vi, int32_t tiles, const
     const int32_t target_blocks = (int32_t)((4 * (int64_t)(forced > 0 ? forced : 4096) + W - 1) / W);
     LaunchShape L;
     L.est = 0.0;
-    int64_t G = base_groups(pd, opt);
+    int64_t G = base_groups(pd, vi, opt);
     if (force_G <= 0 && ((G + W - 1) / W) * tiles < target_blocks) {
         const int64_t most = (pd.n_prog + W - 1) / W;
         int64_t best = (G + W - 1) / W;
@@ -688,7 +690,7 @@ hipError_t timed_launch_end(hipStream_t s, int slot) {
 
 static void plan_rows_for(const ProgData& pd, int vi, RowPlan& rows) {
     const int32_t W = core_variant_waves(vi);
-    plan_rows(pd, vi, (base_groups(pd, nullptr) + W - 1) / W, rows);
+    plan_rows(pd, vi, (base_groups(pd, vi, nullptr) + W - 1) / W, rows);
 }
 
 // The translation that an evaluation takes, as a key of dps: with rows (vi) or without (vi + kNoRows).  Every block
@@ -702,7 +704,7 @@ static int translation_for(const ProgData& pd, int vi, std::map<int, DevProgs>& 
     if (fresh || !dp.uploaded) plan_rows_for(pd, vi, dp.rows);
     if (dp.rows.n() == 0) return vi;
     RowPlan none;
-    no_rows(pd, none);
+    no_rows(pd, vi, none);
     if (launch_shape(pd, vi, tiles, opt, dp.rows).est <= launch_shape(pd, vi, tiles, opt, none).est) return vi;
     if (fresh) {
         dp.rows = std::move(none);
@@ -721,7 +723,7 @@ static int translation_for(const ProgData& pd, int vi, std::map<int, DevProgs>& 
 int default_variant(const ProgData& pd) {
     if (pd.variant >= 0) return pd.variant;
     return pick_core_variant(pd.n_load, pd.max_depth, pd.n_named ? (double)pd.n_transc / pd.n_named : 0.0,
-                             pd.n_transc > 0, pd.opset == OPSET_BOOL, pd.form == FORM_TREE);
+                             pd.n_transc > 0, pd.opset == OPSET_BOOL, pd.form == FORM_TREE, true);
 }
 
 // The variant an evaluation without an explicit one launches: GP2D_VARIANT
@@ -729,9 +731,7 @@ int default_variant(const ProgData& pd) {
 // programs, else the default.
 static int tuned_variant(const ProgData& pd) {
     const int32_t ev = env_int("GP2D_VARIANT", 0) - 1;
-    if (ev >= 0 && ev < core_variants() && core_variant_nf(ev) >= pd.n_load && core_variant_d(ev) >= pd.max_depth &&
-        !(core_variant_arith(ev) && pd.n_transc > 0) && core_variant_bool(ev) == (pd.opset == OPSET_BOOL) &&
-        !(core_variant_trees_only(ev) && pd.form != FORM_TREE))
+    if (ev >= 0 && ev < core_variants() && core_variant_fits(ev, pd))
         return ev;
     return default_variant(pd);
 }
@@ -757,9 +757,7 @@ gp_status eval_core(const ProgData& pd, std::map<int, DevProgs>& dps, bool fresh
                                             : tuned_variant(pd);
     if (vi < 0 || vi >= core_variants())
         return fail(GP_E_DEPTH, "no kernel variant for %d features and depth %d", pd.n_load, pd.max_depth);
-    if (core_variant_nf(vi) < pd.n_load || core_variant_d(vi) < pd.max_depth ||
-        (core_variant_arith(vi) && pd.n_transc > 0) || core_variant_bool(vi) != boolean ||
-        (core_variant_trees_only(vi) && pd.form != FORM_TREE))
+    if (!core_variant_fits(vi, pd))
         return fail(GP_E_INVAL, "variant %d cannot hold these programs", vi);
     const bool no_alloc = opt && opt->no_alloc;
     gp_status st;
@@ -816,7 +814,7 @@ gp_status eval_core(const ProgData& pd, std::map<int, DevProgs>& dps, bool fresh
     a.X = X;
     a.y = kind == GP_OUT_CASES ? nullptr : y;
     a.N = N;
-    a.n_load = pd.n_load;
+    a.n_load = std::min(pd.n_load, core_variant_nf(vi));
     a.kind = kind;
     a.tiles = tiles;
     a.n_units = (int32_t)units;
@@ -961,7 +959,7 @@ static gp_status progset_finish(ProgData&& pd, void* stream, gp_progset** ps) {
         if ((st = core_ready(vi, s)) != GP_OK) return st;
         Workspace& w = workspace(s);
         std::lock_guard<std::mutex> g(w.mu);
-        p->groups = base_groups(p->pd, nullptr);
+        p->groups = base_groups(p->pd, vi, nullptr);
         plan_rows_for(p->pd, vi, p->dps[vi].rows);
         if ((st = prepare_programs(p->pd, vi, p->dps[vi], false, p->groups, s, w, nullptr)) != GP_OK)
             return st;

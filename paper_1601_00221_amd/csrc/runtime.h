@@ -107,12 +107,14 @@ struct ProgData {
 // all its programs (ring cores with those functions).
 struct RowPlan {
     std::vector<int32_t> row;      // by function and feature: the row, or -1
-    std::vector<uint32_t> op;      // of each row
+    std::vector<uint32_t> op;      // of each row: GP_SIN .. GP_PLOG, or OP_PUSH: the feature itself
     std::vector<int32_t> feat;
     std::vector<uint32_t> rec;     // first record of each wave's share of the rows' programs, and the end
     std::vector<uint32_t> cost;    // of each program, its rows read instead of computed
     double total = 0.0;            // of all of them
+    int32_t first_lds = 0;         // the first rows are the features from here on, on cores that hold them in LDS
     int32_t n() const { return (int32_t)op.size(); }
+    int32_t feature(int f) const { return f - first_lds; }
     uint32_t longest = 0;          // the largest of them
     void sum() {
         total = 0.0;
@@ -227,6 +229,6 @@ gp_status progset_eval_no_alloc(gp_progset* ps, const float* X, int32_t n_feat, 
                                 int32_t kind, void* out, hipStream_t s, double* partials, size_t partials_bytes);
 // Program groups of a launch of variant vi over plentiful case tiles (the
 // layout a program set uploads when it is created).
-int32_t base_groups(const ProgData& pd, const EvalOptions* opt);
+int32_t base_groups(const ProgData& pd, int vi, const EvalOptions* opt);
 
 }  // namespace gpx

@@ -690,3 +690,53 @@ def test_rows_are_computed_and_pushed(vi):
     out[:] = np.nan
     emu.run(dict(s, **{}) | {56: 16 * n_own, 57: 16 * n_own})     # no programs of its own
     assert np.isnan(out).all()
+
+
+@pytest.mark.parametrize("vi", [i for i in REAL if ALL[i] in gen_core.WIDE])
+@pytest.mark.parametrize("N", [1, 64, 200, 256])
+def test_features_in_lds(vi, N):
+    """A unit whose features lie in LDS beyond those in registers: the programs of the rows load them (nothing is read
+    past the data), as they are and as operands of functions, and the wave's own programs push them."""
+    T, D, NF, NCV, mode = ALL[vi]
+    emu = BlockEmu(vi)
+    tag, V0, FO, hs, _ = gen_core.gen_variant(T, D, NF, NCV, mode, True)
+    K, ph = gen_core.K, gen_core.RING_PHASE
+    slot = {(h.kind, h.op, h.p1, h.p2): emu.table + h.slot * gen_core.RING_SLOT for h in hs}
+    base = gen_core.rows_base(T, D, NF, NCV, mode)
+
+    def records(*items):
+        out, k = [], 0
+        for kind, op, p1, pay, cst in items:
+            a = slot[(K[kind] | (k << ph), op, p1, 0)]
+            out.append((a & M32, a >> 32, pay, cst))
+            k = 0 if kind == "EXIT" else (k + 1) & 3
+        return out
+    F = NF + 3
+    load = lambda f: ("EXIT", 0, 0, 14 << 24 | f, 0)   # noqa: E731
+    end = lambda r, n: ("EXIT", 0, 0, 15 << 24 | n, r)   # noqa: E731
+    own = [records(("PUSHR", 0, 0, 0, 0), ("PUSHR", 0, 1, 256 * T, 0), ("SS", 1, 0, 0, 0), ("PUSHR", 0, 1, 512 * T, 0),
+                   ("SS", 2, 0, 0, 0), ("SX", 0, 0, FO, 0), end(0, 0))]
+    derived = [records(load(F - 1), end(0, 2)), records(load(NF), end(1, 3)),
+               records(load(F - 2), ("EXIT", 0, 0, 4 << 24, 0), end(2, 0))]
+    code = sum(own, []) + sum(derived, [])
+    words = np.array(code + [(0, 0, 0, 0)] * 8, np.uint64).astype(np.uint32).reshape(-1)
+    X = synth.uniform_cases(synth.rng_for(70 + vi), F, N, -2, 2)
+    out = np.full((1, N), np.nan, np.float32)
+    tab, coef = tables()
+    emu.lds[:] = 0xA5
+    emu.lds[:8 * len(tab)] = tab.view(np.uint8)
+    emu.lds_used = base + 256 * T * 3
+    for b, arr in ((CODE, words), (XBASE, X), (YBASE, np.zeros(N, np.float32)), (CASES, out), (COEF, coef),
+                   (PART, np.zeros((1, 1)))):
+        emu.region(b, arr)
+    s = {63: 0, 62: 16 * len(own[0]), 78: 14, 86: NF, 87: N, 92: 8, 93: gen_core.TO_ROW, 96: 16 * len(code), 97: 8 * len(tab),
+         56: 0, 57: 16 * len(own[0]), 98: KIND["cases"]}
+    for r, val in ((60, CODE), (82, XBASE), (84, 4 * N), (88, YBASE), (90, PART), (94, CASES), (100, COEF)):
+        s[r], s[r + 1] = val & M32, val >> 32
+    emu.run(s)
+    sin = np.array([oracle.apply(4, v) for v in X[F - 2]], np.float32)
+    prod = ((X[F - 1] - X[NF]) * sin).astype(np.float32)
+    want = (prod + X[0]).astype(np.float32)
+    # the sine may be off by a unit of its last place, the product by two then, and the sum is rounded once more
+    assert (np.abs(out[0] - want) <= 2 * np.spacing(np.abs(prod)) + np.spacing(np.abs(want))).all()
+    assert (emu.lds[emu.lds_used:] == 0xA5).all()
