@@ -252,7 +252,7 @@ typedef struct {
     int32_t form;              /* 0 = tree, 1 = linear */
     int32_t n_feat;            /* features the programs may read */
     int32_t max_depth;         /* stack levels needed (trees) */
-    int64_t n_instr;           /* device instructions over all programs */
+    int64_t n_instr;           /* instructions over all programs: lowered trees, register programs as given */
     int64_t n_gpop;            /* GP operations per fitness case: tree nodes, or linear instructions */
     int32_t variant;           /* kernel variant gp_progset_eval launches for the set */
     int32_t pad;
@@ -358,10 +358,12 @@ gp_status gp_tune_batch(const gp_dataset* ds, int32_t n_ds, const gp_job* jobs, 
  * function set for gp_eval_bool, whose slots are 32-bit words;
  * GP_VARIANT_TREES_ONLY (with GP_VARIANT_NO_TRANSC) an arithmetic kernel for
  * trees only (no linear-program handlers), which one-shot and program-set
- * evaluations of trees prefer and batches do not use.  The variant's kernel
- * is named k_core_<t>_<depth>_<n_feat>_<vgprs>, with "_a" appended for an
- * arithmetic-only, "_at" for a trees-only and "_b" for a Boolean kernel.  Any
- * pointer may be NULL. */
+ * evaluations of trees prefer and batches do not use.  GP_VARIANT_TREES_ONLY
+ * alone is one with that code; k_core_4_9_11_48_t holds up to GP_MAX_FEAT
+ * features, those beyond its slots in LDS.  The variant's kernel is named
+ * k_core_<t>_<depth>_<n_feat>_<vgprs>, with "_a" appended for an
+ * arithmetic-only, "_at" for a trees-only, "_t" for a trees-only one with
+ * sin/cos/exp/log and "_b" for a Boolean kernel.  Any pointer may be NULL. */
 enum { GP_VARIANT_NO_TRANSC = 1, GP_VARIANT_BOOLEAN = 2, GP_VARIANT_TREES_ONLY = 4 };
 int32_t gp_num_variants(void);
 gp_status gp_variant_info(int32_t i, int32_t* t, int32_t* depth, int32_t* n_feat, int32_t* vgprs, int32_t* flags);

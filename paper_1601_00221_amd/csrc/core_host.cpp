@@ -99,9 +99,9 @@ static bool mode_no_transc(int mode) { return mode == 1 || mode == 2 || mode == 
 static constexpr int kShallowDepth = 12;
 
 int pick_core_variant(int n_load, int depth, double transc_frac, bool has_transc, bool boolean, bool trees_only, bool wide) {
-    // Programs rich in sin/cos/exp/log (binary64, evaluated by compiled code
-    // outside the core) run best with room for that code (no spills) and as
-    // many waves per SIMD as that leaves, to hide its latency; the others with
+    // Programs rich in sin/cos/exp/log (binary64) run best where two slots of
+    // them are computed side by side, and with as many waves per SIMD as that
+    // leaves, to hide the latency; the others with
     // the widest tile, on a kernel without that code if they use none of it.  Ties go to the fewest feature slots, then the fewest
     // handlers (least code).  (Measured on the 4096 x 65,536 tree workloads.)
     const bool heavy = transc_frac > 0.2;
@@ -122,7 +122,7 @@ int pick_core_variant(int n_load, int depth, double transc_frac, bool has_transc
     };
     // Boolean programs: the most slots in flight per SIMD (waves x tile width); ties go to more waves (they
     // hide the dispatch chain of the one-instruction handlers: measured 5 % on the 20-multiplexer), then to
-    // more VGPRs for the compiled code, then to fewer feature slots
+    // fewer feature slots
     auto score_bool = [&](const CoreVariantDesc& v) {
         return waves(v) * v.t * 100000 + waves(v) * 1000 + v.ncv * 10 - v.nf;
     };

@@ -59,7 +59,7 @@ struct CoreArgs {
     const JobDesc* jobs;
     const DatasetDesc* datasets;
     uint32_t* counter;          // next unit, persistent form
-    // implicit units: block unit b = (group quad b div chunks, chunk b mod
+    // implicit units: block unit b = (the W groups from W (b div chunks) on, chunk b mod
     // chunks); a chunk is tiles_per_wave consecutive tiles
     const uint32_t* group_off;  // group g holds the core records group_off[g] .. group_off[g + 1)
     const float* X;

@@ -2,9 +2,9 @@
 
     python gen_core.py OUT_DIR
 
-Writes ``core_gen.inc``: for every kernel variant (T case slots per lane, D
-stack levels, NF feature slots) one inline-asm interpreter loop plus the
-host-side table naming its handlers.
+Writes ``core_gen.inc`` (the tables that name every variant's handlers), one
+``core_v_*.hip`` a kernel variant (T case slots per lane, D stack levels, NF
+feature slots) with its inline-asm block, and ``core_dispatch.inc``.
 
 Design.  The whole two-dimensional stack (level l, slot j), the registers of
 a linear program and the wave's case tile live in a VGPR range the compiler
@@ -24,24 +24,34 @@ A program is a list of 16-byte instructions
                for an exit: A, B, destination offsets and the operation)
     dword 3    constant operand (binary32 bits)
 
-A handler loads the next instruction with one scalar load, executes its own
-T vector instructions with the wave-uniform operand offset applied through
-the gfx9 VGPR index mode (one index per instruction; the other operands of
-the handler are fixed registers, so handlers are specialised on stack level
-or register number), waits for the load and jumps to the next handler's
-address.  Every lane runs the same program, so the jump is uniform.
-Protected division and the classification functions have handlers of
-their own that read their operands at any offsets.  Work the core does not
-do itself (sin/cos/exp/log, the end of a program) leaves the asm block
-through the exit handler with the instruction's payload; the compiled
-kernel does it and re-enters.
+A handler executes its own T vector instructions with the wave-uniform
+operand offset applied through the gfx9 VGPR index mode (one index per
+instruction; the other operands of the handler are fixed registers, so
+handlers are specialised on stack level or register number) and jumps to the
+next handler's address.  Every lane runs the same program, so the jump is
+uniform.  Records are loaded ahead: two at a time by pair cores, whose
+handlers come in two phases; in ring cores four lie in s[b:b+15], handlers
+come in four phases, and each waits only for the pair that was requested two
+instructions before.
 
-Fixed SGPRs used by the block: s[60:61] code base, s62 byte offset of the
-current instruction, s63 probe flag, s[64:71] the current and next
-instruction records, s72-s74 and s79 a constant copy and index temporaries,
-s[80:81] the division threshold or a compare's mask, vcc flags, s75 the
-end of the program's code and s78 the loads in flight for its burst load
-into the scalar cache, s[76:77] table address (probe).
+The block runs a whole unit.  It loads the tile (features into VGPRs, targets
+into LDS), computes the block's share of the tile's rows, and runs the unit's
+programs one after another: protected division and the classification
+functions in handlers of their own, sin/cos/exp/log in the block's tail
+(transc), and at the end of a program, which is an exit with operation 15,
+the fitness terms and their sum over the wave (program_end), while the next
+program's first records and code lines are already under way.
+
+SGPRs used by the block: s[60:61] code base, s62 byte offset of the record
+loaded next, s63 probe flag, s[64:71] the records of pair cores, s[36:51] or
+s[8:23] those of ring cores (ring_base), s[66:67] an exit's payload and
+constant, s72-s77, s79-s81 temporaries (s[76:77] also the return of a shared
+body and, when probed, the table's address), s78 code lines fetched at a time,
+s[58:59] and s99 the lines still to fetch, s[82:85] X and its stride, s86
+features, s87 cases left in the tile, s[88:95] y, partials, their stride and
+the outputs, s93 the fitness kind, s96 the end of the unit's records, s97 the
+targets in LDS, s98 bits left (Boolean) or the kind after the rows, s56 and
+s57 the wave's own records meanwhile, s[24:55] and s[100:101] coefficients.
 """
 import os
 import sys
@@ -52,14 +62,13 @@ LIN_REGS = 8              # register slots reserved for linear programs (and sta
 # (T, D, NF, NCV, MODE) variants: T case slots per lane, D stack levels, NF
 # feature slots, NCV VGPRs left to the compiler (the core owns v[NCV ...]),
 # MODE = 0 for the arithmetic function set with the sin/cos/exp/log code,
-# 1 without that code (for programs that use none; its compiled part is
-# small, so nothing spills), 2 for the Boolean function set (slots are
+# 1 without that code (for programs that use none), 2 for the Boolean function set (slots are
 # 32-bit words of bit-packed cases), 3 like 1 for trees only (no linear
 # handlers or registers: a handler table half the size, and the stack
 # levels start the VGPR range), 4 like 0 for trees only (the core of mode
-# 3 with the sin/cos/exp/log code: room for many feature slots).  Work that
-# leaves the core (sin/cos/exp/log in binary64) runs in the compiler's VGPRs:
-# programs rich in it take a variant with room for it.
+# 3 with the sin/cos/exp/log code).  sin/cos/exp/log (binary64) run in the
+# registers below the core's: from 48 on two slots side by side, from 64 on
+# with the constants kept.
 VARIANTS = [
     (8, 6, 8, 40, 0),
     (8, 6, 8, 128, 0),

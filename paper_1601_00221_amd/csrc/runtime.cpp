@@ -262,10 +262,9 @@ void parallel_for(int64_t n, const std::function<void(int64_t, int64_t)>& fn) {
 // ---------------------------------------------------------------------------
 // Relative cost of one instruction, used only to balance program groups:
 // the vector instructions it issues per slot, plus one for its dispatch.
-// Protected division (about 15 per slot), the compares, IF and AND/OR (a
-// compare or two and a select) run in the core; sin/cos/exp/log are exits to
-// binary64 code of some 34 (sin, cos) or 24 (exp, log) per value.  Every
-// Boolean function is one bitwise instruction per slot.
+// Protected division takes 13 to 15 a slot, the compares, IF and AND/OR a
+// compare or two and a select, sin and cos some 34, exp and log 24 (binary64).
+// Every Boolean function is one bitwise instruction per slot.
 static uint32_t op_cost(uint32_t op, int opset) {
     if (opset == OPSET_BOOL) return 2;
     switch (op) {
