@@ -544,9 +544,11 @@ static gp_status prepare_programs(const ProgData& pd, int vi, DevProgs& dp, bool
 
 // Launch shape of one evaluation.  Programs are cut into G groups; each block
 // runs W groups (one per wave) on a chunk of tiles_per_wave tiles.  With tiles
-// enough for the chip a group holds about `group_instr` core instructions;
-// chunks lengthen only while four times the waves of 4096 blocks of four
-// remain.  With fewer tiles the programs are cut into more groups, by the
+// enough for the chip a group holds about `group_instr` core instructions.  A
+// block takes one tile (two or more were no faster anywhere: 1, 2, 4 tiles took
+// 38.2, 38.5, 39.2 ms on 41-feature classification trees x 494021 cases, 6.30,
+// 6.40, 7.04 ms on 8-feature trees x 65536), until there are 2^24 blocks.  With
+// fewer tiles the programs are cut into more groups, by the
 // estimate below.  (Cutting them until there were those 4096 blocks had waves
 // of one or two programs that mostly loaded their tile: the estimate takes
 // 158 -> 109 us for 100 programs of up to 512 nodes x 30000 cases, 235 -> 160
@@ -576,14 +578,16 @@ int32_t code_prefetch() {
 
 // Groups of a launch with tiles enough for them.
 int32_t base_groups(const ProgData& pd, int vi, const EvalOptions* opt) {
-    // Program groups of about 1536 core instructions when the programs read at most 12 features, else 4096 (2048
-    // where features lie in LDS): every wave loads the features of its tile before it runs its group, and a longer
+    // Program groups of about 1536 core instructions when the programs read at most 12 features, else 6144 (4096 of
+    // Boolean programs, 2048 where features lie in LDS): every wave loads the features of its tile before it runs its group, and a longer
     // group spreads those loads over more instructions; a block's rows, too, are computed for all its groups.
     // Measured on the 4096-program workloads (1024, 1536, 2048, 4096): 8-feature trees 6.34, 6.29, 6.29, 6.4 ms
     // (sin/cos/exp/log) and 587, 578, 582, 600 us (+, -, *), 9-feature classification trees 1.48, 1.47, 1.47, 1.51 ms;
-    // 16-feature linear programs 3.17, 3.16, 3.16, 3.02 ms, 20-input multiplexer trees 455, 452, 453, 449 us, and
+    // 16-feature linear programs 3.17, 3.16, 3.16, 3.02 ms (2.96 with 6144), 16-feature classification trees without
+    // sin/cos/exp/log 1.61 and 1.58 ms (4096, 6144), 20-input multiplexer trees 455, 452, 453, 449 us, and
     // 41-feature classification trees with features in LDS 2048 against 4096: 39.5, 40.1 ms.
-    const int32_t usual = core_variant_cap(vi) > core_variant_nf(vi) ? 2048 : pd.n_load <= 12 ? 1536 : 4096;
+    const int32_t usual = core_variant_cap(vi) > core_variant_nf(vi) ? 2048
+                          : pd.n_load <= 12 ? 1536 : pd.opset == OPSET_BOOL ? 4096 : 6144;
     const int32_t group_instr = opt && opt->group_instr > 0 ? opt->group_instr : env_int("GP2D_GROUP_INSTR", usual);
     // (the end of a program takes about as long as four instructions)
     const int64_t G = (pd.n_instr + 4 * (int64_t)pd.n_prog + group_instr - 1) / group_instr;
@@ -630,11 +634,16 @@ static LaunchShape launch_shape(const ProgData& pd, int vi, int32_t tiles, const
         int64_t best = (G + W - 1) / W;
         if (forced > 0) {
             best = (target_blocks + tiles - 1) / tiles;
+        } else if (rows.shape.tiles == tiles && rows.shape.base == G) {
+            best = rows.shape.blocks;
+            L.est = rows.shape.est;
         } else {
+            const int64_t base = G;
             for (int64_t b = best; b <= most; b += std::max<int64_t>(1, b / 16)) {
                 const double t = launch_time(pd, vi, tiles, 1, b, rows);
                 if (L.est == 0.0 || t < L.est) L.est = t, best = b;
             }
+            rows.shape = {tiles, base, best, L.est};
         }
         G = std::min<int64_t>(best * W, pd.n_prog);
     }
@@ -643,7 +652,7 @@ static LaunchShape launch_shape(const ProgData& pd, int vi, int32_t tiles, const
     int32_t tpw = opt && opt->tiles_per_wave > 0 ? opt->tiles_per_wave : env_int("GP2D_TILES_PER_WAVE", 0);
     if (tpw <= 0) {
         tpw = 1;
-        while (tpw < 16 && quads * ((tiles + 2 * tpw - 1) / (2 * tpw)) >= 4 * (int64_t)target_blocks) tpw *= 2;
+        while (tpw < 16 && quads * ((tiles + tpw - 1) / tpw) >= (1 << 24)) tpw *= 2;
     }
     L.G = (int32_t)G;
     L.tiles_per_wave = tpw;
@@ -702,19 +711,21 @@ static int translation_for(const ProgData& pd, int vi, std::map<int, DevProgs>& 
     DevProgs& dp = dps[vi];
     if (fresh || !dp.uploaded) plan_rows_for(pd, vi, dp.rows);
     if (dp.rows.n() == 0) return vi;
-    RowPlan none;
-    no_rows(pd, vi, none);
-    if (launch_shape(pd, vi, tiles, opt, dp.rows).est <= launch_shape(pd, vi, tiles, opt, none).est) return vi;
     if (fresh) {
-        dp.rows = std::move(none);
+        RowPlan none;
+        no_rows(pd, vi, none);
+        if (launch_shape(pd, vi, tiles, opt, dp.rows).est > launch_shape(pd, vi, tiles, opt, none).est) dp.rows = std::move(none);
         return vi;
     }
     DevProgs& plain = dps[vi + kNoRows];
+    if (plain.rows.cost.empty()) no_rows(pd, vi, plain.rows);
+    if (launch_shape(pd, vi, tiles, opt, dp.rows).est <= launch_shape(pd, vi, tiles, opt, plain.rows).est) return vi;
     if (!plain.uploaded) {
-        // (made on its first use, but not while the stream is being captured)
+        // made when it is wanted for the fourth time (some 100 us, against 5 to 40 a call that it saves), and not while
+        // the stream is being captured
         hipStreamCaptureStatus cap = hipStreamCaptureStatusActive;
-        if (hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) return vi;
-        plain.rows = std::move(none);
+        if (++plain.wanted < 4 || hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone)
+            return vi;
     }
     return vi + kNoRows;
 }

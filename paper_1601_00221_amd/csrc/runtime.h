@@ -113,6 +113,9 @@ struct RowPlan {
     std::vector<uint32_t> cost;    // of each program, its rows read instead of computed
     double total = 0.0;            // of all of them
     int32_t first_lds = 0;         // the first rows are the features from here on, on cores that hold them in LDS
+    // The number of blocks a tile found best for the last number of tiles (and of groups to begin with): the search
+    // for it takes some 2 us.  Written under the lock of the programs it belongs to.
+    mutable struct { int32_t tiles = -1; int64_t base = 0, blocks = 0; double est = 0.0; } shape;
     int32_t n() const { return (int32_t)op.size(); }
     int32_t feature(int f) const { return f - first_lds; }
     uint32_t longest = 0;          // the largest of them
@@ -132,6 +135,7 @@ struct RowPlan {
 // on any stream waits for it.
 struct DevProgs {
     bool uploaded = false;
+    int32_t wanted = 0;            // evaluations that would have taken it before it was made (runtime.cpp, translation_for)
     DevBuf code;
     std::vector<uint32_t> order;   // programs in the order of the code (host)
     std::vector<int64_t> rec;      // first record of each, in that order, and the end (host)
