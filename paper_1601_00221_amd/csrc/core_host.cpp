@@ -609,10 +609,10 @@ static gp_status translate_with(const ProgData& pd, int vi, const VariantMap& m,
         return linear_records(pd.code.data() + src.code_off, src.len, src.live);
     };
     for (int32_t i = 0; i < P; i++) start[i + 1] = start[i] + records(at(i));
-    if (start[P] * 16 > 0xFFFFFFF0ll) return fail(GP_E_INVAL, "programs exceed 4 GiB of core code");
+    const int32_t R = rows ? rows->n() : 0;
+    if ((start[P] + 3 * R) * 16 > 0xFFFFFFF0ll) return fail(GP_E_INVAL, "programs exceed 4 GiB of core code");
     // the core reads records two or four at a time, ahead of the one it runs: up
     // to seven past a program's last one, so the code ends with padding
-    const int32_t R = rows ? rows->n() : 0;
     code.resize((size_t)(start[P] + 3 * R) * 4 + kCodePadding);
     std::fill(code.begin() + 4 * start[P], code.end(), 0u);
     if (rows) {
