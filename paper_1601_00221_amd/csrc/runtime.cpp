@@ -471,6 +471,21 @@ void cut_groups(const std::vector<uint32_t>& cost, const std::vector<uint32_t>& 
     }
 }
 
+// Whether an event has passed.  Not asked while s is being captured (that
+// would end the capture), and asked in the relaxed capture mode: a query in
+// the default mode is refused while any thread captures a stream in the global
+// mode, and ends that capture.
+static bool has_passed(hipEvent_t ev, hipStream_t s) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusActive;
+    if (hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) return false;
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) return false;
+    const hipError_t q = hipEventQuery(ev);
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    if (q != hipSuccess) (void)hipGetLastError();   // "not yet" is no error: it must not be taken for a launch's
+    return q == hipSuccess;
+}
+
 // Translate and upload the programs for variant vi (when `fresh` or not yet
 // uploaded; dp.rows is planned) and the group layout for G groups (when not cached), all in one
 // staging pass on stream s, then record dp.ready on s.  One-shot calls
@@ -483,14 +498,8 @@ static gp_status prepare_programs(const ProgData& pd, int vi, DevProgs& dp, bool
     gp_status st;
     const bool upload = fresh || !dp.uploaded;
     if (!upload && dp.ready && !dp.settled) {
-        // Uploaded earlier, possibly on another stream: order this launch after it, unless it has passed (not asked
-        // while the stream is being captured: that would end the capture).
-        hipStreamCaptureStatus cap = hipStreamCaptureStatusActive;
-        if (hipStreamIsCapturing(s, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone) {
-            const hipError_t q = hipEventQuery(dp.ready);
-            dp.settled = q == hipSuccess;
-            if (q == hipErrorNotReady) (void)hipGetLastError();   // no error: it must not be taken for a launch's
-        }
+        // Uploaded earlier, possibly on another stream: order this launch after it, unless it has passed.
+        dp.settled = has_passed(dp.ready, s);
         if (!dp.settled) {
             hipError_t e = hipStreamWaitEvent(s, dp.ready, 0);
             if (e != hipSuccess) return fail(GP_E_DEVICE, "hipStreamWaitEvent: %s", hipGetErrorString(e));
