@@ -514,6 +514,7 @@ static gp_status prepare_programs(const ProgData& pd, int vi, DevProgs& dp, bool
         const DevProg& last = progs[dp.order[pd.n_prog - 1]];
         dp.rec[pd.n_prog] = last.code_off / 4 + last.len;
     }
+    DevBuf made;   // a new layout of a program set: kept once it has been uploaded
     DevBuf* gb = nullptr;
     if (fresh) {
         gb = &dp.groups_once;
@@ -528,7 +529,7 @@ static gp_status prepare_programs(const ProgData& pd, int vi, DevProgs& dp, bool
         g.insert(g.end(), dp.rows.rec.begin(), dp.rows.rec.end());
         g.insert(g.end(), gprog.begin(), gprog.end());
         g.insert(g.end(), dp.order.begin(), dp.order.end());
-        if (!fresh) gb = &dp.groups_by_G[G];
+        if (!fresh) gb = &made;
         if ((st = gb->reserve(g.size() * 4)) != GP_OK) return st;
     }
     if (upload || new_groups) {
@@ -546,6 +547,7 @@ static gp_status prepare_programs(const ProgData& pd, int vi, DevProgs& dp, bool
         if (e != hipSuccess) return fail(GP_E_DEVICE, "hipEventRecord: %s", hipGetErrorString(e));
         dp.uploaded = true;
         dp.settled = false;
+        if (gb == &made) gb = &(dp.groups_by_G[G] = std::move(made));
     }
     if (goff) *goff = gb ? (const uint32_t*)gb->p : nullptr;
     return GP_OK;

@@ -1,0 +1,79 @@
+"""Scenarios of the library's host runtime, on a HIP runtime of host memory
+(fake_hip.cpp).
+
+    python host_scenarios.py LIBGP SCENARIO [ARGUMENT ...]
+
+Started by tests/test_host_runtime.py, one process a scenario; the last line
+is "ok" if every check held."""
+import ctypes as C
+import os
+import sys
+
+import numpy as np
+
+ROOT = os.path.dirname(os.path.dirname(os.path.dirname(os.path.abspath(__file__))))
+sys.path.insert(0, ROOT)
+
+import paper_1601_00221_amd as gp  # noqa: E402
+import synth                       # noqa: E402
+
+gp.LIB_PATH = sys.argv[1]
+gp.stream_ptr = lambda stream=None: None   # the null stream
+LAUNCHES, ROWS, GROUPS, VARIANT, TABLE, BAD_LAYOUTS, UPLOADS = range(7)
+
+
+def fake(what):
+    return gp.lib().fake_int(what)
+
+
+class Array:
+    """Stands for a device tensor: a numpy array the fake runtime takes as device memory."""
+
+    def __init__(self, a):
+        self.a, self.shape = np.ascontiguousarray(a), a.shape
+
+    def data_ptr(self):
+        return self.a.ctypes.data
+
+
+def tree_set(rng, P, F, fset):
+    pop = synth.ptc2_population(rng, P, fset, F, 1, 60, 0.1)
+    return gp.ProgSet.tree(pop.tok, pop.cst, pop.off, F)
+
+
+def evaluate(ps, X, y, out, N):
+    gp.check(gp.lib().gp_progset_eval(ps._h, X.data_ptr(), X.shape[0], N, y.data_ptr(), gp.kind_id("sum_abs"),
+                                      out.data_ptr(), None))
+
+
+def failed_allocation_leaves_no_layout():
+    """An evaluation whose k-th allocation fails reports it and launches nothing; the next one uploads what is missing
+    and launches with a whole layout."""
+    rng = synth.rng_for(5)
+    F, P, N = 16, 700, 3000
+    X, y, out = Array(np.zeros((F, N), np.float32)), Array(np.zeros(N, np.float32)), Array(np.zeros(P, np.float32))
+    failures = 0
+    for k in range(1, 12):
+        ps = tree_set(rng, P, F, synth.FULL)
+        launched = fake(LAUNCHES)
+        gp.lib().fake_fail_malloc(k)
+        try:
+            evaluate(ps, X, y, out, N)
+            assert fake(LAUNCHES) == launched + 1
+        except gp.GPError as e:
+            assert e.status == -2, e
+            assert fake(LAUNCHES) == launched
+            failures += 1
+        gp.lib().fake_fail_malloc(0)
+        for _ in range(6):
+            evaluate(ps, X, y, out, N)
+            assert fake(BAD_LAYOUTS) == 0, (k, fake(BAD_LAYOUTS))
+        ps.close()
+    assert failures > 0
+
+
+SCENARIOS = {f.__name__: f for f in (failed_allocation_leaves_no_layout,)}
+
+if __name__ == "__main__":
+    SCENARIOS[sys.argv[2]](*sys.argv[3:])
+    print("ok", flush=True)

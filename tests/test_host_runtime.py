@@ -1,0 +1,63 @@
+"""The library's host runtime on a HIP runtime of host memory: what it
+uploads, which layouts and kernels it launches with, and what a failing
+allocation leaves behind, with the address and undefined-behaviour sanitizers
+on (no device; scenarios in native/host_scenarios.py)."""
+import concurrent.futures as cf
+import os
+import subprocess
+import sys
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+CSRC = os.path.join(ROOT, "paper_1601_00221_amd", "csrc")
+SOURCES = [os.path.join(CSRC, s) for s in
+           ("lower.cpp", "runtime.cpp", "batch.cpp", "serve.cpp", "core_host.cpp", "evolve.cpp", "blockgp.cpp")]
+SOURCES.append(os.path.join(HERE, "native", "fake_hip.cpp"))
+SAN = ["-fsanitize=address,undefined", "-fno-sanitize-recover=undefined", "-fno-omit-frame-pointer"]
+
+
+def _runtime(name):
+    p = subprocess.run(["gcc", "-print-file-name=" + name], capture_output=True, text=True).stdout.strip()
+    return p if os.path.isabs(p) and os.path.exists(p) else None
+
+
+pytestmark = pytest.mark.skipif(not os.path.exists("/opt/rocm/include/hip/hip_runtime_api.h") or
+                                _runtime("libasan.so") is None,
+                                reason="needs the HIP headers and the gcc sanitizer runtimes")
+
+
+@pytest.fixture(scope="module")
+def library(tmp_path_factory):
+    d = tmp_path_factory.mktemp("host_runtime")
+    sys.path.insert(0, CSRC)
+    import gen_core
+    gen_core.main(str(d / "gen"))
+    flags = ["-std=c++17", "-O1", "-g", "-fPIC", "-D__HIP_PLATFORM_AMD__", "-D__device__=", "-D__forceinline__=inline",
+             "-I/opt/rocm/include", "-I%s" % (d / "gen"), "-I" + CSRC, "-I" + os.path.join(ROOT, "include")] + SAN
+
+    def compile_one(src):
+        o = str(d / (os.path.basename(src) + ".o"))
+        subprocess.run(["g++", *flags, "-c", src, "-o", o], check=True)
+        return o
+    with cf.ThreadPoolExecutor(max_workers=4) as ex:
+        objs = list(ex.map(compile_one, SOURCES))
+    lib = str(d / "libgp_host.so")
+    subprocess.run(["g++", "-shared", "-Wl,-Bsymbolic", *SAN, "-o", lib, *objs, "-lpthread"], check=True)
+    return lib
+
+
+def run(library, scenario, *args, **env):
+    e = dict(os.environ, **env)
+    pre = [p for p in (_runtime("libasan.so"), _runtime("libubsan.so"), e.get("LD_PRELOAD")) if p]
+    e["LD_PRELOAD"] = " ".join(pre)
+    e["ASAN_OPTIONS"] = "detect_leaks=0:abort_on_error=0:exitcode=23"
+    e["UBSAN_OPTIONS"] = "halt_on_error=1:print_stacktrace=1:exitcode=24"
+    r = subprocess.run([sys.executable, os.path.join(HERE, "native", "host_scenarios.py"), library, scenario, *args],
+                       env=e, capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0 and r.stdout.strip().endswith("ok"), (r.returncode, r.stdout[-2000:], r.stderr[-4000:])
+
+
+def test_failed_allocation_leaves_no_layout(library):
+    run(library, "failed_allocation_leaves_no_layout")
