@@ -407,7 +407,7 @@ gp_status check_datasets(const gp_dataset* ds, int32_t n_ds) {
     return GP_OK;
 }
 
-gp_status build_job(const gp_job& j, const gp_dataset* ds, int32_t n_ds, ProgData& pd) {
+static gp_status begin_job(const gp_job& j, const gp_dataset* ds, int32_t n_ds, ProgData& pd, ProgBuild& b) {
     if (j.dataset < 0 || j.dataset >= n_ds) return fail(GP_E_NOTFOUND, "dataset %d does not exist", j.dataset);
     if (j.kind != GP_FIT_SUM_ABS && j.kind != GP_FIT_MSE && j.kind != GP_FIT_HITS && j.kind != GP_FIT_CLASS_ERR)
         return fail(GP_E_INVAL, "batched jobs take GP_FIT_SUM_ABS, GP_FIT_MSE, GP_FIT_HITS or GP_FIT_CLASS_ERR (got %d)",
@@ -415,16 +415,39 @@ gp_status build_job(const gp_job& j, const gp_dataset* ds, int32_t n_ds, ProgDat
     if (!j.out && j.n_prog > 0) return fail(GP_E_INVAL, "job output is null");
     if (!ds[j.dataset].y) return fail(GP_E_INVAL, "dataset %d has no targets", j.dataset);
     const int32_t F = ds[j.dataset].n_feat;
-    gp_status st;
-    if (j.form == FORM_TREE) st = build_tree(j.tok, j.tcst, j.toff, j.n_prog, F, pd);
-    else if (j.form == FORM_LINEAR)
-        st = build_linear(j.code, j.loff, j.lcst, j.lcst_off, j.n_prog, j.n_reg, F, pd);
-    else return fail(GP_E_INVAL, "unknown program form %d", j.form);
+    if (j.form == FORM_TREE) return b.begin_tree(j.tok, j.tcst, j.toff, j.n_prog, F, pd);
+    if (j.form == FORM_LINEAR) return b.begin_linear(j.code, j.loff, j.lcst, j.lcst_off, j.n_prog, j.n_reg, F, pd);
+    return fail(GP_E_INVAL, "unknown program form %d", j.form);
+}
+
+static gp_status finish_job(const ProgData& pd, ProgBuild& b) {
+    const gp_status st = b.finish();
     if (st != GP_OK) return st;
     if (pd.n_load > GP_MAX_FEAT)
         return fail(GP_E_INVAL, "programs read feature %d; at most %d features are supported", pd.n_load - 1,
                     GP_MAX_FEAT);
     return GP_OK;
+}
+
+gp_status build_job(const gp_job& j, const gp_dataset* ds, int32_t n_ds, ProgData& pd) {
+    ProgBuild b;
+    const gp_status st = begin_job(j, ds, n_ds, pd, b);
+    if (st != GP_OK) return st;
+    parallel_for(b.n(), [&](int64_t p0, int64_t p1) { b.lower(p0, p1); });
+    return finish_job(pd, b);
+}
+
+// Calls fn(part, first, end) for the parts of [p0, p1) that lie in each of
+// consecutive ranges; range k is [start[k], start[k + 1]).
+template <typename Fn>
+static void each_part(const std::vector<int64_t>& start, int64_t p0, int64_t p1, Fn&& fn) {
+    size_t k = (size_t)(std::upper_bound(start.begin(), start.end(), p0) - start.begin()) - 1;
+    while (p0 < p1) {
+        const int64_t e = std::min(p1, start[k + 1]);
+        if (p0 < e) fn(k, p0 - start[k], e - start[k]);
+        p0 = e;
+        k++;
+    }
 }
 
 }  // namespace gpx
@@ -452,14 +475,28 @@ gp_status intake(const gp_dataset* ds, int32_t n_ds, const gp_job* jobs, int32_t
     gp_status st = check_datasets(ds, n_ds);
     if (st != GP_OK) return st;
     if (n_jobs < 0 || (n_jobs > 0 && !jobs)) return fail(GP_E_INVAL, "bad job array");
+    // The jobs' programs are lowered in one walk of the host threads (a call with 40 jobs of 250 programs took 5.4 ms of
+    // host time with a walk a job, 4.0 so).  The first job that is wrong is the one reported: its arrays (number `begun`)
+    // or one of its programs.
     pds.resize(n_jobs);
-    for (int32_t i = 0; i < n_jobs; i++) {
-        if ((st = build_job(jobs[i], ds, n_ds, pds[i])) != GP_OK) {
-            char msg[512];
+    std::vector<ProgBuild> builds(n_jobs);
+    std::vector<int64_t> start(1, 0);
+    int32_t begun = 0;
+    while (begun < n_jobs && (st = begin_job(jobs[begun], ds, n_ds, pds[begun], builds[begun])) == GP_OK)
+        start.push_back(start.back() + builds[begun++].n());
+    char msg[512];
+    snprintf(msg, sizeof msg, "%s", st == GP_OK ? "" : last_error());
+    parallel_for(start.back(), [&](int64_t p0, int64_t p1) {
+        each_part(start, p0, p1, [&](size_t k, int64_t a, int64_t b) { builds[k].lower(a, b); });
+    });
+    for (int32_t i = 0; i < begun; i++) {
+        const gp_status done = finish_job(pds[i], builds[i]);
+        if (done != GP_OK) {
             snprintf(msg, sizeof msg, "%s", last_error());
-            return fail(st, "job %d: %s", i, msg);
+            return fail(done, "job %d: %s", i, msg);
         }
     }
+    if (st != GP_OK) return fail(st, "job %d: %s", begun, msg);
     for (int32_t i = 0; i < n_jobs; i++) {
         if (pds[i].n_prog == 0) continue;
         refs.push_back(BatchJobRef{&pds[i], jobs[i].dataset, jobs[i].kind, jobs[i].out});
@@ -470,7 +507,7 @@ gp_status intake(const gp_dataset* ds, int32_t n_ds, const gp_job* jobs, int32_t
 
 // Jobs that share form, table, fitness kind and registers, as one population.
 struct MergedSet {
-    std::vector<int32_t> jobs;
+    const BatchJobRef* job;                // the first of them
     std::vector<EvalSegment> segments;
     ProgData pd;
 };
@@ -484,118 +521,105 @@ struct MergedSet {
 // 128 ms a call all in one launch, 95 ms by sets.
 constexpr double kMergedWork = 2e9;
 
-// Sort the jobs of a batch into such sets and build their programs.  False:
-// something is wrong with a job (intake then says what), or no set is large.
-bool merge_jobs(const gp_dataset* ds, int32_t n_ds, const gp_job* jobs, int32_t n_jobs, std::vector<MergedSet>& sets,
-                std::vector<int32_t>& rest) {
-    std::map<std::tuple<int32_t, int32_t, int32_t, int32_t>, std::vector<int32_t>> by;
-    for (int32_t i = 0; i < n_jobs; i++) {
-        const gp_job& j = jobs[i];
-        const bool tree = j.form == FORM_TREE;
-        if (j.dataset < 0 || j.dataset >= n_ds || (!tree && j.form != FORM_LINEAR) || j.n_prog < 0) return false;
-        if (j.n_prog == 0) {
-            rest.push_back(i);
-            continue;
-        }
-        if (j.kind != GP_FIT_SUM_ABS && j.kind != GP_FIT_MSE && j.kind != GP_FIT_HITS && j.kind != GP_FIT_CLASS_ERR)
-            return false;
-        if (!j.out || !ds[j.dataset].y || !(tree ? j.toff : j.loff) || !(tree ? (const void*)j.tok : (const void*)j.code))
-            return false;
-        by[{j.form, j.dataset, j.kind, tree ? 0 : j.n_reg}].push_back(i);
+// Lowered populations of one form, table and register count as one.  False:
+// more than its offsets reach.
+bool merge_programs(const std::vector<const ProgData*>& parts, ProgData& m) {
+    std::vector<int64_t> prog0(1, 0), word0(1, 0);
+    for (const ProgData* a : parts) {
+        prog0.push_back(prog0.back() + a->n_prog);
+        word0.push_back(word0.back() + (int64_t)a->code.size());
     }
+    if (prog0.back() > 0x7FFFFFFFll || word0.back() > 0xFFFFFFFFll) return false;
+    m = ProgData();
+    const ProgData& first = *parts[0];
+    m.form = first.form;
+    m.opset = first.opset;
+    m.n_feat = first.n_feat;
+    m.n_reg = first.n_reg;
+    m.n_prog = (int32_t)prog0.back();
+    for (const ProgData* a : parts) {
+        m.n_load = std::max(m.n_load, a->n_load);
+        m.max_depth = std::max(m.max_depth, a->max_depth);
+        m.n_instr += a->n_instr;
+        m.n_named += a->n_named;
+        m.n_gpop += a->n_gpop;
+        m.n_transc += a->n_transc;
+    }
+    m.code.resize((size_t)word0.back());
+    m.progs.resize((size_t)m.n_prog);
+    m.cost.resize((size_t)m.n_prog);
+    parallel_for(m.n_prog, [&](int64_t p0, int64_t p1) {
+        each_part(prog0, p0, p1, [&](size_t k, int64_t i0, int64_t i1) {
+            const ProgData& a = *parts[k];
+            for (int64_t i = i0; i < i1; i++) {
+                const int64_t p = prog0[k] + i;
+                DevProg d = a.progs[i];
+                const size_t w0 = d.code_off, w1 = i + 1 < a.n_prog ? a.progs[i + 1].code_off : a.code.size();
+                memcpy(m.code.data() + word0[k] + w0, a.code.data() + w0, (w1 - w0) * sizeof(uint32_t));
+                d.code_off = (uint32_t)(word0[k] + (int64_t)w0);
+                d.row = (uint64_t)p;
+                m.progs[p] = d;
+                m.cost[p] = a.cost[i];
+            }
+        });
+    });
+    return true;
+}
+
+// Sort the jobs of a batch into such sets, and the jobs of no set into `rest`.
+// False: a set cannot be built, or no kernel holds it, or there is none.
+bool merge_jobs(const std::vector<BatchJobRef>& refs, const std::vector<gp_dataset>& ds, std::vector<MergedSet>& sets,
+                std::vector<BatchJobRef>& rest) {
+    std::map<std::tuple<int32_t, int32_t, int32_t, int32_t>, std::vector<size_t>> by;
+    for (size_t i = 0; i < refs.size(); i++)
+        by[{refs[i].pd->form, refs[i].ds, refs[i].kind, refs[i].pd->n_reg}].push_back(i);
+    std::vector<size_t> left;
     for (auto& kv : by) {
-        const bool tree = std::get<0>(kv.first) == FORM_TREE;
-        const gp_dataset& d = ds[std::get<1>(kv.first)];
-        int64_t tokens = 0, progs = 0, consts = 0;
-        for (int32_t i : kv.second) {
-            const gp_job& j = jobs[i];
-            const int64_t* off = tree ? j.toff : j.loff;
-            if (off[0] != 0 || off[j.n_prog] < 0) return false;
-            tokens += off[j.n_prog];
-            progs += j.n_prog;
-            if (!tree && j.lcst_off) consts += std::max<int64_t>(0, j.lcst_off[j.n_prog]);
+        double work = 0.0;
+        int64_t progs = 0;
+        for (size_t i : kv.second) {
+            work += (double)refs[i].pd->n_gpop * (double)ds[refs[i].ds].n_cases;
+            progs += refs[i].pd->n_prog;
         }
-        if ((double)tokens * (double)d.n_cases < kMergedWork || progs > 0x7FFFFFFFll) {
-            rest.insert(rest.end(), kv.second.begin(), kv.second.end());
+        if (work < kMergedWork || progs > 0x7FFFFFFFll) {
+            left.insert(left.end(), kv.second.begin(), kv.second.end());
             continue;
         }
         sets.emplace_back();
         MergedSet& m = sets.back();
-        m.jobs = kv.second;
-        std::vector<int64_t> off(1, 0), coff(1, 0);
-        std::vector<int32_t> tok;
-        std::vector<uint32_t> code;
-        std::vector<float> cst;
-        off.reserve((size_t)progs + 1);
-        if (tree) tok.reserve((size_t)tokens);
-        else code.reserve((size_t)tokens);
-        cst.reserve((size_t)(tree ? tokens : consts));
-        for (int32_t i : kv.second) {
-            const gp_job& j = jobs[i];
-            const int64_t* jo = tree ? j.toff : j.loff;
-            const int64_t base = off.back(), cbase = coff.back(), n = jo[j.n_prog];
-            for (int32_t p = 0; p < j.n_prog; p++) {
-                // (a CSR array that runs backwards is not read: intake reports it)
-                if (jo[p + 1] < jo[p] || jo[p + 1] > n) return false;
-                off.push_back(base + jo[p + 1]);
-            }
-            if (tree) {
-                if (!j.tcst) return false;
-                tok.insert(tok.end(), j.tok, j.tok + n);
-                cst.insert(cst.end(), j.tcst, j.tcst + n);
-            } else {
-                code.insert(code.end(), j.code, j.code + n);
-                const int64_t nc = j.lcst_off ? j.lcst_off[j.n_prog] : 0;
-                if (nc < 0 || (nc > 0 && (!j.lcst || j.lcst_off[0] != 0))) return false;
-                for (int32_t p = 0; p < j.n_prog; p++) {
-                    const int64_t c1 = j.lcst_off ? j.lcst_off[p + 1] : 0;
-                    if (c1 < 0 || c1 > nc || (j.lcst_off && c1 < j.lcst_off[p])) return false;
-                    coff.push_back(cbase + c1);
-                }
-                if (nc) cst.insert(cst.end(), j.lcst, j.lcst + nc);
-            }
-            m.segments.push_back(EvalSegment{(int32_t)(off.size() - 1) - j.n_prog, j.n_prog, j.out});
+        m.job = &refs[kv.second[0]];
+        std::vector<const ProgData*> parts;
+        int32_t at = 0;
+        for (size_t i : kv.second) {
+            parts.push_back(refs[i].pd);
+            m.segments.push_back(EvalSegment{at, refs[i].pd->n_prog, refs[i].out});
+            at += refs[i].pd->n_prog;
         }
-        const gp_status st = tree ? build_tree(tok.data(), cst.data(), off.data(), (int32_t)progs, d.n_feat, m.pd)
-                                  : build_linear(code.data(), off.data(), cst.data(), coff.data(), (int32_t)progs,
-                                                 std::get<3>(kv.first), d.n_feat, m.pd);
-        if (st != GP_OK || m.pd.n_load > GP_MAX_FEAT) return false;
+        if (!merge_programs(parts, m.pd)) return false;
         m.pd.variant = default_variant(m.pd);
         if (m.pd.variant < 0) return false;
     }
-    std::sort(rest.begin(), rest.end());
+    std::sort(left.begin(), left.end());
+    for (size_t i : left) rest.push_back(refs[i]);
     return !sets.empty();
 }
 
 // The batch without a configuration of its own.
 gp_status eval_default(const gp_dataset* ds, int32_t n_ds, const gp_job* jobs, int32_t n_jobs, hipStream_t s) {
-    gp_status st = check_datasets(ds, n_ds);
-    if (st != GP_OK) return st;
-    if (n_jobs < 0 || (n_jobs > 0 && !jobs)) return fail(GP_E_INVAL, "bad job array");
-    std::vector<MergedSet> sets;
-    std::vector<int32_t> rest;
-    std::vector<gp_job> small;
-    if (merge_jobs(ds, n_ds, jobs, n_jobs, sets, rest)) {
-        for (int32_t i : rest) small.push_back(jobs[i]);
-    } else {
-        clear_error();
-        sets.clear();
-        small.assign(jobs, jobs + n_jobs);
-    }
-    // the small jobs are taken in before anything is launched, so a call that fails has done nothing
     std::vector<ProgData> pds;
-    std::vector<BatchJobRef> refs;
+    std::vector<BatchJobRef> refs, rest;
     std::vector<gp_dataset> dv;
-    gp_batch_config c;
-    if ((st = intake(ds, n_ds, small.data(), (int32_t)small.size(), pds, refs, dv)) != GP_OK) {
-        if (sets.empty()) return st;
-        // say which job of the caller's it is
-        pds.clear();
-        refs.clear();
-        return intake(ds, n_ds, jobs, n_jobs, pds, refs, dv);
+    gp_status st = intake(ds, n_ds, jobs, n_jobs, pds, refs, dv);
+    if (st != GP_OK || refs.empty()) return st;
+    std::vector<MergedSet> sets;
+    if (!merge_jobs(refs, dv, sets, rest)) {
+        sets.clear();
+        rest = refs;
     }
-    if (!refs.empty()) {
-        c = default_config(refs);
+    // (looked at before anything is launched, so a call that fails here has done nothing)
+    gp_batch_config c;
+    if (!rest.empty()) {
+        c = default_config(rest);
         if (c.variant < 0) return fail(GP_E_DEPTH, "no kernel variant can hold these programs");
     }
     for (MergedSet& m : sets) {
@@ -603,17 +627,16 @@ gp_status eval_default(const gp_dataset* ds, int32_t n_ds, const gp_job* jobs, i
         std::lock_guard<std::mutex> g(w.mu);
         EvalOptions o;
         o.segments = &m.segments;
-        const gp_job& j = jobs[m.jobs[0]];
-        const gp_dataset& d = ds[j.dataset];
-        st = eval_core(m.pd, w.oneshot, true, d.X, d.n_feat, d.n_cases, d.y, j.kind, j.out, s, &w, &o);
+        const gp_dataset& d = dv[m.job->ds];
+        st = eval_core(m.pd, w.oneshot, true, d.X, d.n_feat, d.n_cases, d.y, m.job->kind, m.job->out, s, &w, &o);
         if (st != GP_OK) return st;
     }
-    if (refs.empty()) return GP_OK;
+    if (rest.empty()) return GP_OK;
     BatchScratch& sc = batch_scratch(s);
     std::lock_guard<std::mutex> g(sc.mu);
     if ((st = core_ready(c.variant, s)) != GP_OK) return st;
     BatchPlan plan;
-    if ((st = plan_batch(refs, dv, c, plan)) != GP_OK) return st;
+    if ((st = plan_batch(rest, dv, c, plan)) != GP_OK) return st;
     if ((st = upload_plan(plan, sc, s)) != GP_OK) return st;
     return launch_plan(plan, sc, s);
 }

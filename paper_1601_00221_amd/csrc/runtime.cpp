@@ -277,8 +277,8 @@ static uint32_t op_cost(uint32_t op, int opset) {
     }
 }
 
-gp_status build_tree(const int32_t* tok, const float* cst, const int64_t* off, int32_t P,
-                     int32_t n_feat, ProgData& pd, int opset) {
+gp_status ProgBuild::begin_tree(const int32_t* tok, const float* cst, const int64_t* off, int32_t P, int32_t n_feat,
+                                ProgData& pd, int opset) {
     if (P < 0) return fail(GP_E_INVAL, "n_prog < 0");
     if (P > 0 && (!tok || (!cst && opset != OPSET_BOOL) || !off)) return fail(GP_E_INVAL, "null program array");
     if (n_feat < 1) return fail(GP_E_INVAL, "n_feat < 1");
@@ -300,45 +300,65 @@ gp_status build_tree(const int32_t* tok, const float* cst, const int64_t* off, i
     // Program p is lowered at word 2 * off[p] (at most one instruction per
     // node), so the programs are independent: they are lowered in parallel.
     pd.code.resize((size_t)total * 2);
-    pd.progs.resize(P);
-    pd.cost.resize(P);
-    std::vector<TreeLowering> lst(P);
-    std::vector<int32_t> pfeat(P, -1), prc(P, GP_OK), ptransc(P, 0);
-    parallel_for(P, [&](int64_t p0, int64_t p1) {
-        char err[256];
-        for (int64_t p = p0; p < p1; p++) {
-            const int64_t n = off[p + 1] - off[p];
-            uint32_t* words = pd.code.data() + 2 * off[p];
-            const int rc = lower_tree(tok + off[p], cst ? cst + off[p] : nullptr, n, n_feat, words, &lst[p], err, opset);
-            if (rc != GP_OK) {
-                prc[p] = rc;
-                return;
-            }
-            int32_t mf = -1;
-            for (int64_t i = 0; i < n; i++) {
-                const int32_t t = tok[off[p] + i];
-                if ((t & 0xFF) == GP_VAR) mf = std::max<int32_t>(mf, (int32_t)((uint32_t)t >> 8));
-            }
-            pfeat[p] = mf;
-            uint32_t cost = 0;
-            int32_t nt = 0;
-            for (int32_t i = 0; i < lst[p].n_instr; i++) {
-                const uint32_t op = words[2 * i] & 15u;
-                cost += op_cost(op, opset);
-                nt += opset != OPSET_BOOL && op >= GP_SIN && op <= GP_PLOG;
-            }
-            ptransc[p] = nt;
-            pd.cost[p] = cost + 16;
+    start(pd, off);
+    lst.resize(P);
+    tok_ = tok;
+    tcst_ = cst;
+    return GP_OK;
+}
+
+void ProgBuild::start(ProgData& pd, const int64_t* off) {
+    pd_ = &pd;
+    off_ = off;
+    pd.progs.resize(pd.n_prog);
+    pd.cost.resize(pd.n_prog);
+    pfeat.assign(pd.n_prog, -1);
+    prc.assign(pd.n_prog, GP_OK);
+    ptransc.assign(pd.n_prog, 0);
+}
+
+void ProgBuild::lower_trees(int64_t p0, int64_t p1) {
+    ProgData& pd = *pd_;
+    const int64_t* off = off_;
+    const int opset = pd.opset;
+    char err[256];
+    for (int64_t p = p0; p < p1; p++) {
+        const int64_t n = off[p + 1] - off[p];
+        uint32_t* words = pd.code.data() + 2 * off[p];
+        const int rc = lower_tree(tok_ + off[p], tcst_ ? tcst_ + off[p] : nullptr, n, pd.n_feat, words, &lst[p], err, opset);
+        if (rc != GP_OK) {
+            prc[p] = rc;
+            return;
         }
-    });
+        int32_t mf = -1;
+        for (int64_t i = 0; i < n; i++) {
+            const int32_t t = tok_[off[p] + i];
+            if ((t & 0xFF) == GP_VAR) mf = std::max<int32_t>(mf, (int32_t)((uint32_t)t >> 8));
+        }
+        pfeat[p] = mf;
+        uint32_t cost = 0;
+        int32_t nt = 0;
+        for (int32_t i = 0; i < lst[p].n_instr; i++) {
+            const uint32_t op = words[2 * i] & 15u;
+            cost += op_cost(op, opset);
+            nt += opset != OPSET_BOOL && op >= GP_SIN && op <= GP_PLOG;
+        }
+        ptransc[p] = nt;
+        pd.cost[p] = cost + 16;
+    }
+}
+
+gp_status ProgBuild::finish_trees() {
+    ProgData& pd = *pd_;
+    const int64_t* off = off_;
     int32_t max_feat = -1;
-    for (int32_t p = 0; p < P; p++) {
+    for (int32_t p = 0; p < pd.n_prog; p++) {
         if (prc[p] != GP_OK) {
             // lower the first failing program again on this thread for its message
             char err[256];
             TreeLowering st;
-            lower_tree(tok + off[p], cst ? cst + off[p] : nullptr, off[p + 1] - off[p], n_feat, nullptr, &st, err,
-                       opset);
+            lower_tree(tok_ + off[p], tcst_ ? tcst_ + off[p] : nullptr, off[p + 1] - off[p], pd.n_feat, nullptr, &st, err,
+                       pd.opset);
             return fail((gp_status)prc[p], "program %d: %s", p, err);
         }
         const TreeLowering& st = lst[p];
@@ -360,8 +380,8 @@ gp_status build_tree(const int32_t* tok, const float* cst, const int64_t* off, i
     return GP_OK;
 }
 
-gp_status build_linear(const uint32_t* code, const int64_t* off, const float* cst, const int64_t* cst_off,
-                       int32_t P, int32_t n_reg, int32_t n_feat, ProgData& pd) {
+gp_status ProgBuild::begin_linear(const uint32_t* code, const int64_t* off, const float* cst, const int64_t* cst_off,
+                                  int32_t P, int32_t n_reg, int32_t n_feat, ProgData& pd) {
     if (P < 0) return fail(GP_E_INVAL, "n_prog < 0");
     if (P > 0 && (!code || !off)) return fail(GP_E_INVAL, "null program array");
     if (n_reg < 1 || n_reg > GP_MAX_REG) return fail(GP_E_INVAL, "n_reg %d outside [1, %d]", n_reg, GP_MAX_REG);
@@ -389,45 +409,56 @@ gp_status build_linear(const uint32_t* code, const int64_t* off, const float* cs
     // Program p lies at word off[p] plus the constants before it, so the programs are independent: they are checked,
     // freed of the instructions that the result does not depend on, and copied in parallel.
     pd.code.resize((size_t)total);
-    pd.progs.resize(P);
-    pd.cost.resize(P);
-    std::vector<int32_t> prc(P, GP_OK), pfeat(P, -1), ptransc(P, 0);
-    parallel_for(P, [&](int64_t p0, int64_t p1) {
-        char err[256];
-        for (int64_t p = p0; p < p1; p++) {
-            const int64_t n = off[p + 1] - off[p];
-            const int64_t c0 = cst_off ? cst_off[p] : 0, nc = cst_off ? cst_off[p + 1] - c0 : 0;
-            const uint32_t* src = code + off[p];
-            if ((prc[p] = check_linear(src, n, nc, n_reg, n_feat, err)) != GP_OK) return;
-            for (int64_t i = 0; i < n; i++) {
-                const uint32_t wd = src[i];
-                const bool unary = (wd & 0xFF) >= GP_SIN && (wd & 0xFF) <= GP_PLOG;
-                ptransc[p] += unary;
-                for (int q = 0; q < (unary ? 1 : 2); q++) {
-                    const int32_t id = (int32_t)((wd >> (16 + 8 * q)) & 0xFF);
-                    if (id >= n_reg && id < GP_SRC_CONST) pfeat[p] = std::max(pfeat[p], id - n_reg);
-                }
+    start(pd, off);
+    code_ = code;
+    lcst_ = cst;
+    cst_off_ = cst_off;
+    return GP_OK;
+}
+
+void ProgBuild::lower_linear(int64_t p0, int64_t p1) {
+    ProgData& pd = *pd_;
+    const int64_t *off = off_, *cst_off = cst_off_;
+    const int32_t n_reg = pd.n_reg;
+    char err[256];
+    for (int64_t p = p0; p < p1; p++) {
+        const int64_t n = off[p + 1] - off[p];
+        const int64_t c0 = cst_off ? cst_off[p] : 0, nc = cst_off ? cst_off[p + 1] - c0 : 0;
+        const uint32_t* src = code_ + off[p];
+        if ((prc[p] = check_linear(src, n, nc, n_reg, pd.n_feat, err)) != GP_OK) return;
+        for (int64_t i = 0; i < n; i++) {
+            const uint32_t wd = src[i];
+            const bool unary = (wd & 0xFF) >= GP_SIN && (wd & 0xFF) <= GP_PLOG;
+            ptransc[p] += unary;
+            for (int q = 0; q < (unary ? 1 : 2); q++) {
+                const int32_t id = (int32_t)((wd >> (16 + 8 * q)) & 0xFF);
+                if (id >= n_reg && id < GP_SRC_CONST) pfeat[p] = std::max(pfeat[p], id - n_reg);
             }
-            uint32_t* dst = pd.code.data() + off[p] + c0;
-            DevProg& d = pd.progs[p];
-            d.code_off = (uint32_t)(off[p] + c0);
-            d.len = (uint32_t)needed_linear(src, n, n_reg, dst, &d.live);
-            if (nc) memcpy(dst + d.len, cst + c0, sizeof(float) * (size_t)nc);
-            d.meta = FORM_LINEAR | ((uint32_t)n_reg << 8);
-            d.reserved1 = 0;
-            d.row = (uint64_t)p;
-            uint32_t cost = 2u * (uint32_t)__builtin_popcount(d.live);
-            for (uint32_t i = 0; i < d.len; i++) cost += op_cost(dst[i] & 0xFF, OPSET_REAL);
-            pd.cost[p] = cost + 16;
         }
-    });
-    int32_t max_feat = std::min(n_feat, n_reg) - 1;  // registers start from these features
-    for (int32_t p = 0; p < P; p++) {
+        uint32_t* dst = pd.code.data() + off[p] + c0;
+        DevProg& d = pd.progs[p];
+        d.code_off = (uint32_t)(off[p] + c0);
+        d.len = (uint32_t)needed_linear(src, n, n_reg, dst, &d.live);
+        if (nc) memcpy(dst + d.len, lcst_ + c0, sizeof(float) * (size_t)nc);
+        d.meta = FORM_LINEAR | ((uint32_t)n_reg << 8);
+        d.reserved1 = 0;
+        d.row = (uint64_t)p;
+        uint32_t cost = 2u * (uint32_t)__builtin_popcount(d.live);
+        for (uint32_t i = 0; i < d.len; i++) cost += op_cost(dst[i] & 0xFF, OPSET_REAL);
+        pd.cost[p] = cost + 16;
+    }
+}
+
+gp_status ProgBuild::finish_linear() {
+    ProgData& pd = *pd_;
+    const int64_t *off = off_, *cst_off = cst_off_;
+    int32_t max_feat = std::min(pd.n_feat, pd.n_reg) - 1;  // registers start from these features
+    for (int32_t p = 0; p < pd.n_prog; p++) {
         const int64_t n = off[p + 1] - off[p];
         if (prc[p] != GP_OK) {
             // check the first failing program again on this thread for its message
             char err[256];
-            check_linear(code + off[p], n, cst_off ? cst_off[p + 1] - cst_off[p] : 0, n_reg, n_feat, err);
+            check_linear(code_ + off[p], n, cst_off ? cst_off[p + 1] - cst_off[p] : 0, pd.n_reg, pd.n_feat, err);
             return fail((gp_status)prc[p], "program %d: %s", p, err);
         }
         max_feat = std::max(max_feat, pfeat[p]);
@@ -438,6 +469,34 @@ gp_status build_linear(const uint32_t* code, const int64_t* off, const float* cs
     }
     pd.n_load = max_feat + 1;
     return GP_OK;
+}
+
+void ProgBuild::lower(int64_t p0, int64_t p1) {
+    if (pd_->form == FORM_TREE) lower_trees(p0, p1);
+    else lower_linear(p0, p1);
+}
+
+gp_status ProgBuild::finish() {
+    if (!pd_) return GP_OK;   // no programs
+    return pd_->form == FORM_TREE ? finish_trees() : finish_linear();
+}
+
+static gp_status run_build(gp_status begun, ProgBuild& b) {
+    if (begun != GP_OK) return begun;
+    parallel_for(b.n(), [&](int64_t p0, int64_t p1) { b.lower(p0, p1); });
+    return b.finish();
+}
+
+gp_status build_tree(const int32_t* tok, const float* cst, const int64_t* off, int32_t P, int32_t n_feat, ProgData& pd,
+                     int opset) {
+    ProgBuild b;
+    return run_build(b.begin_tree(tok, cst, off, P, n_feat, pd, opset), b);
+}
+
+gp_status build_linear(const uint32_t* code, const int64_t* off, const float* cst, const int64_t* cst_off, int32_t P,
+                       int32_t n_reg, int32_t n_feat, ProgData& pd) {
+    ProgBuild b;
+    return run_build(b.begin_linear(code, off, cst, cst_off, P, n_reg, n_feat, pd), b);
 }
 
 // Programs by falling cost: the order their code lies in on the device.

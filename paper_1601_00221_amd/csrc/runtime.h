@@ -207,6 +207,35 @@ void cut_groups(const std::vector<uint32_t>& cost, const std::vector<uint32_t>& 
 hipError_t timed_launch_begin(hipStream_t s, int* slot);
 hipError_t timed_launch_end(hipStream_t s, int slot);
 
+// The lowering of one population in steps, so that several are lowered in one
+// walk of the host threads: begin checks the arrays' lengths and makes room
+// (no program is read before), lower takes ranges of its n() programs in any
+// order, side by side, and finish reports the first that failed.  The
+// caller's arrays and pd are used until then.
+class ProgBuild {
+public:
+    gp_status begin_tree(const int32_t* tok, const float* cst, const int64_t* off, int32_t P, int32_t n_feat, ProgData& pd,
+                         int opset = OPSET_REAL);
+    gp_status begin_linear(const uint32_t* code, const int64_t* off, const float* cst, const int64_t* cst_off, int32_t P,
+                           int32_t n_reg, int32_t n_feat, ProgData& pd);
+    int64_t n() const { return pd_ ? pd_->n_prog : 0; }
+    void lower(int64_t p0, int64_t p1);
+    gp_status finish();
+
+private:
+    void start(ProgData& pd, const int64_t* off);
+    void lower_trees(int64_t p0, int64_t p1);
+    void lower_linear(int64_t p0, int64_t p1);
+    gp_status finish_trees();
+    gp_status finish_linear();
+    ProgData* pd_ = nullptr;       // null: nothing to lower
+    const int64_t *off_ = nullptr, *cst_off_ = nullptr;
+    const int32_t* tok_ = nullptr;
+    const uint32_t* code_ = nullptr;
+    const float *tcst_ = nullptr, *lcst_ = nullptr;
+    std::vector<TreeLowering> lst;
+    std::vector<int32_t> pfeat, prc, ptransc;   // of each program: highest feature, status, sin/cos/exp/log
+};
 gp_status build_tree(const int32_t* tok, const float* cst, const int64_t* off, int32_t P, int32_t n_feat,
                      ProgData& pd, int opset = OPSET_REAL);
 gp_status build_linear(const uint32_t* code, const int64_t* off, const float* cst, const int64_t* cst_off,
