@@ -488,7 +488,9 @@ gp_status gp_timing_read(int64_t* launches, double* total_ms, int reset);
  * for no burst load), GP2D_SAME_GROUP=1 (the four waves of a block run one program
  * group on four chunks of tiles instead of four groups on one chunk),
  * GP2D_VARIANT=i+1 (kernel variant i of gp_variant_info, when it can hold the
- * programs).  They change the schedule only; fitness values never depend on
+ * programs), and, at every gp_eval_batch, GP2D_MERGED_WORK (tokens x cases
+ * from which jobs that share form, dataset, kind and registers are launched
+ * by themselves).  They change the schedule only; fitness values never depend on
  * them. */
 
 /* Message of the last failed call on this thread ("" if none). */

@@ -519,7 +519,11 @@ struct MergedSet {
 // a table of units, which must hold trees and register programs alike.
 // Measured on 40 populations of 250 over 4,096, 65,536 and 1,048,576 cases:
 // 128 ms a call all in one launch, 95 ms by sets.
-constexpr double kMergedWork = 2e9;
+// GP2D_MERGED_WORK sets another limit (0: every set by itself).
+double merged_work() {
+    const char* v = getenv("GP2D_MERGED_WORK");
+    return v && *v ? strtod(v, nullptr) : 2e9;
+}
 
 // Lowered populations of one form, table and register count as one.  False:
 // more than its offsets reach.
@@ -574,6 +578,7 @@ bool merge_jobs(const std::vector<BatchJobRef>& refs, const std::vector<gp_datas
     for (size_t i = 0; i < refs.size(); i++)
         by[{refs[i].pd->form, refs[i].ds, refs[i].kind, refs[i].pd->n_reg}].push_back(i);
     std::vector<size_t> left;
+    const double limit = merged_work();
     for (auto& kv : by) {
         double work = 0.0;
         int64_t progs = 0;
@@ -581,7 +586,7 @@ bool merge_jobs(const std::vector<BatchJobRef>& refs, const std::vector<gp_datas
             work += (double)refs[i].pd->n_gpop * (double)ds[refs[i].ds].n_cases;
             progs += refs[i].pd->n_prog;
         }
-        if (work < kMergedWork || progs > 0x7FFFFFFFll) {
+        if (work < limit || progs > 0x7FFFFFFFll) {
             left.insert(left.end(), kv.second.begin(), kv.second.end());
             continue;
         }
