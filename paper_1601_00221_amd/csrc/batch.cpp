@@ -356,12 +356,6 @@ gp_status tune_batch(const std::vector<BatchJobRef>& jobs, const std::vector<gp_
     return GP_OK;
 }
 
-static bool any_tuned() {
-    std::lock_guard<std::mutex> g(g_tune_mu);
-    tune_load_locked();
-    return !g_tune_cache.empty();
-}
-
 // Forget what was tuned for this shape: the launches without a configuration are faster.
 static void drop_tuned(const std::vector<BatchJobRef>& jobs, const std::vector<gp_dataset>& ds) {
     std::lock_guard<std::mutex> g(g_tune_mu);
@@ -372,6 +366,7 @@ static void drop_tuned(const std::vector<BatchJobRef>& jobs, const std::vector<g
 bool tuned_config(const std::vector<BatchJobRef>& jobs, const std::vector<gp_dataset>& ds, gp_batch_config* c) {
     std::lock_guard<std::mutex> g(g_tune_mu);
     tune_load_locked();
+    if (g_tune_cache.empty()) return false;
     auto it = g_tune_cache.find(batch_key(jobs, ds));
     if (it == g_tune_cache.end()) return false;
     *c = it->second;
@@ -610,13 +605,10 @@ bool merge_jobs(const std::vector<BatchJobRef>& refs, const std::vector<gp_datas
 }
 
 // The batch without a configuration of its own.
-gp_status eval_default(const gp_dataset* ds, int32_t n_ds, const gp_job* jobs, int32_t n_jobs, hipStream_t s) {
-    std::vector<ProgData> pds;
-    std::vector<BatchJobRef> refs, rest;
-    std::vector<gp_dataset> dv;
-    gp_status st = intake(ds, n_ds, jobs, n_jobs, pds, refs, dv);
-    if (st != GP_OK || refs.empty()) return st;
+gp_status eval_default(const std::vector<BatchJobRef>& refs, const std::vector<gp_dataset>& dv, hipStream_t s) {
+    gp_status st;
     std::vector<MergedSet> sets;
+    std::vector<BatchJobRef> rest;
     if (!merge_jobs(refs, dv, sets, rest)) {
         sets.clear();
         rest = refs;
@@ -647,9 +639,9 @@ gp_status eval_default(const gp_dataset* ds, int32_t n_ds, const gp_job* jobs, i
 }
 
 // Median device time of the batch without a configuration.
-gp_status time_default(const gp_dataset* ds, int32_t n_ds, const gp_job* jobs, int32_t n_jobs, int32_t reps, hipStream_t s,
+gp_status time_default(const std::vector<BatchJobRef>& refs, const std::vector<gp_dataset>& dv, int32_t reps, hipStream_t s,
                        double* ms) {
-    gp_status st = eval_default(ds, n_ds, jobs, n_jobs, s);   // warm-up
+    gp_status st = eval_default(refs, dv, s);   // warm-up
     if (st != GP_OK) return st;
     hipEvent_t e0, e1;
     if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess)
@@ -658,7 +650,7 @@ gp_status time_default(const gp_dataset* ds, int32_t n_ds, const gp_job* jobs, i
     for (int r = 0; r < reps && st == GP_OK; r++) {
         float x = 0;
         hipError_t e = hipEventRecord(e0, s);
-        st = eval_default(ds, n_ds, jobs, n_jobs, s);
+        st = eval_default(refs, dv, s);
         if (e == hipSuccess) e = hipEventRecord(e1, s);
         if (e == hipSuccess) e = hipEventSynchronize(e1);
         if (e == hipSuccess) e = hipEventElapsedTime(&x, e0, e1);
@@ -681,8 +673,6 @@ gp_status gp_eval_batch(const gp_dataset* ds, int32_t n_ds, const gp_job* jobs, 
                         const gp_batch_config* cfg, void* stream) {
     clear_error();
     hipStream_t s = (hipStream_t)stream;
-    // (a shape is looked up only if any has been tuned: its key needs the lowered programs)
-    if (!cfg && !any_tuned()) return eval_default(ds, n_ds, jobs, n_jobs, s);
     std::vector<ProgData> pds;
     std::vector<BatchJobRef> refs;
     std::vector<gp_dataset> dv;
@@ -690,7 +680,7 @@ gp_status gp_eval_batch(const gp_dataset* ds, int32_t n_ds, const gp_job* jobs, 
     if (st != GP_OK || refs.empty()) return st;
     gp_batch_config c;
     if (cfg) c = *cfg;
-    else if (!tuned_config(refs, dv, &c)) return eval_default(ds, n_ds, jobs, n_jobs, s);
+    else if (!tuned_config(refs, dv, &c)) return eval_default(refs, dv, s);
     BatchScratch& sc = batch_scratch(s);
     std::lock_guard<std::mutex> g(sc.mu);
     if (c.variant < 0) return fail(GP_E_DEPTH, "no kernel variant can hold these programs");
@@ -720,7 +710,7 @@ gp_status gp_tune_batch(const gp_dataset* ds, int32_t n_ds, const gp_job* jobs, 
         if ((st = tune_batch(refs, dv, reps, sc, s, best, &ms)) != GP_OK) return st;
     }
     if (best_ms) *best_ms = ms;
-    if ((st = time_default(ds, n_ds, jobs, n_jobs, reps, s, &dflt)) != GP_OK) return st;
+    if ((st = time_default(refs, dv, reps, s, &dflt)) != GP_OK) return st;
     if (dflt < ms) drop_tuned(refs, dv);
     return GP_OK;
 }

@@ -6,6 +6,7 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include <atomic>
 #include <mutex>
 
 #include "blockgp.h"
@@ -28,12 +29,29 @@ struct FakeState {
 };
 static FakeState g;
 static std::mutex g_mu;
+static std::atomic<int> g_lowered{0};   // programs lowered
+
+// lower.cpp is compiled with these two functions under other names, so that calls are counted
+namespace gpx {
+int real_lower_tree(const int32_t*, const float*, int64_t, int32_t, uint32_t*, TreeLowering*, char*, int);
+int64_t real_needed_linear(const uint32_t*, int64_t, int32_t, uint32_t*, uint32_t*);
+int lower_tree(const int32_t* tok, const float* cst, int64_t n, int32_t n_feat, uint32_t* words, TreeLowering* st, char* err,
+               int opset) {
+    g_lowered++;
+    return real_lower_tree(tok, cst, n, n_feat, words, st, err, opset);
+}
+int64_t needed_linear(const uint32_t* code, int64_t n, int32_t n_reg, uint32_t* out, uint32_t* live) {
+    g_lowered++;
+    return real_needed_linear(code, n, n_reg, out, live);
+}
+}  // namespace gpx
 
 extern "C" {
 FakeState* fake_state() { return &g; }
 void fake_fail_malloc(int n) { g.fail_malloc = n; }
 int fake_int(int what) {
-    const int v[] = {g.launches, g.last_rows, g.last_groups, g.last_variant, g.last_table, g.null_layout, g.uploads};
+    const int v[] = {g.launches, g.last_rows, g.last_groups, g.last_variant, g.last_table, g.null_layout, g.uploads,
+                     g_lowered.load()};
     return v[what];
 }
 void fake_times(double launch, double table) { g.launch_ms = launch; g.table_ms = table; }

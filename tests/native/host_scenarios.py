@@ -19,7 +19,7 @@ import synth                       # noqa: E402
 
 gp.LIB_PATH = sys.argv[1]
 gp.stream_ptr = lambda stream=None: None   # the null stream
-LAUNCHES, ROWS, GROUPS, VARIANT, TABLE, BAD_LAYOUTS, UPLOADS = range(7)
+LAUNCHES, ROWS, GROUPS, VARIANT, TABLE, BAD_LAYOUTS, UPLOADS, LOWERED = range(8)
 
 
 def fake(what):
@@ -72,7 +72,29 @@ def failed_allocation_leaves_no_layout():
     assert failures > 0
 
 
-SCENARIOS = {f.__name__: f for f in (failed_allocation_leaves_no_layout,)}
+def batch(rng, specs, F, N):
+    """A dataset and jobs: (trees?, programs, length)."""
+    X, y = Array(np.zeros((F, N), np.float32)), Array(np.zeros(N, np.float32))
+    jobs = []
+    for tree, P, n in specs:
+        pop = synth.ptc2_population(rng, P, synth.FULL, F, 1, n, 0.1) if tree else \
+            synth.linear_population(rng, P, 1, n, synth.BASIC, 8, F, n_const=2)
+        jobs.append(gp.make_job(pop, 0, "mse", 0x10000))
+    return [(X, y)], jobs
+
+
+def batch_is_lowered_once():
+    """gp_eval_batch without a configuration lowers every program once, merged sets and the others."""
+    for limit, launches in (("0", 2), ("1e18", 1)):
+        os.environ["GP2D_MERGED_WORK"] = limit
+        data, jobs = batch(synth.rng_for(6), [(True, 70, 40), (False, 50, 60), (True, 30, 40)], 8, 1000)
+        lowered, launched = fake(LOWERED), fake(LAUNCHES)
+        gp.gp_eval_batch(data, jobs)
+        assert fake(LAUNCHES) - launched == launches
+        assert fake(LOWERED) - lowered == 150, fake(LOWERED) - lowered
+
+
+SCENARIOS = {f.__name__: f for f in (failed_allocation_leaves_no_layout, batch_is_lowered_once)}
 
 if __name__ == "__main__":
     SCENARIOS[sys.argv[2]](*sys.argv[3:])

@@ -39,7 +39,8 @@ def library(tmp_path_factory):
 
     def compile_one(src):
         o = str(d / (os.path.basename(src) + ".o"))
-        subprocess.run(["g++", *flags, "-c", src, "-o", o], check=True)
+        count = ["-Dlower_tree=real_lower_tree", "-Dneeded_linear=real_needed_linear"] if src.endswith("lower.cpp") else []
+        subprocess.run(["g++", *flags, *count, "-c", src, "-o", o], check=True)
         return o
     with cf.ThreadPoolExecutor(max_workers=4) as ex:
         objs = list(ex.map(compile_one, SOURCES))
@@ -61,3 +62,11 @@ def run(library, scenario, *args, **env):
 
 def test_failed_allocation_leaves_no_layout(library):
     run(library, "failed_allocation_leaves_no_layout")
+
+
+def test_a_batch_is_lowered_once(library, tmp_path):
+    run(library, "batch_is_lowered_once")
+    # the same where configurations of other shapes are stored
+    cache = tmp_path / "tuned.json"
+    cache.write_text('{\n"d7x1;j0,0,1,1,1,1;": [0, 8, 1]\n}\n')
+    run(library, "batch_is_lowered_once", GP2D_TUNE_CACHE=str(cache))
