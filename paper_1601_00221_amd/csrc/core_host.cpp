@@ -594,7 +594,12 @@ static gp_status translate_with(const ProgData& pd, int vi, const VariantMap& m,
     const int32_t P = pd.n_prog;
     progs = pd.progs;
     RowPlan features;
-    const bool in_lds = pd.n_load > kCoreVariants[vi].nf;
+    // (other kernels have no place for a feature beyond their slots: its offset is written as it comes, and an
+    // evaluation never takes such a kernel)
+    const CoreVariantDesc& v = kCoreVariants[vi];
+    const bool in_lds = v.cap > v.nf && pd.n_load > v.nf;
+    if (in_lds && pd.n_load > v.cap)
+        return fail(GP_E_INVAL, "variant %d takes %d features, the programs read %d", vi, v.cap, pd.n_load);
     if (in_lds && !rows) {
         no_rows(pd, vi, features);
         rows = &features;
@@ -605,7 +610,7 @@ static gp_status translate_with(const ProgData& pd, int vi, const VariantMap& m,
         const DevProg& src = pd.progs[p];
         if ((src.meta & 1u) == FORM_TREE)
             return (int64_t)src.len + 1 +
-                   (in_lds ? pushes_of_features(pd.code.data() + src.code_off, src.len, kCoreVariants[vi], *rows) : 0);
+                   (in_lds ? pushes_of_features(pd.code.data() + src.code_off, src.len, v, *rows) : 0);
         return linear_records(pd.code.data() + src.code_off, src.len, src.live);
     };
     for (int32_t i = 0; i < P; i++) start[i + 1] = start[i] + records(at(i));
@@ -617,7 +622,6 @@ static gp_status translate_with(const ProgData& pd, int vi, const VariantMap& m,
     std::fill(code.begin() + 4 * start[P], code.end(), 0u);
     if (rows) {
         // wave w computes rows w, w + W, ...
-        const CoreVariantDesc& v = kCoreVariants[vi];
         auto length = [&](int32_t r) { return rows->op[r] != OP_PUSH && rows->feat[r] >= v.nf ? 3 : 2; };
         int64_t at_rec = start[P];
         char err[256];
