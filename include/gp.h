@@ -350,11 +350,13 @@ gp_status gp_eval_batch(const gp_dataset* ds, int32_t n_ds, const gp_job* jobs, 
  * the environment names a file in GP2D_TUNE_CACHE, in that JSON file. */
 gp_status gp_tune_batch(const gp_dataset* ds, int32_t n_ds, const gp_job* jobs, int32_t n_jobs, int32_t reps,
                         gp_batch_config* best, double* best_ms, void* stream);
-/* Compiled kernel variants: tile width t (case slots per lane), stack levels,
- * feature slots, the VGPRs left to compiled code (the interpreter core owns
- * the VGPRs from that number up) and flags: GP_VARIANT_NO_TRANSC marks a
- * kernel without sin/cos/exp/log code, used for programs without them;
- * GP_VARIANT_BOOLEAN (with GP_VARIANT_NO_TRANSC) a kernel of the Boolean
+/* Compiled kernel variants.  A variant keeps its number from one release to
+ * the next (configurations and GP2D_VARIANT values may be stored).  Tile width
+ * t (case slots per lane), stack levels, feature slots, the VGPRs left to
+ * compiled code (the interpreter core owns the VGPRs from that number up) and
+ * flags: GP_VARIANT_NO_TRANSC marks a kernel without sin/cos/exp/log code,
+ * used for programs without them; GP_VARIANT_BOOLEAN (with
+ * GP_VARIANT_NO_TRANSC) a kernel of the Boolean
  * function set for gp_eval_bool, whose slots are 32-bit words;
  * GP_VARIANT_TREES_ONLY (with GP_VARIANT_NO_TRANSC) an arithmetic kernel for
  * trees only (no linear-program handlers), which one-shot and program-set

@@ -128,7 +128,7 @@ int pick_core_variant(int n_load, int depth, double transc_frac, bool has_transc
     };
     for (int i = 0; i < core_variants(); i++) {
         const CoreVariantDesc& v = kCoreVariants[i];
-        if ((v.arith == 2) != boolean) continue;
+        if (v.by_number_only || (v.arith == 2) != boolean) continue;
         if (v.arith >= 3 && !trees_only) continue;
         // Features in LDS: where fewer than four waves a SIMD would hold them in registers (13 and more with
         // sin/cos/exp/log: 4096 trees x 30000 cases over 13, 24, 41 features 3.63, 4.02, 4.95 ms in registers, 3.34,

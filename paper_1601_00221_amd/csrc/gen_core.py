@@ -86,6 +86,12 @@ VARIANTS = [
     (8, 8, 8, 40, 1),
     (4, 8, 16, 40, 1),
     (4, 12, 32, 40, 1),
+    (8, 6, 8, 56, 3),
+    (8, 8, 8, 40, 3),
+    (4, 8, 16, 48, 3),
+    (4, 8, 44, 48, 4),
+    (8, 6, 20, 48, 2),
+    (8, 8, 20, 32, 2),
     (4, 12, 32, 40, 2),
     # deep programs: every tree of at most GP_MAX_LEN nodes needs at most 20
     # levels (15 without IF), 16 for the binary Boolean set; with more than 32
@@ -93,9 +99,17 @@ VARIANTS = [
     (4, 20, 32, 40, 0),
     (4, 12, 44, 32, 4),
     (4, 16, 32, 40, 2),
+    (4, 6, 20, 24, 2),
+    (4, 8, 12, 48, 3),
     # 4 waves per SIMD at T = 4: register programs over 16 features (13 % faster than (4, 8, 16, 40))
     (4, 8, 16, 32, 1),
 ]
+
+# A kernel's place in VARIANTS + RING_VARIANTS is its number in the interface (gp_batch_config, GP2D_VARIANT), which
+# programs store: kernels are added at the end and keep their places.  These are kept for configurations that name
+# them: ring cores (and (4, 9, 11, 48), below) took their place in the default choice.
+BY_NUMBER_ONLY = {(8, 6, 8, 56, 3), (8, 8, 8, 40, 3), (4, 8, 16, 48, 3), (4, 8, 44, 48, 4), (8, 6, 20, 48, 2),
+                  (8, 8, 20, 32, 2), (4, 6, 20, 24, 2), (4, 8, 12, 48, 3)}
 
 # Variants on ring cores (below): trees of functions that stay in the core, whose instructions are short enough for
 # the scalar cache's latency to show.  5 levels hold the benchmark populations of up to 256 nodes without IF; the
@@ -116,8 +130,6 @@ RING_VARIANTS = [
     (4, 8, 8, 64, 4),
     (4, 6, 12, 56, 4),
     (4, 8, 16, 56, 4),
-    (4, 6, 24, 48, 4),
-    (4, 8, 44, 48, 4),
     (4, 9, 11, 48, 4),
 ]
 
@@ -1737,16 +1749,17 @@ def main(out_dir):
         lines.append("};")
     lines.append("struct CoreVariantDesc { int t, d, nf, ncv, arith; const CoreHandlerKey* keys; const uint16_t* slots; "
                  "int n; int slot_bytes; int xx; bool ring; "
-                 "int waves, rows_base, cap; };")
+                 "int waves, rows_base, cap; bool by_number_only; };")
     lines.append("// xx: levels with one-pass handlers of two variables; waves: waves of a block; rows_base: LDS address of its rows, or 0;")
-    lines.append("// cap: features it takes (more than nf: the others in LDS)")
+    lines.append("// cap: features it takes (more than nf: the others in LDS); by_number_only: never chosen by default")
     lines.append("static const CoreVariantDesc kCoreVariants[] = {")
     for (T, D, NF, NCV, AR, tag, hs, nslots, ring) in host:
-        lines.append("    {%d, %d, %d, %d, %d, kCoreKeys_%s, kCoreSlots_%s, %d, %d, %d, %s, %d, %d, %d},"
+        lines.append("    {%d, %d, %d, %d, %d, kCoreKeys_%s, kCoreSlots_%s, %d, %d, %d, %s, %d, %d, %d, %s},"
                      % (T, D, NF, NCV, AR, tag, tag, len(hs), RING_SLOT if ring else SLOT, xx_levels(D, NF, AR, ring),
                         "true" if ring else "false", waves_per_block(T, D, NF, NCV, AR, ring),
                         rows_base(T, D, NF, NCV, AR) if ring and AR == 4 else 0,
-                        WIDE.get((T, D, NF, NCV, AR), NF) if ring else NF))
+                        WIDE.get((T, D, NF, NCV, AR), NF) if ring else NF,
+                        "true" if (T, D, NF, NCV, AR) in BY_NUMBER_ONLY else "false"))
     lines.append("};")
     path = os.path.join(out_dir, "core_gen.inc")
     write_if_changed(path, "\n".join(lines) + "\n")
