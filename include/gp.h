@@ -347,7 +347,9 @@ gp_status gp_eval_batch(const gp_dataset* ds, int32_t n_ds, const gp_job* jobs, 
  * `stream` and synchronizes on it), store the fastest for the batch's shape
  * (unless the default of gp_eval_batch is faster still) and return it with
  * its median time.  The store is kept in memory and, when
- * the environment names a file in GP2D_TUNE_CACHE, in that JSON file. */
+ * the environment names a file in GP2D_TUNE_CACHE, in that JSON file, where
+ * kernels go by their names.  gp_eval_batch passes over a stored kernel that
+ * it does not have, or that cannot run the batch's programs. */
 gp_status gp_tune_batch(const gp_dataset* ds, int32_t n_ds, const gp_job* jobs, int32_t n_jobs, int32_t reps,
                         gp_batch_config* best, double* best_ms, void* stream);
 /* Compiled kernel variants.  A variant keeps its number from one release to

@@ -44,9 +44,8 @@ static double transc_fraction(const std::vector<BatchJobRef>& jobs) {
     return n ? (double)e / (double)n : 0.0;
 }
 
-gp_status plan_batch(const std::vector<BatchJobRef>& jobs, const std::vector<gp_dataset>& ds,
-                     const gp_batch_config& cfg, BatchPlan& plan) {
-    plan = BatchPlan();
+// Whether a configuration's kernel can run the jobs.
+static gp_status check_config(const std::vector<BatchJobRef>& jobs, const gp_batch_config& cfg) {
     int n_load = 1, depth = 0;
     bool any_transc = false;
     for (const BatchJobRef& j : jobs) {
@@ -56,7 +55,6 @@ gp_status plan_batch(const std::vector<BatchJobRef>& jobs, const std::vector<gp_
     }
     const int vi = cfg.variant;
     if (vi < 0 || vi >= core_variants()) return fail(GP_E_INVAL, "kernel variant %d does not exist", vi);
-    const int vt = core_variant_t(vi);
     if (core_variant_nf(vi) < n_load || core_variant_d(vi) < depth)
         return fail(GP_E_INVAL, "variant %d (%d features, depth %d) cannot hold %d features / depth %d", vi,
                     core_variant_nf(vi), core_variant_d(vi), n_load, depth);
@@ -66,6 +64,15 @@ gp_status plan_batch(const std::vector<BatchJobRef>& jobs, const std::vector<gp_
     if (core_variant_trees_only(vi))
         for (const BatchJobRef& j : jobs)
             if (j.pd->form != FORM_TREE) return fail(GP_E_INVAL, "variant %d runs trees only", vi);
+    return GP_OK;
+}
+
+gp_status plan_batch(const std::vector<BatchJobRef>& jobs, const std::vector<gp_dataset>& ds,
+                     const gp_batch_config& cfg, BatchPlan& plan) {
+    plan = BatchPlan();
+    const gp_status fits = check_config(jobs, cfg);
+    if (fits != GP_OK) return fits;
+    const int vi = cfg.variant, vt = core_variant_t(vi);
     plan.vi = vi;
     const int32_t unit_prog = std::max(1, cfg.unit_programs);
     int64_t n_prog = 0;
@@ -205,8 +212,14 @@ gp_status launch_plan(const BatchPlan& p, BatchScratch& sc, hipStream_t s) {
 // ---------------------------------------------------------------------------
 // Autotuning
 // ---------------------------------------------------------------------------
+// What is stored for a shape.  The kernel goes by its name: a file may have
+// been written by another release.
+struct Tuned {
+    std::string kernel;
+    int unit_programs, persistent;
+};
 static std::mutex g_tune_mu;
-static std::map<std::string, gp_batch_config> g_tune_cache;
+static std::map<std::string, Tuned> g_tune_cache;
 static bool g_tune_loaded = false;
 
 static const char* tune_cache_path() { return getenv("GP2D_TUNE_CACHE"); }
@@ -218,7 +231,8 @@ static void tune_load_locked() {
     if (!path) return;
     FILE* f = fopen(path, "r");
     if (!f) return;
-    // one entry per line: "key": [variant, unit_programs, persistent]
+    // one entry per line: "key": ["kernel", unit_programs, persistent], or, in files of earlier releases, the kernel's
+    // number
     char line[4096];
     while (fgets(line, sizeof line, f)) {
         char* q1 = strchr(line, '"');
@@ -226,10 +240,12 @@ static void tune_load_locked() {
         char* q2 = strchr(q1 + 1, '"');
         if (!q2) continue;
         std::string key(q1 + 1, q2);
-        gp_batch_config c;
-        memset(&c, 0, sizeof c);
-        if (sscanf(q2 + 1, " : [ %d , %d , %d ]", &c.variant, &c.unit_programs, &c.persistent) == 3)
-            g_tune_cache[key] = c;
+        char name[64];
+        int vi, unit, pers;
+        if (sscanf(q2 + 1, " : [ \"%63[^\"]\" , %d , %d ]", name, &unit, &pers) == 3)
+            g_tune_cache[key] = Tuned{name, unit, pers};
+        else if (sscanf(q2 + 1, " : [ %d , %d , %d ]", &vi, &unit, &pers) == 3)
+            g_tune_cache[key] = Tuned{vi >= 0 && vi < core_variants() ? core_variant_name(vi) : std::to_string(vi), unit, pers};
     }
     fclose(f);
 }
@@ -243,7 +259,7 @@ static void tune_save_locked() {
     fprintf(f, "{\n");
     size_t i = 0;
     for (auto& kv : g_tune_cache) {
-        fprintf(f, "\"%s\": [%d, %d, %d]%s\n", kv.first.c_str(), kv.second.variant, kv.second.unit_programs,
+        fprintf(f, "\"%s\": [\"%s\", %d, %d]%s\n", kv.first.c_str(), kv.second.kernel.c_str(), kv.second.unit_programs,
                 kv.second.persistent, ++i < g_tune_cache.size() ? "," : "");
     }
     fprintf(f, "}\n");
@@ -351,7 +367,7 @@ gp_status tune_batch(const std::vector<BatchJobRef>& jobs, const std::vector<gp_
     if (best_ms) *best_ms = best_t;
     std::lock_guard<std::mutex> g(g_tune_mu);
     tune_load_locked();
-    g_tune_cache[batch_key(jobs, ds)] = b;
+    g_tune_cache[batch_key(jobs, ds)] = Tuned{core_variant_name(b.variant), b.unit_programs, b.persistent};
     tune_save_locked();
     return GP_OK;
 }
@@ -369,8 +385,15 @@ bool tuned_config(const std::vector<BatchJobRef>& jobs, const std::vector<gp_dat
     if (g_tune_cache.empty()) return false;
     auto it = g_tune_cache.find(batch_key(jobs, ds));
     if (it == g_tune_cache.end()) return false;
-    *c = it->second;
-    return true;
+    // a kernel that does not exist (any more) or cannot run these programs (the shape's key does not say whether they use
+    // sin/cos/exp/log) is not taken
+    memset(c, 0, sizeof *c);
+    c->variant = core_variant_named(it->second.kernel);
+    c->unit_programs = it->second.unit_programs;
+    c->persistent = it->second.persistent;
+    if (check_config(jobs, *c) == GP_OK) return true;
+    clear_error();
+    return false;
 }
 
 gp_batch_config default_config(const std::vector<BatchJobRef>& jobs) {

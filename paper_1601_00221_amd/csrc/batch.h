@@ -49,6 +49,7 @@ gp_status upload_plan(BatchPlan& p, BatchScratch& sc, hipStream_t s);
 gp_status launch_plan(const BatchPlan& p, BatchScratch& sc, hipStream_t s);
 gp_status tune_batch(const std::vector<BatchJobRef>& jobs, const std::vector<gp_dataset>& ds, int reps,
                      BatchScratch& sc, hipStream_t s, gp_batch_config* best, double* best_ms);
+// The configuration stored for this batch's shape, if its kernel can run these jobs.
 bool tuned_config(const std::vector<BatchJobRef>& jobs, const std::vector<gp_dataset>& ds, gp_batch_config* c);
 gp_batch_config default_config(const std::vector<BatchJobRef>& jobs);
 gp_status check_datasets(const gp_dataset* ds, int32_t n_ds);

@@ -9,6 +9,7 @@
 #include <functional>
 #include <memory>
 #include <mutex>
+#include <string>
 #include <unordered_map>
 #include <vector>
 
@@ -781,6 +782,18 @@ bool core_variant_fits(int vi, const ProgData& pd) {
     // (an operand that is pushed takes the level above)
     return v.cap >= pd.n_load && v.d >= pd.max_depth + (pd.n_load > v.nf) && !(mode_no_transc(v.arith) && pd.n_transc > 0) &&
            (v.arith == 2) == (pd.opset == OPSET_BOOL) && !(v.arith >= 2 && pd.form != FORM_TREE);
+}
+std::string core_variant_name(int vi) {
+    const CoreVariantDesc& v = kCoreVariants[vi];
+    static const char* const suffix[] = {"", "_a", "_b", "_at", "_t"};
+    char s[64];
+    snprintf(s, sizeof s, "k_core_%d_%d_%d_%d%s", v.t, v.d, v.nf, v.ncv, suffix[v.arith]);
+    return s;
+}
+int core_variant_named(const std::string& name) {
+    for (int i = 0; i < core_variants(); i++)
+        if (core_variant_name(i) == name) return i;
+    return -1;
 }
 int core_variant_arith(int vi) { return mode_no_transc(kCoreVariants[vi].arith); }
 bool core_variant_bool(int vi) { return kCoreVariants[vi].arith == 2; }

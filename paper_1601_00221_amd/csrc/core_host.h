@@ -4,6 +4,7 @@
 #include <hip/hip_runtime_api.h>
 #include <stdint.h>
 
+#include <string>
 #include <vector>
 
 #include "../../include/gp.h"
@@ -22,6 +23,8 @@ int core_variant_arith(int vi);    // 1: no sin/cos/exp/log code
 bool core_variant_bool(int vi);    // the Boolean function set (32-bit word slots)
 bool core_variant_trees_only(int vi);   // no linear handlers (Boolean and trees-only arithmetic kernels)
 int core_variant_ncv(int vi);      // VGPRs left to the compiled code
+std::string core_variant_name(int vi);            // of its kernel
+int core_variant_named(const std::string& name);  // -1: none
 int core_reg_levels(int vi);       // register/stack levels before the features
 // Variant for programs reading n_load features, needing `depth` stack levels,
 // with a fraction transc_frac of sin/cos/exp/log instructions (has_transc:

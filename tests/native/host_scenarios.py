@@ -94,7 +94,29 @@ def batch_is_lowered_once():
         assert fake(LOWERED) - lowered == 150, fake(LOWERED) - lowered
 
 
-SCENARIOS = {f.__name__: f for f in (failed_allocation_leaves_no_layout, batch_is_lowered_once)}
+MIXED = [(True, 70, 40), (False, 50, 60)]
+
+
+def tune():
+    """Tunes a batch; prints the kernel and its number."""
+    os.environ["GP2D_MERGED_WORK"] = "1e18"
+    gp.lib().fake_times(C.c_double(5.0), C.c_double(1.0))
+    best, _ = gp.gp_tune_batch(*batch(synth.rng_for(7), MIXED, 8, 1000))
+    print(gp.variants()[best.variant]["kernel"], best.variant, flush=True)
+
+
+def evaluated_with(kernel):
+    """The same batch without a configuration is evaluated, by the kernel named (or any: "-")."""
+    os.environ["GP2D_MERGED_WORK"] = "1e18"
+    launched = fake(LAUNCHES)
+    gp.gp_eval_batch(*batch(synth.rng_for(7), MIXED, 8, 1000))
+    assert fake(LAUNCHES) == launched + 1 and fake(TABLE) == 1
+    name = gp.variants()[fake(VARIANT)]["kernel"]
+    print(name, flush=True)
+    assert kernel in ("-", name), name
+
+
+SCENARIOS = {f.__name__: f for f in (failed_allocation_leaves_no_layout, batch_is_lowered_once, tune, evaluated_with)}
 
 if __name__ == "__main__":
     SCENARIOS[sys.argv[2]](*sys.argv[3:])

@@ -58,6 +58,7 @@ def run(library, scenario, *args, **env):
     r = subprocess.run([sys.executable, os.path.join(HERE, "native", "host_scenarios.py"), library, scenario, *args],
                        env=e, capture_output=True, text=True, timeout=300)
     assert r.returncode == 0 and r.stdout.strip().endswith("ok"), (r.returncode, r.stdout[-2000:], r.stderr[-4000:])
+    return r.stdout.split()
 
 
 def test_failed_allocation_leaves_no_layout(library):
@@ -70,3 +71,21 @@ def test_a_batch_is_lowered_once(library, tmp_path):
     cache = tmp_path / "tuned.json"
     cache.write_text('{\n"d7x1;j0,0,1,1,1,1;": [0, 8, 1]\n}\n')
     run(library, "batch_is_lowered_once", GP2D_TUNE_CACHE=str(cache))
+
+
+def test_stored_configurations_go_by_kernel_name(library, tmp_path):
+    cache = tmp_path / "tuned.json"
+    env = {"GP2D_TUNE_CACHE": str(cache)}
+    default = run(library, "evaluated_with", "-")[0]
+    kernel, number = run(library, "tune", **env)[:2]
+    stored = cache.read_text()
+    assert '["%s", ' % kernel in stored and kernel != default
+    run(library, "evaluated_with", kernel, **env)
+    # a file of an earlier release: the kernel's number
+    cache.write_text(stored.replace('"%s"' % kernel, number))
+    run(library, "evaluated_with", kernel, **env)
+    # kernels that do not exist, or cannot hold the batch (trees only; no sin/cos/exp/log; Boolean): the default
+    for other in ('"k_core_9_9_9_9"', '"k_core_4_8_8_64_t"', '"k_core_8_6_8_40_a"', '"k_core_4_6_20_16_b"', "16", "22", "-1",
+                  "4000"):
+        cache.write_text(stored.replace('"%s"' % kernel, other))
+        run(library, "evaluated_with", default, **env)
