@@ -24,8 +24,8 @@ struct FakeState {
     int last_rows = 0, last_groups = 0, last_variant = -1, last_table = 0;
     int null_layout = 0;       // launches whose group layout was null or not a layout
     int uploads = 0;           // copies to the device
-    double now_ms = 0.0;       // the clock of events: advanced by launches
-    double launch_ms = 1.0, table_ms = 1.0;
+    double now_ms = 0.0;       // the clock of events: advanced by launches and by copies to the device
+    double launch_ms = 1.0, table_ms = 1.0, copy_ms = 0.0;
 };
 static FakeState g;
 static std::mutex g_mu;
@@ -54,7 +54,11 @@ int fake_int(int what) {
                      g_lowered.load()};
     return v[what];
 }
-void fake_times(double launch, double table) { g.launch_ms = launch; g.table_ms = table; }
+void fake_times(double launch, double table, double copy) {
+    g.launch_ms = launch;
+    g.table_ms = table;
+    g.copy_ms = copy;
+}
 
 hipError_t hipMalloc(void** p, size_t n) {
     std::lock_guard<std::mutex> l(g_mu);
@@ -68,7 +72,10 @@ hipError_t hipHostMalloc(void** p, size_t n, unsigned) { return hipMalloc(p, n);
 hipError_t hipHostFree(void* p) { free(p); return hipSuccess; }
 hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind kind, hipStream_t) {
     memcpy(d, s, n);
-    if (kind == hipMemcpyHostToDevice) g.uploads++;
+    if (kind == hipMemcpyHostToDevice) {
+        g.uploads++;
+        g.now_ms += g.copy_ms;
+    }
     return hipSuccess;
 }
 hipError_t hipEventCreate(hipEvent_t* e) { *e = (hipEvent_t) new double(0.0); return hipSuccess; }

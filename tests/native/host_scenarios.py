@@ -100,7 +100,7 @@ MIXED = [(True, 70, 40), (False, 50, 60)]
 def tune():
     """Tunes a batch; prints the kernel and its number."""
     os.environ["GP2D_MERGED_WORK"] = "1e18"
-    gp.lib().fake_times(C.c_double(5.0), C.c_double(1.0))
+    gp.lib().fake_times(C.c_double(5.0), C.c_double(1.0), C.c_double(0.0))
     best, _ = gp.gp_tune_batch(*batch(synth.rng_for(7), MIXED, 8, 1000))
     print(gp.variants()[best.variant]["kernel"], best.variant, flush=True)
 
@@ -116,7 +116,22 @@ def evaluated_with(kernel):
     assert kernel in ("-", name), name
 
 
-SCENARIOS = {f.__name__: f for f in (failed_allocation_leaves_no_layout, batch_is_lowered_once, tune, evaluated_with)}
+def tuning_keeps_the_faster(launch, table, copy, table_kept):
+    """A batch of two sets is tuned; evaluations then take the table of units, or the sets' own launches, whichever
+    whole call is the shorter: 5 copies and a launch of `table` ms, or 4 copies and two launches of `launch` ms."""
+    os.environ["GP2D_MERGED_WORK"] = "0"
+    gp.lib().fake_times(*(C.c_double(float(t)) for t in (launch, table, copy)))
+    data, jobs = batch(synth.rng_for(7), MIXED, 8, 1000)
+    _, ms = gp.gp_tune_batch(data, jobs)
+    assert abs(ms - float(table)) < 1e-3, ms
+    uploads = fake(UPLOADS)
+    gp.gp_eval_batch(data, jobs)
+    assert fake(TABLE) == int(table_kept)
+    assert fake(UPLOADS) - uploads == (5 if int(table_kept) else 4)
+
+
+SCENARIOS = {f.__name__: f for f in (failed_allocation_leaves_no_layout, batch_is_lowered_once, tune, evaluated_with,
+                                     tuning_keeps_the_faster)}
 
 if __name__ == "__main__":
     SCENARIOS[sys.argv[2]](*sys.argv[3:])

@@ -89,3 +89,9 @@ def test_stored_configurations_go_by_kernel_name(library, tmp_path):
                   "4000"):
         cache.write_text(stored.replace('"%s"' % kernel, other))
         run(library, "evaluated_with", default, **env)
+
+
+@pytest.mark.parametrize("launch,table,copy,table_kept", [(1, 3, 0, 0), (2, 3, 0, 1), (0.5, 3, 1, 0), (0.5, 1.5, 1, 0),
+                                                          (4, 3, 1, 1)])
+def test_tuning_compares_whole_calls(library, launch, table, copy, table_kept):
+    run(library, "tuning_keeps_the_faster", *(str(x) for x in (launch, table, copy, table_kept)))
