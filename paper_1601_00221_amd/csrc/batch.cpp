@@ -632,9 +632,10 @@ bool merge_jobs(const std::vector<BatchJobRef>& refs, const std::vector<gp_datas
 gp_status eval_table(const std::vector<BatchJobRef>& refs, const std::vector<gp_dataset>& dv, const gp_batch_config& c,
                      hipStream_t s) {
     if (c.variant < 0) return fail(GP_E_DEPTH, "no kernel variant can hold these programs");
+    gp_status st;
+    if ((st = check_config(refs, c)) != GP_OK) return st;   // (before the kernel is looked for by its number)
     BatchScratch& sc = batch_scratch(s);
     std::lock_guard<std::mutex> g(sc.mu);
-    gp_status st;
     if ((st = core_ready(c.variant, s)) != GP_OK) return st;
     BatchPlan plan;
     if ((st = plan_batch(refs, dv, c, plan)) != GP_OK) return st;

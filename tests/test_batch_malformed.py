@@ -47,3 +47,15 @@ def test_malformed_arrays_are_refused(tree, off, coff, status, message):
                            text=True, timeout=120)
         assert r.returncode == 0, (r.returncode, r.stderr[-500:])
         assert r.stdout.strip() == "%d %s" % (status, message), r.stdout
+
+
+@pytest.mark.parametrize("variant,status,message", [(4000, -1, "kernel variant 4000 does not exist"),
+                                                    (1 << 30, -1, "kernel variant 1073741824 does not exist"),
+                                                    (-1, -3, "no kernel variant can hold these programs"),
+                                                    (22, -1, "variant 22 is a Boolean kernel")])
+def test_unknown_kernels_are_refused(variant, status, message):
+    call = CALL.replace("1, None, None)", "1, C.byref(gp.BatchConfig(%d, 8, 1, 0)), None)" % variant)
+    r = subprocess.run([sys.executable, "-c", call, repr((True, [0, 1], [0, 0], 1000))], capture_output=True, text=True,
+                       timeout=120)
+    assert r.returncode == 0, (r.returncode, r.stderr[-500:])
+    assert r.stdout.strip() == "%d %s" % (status, message), r.stdout
