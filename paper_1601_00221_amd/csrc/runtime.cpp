@@ -771,33 +771,53 @@ static void plan_rows_for(const ProgData& pd, int vi, RowPlan& rows) {
     plan_rows(pd, vi, (base_groups(pd, vi, nullptr) + W - 1) / W, rows);
 }
 
+// Translate and upload a program set for variant vi, with the layout for G
+// groups (0: none): with rows, and, if over some number of cases it is faster
+// so, without them as well (translation_for says which an evaluation takes; a
+// set is uploaded once).  The fewer the tiles, the less rows pay: in a sweep of
+// 125 sets (5 to 5000 programs, 1 to 44 features) rows that were worth it over
+// one tile were so over every number of tiles.  So only small sets hold both:
+// 100 programs of up to 64 nodes, but not 300 of up to 200.  (For want of
+// memory for both, the one with rows serves.)
+static gp_status upload_set(const ProgData& pd, int vi, std::map<int, DevProgs>& dps, int32_t G, hipStream_t s, Workspace& w) {
+    DevProgs& dp = dps[vi];
+    plan_rows_for(pd, vi, dp.rows);
+    const gp_status st = prepare_programs(pd, vi, dp, false, G, s, w, nullptr);
+    if (st != GP_OK) return st;
+    RowPlan none;
+    no_rows(pd, vi, none);
+    if (dp.rows.n() == none.n() ||
+        launch_shape(pd, vi, 1, nullptr, dp.rows).est <= launch_shape(pd, vi, 1, nullptr, none).est)
+        return GP_OK;
+    DevProgs& plain = dps[vi + kNoRows];
+    plain.rows = std::move(none);
+    if (prepare_programs(pd, vi, plain, false, 0, s, w, nullptr) != GP_OK) {
+        dps.erase(vi + kNoRows);
+        clear_error();
+    }
+    return GP_OK;
+}
+
 // The translation that an evaluation takes, as a key of dps: with rows (vi) or without (vi + kNoRows).  Every block
 // computes the rows of its tile, so with few tiles, and thus blocks of few programs, they can cost more than they save
 // (1148 classification programs with 41 rows x 1000 cases: 29 us with them, 18 without; x 8000: 65 and 61; x 383000:
 // 1.72 ms and 1.89): the shorter estimate is taken.  Where the tiles are enough for whole groups both estimates are
 // zero, and the rows stay.
 static int translation_for(const ProgData& pd, int vi, std::map<int, DevProgs>& dps, bool fresh, int32_t tiles,
-                           const EvalOptions* opt, hipStream_t s) {
+                           const EvalOptions* opt) {
     DevProgs& dp = dps[vi];
-    if (fresh || !dp.uploaded) plan_rows_for(pd, vi, dp.rows);
-    if (dp.rows.n() == 0) return vi;
     if (fresh) {
+        plan_rows_for(pd, vi, dp.rows);
+        if (dp.rows.n() == 0) return vi;
         RowPlan none;
         no_rows(pd, vi, none);
         if (launch_shape(pd, vi, tiles, opt, dp.rows).est > launch_shape(pd, vi, tiles, opt, none).est) dp.rows = std::move(none);
         return vi;
     }
-    DevProgs& plain = dps[vi + kNoRows];
-    if (plain.rows.cost.empty()) no_rows(pd, vi, plain.rows);
-    if (launch_shape(pd, vi, tiles, opt, dp.rows).est <= launch_shape(pd, vi, tiles, opt, plain.rows).est) return vi;
-    if (!plain.uploaded) {
-        // made when it is wanted for the fourth time (some 100 us, against 5 to 40 a call that it saves), and not while
-        // the stream is being captured
-        hipStreamCaptureStatus cap = hipStreamCaptureStatusActive;
-        if (++plain.wanted < 4 || hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone)
-            return vi;
-    }
-    return vi + kNoRows;
+    auto plain = dps.find(vi + kNoRows);
+    if (plain == dps.end()) return vi;
+    return launch_shape(pd, vi, tiles, opt, dp.rows).est <= launch_shape(pd, vi, tiles, opt, plain->second.rows).est
+               ? vi : vi + kNoRows;
 }
 
 int default_variant(const ProgData& pd) {
@@ -850,7 +870,10 @@ gp_status eval_core(const ProgData& pd, std::map<int, DevProgs>& dps, bool fresh
     const int64_t tiles64 = (N + 64LL * T - 1) / (64LL * T);
     if (tiles64 > (1LL << 30)) return fail(GP_E_INVAL, "n_cases too large");
     const int32_t tiles = (int32_t)tiles64;
-    const int key = no_alloc ? vi : translation_for(pd, vi, dps, fresh, tiles, opt, s);
+    if (!no_alloc && !w) return fail(GP_E_INVAL, "internal: no workspace");
+    // (a set is uploaded when it is created, and here for another kernel than its own)
+    if (!no_alloc && !fresh && !dps[vi].uploaded && (st = upload_set(pd, vi, dps, 0, s, *w)) != GP_OK) return st;
+    const int key = no_alloc ? vi : translation_for(pd, vi, dps, fresh, tiles, opt);
     auto dit = dps.find(key);
     if (no_alloc && dit == dps.end()) return fail(GP_E_INVAL, "programs are not on the device for variant %d", vi);
     DevProgs& dp = no_alloc ? dit->second : dps[key];
@@ -882,7 +905,6 @@ gp_status eval_core(const ProgData& pd, std::map<int, DevProgs>& dps, bool fresh
         goff = (const uint32_t*)git->second.p;
         partials = opt->partials;
     } else {
-        if (!w) return fail(GP_E_INVAL, "internal: no workspace");
         if ((st = prepare_programs(pd, vi, dp, fresh, G, s, *w, &goff)) != GP_OK) return st;
         if (part_bytes && (st = w->partials.reserve(part_bytes)) != GP_OK) return st;
         partials = (double*)w->partials.p;
@@ -1040,9 +1062,7 @@ static gp_status progset_finish(ProgData&& pd, void* stream, gp_progset** ps) {
         Workspace& w = workspace(s);
         std::lock_guard<std::mutex> g(w.mu);
         p->groups = base_groups(p->pd, vi, nullptr);
-        plan_rows_for(p->pd, vi, p->dps[vi].rows);
-        if ((st = prepare_programs(p->pd, vi, p->dps[vi], false, p->groups, s, w, nullptr)) != GP_OK)
-            return st;
+        if ((st = upload_set(p->pd, vi, p->dps, p->groups, s, w)) != GP_OK) return st;
     }
     *ps = p.release();
     return GP_OK;

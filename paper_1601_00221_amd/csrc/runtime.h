@@ -135,7 +135,6 @@ struct RowPlan {
 // on any stream waits for it.
 struct DevProgs {
     bool uploaded = false;
-    int32_t wanted = 0;            // evaluations that would have taken it before it was made (runtime.cpp, translation_for)
     DevBuf code;
     std::vector<uint32_t> order;   // programs in the order of the code (host)
     std::vector<int64_t> rec;      // first record of each, in that order, and the end (host)

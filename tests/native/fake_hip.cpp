@@ -24,6 +24,7 @@ struct FakeState {
     int last_rows = 0, last_groups = 0, last_variant = -1, last_table = 0;
     int null_layout = 0;       // launches whose group layout was null or not a layout
     int uploads = 0;           // copies to the device
+    int capturing = 0;         // streams are being captured
     double now_ms = 0.0;       // the clock of events: advanced by launches and by copies to the device
     double launch_ms = 1.0, table_ms = 1.0, copy_ms = 0.0;
 };
@@ -54,6 +55,7 @@ int fake_int(int what) {
                      g_lowered.load()};
     return v[what];
 }
+void fake_capturing(int on) { g.capturing = on; }
 void fake_times(double launch, double table, double copy) {
     g.launch_ms = launch;
     g.table_ms = table;
@@ -94,7 +96,7 @@ hipError_t hipStreamDestroy(hipStream_t s) { free(s); return hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
 hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
 hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus* c) {
-    *c = hipStreamCaptureStatusNone;
+    *c = g.capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
     return hipSuccess;
 }
 hipError_t hipThreadExchangeStreamCaptureMode(hipStreamCaptureMode*) { return hipSuccess; }

@@ -53,6 +53,8 @@ def failed_allocation_leaves_no_layout():
     F, P, N = 16, 700, 3000
     X, y, out = Array(np.zeros((F, N), np.float32)), Array(np.zeros(N, np.float32)), Array(np.zeros(P, np.float32))
     failures = 0
+    for _ in range(4):
+        tree_set(rng, P, F, synth.FULL).close()   # (the staging buffers are there)
     for k in range(1, 12):
         ps = tree_set(rng, P, F, synth.FULL)
         launched = fake(LAUNCHES)
@@ -94,6 +96,43 @@ def batch_is_lowered_once():
         assert fake(LOWERED) - lowered == 150, fake(LOWERED) - lowered
 
 
+def every_evaluation_takes_the_translation_that_suits_it():
+    """A small set of trees with sin/cos/exp/log is uploaded with rows and without when it is created: every evaluation
+    takes the translation that suits its number of cases, the first as the later ones, and the first over a number of
+    cases uploads its layout alone, the later ones nothing.  Where there was no memory for both, the rows serve; a
+    large set, whose rows always pay, is uploaded with them alone."""
+    rng = synth.rng_for(5)
+    F, P, few, many = 8, 700, 300, 1000000
+    X, y, out = Array(np.zeros((F, many), np.float32)), Array(np.zeros(many, np.float32)), Array(np.zeros(P, np.float32))
+    for _ in range(4):
+        tree_set(rng, P, F, synth.FULL).close()   # (the kernel is set up and the staging buffers are there)
+    for k in range(1, 8):
+        gp.lib().fake_fail_malloc(0 if k == 7 else k)
+        try:
+            ps = tree_set(rng, P, F, synth.FULL)
+        except gp.GPError as e:
+            assert e.status == -2, e
+            continue
+        finally:
+            gp.lib().fake_fail_malloc(0)
+        rows = []
+        for n in (few, few, many, few, many):
+            uploads = fake(UPLOADS)
+            evaluate(ps, X, y, out, n)
+            rows.append(fake(ROWS))
+            assert fake(UPLOADS) - uploads <= (len(rows) == 1), (k, rows)
+        assert rows[2] > 0 and rows[2] == rows[4] and rows[0] == rows[1] == rows[3]
+        assert rows[0] == 0 or k < 7, (k, rows)
+        assert fake(BAD_LAYOUTS) == 0
+        ps.close()
+    pop = synth.ptc2_population(rng, 1000, synth.FULL, F, 1, 250, 0.1)
+    uploads = fake(UPLOADS)
+    ps = gp.ProgSet.tree(pop.tok, pop.cst, pop.off, F)
+    assert fake(UPLOADS) - uploads == 2       # code and layout
+    evaluate(ps, X, y, Array(np.zeros(1000, np.float32)), few)
+    assert fake(ROWS) > 0
+
+
 MIXED = [(True, 70, 40), (False, 50, 60)]
 
 
@@ -131,7 +170,7 @@ def tuning_keeps_the_faster(launch, table, copy, table_kept):
 
 
 SCENARIOS = {f.__name__: f for f in (failed_allocation_leaves_no_layout, batch_is_lowered_once, tune, evaluated_with,
-                                     tuning_keeps_the_faster)}
+                                     tuning_keeps_the_faster, every_evaluation_takes_the_translation_that_suits_it)}
 
 if __name__ == "__main__":
     SCENARIOS[sys.argv[2]](*sys.argv[3:])

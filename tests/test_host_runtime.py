@@ -95,3 +95,7 @@ def test_stored_configurations_go_by_kernel_name(library, tmp_path):
                                                           (4, 3, 1, 1)])
 def test_tuning_compares_whole_calls(library, launch, table, copy, table_kept):
     run(library, "tuning_keeps_the_faster", *(str(x) for x in (launch, table, copy, table_kept)))
+
+
+def test_every_evaluation_takes_the_translation_that_suits_it(library):
+    run(library, "every_evaluation_takes_the_translation_that_suits_it")
