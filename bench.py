@@ -250,10 +250,17 @@ def kernel_name(vi):
 # ----------------------------------------------------------------------------
 # one population on one case matrix
 # ----------------------------------------------------------------------------
-UNPACKED_CEILING_NOTE = ("this path runs unpacked FP32 (packed FP32 is switched off in every build) with terminals "
-                         "folded into operands: on {+,-,*} trees it performs about 1.54 GP operations per "
-                         "vector lane-operation, so its own ceiling is 39.3 T lane-op/s x 1.54 = 61 T GPop/s")
-UNPACKED_CEILING_T = 61.0
+def add_unpacked_ceiling(r, mix):
+    """The ceiling of this path on the {+,-,*} trees, and the kernel's share of
+    it, from the same counters as op_mix_ceiling (null without them)."""
+    r["frac_of_unpacked_ceiling"] = mix["frac"] if mix else None
+    r["unpacked_ceiling_tgpops"] = mix["gpops"] / 1e12 if mix else None
+    r["unpacked_ceiling_note"] = (
+        "this path runs unpacked FP32 (packed FP32 is switched off in every build) with terminals folded into operands: "
+        "on {+,-,*} trees it performs %.2f GP operations per vector lane-operation, so its own ceiling is "
+        "39.3 T lane-op/s x %.2f = %.1f T GPop/s" % (mix["gpop_per_valu_lane_op"], mix["gpop_per_valu_lane_op"],
+                                                     mix["gpops"] / 1e12)) if mix else \
+        "no counters of the current sources"
 
 
 def time_population(args, w, steps, warmup):
@@ -359,14 +366,13 @@ def bench_single(args):
         log("arith-tree: step %.3f ms, kernel %.3f ms, %.3f T GPop/s" % (ma["step_s"] * 1e3, ma["kern_s"] * 1e3,
                                                                        va / 1e12))
         ra = roofline(ma["gpop_per_step"], ma["kern_s"], ka, wa.name)
-        ra["frac_of_unpacked_ceiling"] = ma["gpop_per_step"] / ma["kern_s"] / (UNPACKED_CEILING_T * 1e12)
-        ra["unpacked_ceiling_tgpops"] = UNPACKED_CEILING_T
-        ra["unpacked_ceiling_note"] = UNPACKED_CEILING_NOTE
+        mix = op_mix_ceiling(ma["gpop_per_step"], ma["kern_s"], ka, wa.name)
+        add_unpacked_ceiling(ra, mix)
         res["arith"] = {"workload": wa.name, "value": va, "unit": "GPop/s", "ms_per_step": ma["step_s"] * 1e3,
                         "step_ms": {"median": ma["step_ms_median"], "p10": ma["step_ms_p10"],
                                     "p90": ma["step_ms_p90"]},
                         "pct_vector_fp32_peak": 100.0 * va / (PEAK_FP32_T * 1e12), "roofline": ra,
-                        "op_mix_ceiling": op_mix_ceiling(ma["gpop_per_step"], ma["kern_s"], ka, wa.name)}
+                        "op_mix_ceiling": mix}
         ma["ps"].close()
     if not args.no_cpu:
         log("cpu baseline ...")
