@@ -260,7 +260,8 @@ typedef struct {
 
 /* Same program arguments as gp_eval_tree / gp_eval_linear.  The upload is
  * stream ordered on `stream`; *ps is owned by the caller until
- * gp_progset_destroy. */
+ * gp_progset_destroy.  (A small set of trees with sin/cos/exp/log is uploaded
+ * in two forms, one for few and one for many cases.) */
 gp_status gp_progset_tree(const int32_t* tok, const float* cst, const int64_t* off, int32_t n_prog,
                           int32_t n_feat, void* stream, gp_progset** ps);
 gp_status gp_progset_linear(const uint32_t* code, const int64_t* off, const float* cst,
@@ -297,10 +298,11 @@ gp_status gp_progset_destroy(gp_progset* ps);
 
 /* ------------------------------------------------------------------------ */
 /* Batched evaluation: several populations (trees and linear programs) over */
-/* several resident case matrices in one persistent launch.  Work is cut   */
-/* into (case tile, program group) units, sorted longest first and pulled  */
+/* several resident case matrices in one call.  Large sets of alike jobs    */
+/* are launched by themselves; the others share one persistent launch, cut  */
+/* into (case tile, program group) units, sorted longest first and pulled   */
 /* by the chip's resident wavefronts from a global counter.  Fitness values */
-/* are the same as from gp_eval_tree / gp_eval_linear, bit for bit.        */
+/* are the same as from gp_eval_tree / gp_eval_linear, bit for bit.         */
 /* ------------------------------------------------------------------------ */
 typedef struct {
     const float* X;            /* DEVICE, feature-major float32[n_feat * n_cases] */
@@ -487,15 +489,15 @@ gp_status gp_timing_read(int64_t* launches, double* total_ms, int reset);
  * every one-shot or program-set evaluation: GP2D_GROUP_INSTR (core
  * instructions per program group), GP2D_TILES_PER_WAVE (case tiles each
  * wavefront walks per group), GP2D_TARGET_BLOCKS (workgroups the launch aims
- * for), GP2D_CODE_PREFETCH=n (scalar loads in flight, 1-15, when each
- * program's code is burst-loaded into the scalar cache; 15 by default, 0
- * for no burst load), GP2D_SAME_GROUP=1 (the four waves of a block run one program
- * group on four chunks of tiles instead of four groups on one chunk),
- * GP2D_VARIANT=i+1 (kernel variant i of gp_variant_info, when it can hold the
- * programs), and, at every gp_eval_batch, GP2D_MERGED_WORK (tokens x cases
- * from which jobs that share form, dataset, kind and registers are launched
- * by themselves).  They change the schedule only; fitness values never depend on
- * them. */
+ * for), GP2D_CODE_PREFETCH=n (64-byte lines of the next program's code fetched
+ * into the scalar cache at a time, 1-14; 14 by default, 0 for none),
+ * GP2D_SAME_GROUP=1 (the waves of a block run one program group on as many
+ * chunks of tiles, instead of as many groups on one chunk, in launches without
+ * rows), GP2D_VARIANT=i+1 (kernel variant i of gp_variant_info, when it can
+ * hold the programs), and, at every gp_eval_batch, GP2D_MERGED_WORK (tokens x
+ * cases from which jobs that share form, dataset, kind and registers are
+ * launched by themselves).  They change the schedule only; fitness values
+ * never depend on them. */
 
 /* Message of the last failed call on this thread ("" if none). */
 const char* gp_last_error(void);

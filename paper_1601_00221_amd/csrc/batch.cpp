@@ -1,7 +1,8 @@
 // Batched evaluation: several program populations (tree and linear) over
-// several resident case matrices in one persistent launch, plus the
-// autotuner that picks tile width, stack depth variant, unit size and
-// schedule for a batch shape.
+// several resident case matrices, large sets of alike ones as one population,
+// the others in one persistent launch over a table of units; and the
+// autotuner that picks kernel variant, unit size and schedule of such a launch
+// for a batch shape.
 #include <hip/hip_runtime_api.h>
 #include <stdio.h>
 #include <stdlib.h>

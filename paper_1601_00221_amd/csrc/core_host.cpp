@@ -232,7 +232,7 @@ struct Emitter {
         o[2] = pay;
         o[3] = cst;
     }
-    // leave the core: operation op on A (offset or constant), B, into D
+    // leave the handlers for the block's tail: operation op on A (offset or constant), B, into D
     void exit(uint32_t op, int oa, int ob, int od, bool a_const, bool b_const, uint32_t cst) {
         const uint32_t fl = (a_const ? 1u : 0u) | (b_const ? 2u : 0u);
         put(CK_EXIT, 0, 0, 0,
@@ -271,8 +271,6 @@ struct Emitter {
         put(kind, (int)op, 0, 0,
             (uint32_t)(oa & 255) | ((uint32_t)(ob & 255) << 8) | ((uint32_t)(od & 255) << 16), cst);
     }
-    // the binary functions the arithmetic kernels apply in their own handlers: protected division and the
-    // classification functions (sin/cos/exp/log are unary and leave the core)
     // ring cores: functions of a stack entry and the one above it or a variable, at level l = offset / T
     static uint32_t swapped(uint32_t op) { return op == GP_GT ? (uint32_t)GP_LT : op == GP_LT ? (uint32_t)GP_GT : op; }
     bool ring_apply(uint32_t op, uint32_t mode, int h, int xa, int xb) {
@@ -298,6 +296,8 @@ struct Emitter {
             default: return false;
         }
     }
+    // protected division and the binary classification functions in their general form: operands at any offsets, or
+    // one of them the constant
     void apply(uint32_t op, bool boolean, int oa, int ob, int od, bool a_const, bool b_const, uint32_t cst) {
         if (!boolean && op == GP_PDIV) {
             div(oa, ob, od, a_const, b_const, cst);
@@ -310,9 +310,9 @@ struct Emitter {
     }
 };
 
-// Functions the core applies itself: + - * and, in Boolean kernels, the four
-// bitwise functions; the others leave the core (in arithmetic trees opcodes 8
-// and 9 are the logical AND and OR, which are exits).
+// Functions with a handler for every operand mode: + - * and, in Boolean
+// kernels, the four bitwise functions (in arithmetic trees opcodes 8 and 9 are
+// the logical AND and OR, which go with the compares).
 bool is_core_op(uint32_t op, bool boolean) {
     return op == GP_ADD || op == GP_SUB || op == GP_MUL || (boolean && op >= GP_AND && op <= GP_NOR);
 }
@@ -459,8 +459,8 @@ static int translate_tree(const uint32_t* w, int64_t n_instr, int vi, const Vari
             }
             continue;
         }
-        // protected division has handlers of its own; the transcendentals and the classification
-        // functions leave the core
+        // protected division and the classification functions: a ring core's forms for operands on the stack, else the
+        // general one.  sin/cos/exp/log are exits to the block's tail (or a row, or, of a constant, a push).
         const bool bl = v.arith == 2;
         if (!bl && (op == GP_PDIV || op == GP_GT || op == GP_LT || op == GP_EQ || op == GP_AND || op == GP_OR) &&
             e.ring_apply(op, mode, h, xa, xb))
@@ -521,7 +521,7 @@ static int translate_linear(const uint32_t* w, int64_t n, uint32_t live, const u
         const int d = (int)((wd >> 8) & 255u), s1 = (int)((wd >> 16) & 255u), s2 = (int)(wd >> 24);
         const bool c1 = s1 >= GP_SRC_CONST, c2 = s2 >= GP_SRC_CONST;
         const uint32_t v1 = c1 ? cst[s1 - GP_SRC_CONST] : 0u, v2 = c2 ? cst[s2 - GP_SRC_CONST] : 0u;
-        if (op >= GP_SIN && op <= GP_PLOG) {  // unary: leave the core
+        if (op >= GP_SIN && op <= GP_PLOG) {  // in the block's tail
             e.exit(op, c1 ? 0 : off(s1), 0, d * T, c1, false, v1);
             continue;
         }

@@ -32,8 +32,7 @@ int core_reg_levels(int vi);       // register/stack levels before the features
 // `trees_only` (then a kernel without linear handlers may be taken); -1 if
 // none fits.
 int pick_core_variant(int n_load, int depth, double transc_frac, bool has_transc, bool boolean = false,
-                      bool trees_only = false,
-                      bool wide = false);
+                      bool trees_only = false, bool wide = false);
 // Locate the variant's handler table on the current device (one probe launch
 // on stream s the first time).
 gp_status core_ready(int vi, hipStream_t s);
@@ -41,7 +40,8 @@ gp_status core_ready(int vi, hipStream_t s);
 bool core_is_ready(int vi);
 int core_variant_waves(int vi);     // of a block
 int core_variant_simd(int vi);      // waves that a SIMD holds
-void no_rows(const ProgData& pd, int vi, RowPlan& plan);    // waves of a block
+// No function has a row: the features that variant vi holds in LDS alone, and the programs' costs as they are.
+void no_rows(const ProgData& pd, int vi, RowPlan& plan);
 // Which functions of a feature a launch computes once a tile into LDS, for variant vi, where `blocks` blocks share a
 // tile's programs; and the programs' costs without them.
 void plan_rows(const ProgData& pd, int vi, int64_t blocks, RowPlan& plan);
