@@ -280,7 +280,11 @@ gp_status gp_progset_eval(gp_progset* ps, const float* X, int32_t n_feat, int64_
  * evaluation as gp_progset_eval, bit for bit, with nothing allocated and
  * nothing copied from the host during the call -- it launches the evaluation
  * and reduction kernels on `stream` and returns.  The programs and their
- * layout were uploaded when the set was created (on this device).  The
+ * layout were uploaded when the set was created (on this device).  A stream
+ * that is being captured may not be able to wait for that upload (GP_E_DEVICE
+ * then): evaluate the set once after it has passed, then capture.
+ * gp_progset_eval is captured likewise, after two evaluations over the same number of cases with
+ * a synchronization between them (the first may upload a layout).  The
  * per-(program, 256-case block) partial sums go to a fixed device array of
  * GP_NOALLOC_MAX_PARTIALS doubles (16 MiB) that each GPU the library runs on
  * holds until the process ends: n_prog * ceil(n_cases / 256) (Boolean sets:

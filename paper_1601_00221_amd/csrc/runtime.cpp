@@ -530,19 +530,28 @@ void cut_groups(const std::vector<uint32_t>& cost, const std::vector<uint32_t>& 
     }
 }
 
-// Whether an event has passed.  Not asked while s is being captured (that
-// would end the capture), and asked in the relaxed capture mode: a query in
-// the default mode is refused while any thread captures a stream in the global
-// mode, and ends that capture.
-static bool has_passed(hipEvent_t ev, hipStream_t s) {
+// Order a launch on stream s after the upload of dp, on whichever stream that
+// was, unless the upload is known to have passed.  The event is not queried
+// while s is being captured (that would end the capture), and otherwise in the
+// relaxed capture mode: in the default mode a query is refused while any thread
+// captures a stream in the global mode, and ends that capture.  A wait for an
+// event from outside a capture may be refused too: a captured evaluation relies
+// on an earlier one's having seen the upload pass.
+static gp_status wait_for_upload(DevProgs& dp, hipStream_t s) {
+    if (dp.settled) return GP_OK;
     hipStreamCaptureStatus cap = hipStreamCaptureStatusActive;
-    if (hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) return false;
     hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-    if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) return false;
-    const hipError_t q = hipEventQuery(ev);
-    (void)hipThreadExchangeStreamCaptureMode(&mode);
-    if (q != hipSuccess) (void)hipGetLastError();   // "not yet" is no error: it must not be taken for a launch's
-    return q == hipSuccess;
+    if (hipStreamIsCapturing(s, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone &&
+        hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess) {
+        dp.settled = hipEventQuery(dp.ready) == hipSuccess;
+        (void)hipThreadExchangeStreamCaptureMode(&mode);
+    }
+    if (dp.settled) return GP_OK;
+    (void)hipGetLastError();   // "not yet" is no error: it must not be taken for a launch's
+    const hipError_t e = hipStreamWaitEvent(s, dp.ready, 0);
+    if (e == hipSuccess) return GP_OK;
+    (void)hipGetLastError();
+    return fail(GP_E_DEVICE, "hipStreamWaitEvent: %s", hipGetErrorString(e));
 }
 
 // Translate and upload the programs for variant vi (when `fresh` or not yet
@@ -556,14 +565,7 @@ static gp_status prepare_programs(const ProgData& pd, int vi, DevProgs& dp, bool
     std::vector<uint32_t> g, gprog;
     gp_status st;
     const bool upload = fresh || !dp.uploaded;
-    if (!upload && dp.ready && !dp.settled) {
-        // Uploaded earlier, possibly on another stream: order this launch after it, unless it has passed.
-        dp.settled = has_passed(dp.ready, s);
-        if (!dp.settled) {
-            hipError_t e = hipStreamWaitEvent(s, dp.ready, 0);
-            if (e != hipSuccess) return fail(GP_E_DEVICE, "hipStreamWaitEvent: %s", hipGetErrorString(e));
-        }
-    }
+    if (!upload && (st = wait_for_upload(dp, s)) != GP_OK) return st;
     if (upload) {
         std::vector<DevProg> progs;
         cost_order(dp.rows.cost, dp.order);
@@ -900,8 +902,7 @@ gp_status eval_core(const ProgData& pd, std::map<int, DevProgs>& dps, bool fresh
             return fail(GP_E_NOMEM, "%lld programs x %lld blocks of 256 cases need %zu bytes of partial sums; "
                         "this entry point has %zu", (long long)pd.n_prog, (long long)n_blocks, part_bytes,
                         opt->partials_bytes);
-        hipError_t e = hipStreamWaitEvent(s, dp.ready, 0);
-        if (e != hipSuccess) return fail(GP_E_DEVICE, "hipStreamWaitEvent: %s", hipGetErrorString(e));
+        if ((st = wait_for_upload(dp, s)) != GP_OK) return st;
         goff = (const uint32_t*)git->second.p;
         partials = opt->partials;
     } else {
