@@ -1,5 +1,6 @@
-"""The bench line's ceiling on {+,-,*} trees comes from the counters of the
-current kernel: its two forms agree, and it is null where there are none."""
+"""What the bench line says of kernels: the ceiling on {+,-,*} trees comes from
+the counters of the current kernel (its two forms agree, and it is null where
+there are none), and a batched step counts all of its launches."""
 import bench
 
 
@@ -21,3 +22,12 @@ def test_no_ceiling_without_counters(monkeypatch):
     r = {}
     bench.add_unpacked_ceiling(r, bench.op_mix_ceiling(1.0, 1.0, "kernel", "workload"))
     assert r["frac_of_unpacked_ceiling"] is None and r["unpacked_ceiling_tgpops"] is None
+
+
+def test_a_batched_step_counts_all_its_launches():
+    ops = 2.3e11
+    one = bench.batched_roofline(ops, 20, 700.0, 20, "k_tuned", "w")       # 20 steps of one launch, 35 ms each
+    six = bench.batched_roofline(ops, 120, 560.0, 20, "k_tuned", "w")      # six launches a step, 28 ms in all
+    assert one["kernel"] == "k_tuned" and abs(one["kernel_ms"] - 35.0) < 1e-9 and "note" not in one
+    assert six["kernel"] == "k_core" and abs(six["kernel_ms"] - 28.0) < 1e-9 and six["launches_per_step"] == 6
+    assert abs(six["achieved"] - ops / 28e-3 / 1e12) < 1e-9
