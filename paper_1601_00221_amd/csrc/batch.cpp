@@ -737,8 +737,11 @@ gp_status gp_tune_batch(const gp_dataset* ds, int32_t n_ds, const gp_job* jobs, 
     if (best_ms) *best_ms = ms;
     // the candidates were timed by their launches; the default prepares several launches, so whole calls are compared
     if ((st = time_whole([&] { return eval_table(refs, dv, *best, s); }, reps, s, &whole)) != GP_OK) return st;
-    if ((st = time_whole([&] { return eval_default(refs, dv, s); }, reps, s, &dflt)) != GP_OK) return st;
-    if (dflt < whole) drop_tuned(refs, dv);
+    if (time_whole([&] { return eval_default(refs, dv, s); }, reps, s, &dflt) == GP_OK) {
+        if (dflt < whole) drop_tuned(refs, dv);
+    } else {
+        clear_error();   // (no memory for it: the configuration serves)
+    }
     return GP_OK;
 }
 

@@ -169,8 +169,23 @@ def tuning_keeps_the_faster(launch, table, copy, table_kept):
     assert fake(UPLOADS) - uploads == (5 if int(table_kept) else 4)
 
 
+def tuning_does_without_the_default():
+    """Where the default launches cannot be made (no memory), the tuned configuration is stored and returned."""
+    gp.lib().fake_times(*(C.c_double(t) for t in (5.0, 1.0, 0.0)))
+    data, jobs = batch(synth.rng_for(7), MIXED, 8, 1000)
+    os.environ["GP2D_MERGED_WORK"] = "1e18"
+    gp.gp_tune_batch(data, jobs)              # (the table route's buffers are there)
+    os.environ["GP2D_MERGED_WORK"] = "0"
+    gp.lib().fake_fail_malloc(1)
+    gp.gp_tune_batch(data, jobs)
+    gp.lib().fake_fail_malloc(0)
+    gp.gp_eval_batch(data, jobs)
+    assert fake(TABLE) == 1
+
+
 SCENARIOS = {f.__name__: f for f in (failed_allocation_leaves_no_layout, batch_is_lowered_once, tune, evaluated_with,
-                                     tuning_keeps_the_faster, every_evaluation_takes_the_translation_that_suits_it)}
+                                     tuning_keeps_the_faster, tuning_does_without_the_default,
+                                     every_evaluation_takes_the_translation_that_suits_it)}
 
 if __name__ == "__main__":
     SCENARIOS[sys.argv[2]](*sys.argv[3:])

@@ -99,3 +99,7 @@ def test_tuning_compares_whole_calls(library, launch, table, copy, table_kept):
 
 def test_every_evaluation_takes_the_translation_that_suits_it(library):
     run(library, "every_evaluation_takes_the_translation_that_suits_it")
+
+
+def test_tuning_does_without_the_default(library):
+    run(library, "tuning_does_without_the_default")
