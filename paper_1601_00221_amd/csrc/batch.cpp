@@ -214,11 +214,15 @@ gp_status launch_plan(const BatchPlan& p, BatchScratch& sc, hipStream_t s) {
 // ---------------------------------------------------------------------------
 // Autotuning
 // ---------------------------------------------------------------------------
-// What is stored for a shape.  The kernel goes by its name: a file may have
-// been written by another release.
+// What is stored for a shape.  In the file the kernel goes by its name: it may
+// have been written by another release, with kernels that this one has not.
 struct Tuned {
     std::string kernel;
     int unit_programs, persistent;
+    int variant;                   // of that name, -1: none
+    Tuned() = default;
+    Tuned(const std::string& name, int unit, int pers)
+        : kernel(name), unit_programs(unit), persistent(pers), variant(core_variant_named(name)) {}
 };
 static std::mutex g_tune_mu;
 static std::map<std::string, Tuned> g_tune_cache;
@@ -245,9 +249,9 @@ static void tune_load_locked() {
         char name[64];
         int vi, unit, pers;
         if (sscanf(q2 + 1, " : [ \"%63[^\"]\" , %d , %d ]", name, &unit, &pers) == 3)
-            g_tune_cache[key] = Tuned{name, unit, pers};
+            g_tune_cache[key] = Tuned(name, unit, pers);
         else if (sscanf(q2 + 1, " : [ %d , %d , %d ]", &vi, &unit, &pers) == 3)
-            g_tune_cache[key] = Tuned{vi >= 0 && vi < core_variants() ? core_variant_name(vi) : std::to_string(vi), unit, pers};
+            g_tune_cache[key] = Tuned(vi >= 0 && vi < core_variants() ? core_variant_name(vi) : std::to_string(vi), unit, pers);
     }
     fclose(f);
 }
@@ -369,7 +373,7 @@ gp_status tune_batch(const std::vector<BatchJobRef>& jobs, const std::vector<gp_
     if (best_ms) *best_ms = best_t;
     std::lock_guard<std::mutex> g(g_tune_mu);
     tune_load_locked();
-    g_tune_cache[batch_key(jobs, ds)] = Tuned{core_variant_name(b.variant), b.unit_programs, b.persistent};
+    g_tune_cache[batch_key(jobs, ds)] = Tuned(core_variant_name(b.variant), b.unit_programs, b.persistent);
     tune_save_locked();
     return GP_OK;
 }
@@ -390,7 +394,7 @@ bool tuned_config(const std::vector<BatchJobRef>& jobs, const std::vector<gp_dat
     // a kernel that does not exist (any more) or cannot run these programs (the shape's key does not say whether they use
     // sin/cos/exp/log) is not taken
     memset(c, 0, sizeof *c);
-    c->variant = core_variant_named(it->second.kernel);
+    c->variant = it->second.variant;
     c->unit_programs = it->second.unit_programs;
     c->persistent = it->second.persistent;
     if (check_config(jobs, *c) == GP_OK) return true;
